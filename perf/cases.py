@@ -1,0 +1,377 @@
+"""The calls a serving program makes of this library, as measurable cases.
+
+Every case is one pass through the public binding (`paper_2601_11589_amd.api`):
+
+* layer      laps_prefill_layer on a ragged batch (the un-captured path: chunks of long prompts, mixed batches,
+             groups of short requests that no captured shape holds)
+* graph      stage + replay + read back of a captured (length bucket, depth) shape of a layer stack
+* attention  laps_attention alone
+* project    one projection with its fused epilogue (laps_gemm_epilogue_bf16)
+* kv         cached K/V out of one set of pools (laps_kv_gather) and into another one (laps_kv_scatter)
+
+Inputs follow the distributions of the benchmark: weights N(0, 0.02^2), norm gains 1 + N(0, 0.02^2), activations
+N(0, 1) in float32, cached K/V N(0, 1), all bf16 but the activations, pages in random order.  Lengths come from
+the case alone (`mix` seeds them), values from the seed.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_2601_11589_amd import api, inputs
+
+PAGE = 16
+MODELS = {"tiny": inputs.tiny_cfg, "7b": inputs.qwen7b_cfg, "14b": inputs.qwen14b_cfg, "32b": inputs.qwen32b_cfg}
+MOST_ROWS = 12000      # rows of the largest batch
+MOST_LONG = 8192       # tokens of the longest prompt
+
+
+# ----------------------------------------------------------------------------------------------- the cases
+def _layer(name, model, n_short, new, pre, n_long=0, long_new=0, long_pre=0, fresh=0.0, bias=False, mix=1):
+    return dict(name=name, kind="layer", model=model, n_short=n_short, new_lo=new[0], new_hi=new[1], pre_lo=pre[0],
+                pre_hi=pre[1], fresh=fresh, n_long=n_long, long_new=long_new, long_pre=long_pre, bias=bias, mix=mix)
+
+
+def _graph(name, model, layers, bucket, depth, n_real, new_lo, pre, fresh=0.0, bias=False, mix=1):
+    return dict(name=name, kind="graph", model=model, layers=layers, bucket=bucket, depth=depth, n_short=n_real,
+                new_lo=new_lo, new_hi=bucket, pre_lo=pre[0], pre_hi=pre[1], fresh=fresh, n_long=0, long_new=0,
+                long_pre=0, bias=bias, mix=mix)
+
+
+def listed():
+    return [
+        # the smallest call: eight short first-turn prompts through one layer of the small test model; launches count
+        _layer("tiny_layer", "tiny", 8, (1, 64), (0, 0), mix=11),
+        # one short turn of one conversation, alone in the smallest captured shape: the latency of an idle server
+        _graph("one_turn_14b", "14b", 1, 8, 1, 1, 7, (900, 900)),
+        # the headline workload: two short prompts in a captured 64 x 2 shape of a four-layer stack, one pass over the
+        # weights per replay (a whole call: the error of four layers in 16 bits)
+        _graph("short_bucket_32b", "32b", 4, 64, 2, 2, 33, (0, 0), mix=3),
+        # short turns over long cached histories in a latency-mode shape
+        _graph("reprefill_32b", "32b", 1, 32, 4, 4, 17, (512, 4096), mix=5),
+        # the wider bucket grid on the 7B shape (7 query heads per kv head, q/k/v bias), between the streaming and the
+        # arithmetic regime
+        _graph("grid_7b_64x4", "7b", 1, 64, 4, 4, 33, (0, 2048), fresh=0.25, bias=True, mix=7),
+        # a group of short requests larger than the latency budget, un-captured: a few hundred rows
+        _layer("short_group_32b", "32b", 12, (16, 64), (0, 4096), fresh=0.25, mix=9),
+        # throughput mode: 64 turns over their histories in the largest captured shape
+        _graph("token_max_32b", "32b", 1, 64, 64, 64, 16, (512, 4096), mix=13),
+        # first chunk of a long prompt
+        _layer("chunk_first_32b", "32b", 0, (1, 1), (0, 0), n_long=1, long_new=2048, long_pre=0),
+        # ragged last chunk of the longest prompt of the benchmark
+        _layer("chunk_last_32b", "32b", 0, (1, 1), (0, 0), n_long=1, long_new=1847, long_pre=6144),
+        # the largest call: a memory-filling mixed batch that takes a long prompt whole with the short ones behind it
+        _layer("unified_32b", "32b", 96, (1, 64), (1, 4096), n_long=1, long_new=7991, long_pre=0, fresh=0.25, mix=15),
+        # one projection as a program with its own layer loop calls it: gate/up with the fused SwiGLU, mid-sized batch
+        dict(name="gate_up_14b", kind="project", model="14b", which="gate_up", rows=700),
+        # hand-over of finished K/V between instances: out of one set of pools, into another one with its own pages
+        dict(name="kv_hand_over_32b", kind="kv", model="32b", n_seq=8, lo=512, hi=4096, mix=17),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi + 0.49)))))
+
+
+def draw(rng):
+    kind = rng.choice(["layer", "layer", "long", "graph", "graph", "graph", "attention", "project", "kv"])
+    model = rng.choice(["tiny", "7b", "14b", "32b", "32b"])
+    mix = rng.randrange(1 << 30)
+    bias = rng.random() < 0.3
+    if kind in ("layer", "attention"):
+        new_hi = rng.choice([16, 64, 64, 256])
+        pre_hi = rng.choice([0, 300, 4096])
+        c = _layer("", model, min(192, _log(rng, 1, 192)), (1, new_hi), (0, pre_hi), fresh=rng.choice([0.0, 0.25]),
+                   bias=bias, mix=mix)
+        room = MOST_ROWS - c["n_short"] * new_hi
+        if rng.random() < 0.4 and room > 300:
+            c.update(n_long=1, long_new=_log(rng, 256, min(room, MOST_LONG - 200)), long_pre=0)
+        if c["n_short"] * new_hi > MOST_ROWS:
+            c["n_short"] = MOST_ROWS // new_hi
+        c["kind"] = kind
+    elif kind == "long":
+        n = _log(rng, 129, 4096)
+        c = _layer("", model, 0, (1, 1), (0, 0), n_long=1, long_new=n, long_pre=rng.randint(0, MOST_LONG - 1 - n), bias=bias,
+                   mix=mix)
+    elif kind == "graph":
+        bucket = rng.choice([8, 16, 32, 64, 128, 256])
+        depth = rng.choice([d for d in (1, 2, 4, 8, 16, 32, 64) if d * bucket <= 4096])
+        n_real = rng.randint(depth // 2 + 1, depth)
+        pre_hi = rng.choice([0, 1000, 4096])
+        c = _graph("", model, 1, bucket, depth, n_real, bucket // 2 + 1, (0, pre_hi), fresh=0.25, bias=bias, mix=mix)
+    elif kind == "project":
+        c = dict(kind="project", model=model, which=rng.choice(["gate_up", "down", "o"]), rows=_log(rng, 1, 4096))
+    else:
+        lo = _log(rng, 1, 2048)
+        c = dict(kind="kv", model=model, n_seq=_log(rng, 1, 16), lo=lo, hi=2 * lo, mix=mix)
+    c.pop("name", None)
+    return c
+
+
+# ----------------------------------------------------------------------------------------------- inputs
+def _cfg(case):
+    return MODELS[case["model"]](case.get("layers", 1))
+
+
+def _lengths(case):
+    """(new, prefix) of every sequence: the long one first, as a queue served in order of arrival would hold it."""
+    g = np.random.default_rng(case["mix"])
+    if case["kind"] == "kv":
+        n = g.integers(case["lo"], case["hi"] + 1, case["n_seq"])
+        return n.astype(np.int64), np.zeros_like(n, dtype=np.int64)
+    n = case["n_short"]
+    new = g.integers(case["new_lo"], case["new_hi"] + 1, n)
+    pre = np.where(g.random(n) < case["fresh"], 0, g.integers(case["pre_lo"], case["pre_hi"] + 1, n))
+    k = case["n_long"]
+    new = np.concatenate([np.full(k, case["long_new"]), new]).astype(np.int64)
+    pre = np.concatenate([np.full(k, case["long_pre"]), pre]).astype(np.int64)
+    return new, pre
+
+
+def _generator(seed, what):
+    return torch.Generator(device="cuda").manual_seed((seed * 1000003 + what) % (1 << 62))
+
+
+def _normal(g, shape, std=1.0, mean=0.0, dtype=torch.bfloat16):
+    return torch.empty(shape, dtype=dtype, device="cuda").normal_(mean, std, generator=g)
+
+
+def _weights(cfg, seed, layer, bias):
+    g = _generator(seed, 100 + layer)
+    d, i = cfg.hidden, cfg.intermediate
+    w = {"ln1": _normal(g, (d,), 0.02, 1.0), "w_qkv": _normal(g, (cfg.qkv_dim, d), 0.02),
+         "w_o": _normal(g, (d, cfg.q_dim), 0.02), "ln2": _normal(g, (d,), 0.02, 1.0),
+         "w_gate": _normal(g, (i, d), 0.02), "w_up": _normal(g, (i, d), 0.02), "w_down": _normal(g, (d, i), 0.02)}
+    if bias:
+        w["b_qkv"] = _normal(g, (cfg.qkv_dim,), 0.5)
+    return w
+
+
+def _pools(cfg, seed, n_pages, layer):
+    g = _generator(seed, 200 + layer)
+    return (_normal(g, (n_pages, cfg.n_kv_heads, PAGE, cfg.head_dim)), _normal(g, (n_pages, cfg.n_kv_heads, cfg.head_dim, PAGE)))
+
+
+def _table(case, seed, new, pre, what, width=0):
+    """int32 [n, width] page table, the pages of the pool in random order, and the pool's size."""
+    need = (new + pre + PAGE - 1) // PAGE
+    n_pages = int(need.sum()) + 3
+    perm = np.random.default_rng([case["mix"], seed, what]).permutation(n_pages).astype(np.int32)
+    table = np.full((len(need), max(int(need.max()), width)), -1, np.int32)
+    o = 0
+    for i, c in enumerate(need):
+        table[i, :c] = perm[o:o + c]
+        o += int(c)
+    return table, n_pages
+
+
+def _i32(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.int32)).cuda()
+
+
+def _cu(n):
+    return np.concatenate([[0], np.cumsum(n)])
+
+
+def _activations(cfg, seed, rows):
+    return _normal(_generator(seed, 1), (rows, cfg.hidden), dtype=torch.float32)
+
+
+def _table_width(case):
+    return (case["pre_hi"] + case["bucket"] + PAGE - 1) // PAGE if case["kind"] == "graph" else 0
+
+
+def _project_operands(case, seed):
+    cfg, rows = _cfg(case), case["rows"]
+    n, k = {"gate_up": (2 * cfg.intermediate, cfg.hidden), "down": (cfg.hidden, cfg.intermediate),
+            "o": (cfg.hidden, cfg.q_dim)}[case["which"]]
+    g = _generator(seed, 2)
+    a, w = _normal(g, (rows, k)), _normal(g, (n, k), 0.02)
+    resid = None if case["which"] == "gate_up" else _normal(g, (rows, n), dtype=torch.float32)
+    return a, w, resid
+
+
+def prepare(case, seed):
+    cfg = _cfg(case)
+    s = {"case": case, "cfg": cfg}
+    if case["kind"] == "project":
+        s["ctx"] = api.LapsCtx(cfg, 64)
+        a, w, s["resid"] = _project_operands(case, seed)
+        if case["which"] == "gate_up":
+            i = cfg.intermediate
+            w = s["ctx"].laps_pack_gate_up(w[:i], w[i:])
+        s["a"], s["w"] = a, w
+        return s
+    new, pre = _lengths(case)
+    s["ctx"] = ctx = api.LapsCtx(cfg, int((new + pre).max()) + 64, bool(case.get("bias")))
+    table, n_pages = _table(case, seed, new, pre, 1, _table_width(case))
+    s["table"], s["cu"], s["pre"] = _i32(table), _i32(_cu(new)), _i32(pre)
+    if case["kind"] == "kv":
+        s["k"], s["v"] = _pools(cfg, seed, n_pages, 0)
+        s["table2"] = _i32(_table(case, seed, new, pre, 2)[0])
+        s["k2"], s["v2"] = _pools(cfg, seed, n_pages, 1)
+        s["rows"] = int(new.sum())
+        return s
+    rows = int(new.sum())
+    pools = [_pools(cfg, seed, n_pages, layer) for layer in range(cfg.n_layers)]
+    s["k"], s["v"] = [p[0] for p in pools], [p[1] for p in pools]
+    if case["kind"] == "attention":
+        s["q"] = _normal(_generator(seed, 1), (rows, cfg.q_dim))
+        return s
+    s["x"] = _activations(cfg, seed, rows)
+    s["out"] = torch.empty_like(s["x"])
+    s["layers"] = []
+    for layer in range(cfg.n_layers):
+        w = _weights(cfg, seed, layer, case["bias"])
+        w["w_gate_up"] = ctx.laps_pack_gate_up(w.pop("w_gate"), w.pop("w_up"))
+        s["layers"].append(w)
+    if case["kind"] == "graph":
+        s["stream"] = torch.cuda.Stream()
+        s["len"] = _i32(new)
+        s["graph"] = ctx.laps_graph_capture(s["layers"], case["bucket"], case["depth"], table.shape[1], s["k"], s["v"], s["stream"])
+    return s
+
+
+# ----------------------------------------------------------------------------------------------- one pass
+def run(s):
+    case, ctx = s["case"], s["ctx"]
+    if case["kind"] == "layer":
+        ctx.laps_prefill_layer(s["layers"][0], s["cu"], None, s["pre"], s["table"], s["k"][0], s["v"][0], s["x"], s["out"])
+        return s["out"], s["k"], s["v"]
+    if case["kind"] == "graph":
+        g = s["graph"]
+        g.laps_graph_stage(case["n_short"], s["len"], s["pre"], s["table"], s["x"], s["stream"])
+        g.laps_graph_replay(s["stream"])
+        g.laps_graph_read_output(s["x"].shape[0], s["out"], s["stream"])
+        return s["out"], s["k"], s["v"]
+    if case["kind"] == "attention":
+        return ctx.laps_attention(s["cu"], None, s["pre"], s["table"], s["k"][0], s["v"][0], s["q"])
+    if case["kind"] == "project":
+        return ctx.laps_gemm_epilogue_bf16(s["a"], s["w"], 2 if case["which"] == "gate_up" else 1, s["resid"])
+    k, v = ctx.laps_kv_gather(s["cu"], s["pre"], s["table"], s["k"], s["v"], s["rows"])
+    ctx.laps_kv_scatter(s["cu"], s["pre"], s["table2"], k, v, s["k2"], s["v2"])
+    return k, v, s["k2"], s["v2"]
+
+
+# ----------------------------------------------------------------------------------------------- what a pass needs
+def work(case):
+    cfg = _cfg(case)
+    if case["kind"] == "project":
+        d, i, r = cfg.hidden, cfg.intermediate, case["rows"]
+        n, k = {"gate_up": (2 * i, d), "down": (d, i), "o": (d, cfg.q_dim)}[case["which"]]
+        out = r * i * 2 if case["which"] == "gate_up" else r * n * 8       # bf16 out, or fp32 residual in and sum out
+        return {"bytes": 2 * n * k + 2 * r * k + out, "flops": 2 * r * n * k}
+    new, pre = _lengths(case)
+    rows, kv_token = int(new.sum()), 2 * 2 * cfg.kv_dim                    # K and V of one token, bf16
+    if case["kind"] == "kv":
+        return {"bytes": 4 * rows * kv_token, "flops": 0}
+    pairs = int((new * pre + new * (new + 1) // 2).sum())                  # visible (query, key) pairs per head
+    flops = 4 * cfg.head_dim * cfg.n_q_heads * pairs
+    if case["kind"] == "attention":
+        return {"bytes": int((new + pre).sum()) * kv_token + 4 * rows * cfg.q_dim, "flops": flops}
+    per_layer = 2 * cfg.params_per_layer + 4 * cfg.hidden + int((new + pre).sum()) * kv_token
+    return {"bytes": cfg.n_layers * per_layer + 8 * rows * cfg.hidden,
+            "flops": cfg.n_layers * (flops + 2 * rows * cfg.params_per_layer)}
+
+
+def tolerance(case):
+    if case["kind"] == "kv":
+        return "exact"
+    # About four times what the path differs from itself with its sums in another order (the same rows in a batch of 81
+    # and of 254: other tiles and K splits), or from 64 bits where the result is one bf16 rounding.
+    if case["kind"] == "project":      # 1.7e-3 from 64 bits (bf16 result); fp32 sums of up to 27648 products
+        return {"rel": 6e-3, "max": 0.02} if case["which"] == "gate_up" else {"rel": 1e-5, "max": 1e-4}
+    if case["kind"] == "attention":    # 2.3e-3 from 64 bits: probabilities and result are bf16
+        return {"rel": 9e-3, "max": 0.1}
+    if case.get("layers", 1) == 1:     # 1.4e-3 (largest single 0.014); up to 4.6e-3 from 64 bits
+        return {"rel": 8e-3, "max": 0.08}
+    return {"rel": 2e-2, "max": 0.15}  # four layers: 5.1e-3 (0.032); 1.1e-2 from 64 bits
+
+
+# ----------------------------------------------------------------------------------------------- the same in 64 bits
+def _rms(x, g, eps):
+    return x * torch.rsqrt((x * x).mean(-1, keepdim=True) + eps) * g.double()
+
+
+def _rotate(x, pos, cfg):
+    """rotate-half RoPE, pairs (j, j + hd / 2); x [T, heads, hd]."""
+    half = cfg.head_dim // 2
+    inv = cfg.rope_theta ** (-2.0 * torch.arange(half, dtype=torch.float64, device="cuda") / cfg.head_dim)
+    a = pos.double()[:, None] * inv
+    c, s = a.cos()[:, None], a.sin()[:, None]
+    lo, hi = x[..., :half], x[..., half:]
+    return torch.cat([lo * c - hi * s, hi * c + lo * s], -1)
+
+
+def _paged(pool_k, pool_v, row, n):
+    """Keys and values of the first n tokens of one page-table row, [n, kv heads, hd] each."""
+    pages = row[: (n + PAGE - 1) // PAGE].long()
+    k = pool_k[pages].transpose(1, 2).reshape(-1, pool_k.shape[1], pool_k.shape[3])[:n]
+    v = pool_v[pages].permute(0, 3, 1, 2).reshape(-1, pool_v.shape[1], pool_v.shape[2])[:n]
+    return k, v
+
+
+def _attend(cfg, q, k, v, h):
+    """Causal grouped-query attention of one sequence; q [L, heads, hd], k / v [h + L, kv heads, hd]."""
+    group, out = cfg.n_q_heads // cfg.n_kv_heads, torch.empty_like(q)
+    hidden = torch.arange(k.shape[0], device="cuda")[None] > torch.arange(q.shape[0], device="cuda")[:, None] + h
+    for head in range(cfg.n_q_heads):
+        s = q[:, head] @ k[:, head // group].T / math.sqrt(cfg.head_dim)
+        out[:, head] = torch.softmax(s.masked_fill_(hidden, -math.inf), -1) @ v[:, head // group]
+    return out
+
+
+def _tokens(new, pre, table):
+    """Position, page and place in the page of every new token."""
+    pos = np.concatenate([np.arange(p, p + n) for n, p in zip(new, pre)])
+    seq = np.repeat(np.arange(len(new)), new)
+    return (torch.from_numpy(a).cuda() for a in (pos, table[seq, pos // PAGE].astype(np.int64), pos % PAGE))
+
+
+def exact(case, seed):
+    cfg = _cfg(case)
+    if case["kind"] == "project":
+        a, w, resid = _project_operands(case, seed)
+        y = a.double() @ w.double().T
+        if resid is not None:
+            return resid.double() + y
+        gate, up = y[:, : cfg.intermediate], y[:, cfg.intermediate:]
+        return torch.nn.functional.silu(gate) * up
+    new, pre = _lengths(case)
+    rows, cu = int(new.sum()), _cu(new)
+    table, n_pages = _table(case, seed, new, pre, 1, _table_width(case))
+    if case["kind"] == "kv":
+        kp, vp = _pools(cfg, seed, n_pages, 0)
+        k, v = (torch.cat(t) for t in zip(*[_paged(kp, vp, _i32(table[i]), int(n)) for i, n in enumerate(new)]))
+        k2, v2 = _pools(cfg, seed, n_pages, 1)
+        _, page, at = _tokens(new, pre, _table(case, seed, new, pre, 2)[0])
+        k2[page, :, at], v2[page, :, :, at] = k, v
+        return k.double(), v.double(), k2.double(), v2.double()
+    pos, page, at = _tokens(new, pre, table)
+    d_table = _i32(table)
+
+    def attend(q, kp, vp):
+        return torch.cat([_attend(cfg, q[cu[i]:cu[i + 1]], *(t.double() for t in _paged(kp, vp, d_table[i], int(n + p))), int(p))
+                          for i, (n, p) in enumerate(zip(new, pre)) if n])
+
+    if case["kind"] == "attention":
+        q = _normal(_generator(seed, 1), (rows, cfg.q_dim)).double().view(rows, cfg.n_q_heads, cfg.head_dim)
+        return attend(q, *_pools(cfg, seed, n_pages, 0)).reshape(rows, -1)
+    x, ks, vs = _activations(cfg, seed, rows).double(), [], []
+    for layer in range(cfg.n_layers):
+        w = _weights(cfg, seed, layer, case["bias"])
+        kp, vp = (t.double() for t in _pools(cfg, seed, n_pages, layer))
+        y = _rms(x, w["ln1"], cfg.rms_eps) @ w["w_qkv"].double().T
+        if case["bias"]:
+            y = y + w["b_qkv"].double()
+        q, k, v = (t.view(rows, -1, cfg.head_dim) for t in y.split([cfg.q_dim, cfg.kv_dim, cfg.kv_dim], 1))
+        kp[page, :, at], vp[page, :, :, at] = _rotate(k, pos, cfg), v
+        x = x + attend(_rotate(q, pos, cfg), kp, vp).reshape(rows, -1) @ w["w_o"].double().T
+        r = _rms(x, w["ln2"], cfg.rms_eps)
+        act = torch.nn.functional.silu(r @ w["w_gate"].double().T)
+        act *= r @ w["w_up"].double().T
+        x = x + act @ w["w_down"].double().T
+        ks.append(kp), vs.append(vp)
+    return x, ks, vs
