@@ -179,6 +179,17 @@ def _activations(cfg, seed, rows):
     return _normal(_generator(seed, 1), (rows, cfg.hidden), dtype=torch.float32)
 
 
+_STREAMS = []
+
+
+def _stream():
+    """The stream that a program's short-request runner replays its graphs on: one for all its shapes, since a step of
+    the schedule runs alone."""
+    if not _STREAMS:
+        _STREAMS.append(torch.cuda.Stream())
+    return _STREAMS[0]
+
+
 def _table_width(case):
     return (case["pre_hi"] + case["bucket"] + PAGE - 1) // PAGE if case["kind"] == "graph" else 0
 
@@ -228,7 +239,7 @@ def prepare(case, seed):
         w["w_gate_up"] = ctx.laps_pack_gate_up(w.pop("w_gate"), w.pop("w_up"))
         s["layers"].append(w)
     if case["kind"] == "graph":
-        s["stream"] = torch.cuda.Stream()
+        s["stream"] = _stream()
         s["len"] = _i32(new)
         s["graph"] = ctx.laps_graph_capture(s["layers"], case["bucket"], case["depth"], table.shape[1], s["k"], s["v"], s["stream"])
     return s
