@@ -87,8 +87,37 @@ static size_t partial_bytes_for(const laps_model_cfg& c, int m) {
     return t > b ? t : b;
 }
 
+static constexpr int kAnyPages = 1 << 24;
+
+static size_t widest_projection(const laps_model_cfg& c) {
+    const int qkv = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+    int n = 2 * c.intermediate > qkv ? 2 * c.intermediate : qkv;
+    return c.hidden > n ? c.hidden : n;
+}
+
+// What the K splits of a batch of more than 128 rows may take: one slice of the widest projection or, if that is more,
+// what the attention's key-split results take with wide page tables (51 MB at head_dim 128).
+static size_t partial_cap_for(const laps_model_cfg& c, int m) {
+    const size_t one = (size_t)m * widest_projection(c) * sizeof(float), at = laps_attn_partial_bytes(c.head_dim, kAnyPages);
+    const size_t cap = one > at ? one : at;
+    return cap < LAPS_PARTIAL_CAP ? cap : LAPS_PARTIAL_CAP;
+}
+
+// Bytes of the partial sums a batch of exactly m > 128 rows writes (run_layers makes the same plans).
+static size_t split_bytes_for(const laps_model_cfg& c, int m) {
+    const int qd = c.n_q_heads * c.head_dim, qkv = qd + 2 * c.n_kv_heads * c.head_dim;
+    const int shape[4][3] = {{qkv, c.hidden, EPI_PARTIAL}, {c.hidden, qd, EPI_RESID}, {2 * c.intermediate, c.hidden, EPI_SWIGLU},
+                             {c.hidden, c.intermediate, EPI_RESID}};
+    size_t b = 0;
+    for (const auto& p : shape) {
+        const size_t t = (size_t)laps_gemm_plan(m, p[0], p[1], 0, p[2], partial_cap_for(c, m)).split * m * p[0] * sizeof(float);
+        b = t > b ? t : b;
+    }
+    return b;
+}
+
 // max_pages: width of the page tables the workspace will serve (default: any width)
-static WsLayout ws_layout(const laps_model_cfg& c, int max_tokens, int max_seqs, int max_pages = 1 << 24) {
+static WsLayout ws_layout(const laps_model_cfg& c, int max_tokens, int max_seqs, int max_pages = kAnyPages) {
     WsLayout w;
     const size_t M = (size_t)max_tokens;
     const int qd = c.n_q_heads * c.head_dim;
@@ -103,16 +132,14 @@ static WsLayout ws_layout(const laps_model_cfg& c, int max_tokens, int max_seqs,
     w.attn = o;       o += align256(M * qd * 2);
     w.act = o;        o += align256(M * c.intermediate * 2);
     w.x_mid = o;      o += align256(M * c.hidden * 4);
-    // split-K partial sums: the split factor depends on the number of row tiles, and the byte count
-    // grows with m inside one row-tile count, so the maximum over m <= max_tokens is reached at a
-    // row-tile boundary (or at max_tokens, or at the largest skinny m = 128).
-    size_t pb = partial_bytes_for(c, max_tokens);
+    // Partial sums of the K splits.  With page tables of any width this grows with max_tokens, so that a workspace
+    // sized for a maximum serves every smaller batch.
+    size_t pb = partial_bytes_for(c, max_tokens < 128 ? max_tokens : 128);
     if (max_tokens > 128) {
-        const size_t t = partial_bytes_for(c, 128);
+        size_t t = M * widest_projection(c) * sizeof(float);
         pb = t > pb ? t : pb;
-    }
-    for (int m = 256; m < max_tokens; m += 256) {
-        const size_t t = partial_bytes_for(c, m);
+        if (max_pages != kAnyPages) t = split_bytes_for(c, max_tokens);        // exactly these rows (a captured graph)
+        else t = laps_attn_partial_bytes(c.head_dim, kAnyPages);               // at least partial_cap_for any rows
         pb = t > pb ? t : pb;
     }
     {   // the same region holds the attention's key-split partial results (the two uses never overlap in time)
@@ -270,9 +297,9 @@ struct BatchDesc {
 // One projection.  `want` is the epilogue the caller would like fused; the plan falls back to raw
 // K-slice partial sums when it splits K.  Returns the plan so the caller knows which case ran.
 static int run_gemm(laps_ctx* c, int cls, bool capturing, const bf16_t* a, const bf16_t* w, int m, int n, int k,
-                    int want, float* partial, float* out_f32, const float* resid, bf16_t* out_bf16, const int* row_live,
-                    GemmPlan* plan, hipStream_t s) {
-    const GemmPlan p = laps_gemm_plan(m, n, k, 0, want);
+                    int want, float* partial, size_t partial_cap, float* out_f32, const float* resid, bf16_t* out_bf16,
+                    const int* row_live, GemmPlan* plan, hipStream_t s) {
+    const GemmPlan p = laps_gemm_plan(m, n, k, 0, want, partial_cap);
     *plan = p;
     ProfScope ps(c, s, cls, capturing);
     if (p.epi == EPI_PARTIAL) return laps_gemm_launch(p, a, w, m, n, k, partial, nullptr, nullptr, row_live, s);
@@ -300,6 +327,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
     bf16_t* act = reinterpret_cast<bf16_t*>(ws + L.act);
     float* x_mid = reinterpret_cast<float*>(ws + L.x_mid);
     float* partial = reinterpret_cast<float*>(ws + L.partial);
+    const size_t partial_cap = partial_cap_for(cf, M);
 
     if (r0_staged == nullptr) {
         {
@@ -325,7 +353,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         // q, k, v: GEMM -> K-slice sums -> bias + RoPE + KV append
         const bf16_t* r_in = (l == 0 && r0_staged != nullptr) ? r0_staged : r;
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_QKV, capturing, r_in, static_cast<const bf16_t*>(lw.w_qkv), M, qkv, d, EPI_PARTIAL,
-                          partial, nullptr, nullptr, nullptr, tok_pos, &gp, s));
+                          partial, partial_cap, nullptr, nullptr, nullptr, tok_pos, &gp, s));
         {
             ProfScope ps(c, s, LAPS_K_EPI_QKV, capturing);
             LAPS_TRY(laps_launch_epi_qkv(partial, gp.split, cf.has_qkv_bias ? static_cast<const bf16_t*>(lw.b_qkv) : nullptr,
@@ -340,7 +368,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         // x_mid = resid + attn W_o^T ; r = rmsnorm(x_mid; ln2)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_O, capturing, attn, static_cast<const bf16_t*>(lw.w_o), M, d, qd, EPI_RESID,
-                          partial, x_mid, resid, nullptr, tok_pos, &gp, s));
+                          partial, partial_cap, x_mid, resid, nullptr, tok_pos, &gp, s));
         if (gp.epi == EPI_RESID) {
             ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);
             LAPS_TRY(laps_launch_rmsnorm(x_mid, static_cast<const bf16_t*>(lw.ln2_w), r, M, d, cf.rms_eps, tok_pos, s));
@@ -351,7 +379,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         // act = silu(r W_g^T) * (r W_u^T)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_GATEUP, capturing, r, static_cast<const bf16_t*>(lw.w_gate_up), M, 2 * I, d,
-                          EPI_SWIGLU, partial, nullptr, nullptr, act, tok_pos, &gp, s));
+                          EPI_SWIGLU, partial, partial_cap, nullptr, nullptr, act, tok_pos, &gp, s));
         if (gp.epi != EPI_SWIGLU) {
             ProfScope ps(c, s, LAPS_K_EPI_SWIGLU, capturing);
             LAPS_TRY(laps_launch_epi_swiglu(partial, gp.split, act, M, I, tok_pos, s));
@@ -359,7 +387,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         // x_out = x_mid + act W_d^T ; r = rmsnorm(x_out; next layer's ln1)
         const bf16_t* next_ln = (l + 1 < n_layers) ? static_cast<const bf16_t*>(w[l + 1].ln1_w) : nullptr;
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_DOWN, capturing, act, static_cast<const bf16_t*>(lw.w_down), M, d, I, EPI_RESID,
-                          partial, x_out, x_mid, nullptr, tok_pos, &gp, s));
+                          partial, partial_cap, x_out, x_mid, nullptr, tok_pos, &gp, s));
         if (gp.epi == EPI_RESID) {
             if (next_ln) {
                 ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);

@@ -43,6 +43,9 @@ struct Traits {
     static constexpr int MI = WTM / 32, NI = WTN / 32;
     static constexpr int A_LOADS = BM * CHUNKS / NT, B_LOADS = BN * CHUNKS / NT;
     static constexpr int LDS_BYTES = 2 * (BM + BN) * BK * 2;
+    // 4-wave workgroups small enough for two of them on a compute unit get the registers for it (two waves per SIMD):
+    // one's epilogue and barriers then hide under the other's products
+    static constexpr int WAVES_PER_SIMD = (NT == 256 && 2 * LDS_BYTES <= 160 * 1024) ? 2 : 1;
     static_assert(BM * CHUNKS % NT == 0 && BN * CHUNKS % NT == 0, "tile rows must divide over threads");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA");
 };
@@ -152,7 +155,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
 // WS > 1 is for the bandwidth-bound skinny shapes; the K loop is then unrolled WS times so every set
 // index is static, and the K slice must hold a multiple of WS slabs.
 template <int BM, int BN, int WM, int WN, int EPI, int WS>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIMD)) void gemm_kernel(const GemmArgs g) {
     using T = Traits<BM, BN, WM, WN>;
     extern __shared__ __align__(16) unsigned char smem[];
     u32x4* As = reinterpret_cast<u32x4*>(smem);  // [2][BM][CHUNKS]
@@ -170,7 +173,16 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_kernel(const GemmArgs g) {
     if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
         bool any = false;
         for (int r = tid; r < BM; r += T::NT) any |= (m0 + r < M) && g.row_live[m0 + r] >= 0;
-        if (!__syncthreads_or(any)) return;
+        // in the slab buffers, not in LDS of its own: two 192x128 workgroups take exactly a unit's 160 KB
+        int* flag = reinterpret_cast<int*>(smem);
+        const bool wave_any = __builtin_amdgcn_ballot_w64(any) != 0;
+        if ((tid & 63) == 0) flag[tid >> 6] = wave_any;
+        __syncthreads();
+        int live = 0;
+#pragma unroll
+        for (int w = 0; w < T::NT / 64; ++w) live |= flag[w];
+        if (!live) return;
+        __syncthreads();   // the flags are read before the first slab overwrites them
     }
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -359,37 +371,45 @@ int launch_tile(const GemmArgs& a, hipStream_t s) {
 
 struct TileDef {
     int bm, bn;
-    double eff;  // relative MFMA efficiency of the tile shape (operand reuse), 256x256 = 1
+    int ws;            // slabs kept in flight per workgroup where the K slices allow it
+    double fill, slab, part;   // cost model of launches above 128 rows, see laps_gemm_plan
 };
-// index = GemmPlan::cfg
+// index = GemmPlan::cfg.  The cost columns are a fit over 4600 launches (all tiles and K splits on the 7B, 14B and
+// 32B projections at 23 row counts from 129 to 8192, weights cold; rms error 6 %): microseconds a workgroup takes besides its slabs,
+// microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.
 constexpr TileDef kTiles[] = {
-    {128, 128, 0.70},  // 0: skinny fallback (n % 256 != 0), 4 waves of 64x64
-    {128, 64, 0.50},   // 1: skinny fallback (n % 128 != 0)
-    {256, 256, 1.00},  // 2: 4 waves of 128x128
-    {256, 224, 0.93},  // 3: 4 waves of 64x224 (N = 7168 -> 32 column tiles)
-    {256, 160, 0.85},  // 4: 4 waves of 64x160 (N = 5120 -> 32 column tiles)
-    {128, 256, 0.80},  // 5: skinny, 8 waves of 64x64: one workgroup per CU, A slab shared by 256 columns
+    {128, 128, 2, 1.28, 0.524, 0.00},  // 0: 4 waves of 64x64, two workgroups per compute unit
+    {128, 64, 2, 1.20, 0.350, 0.00},   // 1: 4 waves of 64x32, for n % 128 != 0
+    {256, 256, 1, 5.95, 1.515, 0.26},  // 2: 4 waves of 128x128
+    {256, 224, 1, 5.86, 1.329, 0.24},  // 3: 4 waves of 64x224 (N = 7168 -> 32 column tiles)
+    {256, 160, 1, 4.31, 1.078, 0.27},  // 4: 4 waves of 64x160 (N = 5120 -> 32 column tiles)
+    {128, 256, 2, 4.89, 0.943, 0.13},  // 5: 8 waves of 64x64: the streaming tile, A slab shared by 256 columns
+    {192, 256, 2, 5.76, 1.163, 0.21},  // 6: 4 waves of 96x128
+    {192, 128, 1, 2.10, 0.715, 0.08},  // 7: 4 waves of 96x64, two workgroups per compute unit
+    {256, 128, 2, 4.54, 0.866, 0.27},  // 8: 4 waves of 128x64
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 }  // namespace
 
+// Row class and columns of a tile shape.  A 192-row tile counts as one of the 256-row class: it is only taken where
+// cutting m into ceil(m / 256) row tiles leaves at most 192 rows to each, so the number of row tiles is that class's.
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn) {
-    *bm = (cfg >= 0 && cfg < kNumTiles) ? kTiles[cfg].bm : 0;
+    *bm = (cfg >= 0 && cfg < kNumTiles) ? (kTiles[cfg].bm == 192 ? 256 : kTiles[cfg].bm) : 0;
     *bn = (cfg >= 0 && cfg < kNumTiles) ? kTiles[cfg].bn : 0;
 }
 
 // Picks tile shape and K split.
-GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi) {
+GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap) {
     GemmPlan p;
     const int ksteps = k / BK;
     auto finish = [&](int cfg, int split) {
         if (split > ksteps) split = ksteps;
         if (split < 1) split = 1;
         int per = (ksteps + split - 1) / split;
-        // skinny tiles keep 2 slabs in flight: every K slice must then hold a multiple of 2 slabs
+        // with 2 slabs in flight every K slice must hold a multiple of 2 slabs
         p.ws = 1;
-        if (kTiles[cfg].bm == 128 && ksteps % 2 == 0) {
+        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0) {
             per = (per + 1) / 2 * 2;
             p.ws = 2;
         }
@@ -425,40 +445,54 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi) {
         const int split = force_split > 0 ? force_split : auto_split(cfg);
         return finish(cfg, split);
     }
-    // compute-bound: minimise rounds(tiles*split over 256 CUs) * per-workgroup MFMA time + the
-    // time to write and re-read the partial sums of a split
+    // Above 128 rows no bound decides alone: at a few hundred rows the weight stream, the number of workgroups and the
+    // rows a tile pads all count, further up the rounds of tiles over the 256 compute units do.  Time of a launch:
+    //   rounds * (fill + slabs * slab) [a partly filled chip runs its slabs up to `part` faster: less traffic, more
+    //   clock], not less than the weights take from HBM; a split adds the partial sums written, the reduce launch and
+    //   the reading back; an un-split residual epilogue adds the RMSNorm launch that the reduce kernel would contain.
+    // Over the 230 measured shapes the choice is 1 % slower than the fastest measured one on average, more than 5 % in
+    // 18.  Against the one rule before it (256-row tiles only) the 32B layer's projections take, q/k/v, o, gate/up,
+    // down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows 42 -> 36, 41 -> 36, 272 -> 217,
+    // 142 -> 116; 7B at 256 rows 35 -> 19, 38 -> 22, 92 -> 92, 63 -> 53.
     double best = 1e30;
-    int best_cfg = 2, best_split = 1;
-    for (int cfg = 2; cfg <= 4; ++cfg) {
+    int best_cfg = -1, best_split = 1;
+    for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
-        if (n % t.bn != 0) continue;
-        if (want_epi == EPI_SWIGLU && cfg != 2) continue;
-        const int tiles = ((m + t.bm - 1) / t.bm) * (n / t.bn);
-        for (int s = 1; s <= 8; ++s) {
-            if (force_split > 0 && s != force_split) continue;
-            if (s > 1 && ksteps / s < 16) break;
-            const long wgs = (long)tiles * s;
+        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0)) continue;
+        if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
+        const int tiles_m = (m + t.bm - 1) / t.bm;
+        if (t.bm == 192 && tiles_m != (m + 255) / 256) continue;
+        const int max_split = force_split > 0 ? force_split : 16;
+        for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
+            const double partial = 4.0 * s * (double)m * n;
+            if (force_split == 0 && s > 1 && (ksteps / s < 4 || partial > (double)partial_cap)) break;
+            int per = (ksteps + s - 1) / s;
+            if (t.ws == 2 && ksteps % 2 == 0) per = (per + 1) / 2 * 2;
+            const long wgs = (long)tiles_m * (n / t.bn) * s;
             const long rounds = (wgs + 255) / 256;
-            const double wg_flops = 2.0 * t.bm * t.bn * (double)k / s;
-            const double t_mma = rounds * wg_flops / (2.5e15 / 256 * 0.62 * t.eff);
-            const double t_part = s > 1 ? (2.0 * s * m * (double)n * 4) / 4.0e12 + 4e-6 : 0.0;
-            const double cost = t_mma + t_part;
-            if (cost < best) {
-                best = cost;
+            const double filled = wgs < 256 ? wgs / 256.0 : 1.0;
+            double us = 4.0 + rounds * (t.fill + per * t.slab * (1.0 - t.part * (1.0 - filled)));
+            const double stream = 4.0 + 2.0 * n * (double)k / 3.94e6;
+            us = us > stream ? us : stream;
+            if (s > 1) us += partial / 8.5e6;
+            if (want_epi == EPI_PARTIAL || s > 1) us += partial / 6.2e6;   // the row kernel's reading
+            if (want_epi != EPI_PARTIAL && s > 1) us += 3.9;
+            if (want_epi == EPI_RESID && s == 1) us += 4.0 + 6.0 * m * (double)n / 4.5e6;
+            if (us < best) {
+                best = us;
                 best_cfg = cfg;
                 best_split = s;
             }
         }
     }
-    if (best >= 1e30) {  // no wide tile divides n: fall back to the 128- or 64-wide panels
-        const int cfg = (n % 128 == 0) ? 0 : 1;
-        if (cfg == 1 && want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
-        return finish(cfg, force_split > 0 ? force_split : 1);
+    if (best_cfg < 0) {  // SwiGLU on n % 128 != 0: partial sums of the 64-column panels
+        want_epi = EPI_PARTIAL;
+        return finish(1, force_split > 0 ? force_split : 1);
     }
     return finish(best_cfg, best_split);
 }
 
-size_t laps_gemm_partial_bytes(int m, int n, int k) {
+size_t laps_gemm_partial_bytes(int m, int n, int k) {   // m <= 128
     // upper bound over the epilogue kinds the layer driver may request
     size_t b = 0;
     for (int e = 0; e < 3; ++e) {
@@ -525,6 +559,21 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_RESID, 2);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_SWIGLU, 1);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_SWIGLU, 2);
+        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_PARTIAL, 2);
+        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_RESID, 1);
+        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_RESID, 2);
+        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_SWIGLU, 1);
+        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_SWIGLU, 2);
+        LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_RESID, 1);
+        LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_SWIGLU, 1);
+        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_PARTIAL, 2);
+        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_RESID, 1);
+        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_RESID, 2);
+        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_SWIGLU, 1);
+        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_SWIGLU, 2);
         default: break;
     }
 #undef LAPS_TILE_CASE

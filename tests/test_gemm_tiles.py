@@ -1,0 +1,64 @@
+"""The GEMM tiles above 128 rows, at the edges of the row tiles and with K slices of an odd and an even number of
+slabs, against float64; and, on the CPU, the bound that the partial sums of their K splits keep."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2601_11589_amd import api, inputs
+
+PARTIAL, RESID, SWIGLU = 0, 1, 2
+
+
+def plan(m, n, k, epi):
+    out = (C.c_int32 * 7)()
+    assert api.lib().laps_gemm_plan_info(C.c_int32(m), C.c_int32(n), C.c_int32(k), C.c_int32(0), C.c_int32(epi), out) == 0
+    return dict(zip(("bm", "bn", "split", "k_per", "epi", "ws", "wgs"), list(out)))
+
+
+@pytest.mark.parametrize("cfgf", [inputs.tiny_cfg, inputs.qwen7b_cfg, inputs.qwen14b_cfg, inputs.qwen32b_cfg])
+def test_partial_sums_of_an_automatic_split_stay_within_48_mib(cfgf):
+    c = cfgf(1)
+    shapes = ((c.qkv_dim, c.hidden, PARTIAL), (c.hidden, c.q_dim, RESID), (2 * c.intermediate, c.hidden, SWIGLU),
+              (c.hidden, c.intermediate, RESID))
+    for m in list(range(129, 800, 7)) + [1024, 2048, 4096, 12000]:
+        for n, k, epi in shapes:
+            p = plan(m, n, k, epi)
+            assert p["split"] == 1 or p["split"] * m * n * 4 <= 48 << 20, (m, n, k, p)
+
+
+# (rows, columns, K): 128x128 with odd / even slabs and K splits, 192x128 with one and two slices, 256x128 with odd /
+# even slabs, 192x256 with even slabs (one row tile and two) and 256x256 at a ragged last row tile
+SHAPES = [(129, 128, 64), (191, 256, 192), (257, 128, 1088), (255, 384, 128), (513, 8192, 64), (576, 8192, 128),
+          (513, 3584, 1024), (576, 3584, 1088), (1025, 4096, 576), (1025, 4096, 512), (192, 27648, 5120),
+          (300, 27648, 5120), (384, 5120, 13824), (700, 27648, 1024)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", SHAPES)
+def test_tiles_above_128_rows_match_float64(m, n, k):
+    ctx = api.LapsCtx(inputs.tiny_cfg(1), max_positions=64)
+    g = torch.Generator(device="cuda").manual_seed(m * 31 + n + k)
+    a = torch.empty((m, k), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=g)
+    want = a.double() @ w.double().T
+    print("plan", plan(m, n, k, PARTIAL), plan(m, n, k, RESID), plan(m, n, k, SWIGLU), flush=True)
+
+    def rel(got, ref):
+        return float((got.double() - ref).norm() / ref.norm())
+
+    assert rel(ctx.laps_gemm_bf16(a, w), want) < 2e-6          # fp32 sums of exact products
+    if n <= 8192:
+        resid = torch.empty((m, n), device="cuda").normal_(0, 4, generator=g)
+        assert rel(ctx.laps_gemm_epilogue_bf16(a, w, 1, resid=resid), resid.double() + want) < 2e-6
+    gate, up = want.view(m, n // 64, 2, 32).unbind(2)            # gate and up columns interleaved in blocks of 32
+    ref = (torch.nn.functional.silu(gate) * up).reshape(m, n // 2)
+    got = ctx.laps_gemm_epilogue_bf16(a, w, 2).double()
+    # One bf16 rounding (half an ulp is at most 2^-8 of the value) of fp32 sums and an fp32 SiLU.  A sum of k products,
+    # std 0.02 sqrt(k), takes k / 16 roundings of 2^-24 in a random walk: six standard deviations are
+    # delta = 6 * 2^-24 * 0.02 sqrt(k) * sqrt(k / 16); silu' is below 1.1, so the product moves by at most
+    # delta * (1.1 |up| + |gate|).
+    delta = 6 * 2.0 ** -24 * 0.02 * k / 4
+    slack = (delta * (1.1 * up.abs() + gate.abs())).reshape(m, n // 2) + 1e-6
+    assert bool(((got - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all())
+    ctx.close()
