@@ -31,23 +31,29 @@
 // the splits a given sequence really uses is decided on the device from its length.
 #include "laps_internal.h"
 
+#include <climits>
 #include <type_traits>
 
 namespace {
 
-constexpr int KT = 64;      // keys per tile (4 pages)
+constexpr int KT = LAPS_ATTN_KT;   // keys per tile (4 pages)
 
 __device__ __forceinline__ int swz8(int row, int c) { return c ^ ((row & 7) ^ ((row >> 3) & 1)); }
 __device__ __forceinline__ int swz16(int row, int c) { return c ^ (row & 15); }
 
 // per-sequence number of query-row blocks, their exclusive prefix sum, and the sequence of every work item
 // (single workgroup).  The item table spares each attention workgroup a chain of dependent loads.
-__global__ __launch_bounds__(256) void attn_sched_kernel(const int* __restrict__ new_len, int n_seq, int group,
-                                                          int rows_per_wg, int* __restrict__ tile_start,
-                                                          int* __restrict__ item_seq, int max_items) {
+__global__ __launch_bounds__(256) void attn_sched_kernel(const int* __restrict__ new_len,
+                                                          const int* __restrict__ prefix_len, int n_seq, int group,
+                                                          int n_kv, int max_pages, int rows_per_wg,
+                                                          int* __restrict__ tile_start, int* __restrict__ item_seq,
+                                                          int max_items, int n_wgs, int* pre, int4* bounds) {
     __shared__ int buf[256];
     __shared__ int carry;
     laps_dev_attn_sched(new_len, n_seq, group, rows_per_wg, tile_start, item_seq, max_items, buf, &carry);
+    if (n_wgs > 0)
+        laps_dev_attn_bounds(new_len, prefix_len, n_seq, group, n_kv, max_pages, tile_start, item_seq, max_items, n_wgs,
+                             pre, bounds, buf, &carry);
 }
 
 // NW waves per workgroup, one 32-row query tile per wave: rows per workgroup = 32 * NW.  With NW = 8
@@ -62,17 +68,11 @@ __device__ __forceinline__ void split_geometry(int kv_end, int n_split, int* eff
     *per = (nt + e - 1) / e;
 }
 
-// A prefix length that the page table cannot hold (a corrupted or stale array) must neither index past the
-// table nor make a workgroup walk millions of key tiles: cut to what max_pages pages can address.
-__device__ __forceinline__ int clamp_prefix(int h, int new_len, int max_pages) {
-    const int room = max_pages * LAPS_PAGE - new_len;
-    h = h < room ? h : room;
-    return h > 0 ? h : 0;
-}
-
 // Two waves per SIMD in every variant (second launch-bound argument): with 4 waves per workgroup that is two
 // resident workgroups per compute unit, which the key-streaming launches need to cover the memory latency.
-template <int HD, int NW, bool SPLIT>
+// PERSIST: a fixed number of workgroups, each walking its share of the batch (laps_dev_attn_bounds); a share may begin
+// and end inside a unit, whose parts then go through partial results like the splits.
+template <int HD, int NW, bool SPLIT, bool PERSIST>
 __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         const bf16_t* __restrict__ k_pool,
@@ -83,7 +83,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
                                                         const int* __restrict__ page_table, int max_pages,
                                                         const int* __restrict__ tile_start,
                                                         const int* __restrict__ item_seq, int n_seq, int n_q,
-                                                        int n_kv, float scale_log2e, int n_pool_pages, int n_tokens) {
+                                                        int n_kv, float scale_log2e, int n_pool_pages, int n_tokens,
+                                                        int max_items, const int4* __restrict__ bounds) {
     constexpr int NTHR = NW * 64;
     constexpr int CPR = HD / 8;            // 16-byte chunks per K row
     constexpr int CPP = HD * 2;            // 16-byte chunks per page (K and V alike)
@@ -96,13 +97,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
     __shared__ __align__(16) u32x4 Ks[2][KT * CPR];   // double buffered: one barrier per tile
     __shared__ __align__(16) u32x4 Vs[2][HD * 8];
 
-    const int item = blockIdx.x;
-    if (item >= tile_start[n_seq]) return;
+    const int n_items_all = tile_start[n_seq], G = n_q / n_kv;
+    // one unit: (item, kv head), key tiles [t0, t1) of it if PERSIST; slot: where a cut unit's result goes
+    auto unit = [&](const int item, const int kvh, const int t0, const int t1, const int slot) __attribute__((always_inline)) {
+    if (item >= n_items_all) return;
     const int seq = item_seq[item];
     const int qtile = item - tile_start[seq];
-    const int kvh = blockIdx.y;
-    const int G = n_q / n_kv;
-    const int L = new_len[seq], H = clamp_prefix(prefix_len[seq], L, max_pages);
+    const int L = new_len[seq], H = laps_dev_clamp_prefix(prefix_len[seq], L, max_pages);
     // row offsets come from the caller's device array: rows outside the batch are never touched, whatever it holds
     const int rs = row_start[seq];
     if (rs < 0 || L > n_tokens - rs) return;
@@ -124,6 +125,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
         kv_begin = z * per * KT;
         kv_end = (z + 1) * per * KT < kv_end_all ? (z + 1) * per * KT : kv_end_all;
     }
+    if (PERSIST) {
+        kv_begin = t0 * KT;
+        kv_end = t1 < (kv_end_all + KT - 1) / KT ? t1 * KT : kv_end_all;
+    }
+    const bool whole = SPLIT ? eff == 1 : (!PERSIST || (kv_begin == 0 && kv_end == kv_end_all));
     const int* pt = page_table + (size_t)seq * max_pages;
     const size_t tok0 = (size_t)rs;
     const int q_stride = n_q * HD;
@@ -474,9 +480,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
                 half_step(visible(j0 + KT, 0), sm, visible(j0, 0), b ^ 1, 0, s_lo, s_hi, p_hi, b, 0, p_lo);
             }
         };
-        // SPLIT is never combined with this variant: a wave's first half tile always shows key 0 to every row, so
-        // the running maximum is finite from the first softmax on
+        // SPLIT is never combined with this variant: a wave's first half tile always shows a key to every row (key 0,
+        // or the first key after a cut, which laps_dev_attn_bounds places where all rows see it), so the running
+        // maximum is finite from the first softmax on
         static_assert(!SPLIT, "the pipelined loop serves un-split launches only");
+        if (PERSIST) __syncthreads();   // the unit before is done with the LDS tiles
         fetch_ids(kv_begin, kv_begin);
         load_k();
         load_v();
@@ -550,11 +558,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
     //      ni*32 + 8*(i/4) + 4*(lane/32) + i%4
     // the pipelined loop holds complete row sums, the plain one a lane's share
     const float l_tot = (NW == 8) ? l_run : l_run + __shfl_xor(l_run, 32, 64);
-    if (SPLIT && eff > 1) {
+    if (!whole) {
         // partial result of this key range: accumulator as [4-float chunk][row] so that the 32 rows of a half
         // wave write consecutive 16-byte pieces; (running max, row sum) per row
         if (row_id < n_rows) {
-            const size_t blk = ((size_t)item * n_kv + kvh) * gridDim.z + blockIdx.z;
+            const size_t blk = PERSIST ? (size_t)slot : ((size_t)item * n_kv + kvh) * gridDim.z + blockIdx.z;
             const int row = wave * 32 + lm;
             f32x4* po = reinterpret_cast<f32x4*>(part_o) + blk * (size_t)(HD / 4) * ROWS;
 #pragma unroll
@@ -586,6 +594,81 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
                 *reinterpret_cast<u32x2*>(op + ni * 32 + 8 * a + 4 * lh) = w;
             }
     }
+    };   // unit
+
+    if constexpr (!PERSIST) {
+        unit(blockIdx.x, blockIdx.y, 0, 0, 0);
+    } else {
+        // consecutive shares (mostly the same kv head) on one XCD
+        const int w = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+        const int4 b = bounds[w], e = bounds[w + 1];
+        const int n_items = n_items_all < max_items ? n_items_all : max_items;
+        int kvh = b.x, item = b.y, t = b.z, slot = 2 * w;
+        while (kvh < n_kv && (kvh != e.x || item != e.y || t < e.z)) {
+            const bool last = kvh == e.x && item == e.y;
+            unit(item, kvh, t, last ? e.z : INT_MAX, slot);
+            if (last) break;
+            t = 0;
+            slot = 2 * w + 1;   // a share's first unit may be cut at its begin, its last at its end; none between
+            if (++item >= n_items) item = 0, ++kvh;
+        }
+    }
+}
+
+// Merges the cut units of the persistent kernel: out = sum_p 2^(m_p - M) O_p / sum_p 2^(m_p - M) l_p over its parts p
+// in key order, M = max_p m_p.  Workgroup (w, z) stands at the bound between shares w and w + 1; where that is the first
+// cut of a unit it merges the unit's parts for HD / 4 columns, a thread per row.
+template <int HD>
+__global__ __launch_bounds__(LAPS_ATTN_LONG_ROWS) void attn_merge_cut_kernel(
+    bf16_t* __restrict__ out, const float* __restrict__ part_o, const float* __restrict__ part_ml,
+    const int* __restrict__ row_start, const int* __restrict__ new_len, const int* __restrict__ tile_start,
+    const int* __restrict__ item_seq, const int4* __restrict__ bounds, int n_wgs, int n_seq, int n_q, int n_kv, int n_tokens) {
+    constexpr int ROWS = LAPS_ATTN_LONG_ROWS;
+    constexpr int NC = HD / 16;   // 4-float chunks per thread
+    const int w = blockIdx.x + 1;
+    const int4 here = bounds[w];
+    if (here.z == 0 || here.x >= n_kv) return;    // not inside a unit
+    const int4 before = bounds[w - 1];
+    const bool same = before.x == here.x && before.y == here.y;
+    if (same && before.z > 0) return;             // the unit's first cut merges it
+    const int seq = item_seq[here.y], G = n_q / n_kv, L = new_len[seq];
+    const int rs = row_start[seq];
+    if (rs < 0 || L > n_tokens - rs) return;      // as in attn_kernel
+    const int row = threadIdx.x, row_id = (here.y - tile_start[seq]) * ROWS + row;
+    if (row_id >= L * G) return;
+    f32x4 acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_all = -INFINITY, l_all = 0.f;
+    auto add = [&](int slot) {
+        const float m = part_ml[(size_t)slot * 2 * ROWS + row], l = part_ml[(size_t)slot * 2 * ROWS + ROWS + row];
+        const f32x4* po = reinterpret_cast<const f32x4*>(part_o) + ((size_t)slot * (HD / 4) + blockIdx.y * NC) * ROWS + row;
+        f32x4 v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = po[(size_t)c * ROWS];
+        const float m_new = fmaxf(m_all, m);
+        const float a = __builtin_amdgcn_exp2f(m_all - m_new), b = __builtin_amdgcn_exp2f(m - m_new);
+        l_all = l_all * a + l * b;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] = acc[c] * a + v[c] * b;
+        m_all = m_new;
+    };
+    add(2 * (w - 1) + (same ? 0 : 1));            // the part before the cut: share w - 1's only unit, or its last one
+    for (int v = w; v < n_wgs; ++v) {
+        const int4 b = bounds[v], e = bounds[v + 1];
+        if (b.x != here.x || b.y != here.y) break;
+        if (e.x != b.x || e.y != b.y || e.z != b.z) add(2 * v);   // an empty share has written nothing
+    }
+    const float inv = 1.f / l_all;
+    const int tq = row_id / G, gq = row_id - tq * G;
+    bf16_t* op = out + ((size_t)rs + tq) * (size_t)(n_q * HD) + (size_t)(here.x * G + gq) * HD + blockIdx.y * NC * 4;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        u32x2 o2;
+        o2.x = pack_bf16x2(acc[c].x * inv, acc[c].y * inv);
+        o2.y = pack_bf16x2(acc[c].z * inv, acc[c].w * inv);
+        *reinterpret_cast<u32x2*>(op + 4 * c) = o2;
+    }
 }
 
 // Merges the key-range splits of attn_kernel<.., SPLIT = true> in a fixed order: out = sum_z 2^(m_z - M) O_z /
@@ -607,7 +690,7 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     if (item >= tile_start[n_seq]) return;
     const int seq = item_seq[item], qtile = item - tile_start[seq], kvh = blockIdx.y;
     const int G = n_q / n_kv;
-    const int L = new_len[seq], H = clamp_prefix(prefix_len[seq], L, max_pages);   // as in attn_kernel
+    const int L = new_len[seq], H = laps_dev_clamp_prefix(prefix_len[seq], L, max_pages);   // as in attn_kernel
     const int rs = row_start[seq];
     if (rs < 0 || L > n_tokens - rs) return;                                          // as in attn_kernel
     const int n_rows = L * G, R0 = qtile * ROWS;
@@ -677,9 +760,26 @@ int launch_attn(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t
                 const int* item_seq, int n_seq, int max_items, int n_q, int n_kv, int n_pool_pages, int n_tokens,
                 hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
-    hipLaunchKernelGGL((attn_kernel<HD, NW, false>), dim3(max_items, n_kv), dim3(NW * 64), 0, s, q, out, nullptr, nullptr,
-                       k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq,
-                       n_q, n_kv, scale_log2e, n_pool_pages, n_tokens);
+    hipLaunchKernelGGL((attn_kernel<HD, NW, false, false>), dim3(max_items, n_kv), dim3(NW * 64), 0, s, q, out, nullptr,
+                       nullptr, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq,
+                       n_seq, n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, nullptr);
+    LAPS_LAUNCH_CHECK();
+    return LAPS_OK;
+}
+
+template <int HD>
+int launch_attn_persistent(const bf16_t* q, bf16_t* out, float* part, int n_wgs, const int4* bounds, const bf16_t* k_pool,
+                           const bf16_t* v_pool, const int* row_start, const int* new_len, const int* prefix_len,
+                           const int* page_table, int max_pages, const int* tile_start, const int* item_seq, int n_seq,
+                           int max_items, int n_q, int n_kv, int n_pool_pages, int n_tokens, hipStream_t s) {
+    const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
+    float* part_ml = part + (size_t)2 * n_wgs * LAPS_ATTN_LONG_ROWS * HD;
+    hipLaunchKernelGGL((attn_kernel<HD, 8, false, true>), dim3(n_wgs), dim3(512), 0, s, q, out, part, part_ml, k_pool, v_pool,
+                       row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, n_q, n_kv,
+                       scale_log2e, n_pool_pages, n_tokens, max_items, bounds);
+    LAPS_LAUNCH_CHECK();
+    hipLaunchKernelGGL((attn_merge_cut_kernel<HD>), dim3(n_wgs - 1, 4), dim3(LAPS_ATTN_LONG_ROWS), 0, s, out, part, part_ml,
+                       row_start, new_len, tile_start, item_seq, bounds, n_wgs, n_seq, n_q, n_kv, n_tokens);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -693,9 +793,9 @@ int launch_attn_split(const bf16_t* q, bf16_t* out, float* part, const bf16_t* k
     const size_t blocks = (size_t)max_items * n_kv * n_split;
     float* part_o = part;
     float* part_ml = part + blocks * 128 * HD;
-    hipLaunchKernelGGL((attn_kernel<HD, 4, true>), dim3(max_items, n_kv, n_split), dim3(256), 0, s, q, out, part_o, part_ml,
+    hipLaunchKernelGGL((attn_kernel<HD, 4, true, false>), dim3(max_items, n_kv, n_split), dim3(256), 0, s, q, out, part_o, part_ml,
                        k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq,
-                       n_q, n_kv, scale_log2e, n_pool_pages, n_tokens);
+                       n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, nullptr);
     LAPS_LAUNCH_CHECK();
     hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(max_items, n_kv, HD / 4), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
                        row_start, new_len, prefix_len, tile_start, item_seq, n_seq, n_q, n_kv, n_split, max_pages, n_tokens);
@@ -754,16 +854,43 @@ void laps_attn_plan(int n_seq, int n_tokens, int group, int n_kv, int max_pages,
 }
 
 // Work-item table for laps_launch_attention; depends on the batch only, so a layer stack builds it once.
+static size_t item_table_ints(int max_tokens, int max_seqs, int group) {   // items of the smallest blocking, 16-byte units
+    return (((size_t)max_tokens * group / 128 + max_seqs + 2) + 3) / 4 * 4;
+}
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group) {
-    return ((size_t)max_tokens * group / 128 + max_seqs + 1) * sizeof(int);
+    return 2 * item_table_ints(max_tokens, max_seqs, group) * sizeof(int) + (LAPS_ATTN_MAX_WGS + 1) * sizeof(int4);
+}
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds) {
+    const size_t n = item_table_ints(n_tokens, n_seq, group);
+    *pre = item_seq + n;
+    *bounds = reinterpret_cast<int4*>(item_seq + 2 * n);
 }
 
-int laps_launch_attn_sched(const int* new_len, int n_seq, int n_tokens, int max_pages, int* tile_start, int* item_seq,
-                           int n_q, int n_kv, hipStream_t s) {
+// The persistent kernel takes un-split launches of 256-row blocks whose page tables are wide enough for units to differ
+// in length (as many tiles as a key split needs): with a grid of units, the last partly filled round of workgroups and
+// the longest units leave compute units idle.  32B shape (head_dim 128, 40 / 8 heads), attention alone with its scheduling
+// kernels, grid of units against equal shares: 2048 rows over 2048 keys 223 -> 174 us, 1847 rows over 6144 444 -> 308,
+// 12 short turns (573 rows) over up to 4096 keys 130 -> 71, 64 turns 334 -> 297, 2048 rows without a prefix 106 -> 94.
+int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes) {
+    int mt, max_items, n_split;
+    attn_blocking(n_seq, n_tokens, group, n_kv, max_pages, &mt, &max_items, &n_split);
+    if (mt != 2 || n_split != 1 || (max_pages * (long)LAPS_PAGE + KT - 1) / KT < 2 * MIN_TILES_PER_SPLIT) return 0;
+    const size_t slot = (size_t)LAPS_ATTN_LONG_ROWS * (hd + 2) * sizeof(float);
+    size_t wgs = partial_bytes / (2 * slot) / 8 * 8;   // whole groups of the 8 XCDs
+    wgs = wgs < LAPS_ATTN_MAX_WGS ? wgs : LAPS_ATTN_MAX_WGS;
+    return wgs < 64 ? 0 : (int)wgs;
+}
+
+int laps_launch_attn_sched(const int* new_len, const int* prefix_len, int n_seq, int n_tokens, int max_pages,
+                           int* tile_start, int* item_seq, int n_q, int n_kv, int hd, size_t partial_bytes, hipStream_t s) {
     int mt, max_items, n_split;
     attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split);
-    hipLaunchKernelGGL(attn_sched_kernel, dim3(1), dim3(256), 0, s, new_len, n_seq, n_q / n_kv, 128 * mt, tile_start,
-                       item_seq, max_items);
+    int* pre;
+    int4* bounds;
+    laps_attn_item_tables(item_seq, n_tokens, n_seq, n_q / n_kv, &pre, &bounds);
+    hipLaunchKernelGGL(attn_sched_kernel, dim3(1), dim3(256), 0, s, new_len, prefix_len, n_seq, n_q / n_kv, n_kv, max_pages,
+                       128 * mt, tile_start, item_seq, max_items,
+                       laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes), pre, bounds);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -771,9 +898,18 @@ int laps_launch_attn_sched(const int* new_len, int n_seq, int n_tokens, int max_
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,
                           const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
                           int max_pages, int n_seq, int n_tokens, const int* tile_start, const int* item_seq,
-                          float* partial, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s) {
+                          float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s) {
     int mt, max_items, n_split;
     attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split);
+    const int n_wgs = partial ? laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes) : 0;
+    if (n_wgs > 0) {
+        int* pre;
+        int4* bounds;
+        laps_attn_item_tables(const_cast<int*>(item_seq), n_tokens, n_seq, n_q / n_kv, &pre, &bounds);
+        auto launch = hd == 128 ? launch_attn_persistent<128> : launch_attn_persistent<64>;
+        return launch(q, out, partial, n_wgs, bounds, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages,
+                      tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+    }
     if (n_split > 1) {
         if (!partial) {
             laps_set_error("attention: key-split launch needs the partial-result workspace");

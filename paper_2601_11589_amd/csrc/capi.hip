@@ -29,7 +29,9 @@ extern "C" const char* laps_version(void) { return "laps-gfx950 0.1"; }
 // of the process.  In host code the array's name is only a handle for hipGetSymbolAddress; the address the
 // kernels are given is the one resolved below, per device, with that device current.
 #define LAPS_STATIC_SCRATCH_BYTES ((size_t)128 << 20)
-static __device__ __align__(256) unsigned char scratch[LAPS_STATIC_SCRATCH_BYTES];
+// The attention's work-item tables (a few KB) come on top, so that what they take is not missing from the 128 MiB.
+#define LAPS_STATIC_TABLE_BYTES ((size_t)1 << 20)
+static __device__ __align__(256) unsigned char scratch[LAPS_STATIC_SCRATCH_BYTES + LAPS_STATIC_TABLE_BYTES];
 
 static constexpr int kMaxDevices = 64;
 static unsigned char* g_scratch_ptr[kMaxDevices];   // resolved address per device ordinal, nullptr = not yet
@@ -286,6 +288,7 @@ struct BatchDesc {
     int n_seq, n_tokens;
     const int *row_start, *seq_len, *prefix_len, *page_table;
     int max_pages;
+    int ws_pages = kAnyPages;   // page-table width the workspace was laid out for
 };
 
 #define LAPS_TRY(x)                 \
@@ -315,7 +318,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
     const laps_model_cfg& cf = c->cfg;
     const int M = b.n_tokens, d = cf.hidden, hd = cf.head_dim;
     const int qd = cf.n_q_heads * hd, qkv = qd + 2 * cf.n_kv_heads * hd, I = cf.intermediate;
-    const WsLayout L = ws_layout(cf, M, b.n_seq);
+    const WsLayout L = ws_layout(cf, M, b.n_seq, b.ws_pages);
     int* tok_pos = reinterpret_cast<int*>(ws + L.tok_pos);
     int* tok_slot = reinterpret_cast<int*>(ws + L.tok_slot);
     int* new_len = reinterpret_cast<int*>(ws + L.new_len);
@@ -327,7 +330,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
     bf16_t* act = reinterpret_cast<bf16_t*>(ws + L.act);
     float* x_mid = reinterpret_cast<float*>(ws + L.x_mid);
     float* partial = reinterpret_cast<float*>(ws + L.partial);
-    const size_t partial_cap = partial_cap_for(cf, M);
+    const size_t partial_cap = partial_cap_for(cf, M), partial_bytes = L.total - L.partial;
 
     if (r0_staged == nullptr) {
         {
@@ -337,7 +340,8 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         {
             ProfScope ps(c, s, LAPS_K_PREP, capturing);
-            LAPS_TRY(laps_launch_attn_sched(new_len, b.n_seq, M, b.max_pages, tile_start, item_seq, cf.n_q_heads, cf.n_kv_heads, s));
+            LAPS_TRY(laps_launch_attn_sched(new_len, b.prefix_len, b.n_seq, M, b.max_pages, tile_start, item_seq,
+                                            cf.n_q_heads, cf.n_kv_heads, hd, partial_bytes, s));
         }
         {
             ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);
@@ -363,8 +367,8 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         {
             ProfScope ps(c, s, LAPS_K_ATTN, capturing);
             LAPS_TRY(laps_launch_attention(q, attn, kp, vp, b.row_start, new_len, b.prefix_len, b.page_table, b.max_pages,
-                                           b.n_seq, M, tile_start, item_seq, partial, cf.n_q_heads, cf.n_kv_heads, hd,
-                                           c->pool_pages, s));
+                                           b.n_seq, M, tile_start, item_seq, partial, partial_bytes, cf.n_q_heads,
+                                           cf.n_kv_heads, hd, c->pool_pages, s));
         }
         // x_mid = resid + attn W_o^T ; r = rmsnorm(x_mid; ln2)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_O, capturing, attn, static_cast<const bf16_t*>(lw.w_o), M, d, qd, EPI_RESID,
@@ -495,7 +499,8 @@ extern "C" int laps_prefill_stack_static(laps_ctx* c, const laps_layer_weights* 
         return LAPS_EINVAL;
     }
     const size_t need = ws_layout(c->cfg, n_tokens, n_seq).total;
-    if (need > LAPS_STATIC_SCRATCH_BYTES) {
+    const size_t tables = laps_attn_item_table_bytes(n_tokens, n_seq, c->cfg.n_q_heads / c->cfg.n_kv_heads);
+    if (need > LAPS_STATIC_SCRATCH_BYTES + (tables < LAPS_STATIC_TABLE_BYTES ? tables : LAPS_STATIC_TABLE_BYTES)) {
         laps_set_error("prefill_stack_static: %d tokens x %d sequences need %zu bytes of workspace, the static scratch "
                        "holds %zu; use laps_prefill_stack with a caller-owned workspace", n_tokens, n_seq, need,
                        (size_t)LAPS_STATIC_SCRATCH_BYTES);
@@ -507,7 +512,7 @@ extern "C" int laps_prefill_stack_static(laps_ctx* c, const laps_layer_weights* 
         return LAPS_EINVAL;
     }
     return prefill_stack_impl(c, w, n_seq, n_tokens, cu, seq_len, prefix_len, page_table, max_pages, k_pools, v_pools,
-                              x_in, x_out, c->static_ws, LAPS_STATIC_SCRATCH_BYTES, stream, true);
+                              x_in, x_out, c->static_ws, LAPS_STATIC_SCRATCH_BYTES + LAPS_STATIC_TABLE_BYTES, stream, true);
 }
 
 // ----------------------------------------------------------------------------- helpers
@@ -645,13 +650,15 @@ extern "C" int laps_attention(laps_ctx* c, int32_t n_seq, int32_t n_tokens, cons
     int* new_len = reinterpret_cast<int*>(w8 + L.new_len);
     LAPS_TRY(laps_launch_prep(n_tokens, n_seq, cu, seq_len, prefix_len, pt, max_pages, c->pool_pages, new_len,
                               reinterpret_cast<int*>(w8 + L.tok_pos), reinterpret_cast<int*>(w8 + L.tok_slot), s));
-    LAPS_TRY(laps_launch_attn_sched(new_len, n_seq, n_tokens, max_pages, reinterpret_cast<int*>(w8 + L.tile_start),
-                                    reinterpret_cast<int*>(w8 + L.item_seq), c->cfg.n_q_heads, c->cfg.n_kv_heads, s));
+    const size_t partial_bytes = L.total - L.partial;
+    LAPS_TRY(laps_launch_attn_sched(new_len, prefix_len, n_seq, n_tokens, max_pages,
+                                    reinterpret_cast<int*>(w8 + L.tile_start), reinterpret_cast<int*>(w8 + L.item_seq),
+                                    c->cfg.n_q_heads, c->cfg.n_kv_heads, c->cfg.head_dim, partial_bytes, s));
     return laps_launch_attention(static_cast<const bf16_t*>(q), static_cast<bf16_t*>(out),
                                  static_cast<const bf16_t*>(k_pool), static_cast<const bf16_t*>(v_pool), cu, new_len,
                                  prefix_len, pt, max_pages, n_seq, n_tokens, reinterpret_cast<int*>(w8 + L.tile_start),
-                                 reinterpret_cast<int*>(w8 + L.item_seq), reinterpret_cast<float*>(w8 + L.partial), c->cfg.n_q_heads, c->cfg.n_kv_heads,
-                                 c->cfg.head_dim, c->pool_pages, s);
+                                 reinterpret_cast<int*>(w8 + L.item_seq), reinterpret_cast<float*>(w8 + L.partial), partial_bytes,
+                                 c->cfg.n_q_heads, c->cfg.n_kv_heads, c->cfg.head_dim, c->pool_pages, s);
 }
 
 // ----------------------------------------------------------------------------- launch plans (host only)
@@ -715,7 +722,7 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
                               const float* x_rows, int n_rows, hipStream_t s) {
     const laps_model_cfg& cf = g->ctx->cfg;
     const int M = g->depth * g->len_bucket;
-    const WsLayout L = ws_layout(cf, M, g->depth);
+    const WsLayout L = ws_layout(cf, M, g->depth, g->max_pages);
     StageArgs a;
     a.seq_len = seq_len;
     a.prefix_len = prefix_len;
@@ -730,6 +737,8 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
     a.group = cf.n_q_heads / cf.n_kv_heads;
     int n_split = 0, min_tiles = 0;
     laps_attn_plan(g->depth, M, a.group, cf.n_kv_heads, g->max_pages, &a.rows_per_wg, &a.max_items, &n_split, &min_tiles);
+    a.n_kv = cf.n_kv_heads;
+    a.attn_wgs = laps_attn_persistent_wgs(g->depth, M, a.group, cf.n_kv_heads, cf.head_dim, g->max_pages, L.total - L.partial);
     a.seq_len_out = g->seq_len;
     a.prefix_out = g->prefix_len;
     a.row_start_out = g->row_start;
@@ -739,6 +748,7 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
     a.tok_slot = reinterpret_cast<int*>(g->ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(g->ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(g->ws + L.item_seq);
+    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds);
     a.x_in = g->x_in;
     a.ln_w = g->ln1_first;
     a.r0 = g->r0;
@@ -817,7 +827,7 @@ extern "C" int laps_graph_capture(laps_ctx* c, const laps_layer_weights* w, int3
         laps_set_error("graph_capture: staging init failed: %s", hipGetErrorString(e));
         return fail(LAPS_EHIP);
     }
-    const BatchDesc b{depth, (int)M, g->row_start, g->seq_len, g->prefix_len, g->page_table, max_pages};
+    const BatchDesc b{depth, (int)M, g->row_start, g->seq_len, g->prefix_len, g->page_table, max_pages, max_pages};
     // every slot empty: token metadata and work-item table of an empty batch, as the captured kernels expect to find them
     int rc = graph_stage_launch(g, 0, nullptr, nullptr, nullptr, nullptr, 0, s);
     // warm-up pass: loads code objects and sets kernel attributes outside the capture

@@ -448,6 +448,9 @@ __global__ __launch_bounds__(META_THREADS) void stage_meta_kernel(const StageArg
     if (t == META_THREADS - 1) a.row_start_out[depth] = sums[t];
     __syncthreads();   // the lengths written above are read below by other threads of this workgroup
     laps_dev_attn_sched(a.new_len_out, depth, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, sums, &carry);
+    if (a.attn_wgs > 0)
+        laps_dev_attn_bounds(a.new_len_out, a.prefix_out, depth, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
+                             a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, sums, &carry);
 }
 
 // One workgroup per graph row; see StageArgs.  Runs after stage_meta_kernel on the same stream.

@@ -98,8 +98,11 @@ struct StageArgs {
     const float* x_rows;                            // caller's packed input rows or NULL
     int n_real, n_rows, depth, len_bucket, max_pages, n_pool_pages;
     int group, rows_per_wg, max_items;              // attention blocking of the graph's shape
+    int n_kv, attn_wgs;                             // workgroups of the persistent attention kernel (0: not used)
     int *seq_len_out, *prefix_out, *row_start_out, *page_table_out;   // the graph's staging block
     int *new_len_out, *tok_pos, *tok_slot, *tile_start, *item_seq;    // the graph's workspace
+    int* attn_pre;
+    int4* attn_bounds;
     float* x_in;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -142,20 +145,104 @@ static __device__ __forceinline__ void laps_dev_attn_sched(const int* __restrict
     if (threadIdx.x == 0) tile_start[n_seq] = *carry;
 }
 
+// A prefix length that the page table cannot hold (a corrupted or stale array) must neither index past the
+// table nor make a workgroup walk millions of key tiles: cut to what max_pages pages can address.
+static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, int max_pages) {
+    const int room = max_pages * LAPS_PAGE - new_len;
+    h = h < room ? h : room;
+    return h > 0 ? h : 0;
+}
+
+// Equal shares of a batch's attention for `n_wgs` workgroups (the persistent long-prompt kernel).  A unit is one
+// (kv head, work item) pair and costs its key tiles plus COST0 (its prologue and epilogue; 1 to 10 tried, 4 is best or even); the units
+// of all kv heads, one head after the other, are cut into equal lengths.  bounds[w] = (kv head, item, first tile) is
+// where workgroup w begins and w - 1 ends.  A cut inside a unit stays MIN_SEG tiles clear of its ends and where every
+// row of the unit sees the first key after the cut, else it moves to the unit's begin or end; short batches use fewer
+// workgroups.  Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; pre (max_items + 1 ints) holds the
+// prefix sums of the item costs.
+constexpr int LAPS_ATTN_KT = 64;          // keys per tile
+constexpr int LAPS_ATTN_LONG_ROWS = 256;  // query rows per work item of the long-prompt kernel
+constexpr int LAPS_ATTN_MAX_WGS = 256;    // one workgroup per compute unit
+static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restrict__ new_len,
+                                                            const int* __restrict__ prefix_len, int n_seq, int group,
+                                                            int n_kv, int max_pages, const int* tile_start,
+                                                            const int* item_seq, int max_items, int n_wgs, int* pre,
+                                                            int4* bounds, int* buf, int* carry) {
+    constexpr int COST0 = 4, MIN_SEG = 4, MIN_COST = 8;
+    __syncthreads();   // tile_start and item_seq were written by other threads of this workgroup
+    const int total = tile_start[n_seq], n_items = total < max_items ? total : max_items;
+    // key tiles of an item, and the last tile a cut may begin with
+    auto tiles_of = [&](int i, int* last_cut) {
+        const int seq = item_seq[i], L = new_len[seq], H = laps_dev_clamp_prefix(prefix_len[seq], L, max_pages);
+        const int r0 = (i - tile_start[seq]) * LAPS_ATTN_LONG_ROWS, rows = L * group;
+        const int last = (r0 + LAPS_ATTN_LONG_ROWS < rows ? r0 + LAPS_ATTN_LONG_ROWS : rows) - 1;
+        *last_cut = (H + r0 / group) / LAPS_ATTN_KT;
+        return (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT;
+    };
+    if (threadIdx.x == 0) *carry = 0, pre[0] = 0;
+    __syncthreads();
+    for (int base = 0; base < n_items; base += 256) {
+        const int i = base + threadIdx.x;
+        int unused;
+        buf[threadIdx.x] = i < n_items ? tiles_of(i, &unused) + COST0 : 0;
+        __syncthreads();
+        for (int o = 1; o < 256; o <<= 1) {
+            const int add = (threadIdx.x >= o) ? buf[threadIdx.x - o] : 0;
+            __syncthreads();
+            buf[threadIdx.x] += add;
+            __syncthreads();
+        }
+        const int c = *carry;
+        if (i < n_items) pre[i + 1] = c + buf[threadIdx.x];
+        __syncthreads();
+        if (threadIdx.x == 255) *carry = c + buf[255];
+        __syncthreads();
+    }
+    const long per_head = *carry, cost = per_head * n_kv;
+    long used = cost / MIN_COST;
+    used = used < 1 ? 1 : (used > n_wgs ? n_wgs : used);
+    for (int w = threadIdx.x; w <= n_wgs; w += 256) {
+        int4 b = make_int4(n_kv, 0, 0, 0);   // the end
+        const long x = w < used ? cost * w / used : cost;
+        if (x < cost) {
+            const int head = (int)(x / per_head), rem = (int)(x - head * per_head);
+            int lo = 0, hi = n_items;   // item with pre[item] <= rem < pre[item + 1]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (pre[mid] <= rem) lo = mid; else hi = mid;
+            }
+            int last_cut;
+            const int nt = tiles_of(lo, &last_cut);
+            int t = rem - pre[lo] - COST0;
+            if (t < MIN_SEG) t = 0;
+            const bool next = t > 0 && (t > last_cut || nt - t < MIN_SEG);
+            if (!next) b = make_int4(head, lo, t, 0);
+            else if (lo + 1 < n_items) b = make_int4(head, lo + 1, 0, 0);
+            else b = make_int4(head + 1, 0, 0, 0);   // head + 1 == n_kv: the end
+        }
+        bounds[w] = b;
+    }
+}
+
 // ----------------------------------------------------------------------------- attention
 // Both take the same (n_seq, n_tokens, max_pages): the blocking they derive from them must agree.
-// `partial` (laps_attn_partial_bytes, 16-byte aligned) receives per-split results when the launch shape
-// calls for splitting the key range; it may be NULL only if max_pages * 16 < 1024.
+// `partial` (partial_bytes >= laps_attn_partial_bytes, 16-byte aligned) receives per-split results when the launch shape
+// calls for splitting the key range; it may be NULL only if max_pages * 16 < 512.  partial_bytes must be the same in both.
 // tile_start: n_seq + 1 ints; item_seq: laps_attn_item_table_bytes (sequence of every row-block work item).
 size_t laps_attn_partial_bytes(int hd, int max_pages);   // 0 when page tables this narrow never split
+// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel.
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group);
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds);
+// Workgroups of the persistent long-prompt kernel for a launch shape with partial_bytes of room for the results of cut
+// units (two slots per workgroup); 0: the launch does not use it.
+int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes);
 // The blocking laps_launch_attn_sched / laps_launch_attention derive from a launch shape: query rows per workgroup,
 // bound on the (sequence, row block) items, key-range splits (1 = none), fewest key tiles a split may get.
 void laps_attn_plan(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* rows_per_wg, int* max_items,
                     int* n_split, int* min_tiles_per_split);
-int laps_launch_attn_sched(const int* new_len, int n_seq, int n_tokens, int max_pages, int* tile_start, int* item_seq,
-                           int n_q, int n_kv, hipStream_t s);
+int laps_launch_attn_sched(const int* new_len, const int* prefix_len, int n_seq, int n_tokens, int max_pages,
+                           int* tile_start, int* item_seq, int n_q, int n_kv, int hd, size_t partial_bytes, hipStream_t s);
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,
                           const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
                           int max_pages, int n_seq, int n_tokens, const int* tile_start, const int* item_seq,
-                          float* partial, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s);
+                          float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s);
