@@ -82,16 +82,17 @@ struct GemmArgs {
     bf16_t* out_bf16;      // EPI_SWIGLU: [M][N/2]
     const int* row_live;   // [M] or NULL: rows with a negative entry are padding - skinny tiles skip their A loads,
                            // every tile shape skips a row tile that holds nothing else (its output is then not written)
+    const int* n_live;     // NULL, or where the number of leading rows that are not padding is found (at most M count)
 };
 
 // Writes a workgroup's accumulators with the requested epilogue.  Accumulator layout of the 32x32 MFMA:
 // lane -> column (lane & 31); register r -> row 8*(r/4) + 4*(lane/32) + r%4.
 template <typename T, int EPI>
-__device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], const GemmArgs& g, int ks, int m0, int n0,
-                                           int wm, int wn, int lrow, int lk) {
-    const int M = g.M, N = g.N;
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], const GemmArgs& g, int M, int ks, int m0,
+                                           int n0, int wm, int wn, int lrow, int lk) {
+    const int N = g.N;   // M: rows to store
     if constexpr (EPI == EPI_PARTIAL) {
-        float* out = g.out_f32 + (size_t)ks * M * N;
+        float* out = g.out_f32 + (size_t)ks * g.M * N;
 #pragma unroll
         for (int mi = 0; mi < T::MI; ++mi)
 #pragma unroll
@@ -161,8 +162,18 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
     u32x4* As = reinterpret_cast<u32x4*>(smem);  // [2][BM][CHUNKS]
     u32x4* Bs = As + 2 * BM * CHUNKS;            // [2][BN][CHUNKS]
 
-    const int M = g.M, N = g.N, K = g.K;
-    const TileCoord tc = map_block(blockIdx.x, g.tiles_m, g.tiles_n, g.split);
+    // Rows past *n_live are padding: the tiles of the rows before them are dealt out as if there were no others.  (Tiles
+    // of all M rows, the dead ones returning at once, leave whole XCDs idle, since each takes a contiguous range: gate/up
+    // of a 4096-row graph with 2776 live rows 1880 us, this way 1390.)
+    const int N = g.N, K = g.K;
+    int M = g.M, tiles_m = g.tiles_m;
+    if (g.n_live != nullptr) {
+        const int live = *g.n_live;
+        M = live < M ? live : M;
+        tiles_m = (M + BM - 1) / BM;
+        if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
+    }
+    const TileCoord tc = map_block(blockIdx.x, tiles_m, g.tiles_n, g.split);
     const int m0 = tc.tm * BM, n0 = tc.tn * BN;
     const int kbeg = tc.ks * g.kps;
     const int kend = (kbeg + g.kps < K) ? (kbeg + g.kps) : K;
@@ -350,7 +361,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
         }
     }
 
-    store_tile<T, EPI>(acc, g, tc.ks, m0, n0, wm, wn, lrow, lk);
+    store_tile<T, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, int WS = 1>
@@ -506,7 +517,7 @@ size_t laps_gemm_partial_bytes(int m, int n, int k) {   // m <= 128
 }
 
 int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m, int n, int k, float* out_f32,
-                     const float* resid, bf16_t* out_bf16, const int* row_live, hipStream_t s) {
+                     const float* resid, bf16_t* out_bf16, const int* row_live, const int* n_live, hipStream_t s) {
     if (m < 1 || n < 64 || k < BK || k % BK != 0 || p.cfg < 0 || p.cfg >= kNumTiles || n % kTiles[p.cfg].bn != 0) {
         laps_set_error("gemm: unsupported shape m=%d n=%d k=%d for tile %d", m, n, k, p.cfg);
         return LAPS_EINVAL;
@@ -533,6 +544,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     g.resid = resid;
     g.out_bf16 = out_bf16;
     g.row_live = row_live;
+    g.n_live = n_live;
 #define LAPS_TILE_CASE(cfg, BM, BN, WM, WN, EPI, WS) \
     case ((cfg) * 4 + (EPI)) * 8 + (WS): return launch_tile<BM, BN, WM, WN, EPI, WS>(g, s)
     switch ((p.cfg * 4 + p.epi) * 8 + p.ws) {
