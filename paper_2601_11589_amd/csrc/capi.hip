@@ -301,12 +301,12 @@ struct BatchDesc {
 // K-slice partial sums when it splits K.  Returns the plan so the caller knows which case ran.
 static int run_gemm(laps_ctx* c, int cls, bool capturing, const bf16_t* a, const bf16_t* w, int m, int n, int k,
                     int want, float* partial, size_t partial_cap, float* out_f32, const float* resid, bf16_t* out_bf16,
-                    const int* row_live, const int* n_live, GemmPlan* plan, hipStream_t s) {
+                    const int* row_live, const int* n_live, bool live_varies, GemmPlan* plan, hipStream_t s) {
     const GemmPlan p = laps_gemm_plan(m, n, k, 0, want, partial_cap);
     *plan = p;
     ProfScope ps(c, s, cls, capturing);
-    if (p.epi == EPI_PARTIAL) return laps_gemm_launch(p, a, w, m, n, k, partial, nullptr, nullptr, row_live, n_live, s);
-    return laps_gemm_launch(p, a, w, m, n, k, out_f32, resid, out_bf16, row_live, n_live, s);
+    if (p.epi == EPI_PARTIAL) return laps_gemm_launch(p, a, w, m, n, k, partial, nullptr, nullptr, row_live, n_live, live_varies, s);
+    return laps_gemm_launch(p, a, w, m, n, k, out_f32, resid, out_bf16, row_live, n_live, live_varies, s);
 }
 
 // Runs layers [0, n_layers) of `w`.  Token metadata (prep) is computed once.  r0_staged: the first layer's normed
@@ -361,7 +361,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         // q, k, v: GEMM -> K-slice sums -> bias + RoPE + KV append
         const bf16_t* r_in = (l == 0 && r0_staged != nullptr) ? r0_staged : r;
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_QKV, capturing, r_in, static_cast<const bf16_t*>(lw.w_qkv), M, qkv, d, EPI_PARTIAL,
-                          partial, partial_cap, nullptr, nullptr, nullptr, row_live, n_live, &gp, s));
+                          partial, partial_cap, nullptr, nullptr, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
         {
             ProfScope ps(c, s, LAPS_K_EPI_QKV, capturing);
             LAPS_TRY(laps_launch_epi_qkv(partial, gp.split, cf.has_qkv_bias ? static_cast<const bf16_t*>(lw.b_qkv) : nullptr,
@@ -376,7 +376,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         // x_mid = resid + attn W_o^T ; r = rmsnorm(x_mid; ln2)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_O, capturing, attn, static_cast<const bf16_t*>(lw.w_o), M, d, qd, EPI_RESID,
-                          partial, partial_cap, x_mid, resid, nullptr, row_live, n_live, &gp, s));
+                          partial, partial_cap, x_mid, resid, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
         if (gp.epi == EPI_RESID) {
             ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);
             LAPS_TRY(laps_launch_rmsnorm(x_mid, static_cast<const bf16_t*>(lw.ln2_w), r, M, d, cf.rms_eps, tok_pos, s));
@@ -387,7 +387,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         // act = silu(r W_g^T) * (r W_u^T)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_GATEUP, capturing, r, static_cast<const bf16_t*>(lw.w_gate_up), M, 2 * I, d,
-                          EPI_SWIGLU, partial, partial_cap, nullptr, nullptr, act, row_live, n_live, &gp, s));
+                          EPI_SWIGLU, partial, partial_cap, nullptr, nullptr, act, row_live, n_live, r0_staged != nullptr, &gp, s));
         if (gp.epi != EPI_SWIGLU) {
             ProfScope ps(c, s, LAPS_K_EPI_SWIGLU, capturing);
             LAPS_TRY(laps_launch_epi_swiglu(partial, gp.split, act, M, I, tok_pos, s));
@@ -395,7 +395,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         // x_out = x_mid + act W_d^T ; r = rmsnorm(x_out; next layer's ln1)
         const bf16_t* next_ln = (l + 1 < n_layers) ? static_cast<const bf16_t*>(w[l + 1].ln1_w) : nullptr;
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_DOWN, capturing, act, static_cast<const bf16_t*>(lw.w_down), M, d, I, EPI_RESID,
-                          partial, partial_cap, x_out, x_mid, nullptr, row_live, n_live, &gp, s));
+                          partial, partial_cap, x_out, x_mid, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
         if (gp.epi == EPI_RESID) {
             if (next_ln) {
                 ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);
@@ -579,14 +579,14 @@ extern "C" int laps_gemm_bf16(laps_ctx* c, const void* a, const void* w, float* 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const GemmPlan p = laps_gemm_plan(m, n, k, split_k, EPI_PARTIAL);
     if (p.split == 1)
-        return laps_gemm_launch(p, static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(w), m, n, k, out, nullptr, nullptr, nullptr, nullptr, s);
+        return laps_gemm_launch(p, static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(w), m, n, k, out, nullptr, nullptr, nullptr, nullptr, false, s);
     const size_t need = (size_t)p.split * m * n * sizeof(float);
     if (!ws || ws_bytes < need || ((uintptr_t)ws & 255)) {
         laps_set_error("gemm: split-K needs %zu bytes of 256-byte aligned workspace", need);
         return LAPS_ENOMEM;
     }
     LAPS_TRY(laps_gemm_launch(p, static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(w), m, n, k, static_cast<float*>(ws),
-                              nullptr, nullptr, nullptr, nullptr, s));
+                              nullptr, nullptr, nullptr, nullptr, false, s));
     // sum the slices: view [m, n] as rows of `cols` columns, cols | n and cols <= 8192
     int cols = n;
     while (cols > 8192) {
@@ -622,14 +622,14 @@ extern "C" int laps_gemm_epilogue_bf16(laps_ctx* c, const void* a, const void* w
     const GemmPlan p = laps_gemm_plan(m, n, k, 0, epilogue);
     if (p.epi == epilogue)
         return laps_gemm_launch(p, static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(w), m, n, k, out_f32, resid,
-                                static_cast<bf16_t*>(out_bf16), nullptr, nullptr, s);
+                                static_cast<bf16_t*>(out_bf16), nullptr, nullptr, false, s);
     const size_t need = (size_t)p.split * m * n * sizeof(float);
     if (!ws || ws_bytes < need || ((uintptr_t)ws & 255)) {
         laps_set_error("gemm_epilogue: this shape splits K and needs %zu bytes of 256-byte aligned workspace", need);
         return LAPS_ENOMEM;
     }
     LAPS_TRY(laps_gemm_launch(p, static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(w), m, n, k,
-                              static_cast<float*>(ws), nullptr, nullptr, nullptr, nullptr, s));
+                              static_cast<float*>(ws), nullptr, nullptr, nullptr, nullptr, false, s));
     if (epilogue == EPI_RESID)
         return laps_launch_epi_resid(static_cast<const float*>(ws), p.split, resid, out_f32, nullptr, nullptr, m, n, 1.f,
                                      nullptr, s);

@@ -54,6 +54,14 @@ struct TileCoord {
     int tm, tn, ks;
 };
 
+// x / d of a uniform x >= 0: one reciprocal and a correction (the compiler's own division is several times as long, and
+// four of them stood in front of every workgroup's first load).  The quotient is off by one at most below 2^23.
+__device__ __forceinline__ int fast_div(int x, int d) {
+    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)d));
+    const int r = x - q * d;
+    return __builtin_amdgcn_readfirstlane(q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0));
+}
+
 __device__ __forceinline__ TileCoord map_block(int bid, int tiles_m, int tiles_n, int split) {
     const int total = tiles_m * tiles_n * split;
     const int xcd = bid % NUM_XCD, idx = bid / NUM_XCD;
@@ -61,15 +69,20 @@ __device__ __forceinline__ TileCoord map_block(int bid, int tiles_m, int tiles_n
     const int lin = xcd * q + (xcd < r ? xcd : r) + idx;  // contiguous range per XCD
     const int per_split = tiles_m * tiles_n;
     TileCoord c;
-    c.ks = lin / per_split;
+    c.ks = split == 1 ? 0 : fast_div(lin, per_split);
     const int t = lin - c.ks * per_split;
+    if (tiles_m == 1) {
+        c.tm = 0;
+        c.tn = t;
+        return c;
+    }
     const int gsize = GROUP_M * tiles_n;
-    const int grp = t / gsize;
+    const int grp = fast_div(t, gsize);
     const int first_m = grp * GROUP_M;
     const int gm = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
     const int in = t - grp * gsize;
-    c.tm = first_m + in % gm;
-    c.tn = in / gm;
+    c.tn = fast_div(in, gm);
+    c.tm = first_m + in - c.tn * gm;
     return c;
 }
 
@@ -151,39 +164,40 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
     }
 }
 
+// Streaming weight loads and A rows through a buffer descriptor: the skinny tiles.  Its 32-bit offsets hold a tile of 128
+// rows up to K = 2^23; longer rows take the one-slab variant of the 128x64 tile, which addresses like the large tiles.
+constexpr int kSkinnyMaxK = 1 << 23;
+template <int BM, int BN, int WS>
+constexpr bool skinny_loads = BM <= 128 && !(BN == 64 && WS == 1);
+
 // WS = number of register sets that stage slabs: WS slabs (A and W chunks alike - loads return in
 // issue order, so a shallower A stream would throttle the W stream) are in flight per workgroup.
 // WS > 1 is for the bandwidth-bound skinny shapes; the K loop is then unrolled WS times so every set
 // index is static, and the K slice must hold a multiple of WS slabs.
-template <int BM, int BN, int WM, int WN, int EPI, int WS>
-__global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIMD)) void gemm_kernel(const GemmArgs g) {
+//
+// One tile of the rows_in live rows: workgroup `bid` of tiles_m * tiles_n * g.split.  late_live: NULL, or where the number
+// of live rows is found if it does not decide which tile this is (a single row tile): it is then read behind the first
+// weight loads.
+// STREAM: nobody else reads this tile's weights (a single row tile), they bypass the caches.
+template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem, const int rows_in, const int tiles_m,
+                                          const int tiles_n, const int bid, const int* late_live) {
     using T = Traits<BM, BN, WM, WN>;
-    extern __shared__ __align__(16) unsigned char smem[];
     u32x4* As = reinterpret_cast<u32x4*>(smem);  // [2][BM][CHUNKS]
     u32x4* Bs = As + 2 * BM * CHUNKS;            // [2][BN][CHUNKS]
 
-    // Rows past *n_live are padding: the tiles of the rows before them are dealt out as if there were no others.  (Tiles
-    // of all M rows, the dead ones returning at once, leave whole XCDs idle, since each takes a contiguous range: gate/up
-    // of a 4096-row graph with 2776 live rows 1880 us, this way 1390.)
     const int N = g.N, K = g.K;
-    int M = g.M, tiles_m = g.tiles_m;
-    if (g.n_live != nullptr) {
-        const int live = *g.n_live;
-        M = live < M ? live : M;
-        tiles_m = (M + BM - 1) / BM;
-        if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
-    }
-    const TileCoord tc = map_block(blockIdx.x, tiles_m, g.tiles_n, g.split);
+    const TileCoord tc = map_block(bid, tiles_m, tiles_n, g.split);
     const int m0 = tc.tm * BM, n0 = tc.tn * BN;
     const int kbeg = tc.ks * g.kps;
     const int kend = (kbeg + g.kps < K) ? (kbeg + g.kps) : K;
     const int KT = (kend - kbeg) / BK;
 
-    constexpr bool NT = (BM <= 128);  // skinny tiles only
+    constexpr bool NT = skinny_loads<BM, BN, WS>;
     const int tid = threadIdx.x;
     if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
         bool any = false;
-        for (int r = tid; r < BM; r += T::NT) any |= (m0 + r < M) && g.row_live[m0 + r] >= 0;
+        for (int r = tid; r < BM; r += T::NT) any |= (m0 + r < rows_in) && g.row_live[m0 + r] >= 0;
         // in the slab buffers, not in LDS of its own: two 192x128 workgroups take exactly a unit's 160 KB
         int* flag = reinterpret_cast<int*>(smem);
         const bool wave_any = __builtin_amdgcn_ballot_w64(any) != 0;
@@ -203,23 +217,38 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
     const u32x4* ag[T::A_LOADS];
     const u32x4* bg[T::B_LOADS];
     int a_dst[T::A_LOADS], b_dst[T::B_LOADS];
+    u32x4 rrb[WS][T::B_LOADS];   // staged W slabs: slab j lives in set j % WS
+#pragma unroll
+    for (int i = 0; i < T::B_LOADS; ++i) {
+        const int c = tid + i * T::NT, row = c / CHUNKS, kc = c % CHUNKS;
+        bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row) * K + kbeg) + kc;
+        b_dst[i] = row * CHUNKS + swz(row, kc);
+        rrb[0][i] = STREAM ? __builtin_nontemporal_load(bg[i]) : *bg[i];
+    }
+    int M = rows_in;
+    if (late_live != nullptr) {
+        const int live = *late_live;
+        M = live < M ? live : M;
+        if (M <= 0) return;
+    }
     // Skinny tiles: a CU keeps a bounded number of requests in flight, and the A slab's share of them
     // (a third with 256 columns) is taken from the weight stream; rows past M and padding rows are
-    // therefore not loaded at all - their staging registers stay zero.
-    bool a_live[T::A_LOADS];
+    // therefore not loaded at all.  Their lanes address past the end of the A tile's buffer descriptor, which
+    // returns zero without a request and without the branch (and, in the prologue, the wait) that a condition
+    // around each load cost.
+    u32x4 rra[WS][T::A_LOADS];   // staged A slabs, same rule as rrb
+    unsigned a_off[T::A_LOADS];
+    const unsigned a_bytes = NT ? (unsigned)BM * (unsigned)K * 2u : 0u;   // at most 2^31, see kSkinnyMaxK
+    const __amdgpu_buffer_rsrc_t a_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.A) + (size_t)m0 * K, 0, a_bytes, 0x00020000);
 #pragma unroll
     for (int i = 0; i < T::A_LOADS; ++i) {
         const int c = tid + i * T::NT, row = c / CHUNKS, kc = c % CHUNKS;
         const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
         ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc;
         a_dst[i] = row * CHUNKS + swz(row, kc);
-        a_live[i] = !NT || (m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0));
-    }
-#pragma unroll
-    for (int i = 0; i < T::B_LOADS; ++i) {
-        const int c = tid + i * T::NT, row = c / CHUNKS, kc = c % CHUNKS;
-        bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row) * K + kbeg) + kc;
-        b_dst[i] = row * CHUNKS + swz(row, kc);
+        const bool live = m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0);
+        a_off[i] = live ? ((unsigned)row * (unsigned)K + (unsigned)kbeg) * 2u + (unsigned)kc * 16u : 0x80000000u;
     }
     // fragment read offsets (in 16-byte chunks) inside one LDS buffer, per k-step
     int a_src[T::MI], b_src[T::NI];
@@ -237,14 +266,6 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
-    u32x4 rra[WS][T::A_LOADS];   // staged A slabs: slab j lives in set j % WS
-    if constexpr (NT) {
-#pragma unroll
-        for (int w = 0; w < WS; ++w)
-#pragma unroll
-            for (int i = 0; i < T::A_LOADS; ++i) rra[w][i] = u32x4{0u, 0u, 0u, 0u};
-    }
-    u32x4 rrb[WS][T::B_LOADS];   // staged W slabs, same rule
     bf16x8 fa[2][T::MI], fb[2][T::NI];
     constexpr int NM = T::MI * T::NI;            // MFMAs per k-step
     constexpr int NF = T::MI + T::NI;            // fragment reads per k-step
@@ -256,7 +277,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
     auto gload_one = [&](int i, int kt, int ws) {
         if (i < T::A_LOADS) {
             if constexpr (NT) {
-                if (a_live[i]) rra[ws][i] = ag[i][clampk(kt) * CHUNKS];
+                rra[ws][i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], clampk(kt) * (BK * 2), 0);
             } else {
                 rra[ws][i] = ag[i][clampk(kt) * CHUNKS];
             }
@@ -264,7 +285,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
             // weights are read once: streaming (non-temporal) loads keep them from evicting the A slabs,
             // which every workgroup on the CU and on the XCD re-reads, out of L1 / L2
             const u32x4* src = bg[i - T::A_LOADS] + clampk(kt) * CHUNKS;
-            rrb[ws][i - T::A_LOADS] = NT ? __builtin_nontemporal_load(src) : *src;
+            rrb[ws][i - T::A_LOADS] = STREAM ? __builtin_nontemporal_load(src) : *src;
         }
     };
     auto lstore_one = [&](int i, int buf, int ws) {
@@ -283,9 +304,9 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
         acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mi], fb[set][ni], acc[mi][ni], 0, 0, 0);
     };
 
-    // prologue: slab 0 through the registers into LDS buffer 0, then A slab 1 and W slabs 1..WS in flight
+    // prologue: slab 0 through the registers into LDS buffer 0 (its W part is on its way), then slabs 1..WS in flight
 #pragma unroll
-    for (int i = 0; i < NC; ++i) gload_one(i, 0, 0);
+    for (int i = 0; i < T::A_LOADS; ++i) gload_one(i, 0, 0);
 #pragma unroll
     for (int i = 0; i < NC; ++i) lstore_one(i, 0, 0);
 #pragma unroll
@@ -364,10 +385,63 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
     store_tile<T, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int WS = 1>
+// Rows past *n_live are padding: the tiles of the rows before them are dealt out as if there were no others.  (Tiles of all
+// M rows, the dead ones returning at once, leave whole XCDs idle, since each takes a contiguous range: gate/up of a
+// 4096-row graph with 2776 live rows 1880 us, this way 1390.)
+__device__ __forceinline__ int live_rows(const GemmArgs& g) {
+    if (g.n_live == nullptr) return g.M;
+    const int live = *g.n_live;
+    return live < g.M ? live : g.M;
+}
+
+template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
+__global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIMD)) void gemm_kernel(const GemmArgs g) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int M = g.M, tiles_m = g.tiles_m;
+    const int* late_live = g.n_live;
+    if (tiles_m > 1) {
+        late_live = nullptr;
+        M = live_rows(g);
+        tiles_m = (M + BM - 1) / BM;
+        if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
+    }
+    gemm_tile<BM, BN, WM, WN, EPI, WS, STREAM>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x, late_live);
+}
+
+// A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
+// 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 220
+// of 256 x 256 take one: 997 against 700 us).  Widths WN_ (160 or 224), 256 and 128 are therefore one kernel, which takes
+// the width that the cost model gives the live rows; every workgroup comes to the same choice.
+struct WidthCost {
+    float fill[3], slabs[3], part[3];   // as TileDef, slabs = time of all K slabs on a full chip
+};
+template <int W, int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_width_kernel(const GemmArgs g, const WidthCost c) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int M = live_rows(g);
+    if (M <= 0) return;
+    const int tiles_m = (M + 255) / 256;
+    constexpr int width[3] = {W, 256, 128};
+    int pick = 0;
+    float best = 0.f;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int tiles = tiles_m * (g.N / width[i]);
+        const float spare = tiles < 256 ? 1.f - tiles / 256.f : 0.f;
+        const float us = (float)((tiles + 255) / 256) * (c.fill[i] + c.slabs[i] * (1.f - c.part[i] * spare));
+        if (i == 0 || us < best) best = us, pick = i;
+    }
+    const int tiles_n = g.N / width[pick];
+    if ((int)blockIdx.x >= tiles_m * tiles_n) return;
+    if (pick == 0) gemm_tile<256, W, 4, 1, EPI, 1, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else if (pick == 1) gemm_tile<256, 256, 2, 2, EPI, 1, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else gemm_tile<256, 128, 2, 2, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+}
+
+template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
 int launch_tile(const GemmArgs& a, hipStream_t s) {
     using T = Traits<BM, BN, WM, WN>;
-    auto kern = gemm_kernel<BM, BN, WM, WN, EPI, WS>;
+    auto kern = gemm_kernel<BM, BN, WM, WN, EPI, WS, STREAM>;
     static bool attr_set = false;  // per instantiation; idempotent, so a race only repeats the call
     if (!attr_set) {
         LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -401,6 +475,27 @@ constexpr TileDef kTiles[] = {
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
+template <int W, int EPI>
+int launch_width(const GemmArgs& a, hipStream_t s) {
+    constexpr int cfg[3] = {W == 160 ? 4 : 3, 2, 8};
+    constexpr int lds = Traits<256, 256, 2, 2>::LDS_BYTES;
+    auto kern = gemm_width_kernel<W, EPI>;
+    static bool attr_set = false;  // as in launch_tile
+    if (!attr_set) {
+        LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        attr_set = true;
+    }
+    WidthCost c;
+    for (int i = 0; i < 3; ++i) {
+        c.fill[i] = (float)kTiles[cfg[i]].fill;
+        c.slabs[i] = (float)(kTiles[cfg[i]].slab * (a.K / BK));
+        c.part[i] = (float)kTiles[cfg[i]].part;
+    }
+    hipLaunchKernelGGL(kern, dim3((a.M + 255) / 256 * (a.N / 128)), dim3(256), lds, s, a, c);
+    LAPS_LAUNCH_CHECK();
+    return LAPS_OK;
+}
+
 }  // namespace
 
 // Row class and columns of a tile shape.  A 192-row tile counts as one of the 256-row class: it is only taken where
@@ -420,7 +515,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         int per = (ksteps + split - 1) / split;
         // with 2 slabs in flight every K slice must hold a multiple of 2 slabs
         p.ws = 1;
-        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0) {
+        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0 && k <= kSkinnyMaxK) {
             per = (per + 1) / 2 * 2;
             p.ws = 2;
         }
@@ -430,6 +525,10 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         p.epi = (p.split == 1) ? want_epi : EPI_PARTIAL;
         return p;
     };
+    if (k > kSkinnyMaxK && (m <= 128 || n % 256 != 0)) {
+        if (want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
+        return finish(1, force_split > 0 ? force_split : 1);
+    }
     if (m <= 128) {
         // Bandwidth-bound.  A CU keeps a bounded number of requests in flight, and the A slab that every
         // workgroup re-reads per K step (L2 hits) takes its share of them from the weight stream: a
@@ -469,7 +568,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     int best_cfg = -1, best_split = 1;
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
-        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0)) continue;
+        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0) || (t.bm == 128 && k > kSkinnyMaxK)) continue;
         if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
         const int tiles_m = (m + t.bm - 1) / t.bm;
         if (t.bm == 192 && tiles_m != (m + 255) / 256) continue;
@@ -517,13 +616,18 @@ size_t laps_gemm_partial_bytes(int m, int n, int k) {   // m <= 128
 }
 
 int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m, int n, int k, float* out_f32,
-                     const float* resid, bf16_t* out_bf16, const int* row_live, const int* n_live, hipStream_t s) {
+                     const float* resid, bf16_t* out_bf16, const int* row_live, const int* n_live, bool live_varies,
+                     hipStream_t s) {
     if (m < 1 || n < 64 || k < BK || k % BK != 0 || p.cfg < 0 || p.cfg >= kNumTiles || n % kTiles[p.cfg].bn != 0) {
         laps_set_error("gemm: unsupported shape m=%d n=%d k=%d for tile %d", m, n, k, p.cfg);
         return LAPS_EINVAL;
     }
     if (p.ws != 1 && (p.k_per_split / BK) % p.ws != 0) {
         laps_set_error("gemm: K slice of %d slabs is not a multiple of the %d weight stages", p.k_per_split / BK, p.ws);
+        return LAPS_EINVAL;
+    }
+    if (kTiles[p.cfg].bm == 128 && !(p.cfg == 1 && p.ws == 1) && k > kSkinnyMaxK) {
+        laps_set_error("gemm: K = %d is too long for tile %d", k, p.cfg);
         return LAPS_EINVAL;
     }
     if (p.epi != EPI_PARTIAL && p.split != 1) {
@@ -545,8 +649,17 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     g.out_bf16 = out_bf16;
     g.row_live = row_live;
     g.n_live = n_live;
+    // batches of an unknown number of live rows, un-split plans of the 256-row class: the width is chosen on the device
+    if (live_varies && n_live && m > 256 && p.split == 1 && kTiles[p.cfg].bm == 256 && n % 256 == 0 && k % (2 * BK) == 0) {
+        if (n % 160 == 0 && p.epi == EPI_PARTIAL) return launch_width<160, EPI_PARTIAL>(g, s);
+        if (n % 160 == 0 && p.epi == EPI_RESID) return launch_width<160, EPI_RESID>(g, s);
+        if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_width<224, EPI_PARTIAL>(g, s);
+        if (n % 224 == 0 && p.epi == EPI_RESID) return launch_width<224, EPI_RESID>(g, s);
+    }
 #define LAPS_TILE_CASE(cfg, BM, BN, WM, WN, EPI, WS) \
-    case ((cfg) * 4 + (EPI)) * 8 + (WS): return launch_tile<BM, BN, WM, WN, EPI, WS>(g, s)
+    case ((cfg) * 4 + (EPI)) * 8 + (WS):             \
+        if (skinny_loads<BM, BN, WS> && g.tiles_m == 1) return launch_tile<BM, BN, WM, WN, EPI, WS, skinny_loads<BM, BN, WS>>(g, s); \
+        return launch_tile<BM, BN, WM, WN, EPI, WS, false>(g, s)
     switch ((p.cfg * 4 + p.epi) * 8 + p.ws) {
         LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_PARTIAL, 1);
         LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_PARTIAL, 2);

@@ -63,8 +63,10 @@ void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // row class and columns 
 // row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified:
 // the skinny tiles do not load them (they compute with zeros), and a row tile of padding only is skipped.
 // n_live: NULL, or a device int: rows at and past it are padding (batches whose padding is all at the end).
+// live_varies: the launch will be replayed with other values of *n_live (a captured graph).
 int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m, int n, int k, float* out_f32,
-                     const float* resid, bf16_t* out_bf16, const int* row_live, const int* n_live, hipStream_t s);
+                     const float* resid, bf16_t* out_bf16, const int* row_live, const int* n_live, bool live_varies,
+                     hipStream_t s);
 
 // ----------------------------------------------------------------------------- element-wise / epilogues
 int laps_launch_rope_table(float2* table, int max_pos, int head_dim, float theta, hipStream_t s);

@@ -1,0 +1,50 @@
+"""A captured graph of many rows at different fills: the GEMMs choose their tile width and deal out their tiles by the
+number of live rows they find on the device, so every fill has to give what the un-captured path gives."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_11589_amd import api, inputs
+
+pytestmark = pytest.mark.gpu
+
+# q/k/v 3584 = 14 x 256 = 16 x 224 columns, o / down 2560 = 10 x 256 = 16 x 160: all three widths of either kind
+CFG = inputs.ModelCfg(2560, 20, 4, 128, 1024, 1)
+BUCKET, DEPTH = 64, 64
+
+
+@pytest.fixture(scope="module")
+def setup():
+    ctx = api.LapsCtx(CFG, 256)
+    layer = ctx.upload_layer(inputs.make_layer_weights(CFG, 5, 0))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.empty((BUCKET * DEPTH, CFG.hidden), device="cuda").normal_(0, 1, generator=g)
+    table = torch.arange(DEPTH * 4, dtype=torch.int32, device="cuda").view(DEPTH, 4)
+    kp, vp = ctx.new_pools(DEPTH * 4, 1, zero=True)
+    stream = torch.cuda.Stream()
+    graph = ctx.laps_graph_capture([layer], BUCKET, DEPTH, 4, kp, vp, stream)
+    yield ctx, layer, x, table, kp, vp, stream, graph
+    graph.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("lens", [[1], [64] * 4, [64] * 4 + [1], [37] * 19 + [1], [64] * 31 + [63], [64] * 43 + [24],
+                                  [64] * 64])
+def test_every_fill_of_a_graph_matches_the_uncaptured_path(setup, lens):
+    ctx, layer, x, table, kp, vp, stream, graph = setup
+    n, rows = len(lens), sum(lens)
+    d = lambda a: torch.from_numpy(np.asarray(a, np.int32)).cuda()
+    pre, out = d([0] * n), torch.empty((rows, CFG.hidden), device="cuda")
+    graph.laps_graph_stage(n, d(lens), pre, table[:n].contiguous(), x[:rows].contiguous(), stream)
+    graph.laps_graph_replay(stream)
+    graph.laps_graph_read_output(rows, out, stream)
+    torch.cuda.synchronize()
+    k_graph, v_graph = kp[0].clone(), vp[0].clone()
+    want = ctx.laps_prefill_layer(layer, d(np.concatenate([[0], np.cumsum(lens)])), None, pre, table[:n].contiguous(), kp[0], vp[0],
+                                  x[:rows].contiguous())
+    torch.cuda.synchronize()
+    # other K splits on the un-captured side: fp32 sums in another order, re-rounded to bf16 operands four times in the
+    # layer (2^-9 / sqrt(3) each, in part of the elements)
+    assert float((out - want).norm() / want.norm()) < 4 * 2.0 ** -9 / 3 ** 0.5
+    assert float((k_graph.double() - kp[0].double()).norm() / kp[0].double().norm()) < 2.0 ** -9
+    assert float((v_graph.double() - vp[0].double()).norm() / vp[0].double().norm()) < 2.0 ** -9
