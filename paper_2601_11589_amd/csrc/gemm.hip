@@ -551,6 +551,9 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         int cfg;
         if (n % 256 == 0 && (n % 128 != 0 || ksteps / auto_split(5) >= 24)) cfg = 5;
         else cfg = (n % 128 == 0) ? 0 : 1;
+        // SwiGLU on 129..256 tiles of 128 columns: un-split, and so fused, where 256 columns would need two K slices
+        // and the row kernel (14B gate/up at 8 / 64 / 128 rows 56 / 65 / 75 -> 49 / 57 / 66 us with that kernel)
+        if (cfg == 5 && want_epi == EPI_SWIGLU && force_split == 0 && auto_split(5) > 1 && auto_split(0) == 1 && n % 128 == 0) cfg = 0;
         if (cfg == 1 && want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
         const int split = force_split > 0 ? force_split : auto_split(cfg);
         return finish(cfg, split);
