@@ -9,7 +9,9 @@
 //   * fragments of k-step kk+1 are read from LDS into a second register set before the MFMAs of
 //     k-step kk are issued, so LDS latency hides behind 8..16 MFMAs;
 //   * the registers holding slab kt+1 are written to the other LDS buffer in the middle of slab kt
-//     and immediately reloaded with slab kt+2 from HBM (about 1.75 slabs of prefetch distance);
+//     and immediately reloaded from HBM with slab kt+1+WS; WS = 2 sets of staging registers keep two
+//     slabs in flight (the large tiles gain 2-7 % over one: 2048 x 5120 x 27648 on 256x160 527 -> 494 us,
+//     2048 x 55296 x 5120 on 256x256 966 -> 951);
 //   * the one barrier per slab sits in the middle of the last k-step's MFMAs and waits on LDS
 //     traffic only, never on the HBM loads in flight.
 // Epilogues: raw K-slice partial sums (split-K, reduced deterministically by the row kernels in
@@ -164,16 +166,18 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
     }
 }
 
-// Streaming weight loads and A rows through a buffer descriptor: the skinny tiles.  Its 32-bit offsets hold a tile of 128
-// rows up to K = 2^23; longer rows take the one-slab variant of the 128x64 tile, which addresses like the large tiles.
-constexpr int kSkinnyMaxK = 1 << 23;
+// Streaming weight loads and A rows through a buffer descriptor: the skinny tiles.  The 32-bit offsets of buffer
+// descriptors hold a tile of 256 rows up to K = 2^22; longer rows take the one-slab variant of the 128x64 tile, which
+// addresses every row by a pointer.
+constexpr int kMaxBufferK = 1 << 22;
 template <int BM, int BN, int WS>
 constexpr bool skinny_loads = BM <= 128 && !(BN == 64 && WS == 1);
 
 // WS = number of register sets that stage slabs: WS slabs (A and W chunks alike - loads return in
 // issue order, so a shallower A stream would throttle the W stream) are in flight per workgroup.
-// WS > 1 is for the bandwidth-bound skinny shapes; the K loop is then unrolled WS times so every set
-// index is static, and the K slice must hold a multiple of WS slabs.
+// With WS = 2 the K loop is unrolled so that every set index is static, and a K slice must hold a multiple of
+// two slabs; WS = 1 serves K of an odd number of slabs (and 192x128, whose second set costs the second workgroup's
+// registers).
 //
 // One tile of the rows_in live rows: workgroup `bid` of tiles_m * tiles_n * g.split.  late_live: NULL, or where the number
 // of live rows is found if it does not decide which tile this is (a single row tile): it is then read behind the first
@@ -194,6 +198,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const int KT = (kend - kbeg) / BK;
 
     constexpr bool NT = skinny_loads<BM, BN, WS>;
+    constexpr bool WIDE = BM == 256;
     const int tid = threadIdx.x;
     if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
         bool any = false;
@@ -213,17 +218,33 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const int wm = wave / WN, wn = wave % WN;
     const int lrow = lane & 31, lk = lane >> 5;
 
-    // slab copy assignment: 16-byte chunk c = tid + i*NT -> (row, kc)
-    const u32x4* ag[T::A_LOADS];
-    const u32x4* bg[T::B_LOADS];
-    int a_dst[T::A_LOADS], b_dst[T::B_LOADS];
+    // Slab copy assignment: 16-byte chunk c = tid + i*NT -> row c / CHUNKS = row0 + i * RPP, chunk kc.  RPP is a multiple
+    // of 16, so all rows of a thread share one swizzle and their LDS places differ by a constant.  The large tiles
+    // address both operands through buffer descriptors: one 32-bit offset per operand and thread instead of a pointer per
+    // row, which is what lets 256x256 hold two slabs in flight besides its 256 accumulators; A rows past M lie past the
+    // descriptor's end and return zero without a request.
+    constexpr int RPP = T::NT / CHUNKS;
+    static_assert(RPP % 16 == 0, "rows of a thread must share a swizzle");
+    const int row0 = tid / CHUNKS, kc0 = tid % CHUNKS;
+    const int dst0 = row0 * CHUNKS + swz(row0, kc0);
+    const u32x4* ag[WIDE ? 1 : T::A_LOADS];
+    const u32x4* bg[WIDE ? 1 : T::B_LOADS];
     u32x4 rrb[WS][T::B_LOADS];   // staged W slabs: slab j lives in set j % WS
+    const unsigned row_bytes = (unsigned)K * 2u;   // K <= kMaxBufferK: a tile of 256 rows stays below 2^31 bytes
+    __amdgpu_buffer_rsrc_t b_rsrc;
+    const unsigned off0 = (unsigned)row0 * row_bytes + (unsigned)kc0 * 16u;   // of either operand, from its slice's begin
+    if constexpr (WIDE) {
+        b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.W) + (size_t)n0 * K + kbeg, 0,
+                                                   (int)((unsigned)BN * row_bytes - (unsigned)kbeg * 2u), 0x00020000);
 #pragma unroll
-    for (int i = 0; i < T::B_LOADS; ++i) {
-        const int c = tid + i * T::NT, row = c / CHUNKS, kc = c % CHUNKS;
-        bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row) * K + kbeg) + kc;
-        b_dst[i] = row * CHUNKS + swz(row, kc);
-        rrb[0][i] = STREAM ? __builtin_nontemporal_load(bg[i]) : *bg[i];
+        for (int i = 0; i < T::B_LOADS; ++i)
+            rrb[0][i] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, off0, (unsigned)(i * RPP) * row_bytes, 0);
+    } else {
+#pragma unroll
+        for (int i = 0; i < T::B_LOADS; ++i) {
+            bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row0 + i * RPP) * K + kbeg) + kc0;
+            rrb[0][i] = STREAM ? __builtin_nontemporal_load(bg[i]) : *bg[i];
+        }
     }
     int M = rows_in;
     if (late_live != nullptr) {
@@ -237,18 +258,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     // returns zero without a request and without the branch (and, in the prologue, the wait) that a condition
     // around each load cost.
     u32x4 rra[WS][T::A_LOADS];   // staged A slabs, same rule as rrb
-    unsigned a_off[T::A_LOADS];
-    const unsigned a_bytes = NT ? (unsigned)BM * (unsigned)K * 2u : 0u;   // at most 2^31, see kSkinnyMaxK
-    const __amdgpu_buffer_rsrc_t a_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.A) + (size_t)m0 * K, 0, a_bytes, 0x00020000);
+    unsigned a_off[WIDE ? 1 : T::A_LOADS];
+    const unsigned a_rows = WIDE ? (unsigned)(M - m0 < BM ? M - m0 : BM) : (unsigned)BM;
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(g.A) + (size_t)m0 * K, 0, NT || WIDE ? (int)(a_rows * row_bytes) : 0, 0x00020000);
+    if constexpr (WIDE) {
+        a_off[0] = off0 + (unsigned)kbeg * 2u;
+    } else {
 #pragma unroll
-    for (int i = 0; i < T::A_LOADS; ++i) {
-        const int c = tid + i * T::NT, row = c / CHUNKS, kc = c % CHUNKS;
-        const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
-        ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc;
-        a_dst[i] = row * CHUNKS + swz(row, kc);
-        const bool live = m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0);
-        a_off[i] = live ? ((unsigned)row * (unsigned)K + (unsigned)kbeg) * 2u + (unsigned)kc * 16u : 0x80000000u;
+        for (int i = 0; i < T::A_LOADS; ++i) {
+            const int row = row0 + i * RPP;
+            const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
+            ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc0;
+            const bool live = m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0);
+            a_off[i] = live ? off0 + (unsigned)(i * RPP) * row_bytes + (unsigned)kbeg * 2u : 0x80000000u;
+        }
     }
     // fragment read offsets (in 16-byte chunks) inside one LDS buffer, per k-step
     int a_src[T::MI], b_src[T::NI];
@@ -275,22 +299,27 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     auto clampk = [&](int kt) { return kt < KT ? kt : KT - 1; };  // tail: reload a valid slab, never used
     // copy op i of the slab pipeline: i < A_LOADS moves an A chunk, else a W chunk held in set `ws`
     auto gload_one = [&](int i, int kt, int ws) {
+        const int j = i - T::A_LOADS;
         if (i < T::A_LOADS) {
-            if constexpr (NT) {
+            if constexpr (WIDE)   // the row goes into the lane's offset: it is what the range check sees
+                rra[ws][i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[0] + (unsigned)(i * RPP) * row_bytes,
+                                                                   clampk(kt) * (BK * 2), 0);
+            else if constexpr (NT)
                 rra[ws][i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], clampk(kt) * (BK * 2), 0);
-            } else {
+            else
                 rra[ws][i] = ag[i][clampk(kt) * CHUNKS];
-            }
+        } else if constexpr (WIDE) {
+            rrb[ws][j] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, off0, (unsigned)(j * RPP) * row_bytes + clampk(kt) * (BK * 2), 0);
         } else {
             // weights are read once: streaming (non-temporal) loads keep them from evicting the A slabs,
             // which every workgroup on the CU and on the XCD re-reads, out of L1 / L2
-            const u32x4* src = bg[i - T::A_LOADS] + clampk(kt) * CHUNKS;
-            rrb[ws][i - T::A_LOADS] = STREAM ? __builtin_nontemporal_load(src) : *src;
+            const u32x4* src = bg[j] + clampk(kt) * CHUNKS;
+            rrb[ws][j] = STREAM ? __builtin_nontemporal_load(src) : *src;
         }
     };
     auto lstore_one = [&](int i, int buf, int ws) {
-        if (i < T::A_LOADS) As[buf * BM * CHUNKS + a_dst[i]] = rra[ws][i];
-        else Bs[buf * BN * CHUNKS + b_dst[i - T::A_LOADS]] = rrb[ws][i - T::A_LOADS];
+        if (i < T::A_LOADS) As[buf * BM * CHUNKS + dst0 + i * RPP * CHUNKS] = rra[ws][i];
+        else Bs[buf * BN * CHUNKS + dst0 + (i - T::A_LOADS) * RPP * CHUNKS] = rrb[ws][i - T::A_LOADS];
     };
     // order of need by the MFMA sequence (mi-major): A row block 0, every B column block, remaining A
     auto fload_one = [&](int i, int buf, int kk, int set) {
@@ -433,8 +462,8 @@ __global__ __launch_bounds__(256, 1) void gemm_width_kernel(const GemmArgs g, co
     }
     const int tiles_n = g.N / width[pick];
     if ((int)blockIdx.x >= tiles_m * tiles_n) return;
-    if (pick == 0) gemm_tile<256, W, 4, 1, EPI, 1, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
-    else if (pick == 1) gemm_tile<256, 256, 2, 2, EPI, 1, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    if (pick == 0) gemm_tile<256, W, 4, 1, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else if (pick == 1) gemm_tile<256, 256, 2, 2, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
     else gemm_tile<256, 128, 2, 2, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
 }
 
@@ -459,19 +488,20 @@ struct TileDef {
     int ws;            // slabs kept in flight per workgroup where the K slices allow it
     double fill, slab, part;   // cost model of launches above 128 rows, see laps_gemm_plan
 };
-// index = GemmPlan::cfg.  The cost columns are a fit over 4600 launches (all tiles and K splits on the 7B, 14B and
-// 32B projections at 23 row counts from 129 to 8192, weights cold; rms error 6 %): microseconds a workgroup takes besides its slabs,
-// microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.
+// index = GemmPlan::cfg.  The cost columns are a fit over 4800 launches (all tiles and K splits on the 7B, 14B and 32B
+// projections at 24 row counts from 129 to 8192, weights cold; rms error 7 %): microseconds a workgroup takes besides its
+// slabs, microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.
 constexpr TileDef kTiles[] = {
-    {128, 128, 2, 1.28, 0.524, 0.00},  // 0: 4 waves of 64x64, two workgroups per compute unit
+    {128, 128, 2, 1.11, 0.521, 0.06},  // 0: 4 waves of 64x64, two workgroups per compute unit
     {128, 64, 2, 1.20, 0.350, 0.00},   // 1: 4 waves of 64x32, for n % 128 != 0
-    {256, 256, 1, 5.95, 1.515, 0.26},  // 2: 4 waves of 128x128
-    {256, 224, 1, 5.86, 1.329, 0.24},  // 3: 4 waves of 64x224 (N = 7168 -> 32 column tiles)
-    {256, 160, 1, 4.31, 1.078, 0.27},  // 4: 4 waves of 64x160 (N = 5120 -> 32 column tiles)
-    {128, 256, 2, 4.89, 0.943, 0.13},  // 5: 8 waves of 64x64: the streaming tile, A slab shared by 256 columns
-    {192, 256, 2, 5.76, 1.163, 0.21},  // 6: 4 waves of 96x128
-    {192, 128, 1, 2.10, 0.715, 0.08},  // 7: 4 waves of 96x64, two workgroups per compute unit
-    {256, 128, 2, 4.54, 0.866, 0.27},  // 8: 4 waves of 128x64
+    {256, 256, 2, 5.25, 1.430, 0.25},  // 2: 4 waves of 128x128
+    {256, 224, 2, 5.19, 1.234, 0.24},  // 3: 4 waves of 64x224 (N = 7168 -> 32 column tiles)
+    {256, 160, 2, 4.38, 0.985, 0.24},  // 4: 4 waves of 64x160 (N = 5120 -> 32 column tiles)
+    {128, 256, 2, 2.44, 0.904, 0.21},  // 5: 8 waves of 64x64: the streaming tile, A slab shared by 256 columns
+    {192, 256, 2, 5.75, 1.160, 0.20},  // 6: 4 waves of 96x128
+    {192, 128, 1, 1.81, 0.716, 0.09},  // 7: 4 waves of 96x64, two workgroups per compute unit
+    {256, 128, 2, 3.01, 0.863, 0.25},  // 8: 4 waves of 128x64
+    {256, 192, 2, 2.93, 1.199, 0.31},  // 9: 4 waves of 64x192 (N = 55296, 27648, 4608)
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -515,7 +545,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         int per = (ksteps + split - 1) / split;
         // with 2 slabs in flight every K slice must hold a multiple of 2 slabs
         p.ws = 1;
-        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0 && k <= kSkinnyMaxK) {
+        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0 && k < kMaxBufferK) {
             per = (per + 1) / 2 * 2;
             p.ws = 2;
         }
@@ -525,7 +555,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         p.epi = (p.split == 1) ? want_epi : EPI_PARTIAL;
         return p;
     };
-    if (k > kSkinnyMaxK && (m <= 128 || n % 256 != 0)) {
+    if (k >= kMaxBufferK) {
         if (want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
         return finish(1, force_split > 0 ? force_split : 1);
     }
@@ -563,15 +593,15 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     //   rounds * (fill + slabs * slab) [a partly filled chip runs its slabs up to `part` faster: less traffic, more
     //   clock], not less than the weights take from HBM; a split adds the partial sums written, the reduce launch and
     //   the reading back; an un-split residual epilogue adds the RMSNorm launch that the reduce kernel would contain.
-    // Over the 230 measured shapes the choice is 1 % slower than the fastest measured one on average, more than 5 % in
-    // 18.  Against the one rule before it (256-row tiles only) the 32B layer's projections take, q/k/v, o, gate/up,
+    // Over the 240 measured shapes the choice is 1 % slower than the fastest measured one on average, more than 5 % in
+    // 17.  Against the one rule before it (256-row tiles only) the 32B layer's projections take, q/k/v, o, gate/up,
     // down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows 42 -> 36, 41 -> 36, 272 -> 217,
     // 142 -> 116; 7B at 256 rows 35 -> 19, 38 -> 22, 92 -> 92, 63 -> 53.
     double best = 1e30;
     int best_cfg = -1, best_split = 1;
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
-        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0) || (t.bm == 128 && k > kSkinnyMaxK)) continue;
+        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0)) continue;
         if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
         const int tiles_m = (m + t.bm - 1) / t.bm;
         if (t.bm == 192 && tiles_m != (m + 255) / 256) continue;
@@ -584,12 +614,12 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
             const long wgs = (long)tiles_m * (n / t.bn) * s;
             const long rounds = (wgs + 255) / 256;
             const double filled = wgs < 256 ? wgs / 256.0 : 1.0;
-            double us = 4.0 + rounds * (t.fill + per * t.slab * (1.0 - t.part * (1.0 - filled)));
-            const double stream = 4.0 + 2.0 * n * (double)k / 3.94e6;
-            us = us > stream ? us : stream;
-            if (s > 1) us += partial / 8.5e6;
-            if (want_epi == EPI_PARTIAL || s > 1) us += partial / 6.2e6;   // the row kernel's reading
-            if (want_epi != EPI_PARTIAL && s > 1) us += 3.9;
+            const double tiles = 4.0 + rounds * (t.fill + per * t.slab * (1.0 - t.part * (1.0 - filled)));
+            const double stream = 4.0 + 2.0 * n * (double)k / 4.6e6;
+            double us = (tiles > stream ? tiles : stream) + 0.02 * tiles;   // of equal streams, the one with less to compute
+            if (s > 1) us += partial / 8.3e6;
+            if (want_epi == EPI_PARTIAL || s > 1) us += partial / 5.9e6;   // the row kernel's reading
+            if (want_epi != EPI_PARTIAL && s > 1) us += 3.6;
             if (want_epi == EPI_RESID && s == 1) us += 4.0 + 6.0 * m * (double)n / 4.5e6;
             if (us < best) {
                 best = us;
@@ -629,7 +659,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         laps_set_error("gemm: K slice of %d slabs is not a multiple of the %d weight stages", p.k_per_split / BK, p.ws);
         return LAPS_EINVAL;
     }
-    if (kTiles[p.cfg].bm == 128 && !(p.cfg == 1 && p.ws == 1) && k > kSkinnyMaxK) {
+    if (!(p.cfg == 1 && p.ws == 1) && k >= kMaxBufferK) {
         laps_set_error("gemm: K = %d is too long for tile %d", k, p.cfg);
         return LAPS_EINVAL;
     }
@@ -675,12 +705,25 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_RESID, 1);
         LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_RESID, 2);
         LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_PARTIAL, 2);
+        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_PARTIAL, 2);
         LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_RESID, 1);
+        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_RESID, 2);
+        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_RESID, 1);
+        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_RESID, 2);
         LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_SWIGLU, 1);
+        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_SWIGLU, 2);
+        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_SWIGLU, 1);
+        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_SWIGLU, 2);
         LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_PARTIAL, 2);
         LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_RESID, 1);
+        LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_RESID, 2);
         LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_PARTIAL, 1);
+        LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_PARTIAL, 2);
         LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_RESID, 1);
+        LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_RESID, 2);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_PARTIAL, 1);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_PARTIAL, 2);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_RESID, 1);
