@@ -81,34 +81,59 @@ __global__ void prep_kernel(int n_rows, int n_seq, const int* __restrict__ row_s
 }
 
 // ------------------------------------------------------------------ RMSNorm: fp32 row -> bf16 row
-// One row with ROW_THREADS threads; xr may be any fp32 row of d values, red holds ROW_THREADS / 64 floats of LDS.
-__device__ __forceinline__ void rmsnorm_row(const f32x4* __restrict__ xr, const bf16_t* __restrict__ w,
-                                            bf16_t* __restrict__ out_row, int d, float eps, float* red) {
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < d / 4; i += ROW_THREADS) {
-        const f32x4 v = xr[i];
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+// One row of d <= 4 * ROW_THREADS * MAXV values with ROW_THREADS threads, held in registers between the two passes; red
+// holds ROW_THREADS / 64 floats of LDS.
+constexpr int ROW_MAXV = 8192 / 4 / ROW_THREADS;
+template <int MAXV>
+struct RowRegs {
+    f32x4 v[MAXV];
+    __device__ __forceinline__ void load(const f32x4* __restrict__ xr, int d) {
+#pragma unroll
+        for (int j = 0; j < MAXV; ++j) {
+            const int i = threadIdx.x + j * ROW_THREADS;
+            if (i < d / 4) v[j] = xr[i];
+        }
     }
-    const float inv = rsqrtf(block_sum(ss, red) / (float)d + eps);
-    u32x2* orow = reinterpret_cast<u32x2*>(out_row);
-    const u32x2* wr = reinterpret_cast<const u32x2*>(w);
-    for (int i = threadIdx.x; i < d / 4; i += ROW_THREADS) {
-        const f32x4 v = xr[i];
-        const u32x2 g = wr[i];
-        u32x2 o;
-        o.x = pack_bf16x2(v.x * inv * __uint_as_float(g.x << 16), v.y * inv * __uint_as_float(g.x & 0xffff0000u));
-        o.y = pack_bf16x2(v.z * inv * __uint_as_float(g.y << 16), v.w * inv * __uint_as_float(g.y & 0xffff0000u));
-        orow[i] = o;
+    __device__ __forceinline__ void store(f32x4* __restrict__ dst, int d) const {
+#pragma unroll
+        for (int j = 0; j < MAXV; ++j) {
+            const int i = threadIdx.x + j * ROW_THREADS;
+            if (i < d / 4) dst[i] = v[j];
+        }
     }
-}
+    __device__ __forceinline__ void norm(const bf16_t* __restrict__ w, bf16_t* __restrict__ out_row, int d, float eps,
+                                         float* red) const {
+        float ss = 0.f;
+#pragma unroll
+        for (int j = 0; j < MAXV; ++j)
+            if (threadIdx.x + j * ROW_THREADS < d / 4) ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
+        const float inv = rsqrtf(block_sum(ss, red) / (float)d + eps);
+        u32x2* orow = reinterpret_cast<u32x2*>(out_row);
+        const u32x2* wr = reinterpret_cast<const u32x2*>(w);
+#pragma unroll
+        for (int j = 0; j < MAXV; ++j) {
+            const int i = threadIdx.x + j * ROW_THREADS;
+            if (i < d / 4) {
+                const u32x2 g = wr[i];
+                u32x2 o;
+                o.x = pack_bf16x2(v[j].x * inv * __uint_as_float(g.x << 16), v[j].y * inv * __uint_as_float(g.x & 0xffff0000u));
+                o.y = pack_bf16x2(v[j].z * inv * __uint_as_float(g.y << 16), v[j].w * inv * __uint_as_float(g.y & 0xffff0000u));
+                orow[i] = o;
+            }
+        }
+    }
+};
 
+template <int MAXV>
 __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_kernel(const float* __restrict__ x,
                                                                const bf16_t* __restrict__ w, bf16_t* __restrict__ out,
                                                                int d, float eps, const int* __restrict__ row_live) {
     __shared__ float red[ROW_THREADS / 64];
     const size_t row = blockIdx.x;
     if (row_live && row_live[row] < 0) return;  // padding row: nothing reads its output
-    rmsnorm_row(reinterpret_cast<const f32x4*>(x + row * d), w, out + row * d, d, eps, red);
+    RowRegs<MAXV> r;
+    r.load(reinterpret_cast<const f32x4*>(x + row * d), d);
+    r.norm(w, out + row * d, d, eps, red);
 }
 
 // ------------------------------------------------------------------ sum K slices + residual (+ RMSNorm)
@@ -407,89 +432,119 @@ __global__ void kv_move_kernel(int n_seq, int n_tokens, const int* __restrict__ 
     }
 }
 
-// Metadata of one captured bucket, from what the caller staged for its first n_real slots: lengths
-// clamped to [0, len_bucket], prefix lengths to >= 0, the other slots empty, and the sequences packed
-// one after the other (row_start = running sum of the clamped lengths, so the total never exceeds the
-// graph's depth * len_bucket rows whatever the caller's arrays hold); then the attention's work-item table
-// for those lengths.  One workgroup; thread t owns a run of consecutive slots.
-constexpr int META_THREADS = 256;
-__global__ __launch_bounds__(META_THREADS) void stage_meta_kernel(const StageArgs a) {
-    __shared__ int sums[META_THREADS];
-    __shared__ int carry;
-    const int t = threadIdx.x;
-    const int depth = a.depth;
-    const int per = (depth + META_THREADS - 1) / META_THREADS;
-    const int lo = t * per, hi = (lo + per < depth) ? lo + per : depth;
-    auto len_of = [&](int i) {
-        int l = i < a.n_real ? a.seq_len[i] : 0;
-        l = l > a.len_bucket ? a.len_bucket : l;
-        return l < 0 ? 0 : l;
-    };
-    int mine = 0;
-    for (int i = lo; i < hi; ++i) mine += len_of(i);
-    sums[t] = mine;
-    __syncthreads();
-    for (int o = 1; o < META_THREADS; o <<= 1) {  // inclusive scan of the per-thread sums
-        const int v = (t >= o) ? sums[t - o] : 0;
-        __syncthreads();
-        sums[t] += v;
-        __syncthreads();
-    }
-    int run = sums[t] - mine;
-    for (int i = lo; i < hi; ++i) {
-        const int l = len_of(i);
-        a.row_start_out[i] = run;
-        a.seq_len_out[i] = l;
-        a.new_len_out[i] = l;
-        const int pf = i < a.n_real ? a.prefix_len[i] : 0;
-        a.prefix_out[i] = pf < 0 ? 0 : pf;
-        run += l;
-    }
-    if (t == META_THREADS - 1) a.row_start_out[depth] = sums[t];
-    __syncthreads();   // the lengths written above are read below by other threads of this workgroup
-    laps_dev_attn_sched(a.new_len_out, depth, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, sums, &carry);
-    if (a.attn_wgs > 0)
-        laps_dev_attn_bounds(a.new_len_out, a.prefix_out, depth, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
-                             a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, sums, &carry);
+// Staging of a captured bucket, one launch: workgroup 0 writes the batch's metadata, workgroup 1 + r prepares row r.  Every
+// row workgroup scans the slots' lengths itself instead of waiting for workgroup 0 (two launches, 4.8 + 9.4 us for 128
+// rows; one, 9 us; short re-prefill replay 285 -> 280, single turn 161 -> 156), and its input row is on the way meanwhile.
+//
+// The lengths the caller staged for the first n_real slots are clamped to [0, len_bucket], the other slots are empty, and
+// the sequences are packed one after the other (row_start = running sum of the clamped lengths, so the total never
+// exceeds the graph's depth * len_bucket rows whatever the caller's arrays hold).
+__device__ __forceinline__ int staged_len(const StageArgs& a, int i) {
+    int l = i < a.n_real ? a.seq_len[i] : 0;
+    l = l > a.len_bucket ? a.len_bucket : l;
+    return l < 0 ? 0 : l;
 }
 
-// One workgroup per graph row; see StageArgs.  Runs after stage_meta_kernel on the same stream.
-__global__ __launch_bounds__(ROW_THREADS) void stage_rows_kernel(const StageArgs a) {
+// Rows before this thread's run of consecutive slots [lo, hi) and rows in it; sums: ROW_THREADS / 64 ints of LDS.
+__device__ __forceinline__ int staged_scan(const StageArgs& a, int lo, int hi, int* mine_out, int* sums) {
+    int mine = 0;
+    for (int i = lo; i < hi; ++i) mine += staged_len(a, i);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) sums[wave] = incl;
+    __syncthreads();
+    int before = incl - mine;
+    for (int w = 0; w < wave; ++w) before += sums[w];
+    *mine_out = mine;
+    return before;
+}
+
+__global__ __launch_bounds__(ROW_THREADS) void stage_kernel(const StageArgs a) {
+    __shared__ int sums[ROW_THREADS / 64];
+    __shared__ int buf[ROW_THREADS];
+    __shared__ int carry;
     __shared__ float red[ROW_THREADS / 64];
-    __shared__ int live;
-    const int row = blockIdx.x;
-    {   // this workgroup's share of the page-table copy
-        const int total = a.depth * a.max_pages, n_src = a.n_real * a.max_pages;
-        const int chunk = (total + (int)gridDim.x - 1) / (int)gridDim.x;
-        const int end = (row + 1) * chunk < total ? (row + 1) * chunk : total;
-        for (int i = row * chunk + threadIdx.x; i < end; i += ROW_THREADS) a.page_table_out[i] = i < n_src ? a.page_table[i] : 0;
+    __shared__ int where[3];   // slot of this row, its first row, live
+    const int t = threadIdx.x, depth = a.depth;
+    const int per = (depth + ROW_THREADS - 1) / ROW_THREADS;
+    const int lo = t * per, hi = (lo + per < depth) ? lo + per : depth;
+    int mine;
+    if (blockIdx.x == 0) {
+        int run = staged_scan(a, lo, hi, &mine, sums);
+        for (int i = lo; i < hi; ++i) {
+            const int l = staged_len(a, i);
+            a.row_start_out[i] = run;
+            a.seq_len_out[i] = l;
+            a.new_len_out[i] = l;
+            const int pf = i < a.n_real ? a.prefix_len[i] : 0;
+            a.prefix_out[i] = pf < 0 ? 0 : pf;
+            run += l;
+        }
+        if (t == ROW_THREADS - 1) a.row_start_out[depth] = run;
+        __syncthreads();   // the lengths written above are read below by other threads of this workgroup
+        laps_dev_attn_sched(a.new_len_out, depth, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, buf, &carry);
+        if (a.attn_wgs > 0)
+            laps_dev_attn_bounds(a.new_len_out, a.prefix_out, depth, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
+                                 a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, buf, &carry);
+        return;
     }
-    if (threadIdx.x == 0) {
-        int pos, slot;   // lengths, prefixes and row offsets as clamped by stage_meta_kernel; page ids from the caller's table
-        token_meta(row, a.depth, a.row_start_out, a.seq_len_out, a.prefix_out, a.page_table, a.max_pages, a.n_pool_pages,
-                   &pos, &slot);
-        a.tok_pos[row] = pos;
-        a.tok_slot[row] = slot;
-        live = pos >= 0;
-    }
+    const int row = blockIdx.x - 1, n_rows = gridDim.x - 1;
     const f32x4* src = reinterpret_cast<const f32x4*>(a.x_in + (size_t)row * a.d);
+    f32x4* copy_to = nullptr;
     if (a.x_rows != nullptr && row < a.n_rows) {
+        copy_to = reinterpret_cast<f32x4*>(a.x_in + (size_t)row * a.d);
         src = reinterpret_cast<const f32x4*>(a.x_rows + (size_t)row * a.d);
-        f32x4* dst = reinterpret_cast<f32x4*>(a.x_in + (size_t)row * a.d);
-        if (src != dst)
-            for (int i = threadIdx.x; i < a.d / 4; i += ROW_THREADS) dst[i] = src[i];
+        if (src == copy_to) copy_to = nullptr;
+    }
+    RowRegs<ROW_MAXV> r;
+    r.load(src, a.d);
+    if (t == 0) where[2] = 0;
+    int run = staged_scan(a, lo, hi, &mine, sums);   // its barrier orders the line above before the lines below
+    if (row >= run && row < run + mine)
+        for (int i = lo; i < hi; ++i) {
+            const int l = staged_len(a, i);
+            if (row < run + l) {
+                where[0] = i;
+                where[1] = run;
+                where[2] = 1;
+                break;
+            }
+            run += l;
+        }
+    {   // this workgroup's share of the page-table copy
+        const int total = depth * a.max_pages, n_src = a.n_real * a.max_pages;
+        const int chunk = (total + n_rows - 1) / n_rows;
+        const int end = (row + 1) * chunk < total ? (row + 1) * chunk : total;
+        for (int i = row * chunk + t; i < end; i += ROW_THREADS) a.page_table_out[i] = i < n_src ? a.page_table[i] : 0;
     }
     __syncthreads();
+    const bool live = where[2] != 0;
+    if (t == 0) {   // token position and cache slot, as in token_meta; page ids from the caller's table
+        int pos = -1, slot = -1;
+        if (live) {
+            const int s = where[0], h = a.prefix_len[s];
+            pos = (h > 0 ? h : 0) + row - where[1];
+            const int pi = pos / LAPS_PAGE;
+            const int page = pi < a.max_pages ? a.page_table[(size_t)s * a.max_pages + pi] : -1;
+            slot = (page >= 0 && page < a.n_pool_pages) ? page * LAPS_PAGE + pos % LAPS_PAGE : -1;
+        }
+        a.tok_pos[row] = pos;
+        a.tok_slot[row] = slot;
+    }
+    if (copy_to) r.store(copy_to, a.d);
     if (!live) return;   // padding row: nothing reads its normed row
-    rmsnorm_row(src, a.ln_w, a.r0 + (size_t)row * a.d, a.d, a.eps, red);
+    r.norm(a.ln_w, a.r0 + (size_t)row * a.d, a.d, a.eps, red);
 }
 
 }  // namespace
 
 int laps_launch_stage(const StageArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(stage_meta_kernel, dim3(1), dim3(META_THREADS), 0, s, a);
-    LAPS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(stage_rows_kernel, dim3(a.depth * a.len_bucket), dim3(ROW_THREADS), 0, s, a);
+    hipLaunchKernelGGL(stage_kernel, dim3(a.depth * a.len_bucket + 1), dim3(ROW_THREADS), 0, s, a);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -515,7 +570,8 @@ int laps_launch_prep(int n_rows, int n_seq, const int* row_start, const int* seq
 
 int laps_launch_rmsnorm(const float* x, const bf16_t* w, bf16_t* out, int rows, int d, float eps, const int* row_live,
                         hipStream_t s) {
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(ROW_THREADS), 0, s, x, w, out, d, eps, row_live);
+    auto kern = d <= 4 * ROW_THREADS ? rmsnorm_kernel<1> : rmsnorm_kernel<ROW_MAXV>;   // d <= 8192 (check_cfg)
+    hipLaunchKernelGGL(kern, dim3(rows), dim3(ROW_THREADS), 0, s, x, w, out, d, eps, row_live);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }

@@ -90,12 +90,12 @@ int laps_launch_pack_gate_up(const bf16_t* wg, const bf16_t* wu, bf16_t* dst, in
 int laps_launch_kv_move(bool scatter, int n_seq, int n_tokens, const int* cu, const int* start_pos,
                         const int* page_table, int max_pages, bf16_t* k_tok, bf16_t* v_tok, bf16_t* k_pool,
                         bf16_t* v_pool, int n_kv, int hd, int n_pool_pages, hipStream_t s);
-// Graph staging, two launches that leave a captured stack nothing to prepare:
-// (1) one workgroup: clamped lengths / prefixes of `depth` slots (the first n_real from the caller's device arrays,
-//     the rest empty), packed row offsets row_start_out[depth + 1], and the attention's work-item table for them;
-// (2) one workgroup per graph row: token position and cache slot (as laps_launch_prep), the row's input copied from
-//     x_rows (rows below n_rows; NULL: the graph's input rows are used as they are) into x_in, its RMSNorm with the
-//     first layer's gain into r0, and a share of the page-table copy (entries past n_real rows become 0).
+// Graph staging, one launch that leaves a captured stack nothing to prepare.  One workgroup writes the clamped lengths /
+// prefixes of `depth` slots (the first n_real from the caller's device arrays, the rest empty), packed row offsets
+// row_start_out[depth + 1], and the attention's work-item table for them; one workgroup per graph row its token position
+// and cache slot (as laps_launch_prep), the row's input copied from x_rows (rows below n_rows; NULL: the graph's input
+// rows are used as they are) into x_in, its RMSNorm with the first layer's gain into r0, and a share of the page-table
+// copy (entries past n_real rows become 0).
 struct StageArgs {
     const int *seq_len, *prefix_len, *page_table;   // caller's device arrays: [n_real], [n_real], [n_real][max_pages]
     const float* x_rows;                            // caller's packed input rows or NULL
