@@ -41,21 +41,6 @@ constexpr int KT = LAPS_ATTN_KT;   // keys per tile (4 pages)
 __device__ __forceinline__ int swz8(int row, int c) { return c ^ ((row & 7) ^ ((row >> 3) & 1)); }
 __device__ __forceinline__ int swz16(int row, int c) { return c ^ (row & 15); }
 
-// per-sequence number of query-row blocks, their exclusive prefix sum, and the sequence of every work item
-// (single workgroup).  The item table spares each attention workgroup a chain of dependent loads.
-__global__ __launch_bounds__(256) void attn_sched_kernel(const int* __restrict__ new_len,
-                                                          const int* __restrict__ prefix_len, int n_seq, int group,
-                                                          int n_kv, int max_pages, int rows_per_wg,
-                                                          int* __restrict__ tile_start, int* __restrict__ item_seq,
-                                                          int max_items, int n_wgs, int* pre, int4* bounds) {
-    __shared__ int buf[256];
-    __shared__ int carry;
-    laps_dev_attn_sched(new_len, n_seq, group, rows_per_wg, tile_start, item_seq, max_items, buf, &carry);
-    if (n_wgs > 0)
-        laps_dev_attn_bounds(new_len, prefix_len, n_seq, group, n_kv, max_pages, tile_start, item_seq, max_items, n_wgs,
-                             pre, bounds, buf, &carry);
-}
-
 // NW waves per workgroup, one 32-row query tile per wave: rows per workgroup = 32 * NW.  With NW = 8
 // two waves share a SIMD, so one wave's softmax (VALU, exp) overlaps the other's MFMAs.
 // key tiles per split (lower bound) and the split geometry shared by the attention and the merge kernel
@@ -879,20 +864,6 @@ int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int h
     size_t wgs = partial_bytes / (2 * slot) / 8 * 8;   // whole groups of the 8 XCDs
     wgs = wgs < LAPS_ATTN_MAX_WGS ? wgs : LAPS_ATTN_MAX_WGS;
     return wgs < 64 ? 0 : (int)wgs;
-}
-
-int laps_launch_attn_sched(const int* new_len, const int* prefix_len, int n_seq, int n_tokens, int max_pages,
-                           int* tile_start, int* item_seq, int n_q, int n_kv, int hd, size_t partial_bytes, hipStream_t s) {
-    int mt, max_items, n_split;
-    attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split);
-    int* pre;
-    int4* bounds;
-    laps_attn_item_tables(item_seq, n_tokens, n_seq, n_q / n_kv, &pre, &bounds);
-    hipLaunchKernelGGL(attn_sched_kernel, dim3(1), dim3(256), 0, s, new_len, prefix_len, n_seq, n_q / n_kv, n_kv, max_pages,
-                       128 * mt, tile_start, item_seq, max_items,
-                       laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes), pre, bounds);
-    LAPS_LAUNCH_CHECK();
-    return LAPS_OK;
 }
 
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,

@@ -309,6 +309,33 @@ static int run_gemm(laps_ctx* c, int cls, bool capturing, const bf16_t* a, const
     return laps_gemm_launch(p, a, w, m, n, k, out_f32, resid, out_bf16, row_live, n_live, live_varies, s);
 }
 
+// What both users of laps_launch_begin fill in alike; no rows.
+static BeginArgs begin_args(const laps_ctx* c, const BatchDesc& b, unsigned char* ws, const WsLayout& L) {
+    const laps_model_cfg& cf = c->cfg;
+    BeginArgs a = {};
+    a.row_start = b.row_start;
+    a.seq_len = b.seq_len;
+    a.prefix_len = b.prefix_len;
+    a.page_table = b.page_table;
+    a.n_seq = b.n_seq;
+    a.max_pages = b.max_pages;
+    a.n_pool_pages = c->pool_pages;
+    a.group = cf.n_q_heads / cf.n_kv_heads;
+    int n_split = 0, min_tiles = 0;
+    laps_attn_plan(b.n_seq, b.n_tokens, a.group, cf.n_kv_heads, b.max_pages, &a.rows_per_wg, &a.max_items, &n_split, &min_tiles);
+    a.n_kv = cf.n_kv_heads;
+    a.attn_wgs = laps_attn_persistent_wgs(b.n_seq, b.n_tokens, a.group, cf.n_kv_heads, cf.head_dim, b.max_pages, L.total - L.partial);
+    a.new_len = reinterpret_cast<int*>(ws + L.new_len);
+    a.tok_pos = reinterpret_cast<int*>(ws + L.tok_pos);
+    a.tok_slot = reinterpret_cast<int*>(ws + L.tok_slot);
+    a.tile_start = reinterpret_cast<int*>(ws + L.tile_start);
+    a.item_seq = reinterpret_cast<int*>(ws + L.item_seq);
+    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds);
+    a.d = cf.hidden;
+    a.eps = cf.rms_eps;
+    return a;
+}
+
 // Runs layers [0, n_layers) of `w`.  Token metadata (prep) is computed once.  r0_staged: the first layer's normed
 // rows, with token metadata and the attention's work-item table already in the workspace (a captured graph:
 // laps_graph_stage prepared them, so that a replay starts with the first projection).
@@ -337,20 +364,13 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
     const size_t partial_cap = partial_cap_for(cf, M), partial_bytes = L.total - L.partial;
 
     if (r0_staged == nullptr) {
-        {
-            ProfScope ps(c, s, LAPS_K_PREP, capturing);
-            LAPS_TRY(laps_launch_prep(M, b.n_seq, b.row_start, b.seq_len, b.prefix_len, b.page_table, b.max_pages,
-                                      c->pool_pages, new_len, tok_pos, tok_slot, s));
-        }
-        {
-            ProfScope ps(c, s, LAPS_K_PREP, capturing);
-            LAPS_TRY(laps_launch_attn_sched(new_len, b.prefix_len, b.n_seq, M, b.max_pages, tile_start, item_seq,
-                                            cf.n_q_heads, cf.n_kv_heads, hd, partial_bytes, s));
-        }
-        {
-            ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);
-            LAPS_TRY(laps_launch_rmsnorm(x_in, static_cast<const bf16_t*>(w[0].ln1_w), r, M, d, cf.rms_eps, tok_pos, s));
-        }
+        ProfScope ps(c, s, LAPS_K_PREP, capturing);
+        BeginArgs a = begin_args(c, b, ws, L);
+        a.n_rows = M;
+        a.x = x_in;
+        a.ln_w = static_cast<const bf16_t*>(w[0].ln1_w);
+        a.r0 = r;
+        LAPS_TRY(laps_launch_begin(a, s));
     }
     for (int l = 0; l < n_layers; ++l) {
         const laps_layer_weights& lw = w[l];
@@ -652,12 +672,16 @@ extern "C" int laps_attention(laps_ctx* c, int32_t n_seq, int32_t n_tokens, cons
     unsigned char* w8 = static_cast<unsigned char*>(ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int* new_len = reinterpret_cast<int*>(w8 + L.new_len);
-    LAPS_TRY(laps_launch_prep(n_tokens, n_seq, cu, seq_len, prefix_len, pt, max_pages, c->pool_pages, new_len,
-                              reinterpret_cast<int*>(w8 + L.tok_pos), reinterpret_cast<int*>(w8 + L.tok_slot), s));
+    BatchDesc b = {};
+    b.n_seq = n_seq;
+    b.n_tokens = n_tokens;
+    b.row_start = cu;
+    b.seq_len = seq_len;
+    b.prefix_len = prefix_len;
+    b.page_table = pt;
+    b.max_pages = max_pages;
+    LAPS_TRY(laps_launch_begin(begin_args(c, b, w8, L), s));
     const size_t partial_bytes = L.total - L.partial;
-    LAPS_TRY(laps_launch_attn_sched(new_len, prefix_len, n_seq, n_tokens, max_pages,
-                                    reinterpret_cast<int*>(w8 + L.tile_start), reinterpret_cast<int*>(w8 + L.item_seq),
-                                    c->cfg.n_q_heads, c->cfg.n_kv_heads, c->cfg.head_dim, partial_bytes, s));
     return laps_launch_attention(static_cast<const bf16_t*>(q), static_cast<bf16_t*>(out),
                                  static_cast<const bf16_t*>(k_pool), static_cast<const bf16_t*>(v_pool), cu, new_len,
                                  prefix_len, pt, max_pages, n_seq, n_tokens, reinterpret_cast<int*>(w8 + L.tile_start),

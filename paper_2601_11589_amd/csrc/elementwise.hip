@@ -61,25 +61,6 @@ __device__ __forceinline__ void token_meta(int row, int n_seq, const int* __rest
     *slot_out = slot;
 }
 
-// One thread per row (and per sequence for the clamped lengths).
-__global__ void prep_kernel(int n_rows, int n_seq, const int* __restrict__ row_start, const int* __restrict__ seq_len,
-                            const int* __restrict__ prefix_len, const int* __restrict__ page_table, int max_pages,
-                            int n_pool_pages, int* __restrict__ new_len_out, int* __restrict__ tok_pos,
-                            int* __restrict__ tok_slot) {
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
-    if (row < n_seq) {
-        const int cap = row_start[row + 1] - row_start[row];
-        int l = seq_len ? seq_len[row] : cap;
-        l = l > cap ? cap : l;
-        new_len_out[row] = l < 0 ? 0 : l;
-    }
-    if (row >= n_rows) return;
-    int pos, slot;
-    token_meta(row, n_seq, row_start, seq_len, prefix_len, page_table, max_pages, n_pool_pages, &pos, &slot);
-    tok_pos[row] = pos;
-    tok_slot[row] = slot;
-}
-
 // ------------------------------------------------------------------ RMSNorm: fp32 row -> bf16 row
 // One row of d <= 4 * ROW_THREADS * MAXV values with ROW_THREADS threads, held in registers between the two passes; red
 // holds ROW_THREADS / 64 floats of LDS.
@@ -134,6 +115,45 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_kernel(const float* __res
     RowRegs<MAXV> r;
     r.load(reinterpret_cast<const f32x4*>(x + row * d), d);
     r.norm(w, out + row * d, d, eps, red);
+}
+
+// ------------------------------------------------------------------ begin of an un-captured batch
+// Workgroup 0: clamped lengths and the attention's work-item table (and shares).  Workgroup 1 + r: row r's position and
+// cache slot and its first RMSNorm.  All of it is latency: three launches one after the other took 4.7 + 8.1 + 7.4 us
+// ahead of 573 rows of the 32B shape, this one 11.7 (2048 rows: 29 and 19).
+template <int MAXV>
+__global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
+    __shared__ int buf[ROW_THREADS];
+    __shared__ int carry;
+    __shared__ float red[ROW_THREADS / 64];
+    __shared__ int row_pos;
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i < a.n_seq; i += ROW_THREADS) {
+            const int cap = a.row_start[i + 1] - a.row_start[i];
+            int l = a.seq_len ? a.seq_len[i] : cap;
+            l = l > cap ? cap : l;
+            a.new_len[i] = l < 0 ? 0 : l;
+        }
+        __syncthreads();   // the lengths written above are read below by other threads of this workgroup
+        laps_dev_attn_sched(a.new_len, a.n_seq, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, buf, &carry);
+        if (a.attn_wgs > 0)
+            laps_dev_attn_bounds(a.new_len, a.prefix_len, a.n_seq, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
+                                 a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, buf, &carry);
+        return;
+    }
+    const int row = blockIdx.x - 1;
+    RowRegs<MAXV> r;
+    r.load(reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.d), a.d);
+    if (threadIdx.x == 0) {
+        int pos, slot;
+        token_meta(row, a.n_seq, a.row_start, a.seq_len, a.prefix_len, a.page_table, a.max_pages, a.n_pool_pages, &pos, &slot);
+        a.tok_pos[row] = pos;
+        a.tok_slot[row] = slot;
+        row_pos = pos;
+    }
+    __syncthreads();
+    if (row_pos < 0) return;   // padding row: nothing reads its normed row
+    r.norm(a.ln_w, a.r0 + (size_t)row * a.d, a.d, a.eps, red);
 }
 
 // ------------------------------------------------------------------ sum K slices + residual (+ RMSNorm)
@@ -603,12 +623,9 @@ int laps_launch_rope_table(float2* table, int max_pos, int head_dim, float theta
     return LAPS_OK;
 }
 
-int laps_launch_prep(int n_rows, int n_seq, const int* row_start, const int* seq_len, const int* prefix_len,
-                     const int* page_table, int max_pages, int n_pool_pages, int* new_len_out, int* tok_pos,
-                     int* tok_slot, hipStream_t s) {
-    const int n = n_rows > n_seq ? n_rows : n_seq;
-    hipLaunchKernelGGL(prep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n_rows, n_seq, row_start, seq_len,
-                       prefix_len, page_table, max_pages, n_pool_pages, new_len_out, tok_pos, tok_slot);
+int laps_launch_begin(const BeginArgs& a, hipStream_t s) {
+    auto kern = a.d <= 4 * ROW_THREADS ? begin_kernel<1> : begin_kernel<ROW_MAXV>;   // d <= 8192 (check_cfg)
+    hipLaunchKernelGGL(kern, dim3(1 + a.n_rows), dim3(ROW_THREADS), 0, s, a);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }

@@ -72,9 +72,22 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
 int laps_launch_rope_table(float2* table, int max_pos, int head_dim, float theta, hipStream_t s);
 // n_pool_pages (here, in the K/V movers and in the attention): page ids outside [0, n_pool_pages) are treated as
 // unset entries - no cache write, no wild read.  INT_MAX when the caller has not said how many pages its pools hold.
-int laps_launch_prep(int n_rows, int n_seq, const int* row_start, const int* seq_len, const int* prefix_len,
-                     const int* page_table, int max_pages, int n_pool_pages, int* new_len_out, int* tok_pos,
-                     int* tok_slot, hipStream_t s);
+// Begin of an un-captured batch: clamped lengths, attention work-item table (and shares); for each of n_rows rows (0: the
+// attention alone, rows and first layer unused) its position and cache slot (page * 16 + offset, -1: padding or no
+// cache write) and its RMSNorm with the first layer's gain.
+struct BeginArgs {
+    const int *row_start, *seq_len, *prefix_len, *page_table;   // seq_len may be NULL
+    int n_seq, n_rows, max_pages, n_pool_pages;
+    int group, rows_per_wg, max_items, n_kv, attn_wgs;          // attention blocking; attn_wgs as laps_attn_persistent_wgs
+    int *new_len, *tok_pos, *tok_slot, *tile_start, *item_seq, *attn_pre;
+    int4* attn_bounds;
+    const float* x;
+    const bf16_t* ln_w;
+    bf16_t* r0;
+    int d;
+    float eps;
+};
+int laps_launch_begin(const BeginArgs& a, hipStream_t s);
 // row_live (here and below): NULL, or one entry per row; rows with a negative entry are padding and are skipped.
 int laps_launch_rmsnorm(const float* x, const bf16_t* w, bf16_t* out, int rows, int d, float eps, const int* row_live,
                         hipStream_t s);
@@ -93,7 +106,7 @@ int laps_launch_kv_move(bool scatter, int n_seq, int n_tokens, const int* cu, co
 // Graph staging, one launch that leaves a captured stack nothing to prepare.  One workgroup writes the clamped lengths /
 // prefixes of `depth` slots (the first n_real from the caller's device arrays, the rest empty), packed row offsets
 // row_start_out[depth + 1], and the attention's work-item table for them; one workgroup per graph row its token position
-// and cache slot (as laps_launch_prep), the row's input copied from x_rows (rows below n_rows; NULL: the graph's input
+// and cache slot (as laps_launch_begin), the row's input copied from x_rows (rows below n_rows; NULL: the graph's input
 // rows are used as they are) into x_in, its RMSNorm with the first layer's gain into r0, and a share of the page-table
 // copy (entries past n_real rows become 0).
 struct StageArgs {
@@ -116,7 +129,7 @@ int laps_launch_stage(const StageArgs& a, hipStream_t s);
 
 // Work-item table of the attention for one batch: per-sequence number of query-row blocks, their exclusive prefix
 // sum (tile_start[n_seq + 1]) and the sequence of every work item.  Runs in ONE workgroup of 256 threads; buf holds
-// 256 ints and carry one int of LDS.  Shared by the stand-alone scheduling kernel and the staging kernel of graphs.
+// 256 ints and carry one int of LDS.  Shared by the kernel that begins a batch and the staging kernel of graphs.
 static __device__ __forceinline__ void laps_dev_attn_sched(const int* __restrict__ new_len, int n_seq, int group,
                                                            int rows_per_wg, int* __restrict__ tile_start,
                                                            int* __restrict__ item_seq, int max_items, int* buf,
@@ -228,9 +241,9 @@ static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restric
 }
 
 // ----------------------------------------------------------------------------- attention
-// Both take the same (n_seq, n_tokens, max_pages): the blocking they derive from them must agree.
+// The work-item table is made with the blocking of the same (n_seq, n_tokens, max_pages) (laps_attn_plan).
 // `partial` (partial_bytes >= laps_attn_partial_bytes, 16-byte aligned) receives per-split results when the launch shape
-// calls for splitting the key range; it may be NULL only if max_pages * 16 < 512.  partial_bytes must be the same in both.
+// calls for splitting the key range; it may be NULL only if max_pages * 16 < 512.  partial_bytes must be that of the table's shares.
 // tile_start: n_seq + 1 ints; item_seq: laps_attn_item_table_bytes (sequence of every row-block work item).
 size_t laps_attn_partial_bytes(int hd, int max_pages);   // 0 when page tables this narrow never split
 // Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel.
@@ -239,12 +252,10 @@ void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, in
 // Workgroups of the persistent long-prompt kernel for a launch shape with partial_bytes of room for the results of cut
 // units (two slots per workgroup); 0: the launch does not use it.
 int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes);
-// The blocking laps_launch_attn_sched / laps_launch_attention derive from a launch shape: query rows per workgroup,
+// The blocking laps_launch_attention derives from a launch shape, for the work-item table: query rows per workgroup,
 // bound on the (sequence, row block) items, key-range splits (1 = none), fewest key tiles a split may get.
 void laps_attn_plan(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* rows_per_wg, int* max_items,
                     int* n_split, int* min_tiles_per_split);
-int laps_launch_attn_sched(const int* new_len, const int* prefix_len, int n_seq, int n_tokens, int max_pages,
-                           int* tile_start, int* item_seq, int n_q, int n_kv, int hd, size_t partial_bytes, hipStream_t s);
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,
                           const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
                           int max_pages, int n_seq, int n_tokens, const int* tile_start, const int* item_seq,
