@@ -213,7 +213,7 @@ int laps_prefill_stack_static(laps_ctx* ctx, const laps_layer_weights* w, int32_
  * What the library would launch for a shape; for tests of the launch arithmetic and for tuning.
  * laps_gemm_plan_info: the projection C[m,n] = A[m,k] W[n,k]^T with the epilogue the layer driver would ask for
  * (0 = K-slice partial sums, 1 = residual add, 2 = SwiGLU) and split_k as in laps_gemm_bf16 (0 = automatic).
- * out[7] = { tile rows, tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
+ * out[7] = { row class of the tile (192-row tiles count as 256), tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
  * split), slabs kept in flight per workgroup, workgroups }.
  * laps_attn_plan_info: the attention launch of a batch shape (n_tokens rows, n_seq sequences, page tables
  * max_pages wide).  out[6] = { query rows per workgroup, bound on the (sequence, row block) work items,
@@ -289,7 +289,8 @@ int laps_attention(laps_ctx* ctx, int32_t n_seq, int32_t n_tokens, const int32_t
 /* ------------------------------------------------------------------ per-kernel timing
  * When enabled, un-captured laps_prefill_* calls bracket every kernel launch with HIP events on
  * the caller's stream.  laps_prof_read synchronises those events and returns, per kernel class,
- * the summed milliseconds and the launch count since the last laps_prof_enable(ctx, 1). */
+ * the summed milliseconds and the launch count since the last laps_prof_enable(ctx, 1).  LAPS_K_PREP is the launch
+ * that begins a batch, the first layer's RMSNorm included. */
 enum { LAPS_K_PREP = 0, LAPS_K_RMSNORM, LAPS_K_GEMM_QKV, LAPS_K_GEMM_O, LAPS_K_GEMM_GATEUP, LAPS_K_GEMM_DOWN,
        LAPS_K_EPI_QKV, LAPS_K_EPI_RESID, LAPS_K_EPI_SWIGLU, LAPS_K_ATTN, LAPS_K_COUNT };
 int laps_prof_enable(laps_ctx* ctx, int32_t on);

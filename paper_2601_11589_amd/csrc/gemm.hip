@@ -555,7 +555,8 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         p.epi = (p.split == 1) ? want_epi : EPI_PARTIAL;
         return p;
     };
-    if (k >= kMaxBufferK) {
+    if (k >= kMaxBufferK) {   // the tiles that address their rows with pointers; only the wider one has gate / up pairs
+        if (want_epi == EPI_SWIGLU && n % 128 == 0 && force_split <= 1) return finish(7, 1);
         if (want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
         return finish(1, force_split > 0 ? force_split : 1);
     }
@@ -659,7 +660,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         laps_set_error("gemm: K slice of %d slabs is not a multiple of the %d weight stages", p.k_per_split / BK, p.ws);
         return LAPS_EINVAL;
     }
-    if (!(p.cfg == 1 && p.ws == 1) && k >= kMaxBufferK) {
+    if (!(p.cfg == 1 && p.ws == 1) && p.cfg != 7 && k >= kMaxBufferK) {
         laps_set_error("gemm: K = %d is too long for tile %d", k, p.cfg);
         return LAPS_EINVAL;
     }

@@ -62,3 +62,26 @@ def test_tiles_above_128_rows_match_float64(m, n, k):
     slack = (delta * (1.1 * up.abs() + gate.abs())).reshape(m, n // 2) + 1e-6
     assert bool(((got - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all())
     ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(4, 128, (1 << 22) + 64), (130, 128, 1 << 22), (130, 64, 1 << 22), (130, 256, (1 << 22) - 128)])
+def test_rows_at_the_reach_of_32_bit_offsets(m, n, k):
+    """Rows of 2^22 values and more are addressed by pointers, shorter ones by 32-bit offsets.  Operands of -1, 0 and 1:
+    every fp32 sum is a whole number below 2^24, hence exact."""
+    ctx = api.LapsCtx(inputs.tiny_cfg(1), max_positions=64)
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    a, w = (torch.randint(-1, 2, (r, k), generator=g, device="cuda", dtype=torch.int8).to(torch.bfloat16) for r in (m, n))
+    want = sum(a[:, c:c + (1 << 19)].float() @ w[:, c:c + (1 << 19)].float().T for c in range(0, k, 1 << 19))
+    resid = torch.randint(-9, 10, (m, n), generator=g, device="cuda").float()
+    assert torch.equal(ctx.laps_gemm_bf16(a, w), want)
+    assert torch.equal(ctx.laps_gemm_epilogue_bf16(a, w, 1, resid=resid), resid + want)
+    if n % 128 == 0:
+        gate, up = want.double().view(m, n // 64, 2, 32).unbind(2)
+        ref = (torch.nn.functional.silu(gate) * up).reshape(m, n // 2)
+        got = ctx.laps_gemm_epilogue_bf16(a, w, 2).double()
+        # the sums are exact; one bf16 rounding (at most 2^-8) and an fp32 SiLU, whose exponential of x is formed from a
+        # product rounded to 2^-24 of |x|
+        slack = 2.0 ** -8 + 2.0 ** -20 + (2.0 ** -22 * gate.abs()).reshape(m, n // 2)
+        assert bool(((got - ref).abs() <= ref.abs() * slack + 1e-6).all())
+    ctx.close()
