@@ -213,7 +213,7 @@ int laps_prefill_stack_static(laps_ctx* ctx, const laps_layer_weights* w, int32_
  * What the library would launch for a shape; for tests of the launch arithmetic and for tuning.
  * laps_gemm_plan_info: the projection C[m,n] = A[m,k] W[n,k]^T with the epilogue the layer driver would ask for
  * (0 = K-slice partial sums, 1 = residual add, 2 = SwiGLU) and split_k as in laps_gemm_bf16 (0 = automatic).
- * out[7] = { row class of the tile (192-row tiles count as 256), tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
+ * out[7] = { tile rows, tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
  * split), slabs kept in flight per workgroup, workgroups }.
  * laps_attn_plan_info: the attention launch of a batch shape (n_tokens rows, n_seq sequences, page tables
  * max_pages wide).  out[6] = { query rows per workgroup, bound on the (sequence, row block) work items,

@@ -528,10 +528,8 @@ int launch_width(const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Row class and columns of a tile shape.  A 192-row tile counts as one of the 256-row class: it is only taken where
-// cutting m into ceil(m / 256) row tiles leaves at most 192 rows to each, so the number of row tiles is that class's.
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn) {
-    *bm = (cfg >= 0 && cfg < kNumTiles) ? (kTiles[cfg].bm == 192 ? 256 : kTiles[cfg].bm) : 0;
+    *bm = (cfg >= 0 && cfg < kNumTiles) ? kTiles[cfg].bm : 0;
     *bn = (cfg >= 0 && cfg < kNumTiles) ? kTiles[cfg].bn : 0;
 }
 
@@ -605,7 +603,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0)) continue;
         if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
         const int tiles_m = (m + t.bm - 1) / t.bm;
-        if (t.bm == 192 && tiles_m != (m + 255) / 256) continue;
+        if (t.bm == 192 && tiles_m != (m + 255) / 256) continue;   // 192 rows where they need no more row tiles than 256
         const int max_split = force_split > 0 ? force_split : 16;
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
             const double partial = 4.0 * s * (double)m * n;

@@ -59,7 +59,7 @@ struct GemmPlan {
 constexpr size_t LAPS_PARTIAL_CAP = (size_t)48 << 20;
 GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap = LAPS_PARTIAL_CAP);
 size_t laps_gemm_partial_bytes(int m, int n, int k);
-void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // row class and columns of tile shape `cfg` (0, 0 if unknown)
+void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // rows and columns of tile shape `cfg` (0, 0 if unknown)
 // row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified:
 // the skinny tiles do not load them (they compute with zeros), and a row tile of padding only is skipped.
 // n_live: NULL, or a device int: rows at and past it are padding (batches whose padding is all at the end).

@@ -34,7 +34,7 @@ def test_gemm_plans_satisfy_the_kernels_assumptions(model):
         for m in ROWS:
             p = gemm_plan(m, n, k, 0, want)
             what = (model, name, m, p)
-            assert p["bm"] in (128, 256) and n % p["bn"] == 0, what
+            assert p["bm"] in (128, 192, 256) and n % p["bn"] == 0, what
             assert p["k_per"] % 64 == 0 and p["split"] >= 1, what
             slabs = p["k_per"] // 64
             assert p["ws"] in (1, 2) and slabs % p["ws"] == 0, what
@@ -53,6 +53,15 @@ def test_gemm_plans_satisfy_the_kernels_assumptions(model):
             q = gemm_plan(m, n, k, 0, PARTIAL)
             need = lib.laps_gemm_workspace_bytes(C.c_int32(m), C.c_int32(n), C.c_int32(k), C.c_int32(0))
             assert need == (q["split"] * m * n * 4 if q["split"] > 1 else 0), what
+
+
+@pytest.mark.parametrize("m,n,k,epi,tile,wgs", [
+    (192, 7168, 5120, PARTIAL, (192, 128), 56), (576, 55296, 5120, SWIGLU, (192, 256), 648), (573, 55296, 5120, SWIGLU, (192, 256), 648),
+    (192, 55296, 5120, SWIGLU, (192, 256), 216), (256, 55296, 5120, SWIGLU, (256, 256), 216)])
+def test_plan_info_reports_the_tile_that_is_launched(m, n, k, epi, tile, wgs):
+    """192-row tiles are reported as such, and the workgroups are those of the rows really covered by one."""
+    p = gemm_plan(m, n, k, 0, epi)
+    assert (p["bm"], p["bn"]) == tile and p["wgs"] == wgs * p["split"], p
 
 
 def test_forced_k_splits_are_clamped_to_whole_slices():
