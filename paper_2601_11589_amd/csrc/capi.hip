@@ -78,17 +78,6 @@ struct WsLayout {
     size_t tok_pos, tok_slot, new_len, tile_start, item_seq, r, q, attn, act, x_mid, partial, total;
 };
 
-static size_t partial_bytes_for(const laps_model_cfg& c, int m) {
-    const int qd = c.n_q_heads * c.head_dim, qkv = qd + 2 * c.n_kv_heads * c.head_dim;
-    size_t b = laps_gemm_partial_bytes(m, qkv, c.hidden);
-    size_t t = laps_gemm_partial_bytes(m, c.hidden, qd);
-    b = t > b ? t : b;
-    t = laps_gemm_partial_bytes(m, 2 * c.intermediate, c.hidden);
-    b = t > b ? t : b;
-    t = laps_gemm_partial_bytes(m, c.hidden, c.intermediate);
-    return t > b ? t : b;
-}
-
 static constexpr int kAnyPages = 1 << 24;
 
 static size_t widest_projection(const laps_model_cfg& c) {
@@ -103,6 +92,18 @@ static size_t partial_cap_for(const laps_model_cfg& c, int m) {
     const size_t one = (size_t)m * widest_projection(c) * sizeof(float), at = laps_attn_partial_bytes(c.head_dim, kAnyPages);
     const size_t cap = one > at ? one : at;
     return cap < LAPS_PARTIAL_CAP ? cap : LAPS_PARTIAL_CAP;
+}
+
+static size_t partial_bytes_for(const laps_model_cfg& c, int m) {
+    const int qd = c.n_q_heads * c.head_dim, qkv = qd + 2 * c.n_kv_heads * c.head_dim;
+    const size_t cap = partial_cap_for(c, m);
+    size_t b = laps_gemm_partial_bytes(m, qkv, c.hidden, cap);
+    size_t t = laps_gemm_partial_bytes(m, c.hidden, qd, cap);
+    b = t > b ? t : b;
+    t = laps_gemm_partial_bytes(m, 2 * c.intermediate, c.hidden, cap);
+    b = t > b ? t : b;
+    t = laps_gemm_partial_bytes(m, c.hidden, c.intermediate, cap);
+    return t > b ? t : b;
 }
 
 // Bytes of the partial sums a batch of exactly m > 128 rows writes (run_layers makes the same plans).

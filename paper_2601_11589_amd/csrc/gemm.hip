@@ -167,8 +167,8 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
 }
 
 // Streaming weight loads and A rows through a buffer descriptor: the skinny tiles.  The 32-bit offsets of buffer
-// descriptors hold a tile of 256 rows up to K = 2^22; longer rows take the one-slab variant of the 128x64 tile, which
-// addresses every row by a pointer.
+// descriptors hold a tile of 256 rows up to K = 2^22; longer rows take the tiles that address every row by a pointer:
+// the 192-row ones and the one-slab variant of 128x64.
 constexpr int kMaxBufferK = 1 << 22;
 template <int BM, int BN, int WS>
 constexpr bool skinny_loads = BM <= 128 && !(BN == 64 && WS == 1);
@@ -537,13 +537,15 @@ void laps_gemm_tile_dims(int cfg, int* bm, int* bn) {
 GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap) {
     GemmPlan p;
     const int ksteps = k / BK;
+    const bool far = k >= kMaxBufferK;   // rows that only the pointer-addressed tiles (1, 6, 7) reach
+    if (far && want_epi == EPI_SWIGLU && n % 128 != 0) want_epi = EPI_PARTIAL;
     auto finish = [&](int cfg, int split) {
         if (split > ksteps) split = ksteps;
         if (split < 1) split = 1;
         int per = (ksteps + split - 1) / split;
         // with 2 slabs in flight every K slice must hold a multiple of 2 slabs
         p.ws = 1;
-        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0 && k < kMaxBufferK) {
+        if (kTiles[cfg].ws == 2 && ksteps % 2 == 0 && !(far && cfg == 1)) {
             per = (per + 1) / 2 * 2;
             p.ws = 2;
         }
@@ -553,12 +555,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         p.epi = (p.split == 1) ? want_epi : EPI_PARTIAL;
         return p;
     };
-    if (k >= kMaxBufferK) {   // the tiles that address their rows with pointers; only the wider one has gate / up pairs
-        if (want_epi == EPI_SWIGLU && n % 128 == 0 && force_split <= 1) return finish(7, 1);
-        if (want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
-        return finish(1, force_split > 0 ? force_split : 1);
-    }
-    if (m <= 128) {
+    if (m <= 128 && !far) {
         // Bandwidth-bound.  A CU keeps a bounded number of requests in flight, and the A slab that every
         // workgroup re-reads per K step (L2 hits) takes its share of them from the weight stream: a
         // 256-column tile halves the A share of a 128-column one, which decides the wide projections
@@ -596,15 +593,18 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     // 17.  Against the one rule before it (256-row tiles only) the 32B layer's projections take, q/k/v, o, gate/up,
     // down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows 42 -> 36, 41 -> 36, 272 -> 217,
     // 142 -> 116; 7B at 256 rows 35 -> 19, 38 -> 22, 92 -> 92, 63 -> 53.
+    // Rows of 2^22 values and more take this model at any row count, with as many K slices as fill the chip.  K = 2^22 at
+    // 256 columns, 1 / 64 / 128 / 256 / 700 rows: 0.53 / 0.69 / 0.91 / 1.7 / 2.8 ms (un-split on the same tiles 36 / 48 /
+    // 68 / 64 / 65; tiles that reach no such rows would take 0.50 / 0.62 / 0.75 up to 128).
     double best = 1e30;
     int best_cfg = -1, best_split = 1;
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
-        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0)) continue;
+        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0) || (far && cfg != 1 && cfg != 6 && cfg != 7)) continue;
         if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
         const int tiles_m = (m + t.bm - 1) / t.bm;
-        if (t.bm == 192 && tiles_m != (m + 255) / 256) continue;   // 192 rows where they need no more row tiles than 256
-        const int max_split = force_split > 0 ? force_split : 16;
+        if (t.bm == 192 && tiles_m != (m + 255) / 256 && !far) continue;   // 192 rows where they need no more row tiles than 256
+        const int max_split = force_split > 0 ? force_split : (far ? 256 : 16);   // a few column tiles have to fill the chip
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
             const double partial = 4.0 * s * (double)m * n;
             if (force_split == 0 && s > 1 && (ksteps / s < 4 || partial > (double)partial_cap)) break;
@@ -634,11 +634,11 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     return finish(best_cfg, best_split);
 }
 
-size_t laps_gemm_partial_bytes(int m, int n, int k) {   // m <= 128
+size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap) {   // m <= 128
     // upper bound over the epilogue kinds the layer driver may request
     size_t b = 0;
     for (int e = 0; e < 3; ++e) {
-        const GemmPlan p = laps_gemm_plan(m, n, k, 0, e);
+        const GemmPlan p = laps_gemm_plan(m, n, k, 0, e, partial_cap);
         const size_t t = p.split > 1 ? (size_t)p.split * m * n * sizeof(float) : 0;
         b = t > b ? t : b;
     }
@@ -658,7 +658,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         laps_set_error("gemm: K slice of %d slabs is not a multiple of the %d weight stages", p.k_per_split / BK, p.ws);
         return LAPS_EINVAL;
     }
-    if (!(p.cfg == 1 && p.ws == 1) && p.cfg != 7 && k >= kMaxBufferK) {
+    if (!(p.cfg == 1 && p.ws == 1) && p.cfg != 6 && p.cfg != 7 && k >= kMaxBufferK) {
         laps_set_error("gemm: K = %d is too long for tile %d", k, p.cfg);
         return LAPS_EINVAL;
     }

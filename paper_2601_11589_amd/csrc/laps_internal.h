@@ -54,11 +54,11 @@ struct GemmPlan {
     int epi;          // epilogue the launch will apply: the requested one if split == 1, else EPI_PARTIAL
     int ws;           // weight slabs kept in flight per workgroup (register sets): 1 or 2
 };
-// partial_cap: bytes the partial sums of an automatic split may take above 128 rows (the layer driver passes what its
-// workspace holds if that is less).
+// partial_cap: bytes the partial sums of an automatic split may take above 128 rows or at K >= 2^22 (the layer driver
+// passes what its workspace holds if that is less).
 constexpr size_t LAPS_PARTIAL_CAP = (size_t)48 << 20;
 GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap = LAPS_PARTIAL_CAP);
-size_t laps_gemm_partial_bytes(int m, int n, int k);
+size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap);
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // rows and columns of tile shape `cfg` (0, 0 if unknown)
 // row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified:
 // the skinny tiles do not load them (they compute with zeros), and a row tile of padding only is skipped.

@@ -64,8 +64,20 @@ def test_tiles_above_128_rows_match_float64(m, n, k):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [64, 128, 256, 384])
+@pytest.mark.parametrize("m", [1, 64, 130, 400])
+@pytest.mark.parametrize("k", [1 << 22, (1 << 22) + 64])
+def test_long_rows_fill_the_chip_and_keep_their_sums_short(m, n, k):
+    """Rows of 2^22 values and more: the few tiles there are split K until they fill the chip, as shorter rows do."""
+    for epi in (PARTIAL, RESID, SWIGLU):
+        p = plan(m, n, k, epi)
+        assert p["wgs"] >= 128 and p["k_per"] <= k // 16 and (p["split"] - 1) * p["k_per"] < k <= p["split"] * p["k_per"], p
+        assert p["split"] * m * n * 4 <= 48 << 20, p
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("m,n,k", [(4, 128, (1 << 22) + 64), (130, 128, 1 << 22), (130, 64, 1 << 22), (130, 256, (1 << 22) - 128)])
+@pytest.mark.parametrize("m,n,k", [(4, 128, (1 << 22) + 64), (130, 128, 1 << 22), (130, 64, 1 << 22), (130, 256, (1 << 22) - 128),
+                                   (64, 256, 1 << 22), (200, 256, (1 << 22) + 64), (400, 128, 1 << 22)])
 def test_rows_at_the_reach_of_32_bit_offsets(m, n, k):
     """Rows of 2^22 values and more are addressed by pointers, shorter ones by 32-bit offsets.  Operands of -1, 0 and 1:
     every fp32 sum is a whole number below 2^24, hence exact."""
