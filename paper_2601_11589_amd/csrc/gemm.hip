@@ -688,9 +688,16 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_width<224, EPI_PARTIAL>(g, s);
         if (n % 224 == 0 && p.epi == EPI_RESID) return launch_width<224, EPI_RESID>(g, s);
     }
+    // Weights that one row tile reads alone bypass the caches, but for the K slices of the 64- and 128-column tiles above a
+    // few rows: these wait on the memory less with cached loads.  14B o, 128 columns in 16-slab slices, weights cold / warm
+    // (in the memory-side cache), bypassing against cached: 16 rows 16.7 / 16.1 against 17.1 / 15.7 us, 32 rows 17.8 / 16.9
+    // against 18.2 / 15.8, 128 rows 25.1 / 25.1 against 22.5 / 18.8; down, 36-slab slices: 32 rows 31.2 / 29.9 against
+    // 33.1 / 28.9, 64 rows 34.3 / 33.4 against 34.6 / 29.3.  Un-split (gate/up, 8 / 64 rows, cold) 46.8 / 55.1 against
+    // 50.4 / 58.7; on 256 columns (32B down, 8 / 128 rows, cold) 51.7 / 65.9 against 56.4 / 68.5.
+    const bool bypass = g.tiles_m == 1 && (kTiles[p.cfg].bn == 256 || p.split == 1 || m <= (p.k_per_split >= 32 * BK ? 32 : 16));
 #define LAPS_TILE_CASE(cfg, BM, BN, WM, WN, EPI, WS) \
     case ((cfg) * 4 + (EPI)) * 8 + (WS):             \
-        if (skinny_loads<BM, BN, WS> && g.tiles_m == 1) return launch_tile<BM, BN, WM, WN, EPI, WS, skinny_loads<BM, BN, WS>>(g, s); \
+        if (skinny_loads<BM, BN, WS> && bypass) return launch_tile<BM, BN, WM, WN, EPI, WS, skinny_loads<BM, BN, WS>>(g, s); \
         return launch_tile<BM, BN, WM, WN, EPI, WS, false>(g, s)
     switch ((p.cfg * 4 + p.epi) * 8 + p.ws) {
         LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_PARTIAL, 1);
