@@ -227,15 +227,18 @@ __global__ __launch_bounds__(RESID_THREADS) void epi_resid_kernel(const float* _
 }
 
 // ------------------------------------------------------------------ sum K slices + bias + RoPE + KV append
-// Workgroups [0, rows * chunks): one token row, a chunk of its q and k work items.  Work item = four consecutive rotate-half
-// pairs (j..j+3, j+hd/2..j+hd/2+3) of one head: two 16-byte loads per K slice.  q goes to q_out[row], k to the token's
-// slot in the paged pool.
-// The workgroups behind them: one kv head of 16 rows of v.  A page keeps v as [head_dim][16 tokens], so 8 rows whose
-// tokens lie side by side in an aligned half of a page are turned over in LDS and written as 16 bytes per head_dim index;
-// others go one by one.  Written one by one throughout, the 2-byte stores at a 32-byte stride were a third of the
-// kernel's time: 32B shape, 2048 rows 30 us, now 19; 11104 rows 190, now 92 (478 MB, 5.2 TB/s).
+// One token row and a chunk of its work items (grid: row x chunk; TURN: workgroups [0, rows * chunks)).  Work item = four consecutive rotate-half
+// pairs (j..j+3, j+hd/2..j+hd/2+3) of one head: two 16-byte loads per K slice.  q goes to q_out[row], k and v to the
+// token's slot in the paged pools.
+// TURN: v has workgroups of its own behind these, one kv head of 16 rows each.  A page keeps v as [head_dim][16 tokens],
+// so 8 rows whose tokens lie side by side in an aligned half of a page are turned over in LDS and written as 16 bytes
+// per head_dim index; others go one by one.  Written one by one throughout, the 2-byte stores at a 32-byte stride are a
+// third of the kernel's time in large batches: 32B shape, 2048 rows 30 us, turned over 19; 11104 rows 190 and 92 (478 MB,
+// 5.2 TB/s).  Small ones are all latency, and the two barriers of the way through LDS add to it: 32B / 7B shape, 32
+// rows 5.1 / 5.4 us turned over and 4.0 / 4.0 one by one, 128 rows 6.2 / 5.5 and 5.2 / 4.2, 192 rows 7.6 / 5.6 and 8.3 / 5.6.
 constexpr int V_ROWS = 16;
-template <int HD>
+constexpr int TURN_ABOVE = 128;   // rows
+template <int HD, bool TURN>
 __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __restrict__ partial, int split,
                                                                size_t slice_stride, const bf16_t* __restrict__ bias,
                                                                const int* __restrict__ tok_pos,
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
     __shared__ __align__(16) bf16_t vt[V_ROWS * (HD + 8)];
     __shared__ int vslot[V_ROWS];
     const int n_qk = rows * chunks;
-    if ((int)blockIdx.x >= n_qk) {
+    if (TURN && (int)blockIdx.x >= n_qk) {
         constexpr int ROW = HD + 8, F4 = HD / 4, PASS = ROW_THREADS / F4;   // rows per pass
         const int vb = blockIdx.x - n_qk, g = vb % n_kv, r0 = (vb / n_kv) * V_ROWS;
         const int c = threadIdx.x % F4;
@@ -298,9 +301,9 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
         }
         return;
     }
-    const size_t row = blockIdx.x / chunks;
-    const int it = (blockIdx.x - (int)row * chunks) * ROW_THREADS + threadIdx.x;
-    if (it >= (n_q + n_kv) * per_head) return;
+    const size_t row = TURN ? blockIdx.x / chunks : blockIdx.x;
+    const int it = (TURN ? blockIdx.x - (int)row * chunks : blockIdx.y) * ROW_THREADS + threadIdx.x;
+    if (it >= (n_q + (TURN ? 1 : 2) * n_kv) * per_head) return;
     const int pos = tok_pos[row], slot = tok_slot[row];
     const int head = it / per_head, j = (it % per_head) * 4;
     const int c0 = head * HD + j, c1 = c0 + half;
@@ -325,15 +328,17 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
             b[e] += bf16_to_f32(bias[c1 + e]);
         }
     }
-    // positions past the table are the caller's error; clamp so that the read stays in bounds
-    const float2* cs = rope + (size_t)(pos < max_pos ? pos : max_pos - 1) * half + j;
+    if (TURN || head < n_q + n_kv) {
+        // positions past the table are the caller's error; clamp so that the read stays in bounds
+        const float2* cs = rope + (size_t)(pos < max_pos ? pos : max_pos - 1) * half + j;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float2 t = cs[e];
-        const float ra = a[e] * t.x - b[e] * t.y;
-        const float rb = b[e] * t.x + a[e] * t.y;
-        a[e] = ra;
-        b[e] = rb;
+        for (int e = 0; e < 4; ++e) {
+            const float2 t = cs[e];
+            const float ra = a[e] * t.x - b[e] * t.y;
+            const float rb = b[e] * t.x + a[e] * t.y;
+            a[e] = ra;
+            b[e] = rb;
+        }
     }
     u32x2 wa, wb;
     wa.x = pack_bf16x2(a.x, a.y);
@@ -343,10 +348,17 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
     if (head < n_q) {
         *reinterpret_cast<u32x2*>(q_out + row * (size_t)(n_q * HD) + c0) = wa;
         *reinterpret_cast<u32x2*>(q_out + row * (size_t)(n_q * HD) + c1) = wb;
-    } else {
+    } else if (TURN || head < n_q + n_kv) {
         bf16_t* dst = k_pool + (((size_t)(slot / LAPS_PAGE) * n_kv + (head - n_q)) * LAPS_PAGE + slot % LAPS_PAGE) * HD;
         *reinterpret_cast<u32x2*>(dst + j) = wa;
         *reinterpret_cast<u32x2*>(dst + j + half) = wb;
+    } else {
+        bf16_t* dst = v_pool + ((size_t)(slot / LAPS_PAGE) * n_kv + (head - n_q - n_kv)) * HD * LAPS_PAGE + slot % LAPS_PAGE;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            dst[(size_t)(j + e) * LAPS_PAGE] = f32_to_bf16(a[e]);
+            dst[(size_t)(j + half + e) * LAPS_PAGE] = f32_to_bf16(b[e]);
+        }
     }
 }
 
@@ -659,10 +671,12 @@ int laps_launch_epi_qkv(const float* partial, int split, const bf16_t* bias, con
                         const float2* rope, int max_pos, bf16_t* q_out, bf16_t* k_pool, bf16_t* v_pool, int rows,
                         int n_q, int n_kv, int hd, hipStream_t s) {
     const size_t stride = (size_t)rows * (n_q + 2 * n_kv) * hd;
-    const int chunks = ((n_q + n_kv) * (hd / 8) + ROW_THREADS - 1) / ROW_THREADS;
-    const int grid = rows * chunks + (rows + V_ROWS - 1) / V_ROWS * n_kv;
-    auto kern = hd == 128 ? epi_qkv_kernel<128> : epi_qkv_kernel<64>;   // head_dim is one of the two (check_cfg)
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(ROW_THREADS), 0, s, partial, split, stride, bias, tok_pos, tok_slot, rope,
+    const bool turn = rows > TURN_ABOVE;
+    const int chunks = ((n_q + (turn ? 1 : 2) * n_kv) * (hd / 8) + ROW_THREADS - 1) / ROW_THREADS;
+    const dim3 grid = turn ? dim3(rows * chunks + (rows + V_ROWS - 1) / V_ROWS * n_kv) : dim3(rows, chunks);
+    auto kern = turn ? (hd == 128 ? epi_qkv_kernel<128, true> : epi_qkv_kernel<64, true>)   // head_dim is one of the two
+                     : (hd == 128 ? epi_qkv_kernel<128, false> : epi_qkv_kernel<64, false>);   // (check_cfg)
+    hipLaunchKernelGGL(kern, grid, dim3(ROW_THREADS), 0, s, partial, split, stride, bias, tok_pos, tok_slot, rope,
                        max_pos, q_out, k_pool, v_pool, n_q, n_kv, rows, chunks);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
