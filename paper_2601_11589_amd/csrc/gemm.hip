@@ -688,13 +688,18 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_width<224, EPI_PARTIAL>(g, s);
         if (n % 224 == 0 && p.epi == EPI_RESID) return launch_width<224, EPI_RESID>(g, s);
     }
-    // Weights that one row tile reads alone bypass the caches, but for the K slices of the 64- and 128-column tiles above a
-    // few rows: these wait on the memory less with cached loads.  14B o, 128 columns in 16-slab slices, weights cold / warm
-    // (in the memory-side cache), bypassing against cached: 16 rows 16.7 / 16.1 against 17.1 / 15.7 us, 32 rows 17.8 / 16.9
-    // against 18.2 / 15.8, 128 rows 25.1 / 25.1 against 22.5 / 18.8; down, 36-slab slices: 32 rows 31.2 / 29.9 against
-    // 33.1 / 28.9, 64 rows 34.3 / 33.4 against 34.6 / 29.3.  Un-split (gate/up, 8 / 64 rows, cold) 46.8 / 55.1 against
-    // 50.4 / 58.7; on 256 columns (32B down, 8 / 128 rows, cold) 51.7 / 65.9 against 56.4 / 68.5.
-    const bool bypass = g.tiles_m == 1 && (kTiles[p.cfg].bn == 256 || p.split == 1 || m <= (p.k_per_split >= 32 * BK ? 32 : 16));
+    // Weights that one row tile reads alone bypass the caches.  Above a few rows the K slices of the 64- and 128-column
+    // tiles wait on the memory less with cached loads: 14B o, 16-slab slices, on its own with weights cold / warm (in the
+    // memory-side cache), bypassing against cached: 16 rows 16.7 / 16.1 against 17.1 / 15.7 us, 128 rows 25.1 / 25.1
+    // against 22.5 / 18.8; down, 36-slab slices: 32 rows 31.2 / 29.9 against 33.1 / 28.9, 64 rows 34.3 / 33.4 against 34.6 /
+    // 29.3, 128 rows 40.2 / 40.4 against 39.1 / 31.6.  Inside a layer that is lost again, since the weights then push out
+    // what the kernels around them find in the caches (14B, 64-row graph: 178.2 us cached, 174.8 bypassing; 32B, 128 rows:
+    // even), so only a product of its own (no batch whose live rows are given) takes it.  Un-split and 256-column launches
+    // lose by it (14B gate/up, 8 / 64 rows, cold: 46.8 / 55.1 against 50.4 / 58.7; 32B down, 8 / 128: 51.7 / 65.9 against
+    // 56.4 / 68.5).
+    const bool alone = row_live == nullptr && n_live == nullptr;
+    const bool cached = alone && m > (p.k_per_split < 32 * BK ? 16 : 48) && p.split > 1 && kTiles[p.cfg].bn < 256;
+    const bool bypass = g.tiles_m == 1 && !cached;
 #define LAPS_TILE_CASE(cfg, BM, BN, WM, WN, EPI, WS) \
     case ((cfg) * 4 + (EPI)) * 8 + (WS):             \
         if (skinny_loads<BM, BN, WS> && bypass) return launch_tile<BM, BN, WM, WN, EPI, WS, skinny_loads<BM, BN, WS>>(g, s); \

@@ -33,7 +33,7 @@ SHAPES = [(129, 128, 64), (191, 256, 192), (257, 128, 1088), (255, 384, 128), (5
           (513, 3584, 1024), (576, 3584, 1088), (1025, 4096, 576), (1025, 4096, 512), (192, 27648, 5120),
           (300, 27648, 5120), (384, 5120, 13824), (700, 27648, 1024)]
 # up to 128 rows, either side of the row counts at which the weights of short and long K slices come through the caches
-SHAPES += [(m, n, k) for n, k in ((5120, 5120), (5120, 13824), (4160, 5120)) for m in (16, 17, 32, 33, 128)]
+SHAPES += [(m, n, k) for n, k in ((5120, 5120), (5120, 13824), (4160, 5120)) for m in (16, 17, 48, 49, 128)]
 
 
 @pytest.mark.gpu
