@@ -29,6 +29,11 @@
 // order, so the result does not depend on scheduling.  The split count is a function of launch shapes
 // only (row blocks, kv heads, page-table width), which keeps captured graphs replayable; how many of
 // the splits a given sequence really uses is decided on the device from its length.
+//
+// Many query rows over page tables that allow long prefixes (chunks of long prompts, mixed batches, groups of turns) make
+// blocks of very different lengths.  Such launches run the 8-wave loop in a fixed number of workgroups, each of which walks
+// an equal share of the batch's (kv head, row block) units, worked out on the device from the batch's lengths; a unit cut
+// between shares leaves partial results like a split key range, merged in key order by a kernel of its own.
 #include "laps_internal.h"
 
 #include <climits>
@@ -851,19 +856,39 @@ void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, in
     *bounds = reinterpret_cast<int4*>(item_seq + 2 * n);
 }
 
-// The persistent kernel takes un-split launches of 256-row blocks whose page tables are wide enough for units to differ
-// in length (as many tiles as a key split needs): with a grid of units, the last partly filled round of workgroups and
-// the longest units leave compute units idle.  32B shape (head_dim 128, 40 / 8 heads), attention alone with its scheduling
-// kernels, grid of units against equal shares: 2048 rows over 2048 keys 223 -> 174 us, 1847 rows over 6144 444 -> 308,
-// 12 short turns (573 rows) over up to 4096 keys 130 -> 71, 64 turns 334 -> 297, 2048 rows without a prefix 106 -> 94.
+// The persistent kernel takes un-split launches of 256-row blocks where units differ enough in length for equal shares to
+// outweigh the merge launch and the cuts: with a grid of units, the last partly filled round of workgroups and the longest
+// units leave compute units idle.  32B shape (head_dim 128, 40 / 8 heads), attention alone with its scheduling kernels,
+// grid of units against equal shares: 2048 rows over 2048 keys 223 -> 174 us, 1847 rows over 6144 444 -> 308, 12 short
+// turns (573 rows) over up to 4096 keys 130 -> 71, 64 turns 334 -> 297, 2048 rows without a prefix 106 -> 94.
+// MIN_TILES_PERSIST: with tables of 16 tiles (prefixes of up to 960 keys) 16 / 40 / 64 turns of the 32B shape take 49 / 61 /
+// 83 us in shares and 44 / 67 / 93 on the grid, 30 longer turns of the 7B shape 80 and 74; with 24 tiles 56 / 78 / 106 and
+// 58 / 92 / 120, 92 and 102.
+// One sequence whose units have a workgroup each stays with the grid where its shares would not be cut with the longest
+// prefix the page table holds (with a shorter one even less): 1000 rows without a prefix 57 us in cut shares, 46 on the
+// grid; 1500 over 2048 keys 135 and 123.
+constexpr int MIN_TILES_PERSIST = 20;
+constexpr int GRID_CUT_COST = 20;   // what cutting costs against the grid: the merge launch comes on top
 int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes) {
     int mt, max_items, n_split;
     attn_blocking(n_seq, n_tokens, group, n_kv, max_pages, &mt, &max_items, &n_split);
-    if (mt != 2 || n_split != 1 || (max_pages * (long)LAPS_PAGE + KT - 1) / KT < 2 * MIN_TILES_PER_SPLIT) return 0;
+    const long tiles = (max_pages * (long)LAPS_PAGE + KT - 1) / KT;
+    if (mt != 2 || n_split != 1 || tiles < MIN_TILES_PERSIST) return 0;
     const size_t slot = (size_t)LAPS_ATTN_LONG_ROWS * (hd + 2) * sizeof(float);
-    size_t wgs = partial_bytes / (2 * slot) / 8 * 8;   // whole groups of the 8 XCDs
-    wgs = wgs < LAPS_ATTN_MAX_WGS ? wgs : LAPS_ATTN_MAX_WGS;
-    return wgs < 64 ? 0 : (int)wgs;
+    size_t room = partial_bytes / (2 * slot) / 8 * 8;   // whole groups of the 8 XCDs; 192 at least in a workspace for these tables
+    const int wgs = room < LAPS_ATTN_MAX_WGS ? (int)room : LAPS_ATTN_MAX_WGS;
+    const int items = (n_tokens * group + LAPS_ATTN_LONG_ROWS - 1) / LAPS_ATTN_LONG_ROWS;
+    if (n_seq == 1 && items * n_kv <= wgs) {
+        const long room_h = max_pages * (long)LAPS_PAGE - n_tokens, h = room_h > 0 ? room_h : 0;
+        long cost = 0, longest = 0;
+        for (int i = 1; i <= items; ++i) {
+            const int rows = i * LAPS_ATTN_LONG_ROWS < n_tokens * group ? i * LAPS_ATTN_LONG_ROWS : n_tokens * group;
+            longest = (h + (rows - 1) / group + KT) / KT + LAPS_ATTN_COST0;
+            cost += longest * n_kv;
+        }
+        if (longest <= cost / wgs + GRID_CUT_COST) return 0;
+    }
+    return wgs;
 }
 
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,

@@ -123,8 +123,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_kernel(const float* __res
 // ahead of 573 rows of the 32B shape, this one 11.7 (2048 rows: 29 and 19).
 template <int MAXV>
 __global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
-    __shared__ int buf[ROW_THREADS];
-    __shared__ int carry;
+    __shared__ int sums[ROW_THREADS / 64];
     __shared__ float red[ROW_THREADS / 64];
     __shared__ int row_pos;
     if (blockIdx.x == 0) {
@@ -135,10 +134,10 @@ __global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
             a.new_len[i] = l < 0 ? 0 : l;
         }
         __syncthreads();   // the lengths written above are read below by other threads of this workgroup
-        laps_dev_attn_sched(a.new_len, a.n_seq, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, buf, &carry);
+        laps_dev_attn_sched(a.new_len, a.n_seq, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, sums);
         if (a.attn_wgs > 0)
             laps_dev_attn_bounds(a.new_len, a.prefix_len, a.n_seq, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
-                                 a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, buf, &carry);
+                                 a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, sums);
         return;
     }
     const int row = blockIdx.x - 1;
@@ -543,8 +542,6 @@ __device__ __forceinline__ int staged_scan(const StageArgs& a, int lo, int hi, i
 
 __global__ __launch_bounds__(ROW_THREADS) void stage_kernel(const StageArgs a) {
     __shared__ int sums[ROW_THREADS / 64];
-    __shared__ int buf[ROW_THREADS];
-    __shared__ int carry;
     __shared__ float red[ROW_THREADS / 64];
     __shared__ int where[3];   // slot of this row, its first row, live
     const int t = threadIdx.x, depth = a.depth;
@@ -564,10 +561,10 @@ __global__ __launch_bounds__(ROW_THREADS) void stage_kernel(const StageArgs a) {
         }
         if (t == ROW_THREADS - 1) a.row_start_out[depth] = run;
         __syncthreads();   // the lengths written above are read below by other threads of this workgroup
-        laps_dev_attn_sched(a.new_len_out, depth, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, buf, &carry);
+        laps_dev_attn_sched(a.new_len_out, depth, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, sums);
         if (a.attn_wgs > 0)
             laps_dev_attn_bounds(a.new_len_out, a.prefix_out, depth, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
-                                 a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, buf, &carry);
+                                 a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, sums);
         return;
     }
     const int row = blockIdx.x - 1, n_rows = gridDim.x - 1;

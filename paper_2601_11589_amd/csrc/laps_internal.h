@@ -127,38 +127,47 @@ struct StageArgs {
 };
 int laps_launch_stage(const StageArgs& a, hipStream_t s);
 
+// Inclusive prefix sum over a workgroup of 256 threads, and its total; sums: 4 ints of LDS.  Every thread calls it.
+static __device__ __forceinline__ int laps_dev_scan(int v, int* sums, int* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(v, o, 64);
+        if (lane >= o) v += up;
+    }
+    __syncthreads();   // sums may still be read from a previous call
+    if (lane == 63) sums[wave] = v;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) before += sums[w];
+        all += sums[w];
+    }
+    *total = all;
+    return before + v;
+}
+
 // Work-item table of the attention for one batch: per-sequence number of query-row blocks, their exclusive prefix
-// sum (tile_start[n_seq + 1]) and the sequence of every work item.  Runs in ONE workgroup of 256 threads; buf holds
-// 256 ints and carry one int of LDS.  Shared by the kernel that begins a batch and the staging kernel of graphs.
+// sum (tile_start[n_seq + 1]) and the sequence of every work item.  Runs in ONE workgroup of 256 threads; sums: 4 ints
+// of LDS.  Shared by the kernel that begins a batch and the staging kernel of graphs.
 static __device__ __forceinline__ void laps_dev_attn_sched(const int* __restrict__ new_len, int n_seq, int group,
                                                            int rows_per_wg, int* __restrict__ tile_start,
-                                                           int* __restrict__ item_seq, int max_items, int* buf,
-                                                           int* carry) {
-    if (threadIdx.x == 0) *carry = 0;
-    __syncthreads();
+                                                           int* __restrict__ item_seq, int max_items, int* sums) {
+    int done = 0;   // items of the sequences before
     for (int base = 0; base < n_seq; base += 256) {
         const int i = base + threadIdx.x;
         const int v = (i < n_seq) ? (new_len[i] * group + rows_per_wg - 1) / rows_per_wg : 0;
-        buf[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = 1; o < 256; o <<= 1) {  // inclusive Hillis-Steele scan
-            const int add = (threadIdx.x >= o) ? buf[threadIdx.x - o] : 0;
-            __syncthreads();
-            buf[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const int c = *carry;
+        int total;
+        const int first = done + laps_dev_scan(v, sums, &total) - v;
         if (i < n_seq) {
-            const int first = c + buf[threadIdx.x] - v;
             tile_start[i] = first;
             // bound: lengths that disagree with the row offsets must not write past the table
             for (int k = 0; k < v && first + k < max_items; ++k) item_seq[first + k] = i;
         }
-        __syncthreads();
-        if (threadIdx.x == 255) *carry = c + buf[255];
-        __syncthreads();
+        done += total;
     }
-    if (threadIdx.x == 0) tile_start[n_seq] = *carry;
+    if (threadIdx.x == 0) tile_start[n_seq] = done;
 }
 
 // A prefix length that the page table cannot hold (a corrupted or stale array) must neither index past the
@@ -174,17 +183,22 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
 // of all kv heads, one head after the other, are cut into equal lengths.  bounds[w] = (kv head, item, first tile) is
 // where workgroup w begins and w - 1 ends.  A cut inside a unit stays MIN_SEG tiles clear of its ends and where every
 // row of the unit sees the first key after the cut, else it moves to the unit's begin or end; short batches use fewer
-// workgroups.  Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; pre (max_items + 1 ints) holds the
-// prefix sums of the item costs.
+// workgroups, spread over the compute units.  Where every unit has a workgroup to itself and the longest is no longer
+// than a share with what cutting costs (partial results, their merge, uneven cuts), nothing is cut: 32B shape, 16 short
+// turns (176 units of 5) 32 us in shares of several units, 23 so; 16 turns over up to 1472 keys (units of up to 27, shares
+// of 11) 57 us cut, 63 not; 1000 rows over 600 (160 units of up to 30, shares of 13) 73 cut, 66 not.
+// Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; pre (max_items + 1 ints) holds the prefix sums of the
+// item costs.
 constexpr int LAPS_ATTN_KT = 64;          // keys per tile
 constexpr int LAPS_ATTN_LONG_ROWS = 256;  // query rows per work item of the long-prompt kernel
 constexpr int LAPS_ATTN_MAX_WGS = 256;    // one workgroup per compute unit
+constexpr int LAPS_ATTN_COST0 = 4;        // in key tiles (about 2 us), as CUT_COST
 static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restrict__ new_len,
                                                             const int* __restrict__ prefix_len, int n_seq, int group,
                                                             int n_kv, int max_pages, const int* tile_start,
                                                             const int* item_seq, int max_items, int n_wgs, int* pre,
-                                                            int4* bounds, int* buf, int* carry) {
-    constexpr int COST0 = 4, MIN_SEG = 4, MIN_COST = 8;
+                                                            int4* bounds, int* sums) {
+    constexpr int COST0 = LAPS_ATTN_COST0, MIN_SEG = 4, MIN_COST = 8, CUT_COST = 14;
     __syncthreads();   // tile_start and item_seq were written by other threads of this workgroup
     const int total = tile_start[n_seq], n_items = total < max_items ? total : max_items;
     // key tiles of an item, and the last tile a cut may begin with
@@ -195,33 +209,40 @@ static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restric
         *last_cut = (H + r0 / group) / LAPS_ATTN_KT;
         return (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT;
     };
-    if (threadIdx.x == 0) *carry = 0, pre[0] = 0;
-    __syncthreads();
+    if (threadIdx.x == 0) pre[0] = 0;
+    int per_head = 0, longest = 0;   // cost of the items, and of the longest one this thread, then any, sees
     for (int base = 0; base < n_items; base += 256) {
         const int i = base + threadIdx.x;
-        int unused;
-        buf[threadIdx.x] = i < n_items ? tiles_of(i, &unused) + COST0 : 0;
-        __syncthreads();
-        for (int o = 1; o < 256; o <<= 1) {
-            const int add = (threadIdx.x >= o) ? buf[threadIdx.x - o] : 0;
-            __syncthreads();
-            buf[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const int c = *carry;
-        if (i < n_items) pre[i + 1] = c + buf[threadIdx.x];
-        __syncthreads();
-        if (threadIdx.x == 255) *carry = c + buf[255];
-        __syncthreads();
+        int unused, total_cost;
+        const int own = i < n_items ? tiles_of(i, &unused) + COST0 : 0;
+        longest = own > longest ? own : longest;
+        const int upto = per_head + laps_dev_scan(own, sums, &total_cost);
+        if (i < n_items) pre[i + 1] = upto;
+        per_head += total_cost;
     }
-    const long per_head = *carry, cost = per_head * n_kv;
-    long used = cost / MIN_COST;
-    used = used < 1 ? 1 : (used > n_wgs ? n_wgs : used);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const int other = __shfl_xor(longest, o, 64);
+        longest = other > longest ? other : longest;
+    }
+    __syncthreads();   // sums are read
+    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = longest;
+    __syncthreads();   // and pre is written
+    for (int w = 0; w < 4; ++w) longest = sums[w] > longest ? sums[w] : longest;
+    const long cost = (long)per_head * n_kv, units = (long)n_items * n_kv;
+    const bool cut = units > n_wgs || longest > cost / n_wgs + CUT_COST;
+    long share = cost / MIN_COST;   // as many workgroups get one, but no fewer than there are units
+    share = !cut || share < units ? units : share;
+    share = share < 1 ? 1 : (share > n_wgs ? n_wgs : share);
+    const int used = (int)share;
     for (int w = threadIdx.x; w <= n_wgs; w += 256) {
         int4 b = make_int4(n_kv, 0, 0, 0);   // the end
-        const long x = w < used ? cost * w / used : cost;
-        if (x < cost) {
-            const int head = (int)(x / per_head), rem = (int)(x - head * per_head);
+        const int u = (w * used + n_wgs - 1) / n_wgs;   // share w begins where the u-th of `used` equal ones does
+        const long x = u < used ? cost * u / used : cost;
+        if (!cut) {
+            if (u < units) b = make_int4(u / n_items, u % n_items, 0, 0);
+        } else if (x < cost) {
+            const int head = (int)(x / per_head), rem = (int)(x - (long)head * per_head);
             int lo = 0, hi = n_items;   // item with pre[item] <= rem < pre[item + 1]
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
