@@ -211,8 +211,9 @@ int laps_prefill_stack_static(laps_ctx* ctx, const laps_layer_weights* w, int32_
 
 /* ------------------------------------------------------------------ launch plans (host only, no device work)
  * What the library would launch for a shape; for tests of the launch arithmetic and for tuning.
- * laps_gemm_plan_info: the projection C[m,n] = A[m,k] W[n,k]^T with the epilogue the layer driver would ask for
- * (0 = K-slice partial sums, 1 = residual add, 2 = SwiGLU) and split_k as in laps_gemm_bf16 (0 = automatic).
+ * laps_gemm_plan_info: the product C[m,n] = A[m,k] W[n,k]^T by itself (laps_gemm_bf16, laps_gemm_epilogue_bf16) with
+ * epilogue 0 = plain sums, 1 = residual add, 2 = SwiGLU, and split_k as in laps_gemm_bf16 (0 = automatic).  Inside a layer,
+ * where a row kernel follows, the driver may split K otherwise.
  * out[7] = { tile rows, tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
  * split), slabs kept in flight per workgroup, workgroups }.
  * laps_attn_plan_info: the attention launch of a batch shape (n_tokens rows, n_seq sequences, page tables
@@ -268,7 +269,7 @@ size_t laps_gemm_workspace_bytes(int32_t m, int32_t n, int32_t k, int32_t split_
 int laps_gemm_bf16(laps_ctx* ctx, const void* a_dev, const void* w_dev, float* c_dev, int32_t m, int32_t n,
                    int32_t k, int32_t split_k, void* workspace_dev, size_t workspace_bytes, void* stream);
 /* The same projection with the epilogue the layer driver fuses (steps x1 = x + attn W_o^T, y = x1 + act W_d^T and
- * act = silu(r2 W_g^T) * (r2 W_u^T) of the layer math above), launched as the driver launches it: inside the GEMM
+ * act = silu(r2 W_g^T) * (r2 W_u^T) of the layer math above), launched with the driver's kernels: inside the GEMM
  * kernel when the plan keeps K in one slice, else K-slice partial sums and the row kernel that adds them.
  *   epilogue 1: out_f32[m,n] = resid[m,n] + C (resid may alias out_f32; n <= 8192);
  *   epilogue 2: out_bf16[m,n/2] = silu(gate) * up, with W holding gate and up rows interleaved in blocks of 32 as

@@ -109,11 +109,12 @@ static size_t partial_bytes_for(const laps_model_cfg& c, int m) {
 // Bytes of the partial sums a batch of exactly m > 128 rows writes (run_layers makes the same plans).
 static size_t split_bytes_for(const laps_model_cfg& c, int m) {
     const int qd = c.n_q_heads * c.head_dim, qkv = qd + 2 * c.n_kv_heads * c.head_dim;
-    const int shape[4][3] = {{qkv, c.hidden, EPI_PARTIAL}, {c.hidden, qd, EPI_RESID}, {2 * c.intermediate, c.hidden, EPI_SWIGLU},
-                             {c.hidden, c.intermediate, EPI_RESID}};
+    const int shape[5][4] = {{qkv, c.hidden, EPI_PARTIAL, 1}, {c.hidden, qd, EPI_RESID, 1}, {2 * c.intermediate, c.hidden, EPI_SWIGLU, 0},
+                             {c.hidden, c.intermediate, EPI_RESID, 1}, {c.hidden, c.intermediate, EPI_RESID, 0}};
     size_t b = 0;
     for (const auto& p : shape) {
-        const size_t t = (size_t)laps_gemm_plan(m, p[0], p[1], 0, p[2], partial_cap_for(c, m)).split * m * p[0] * sizeof(float);
+        const GemmPlan g = laps_gemm_plan(m, p[0], p[1], 0, p[2], partial_cap_for(c, m), p[3] != 0);
+        const size_t t = (size_t)g.split * m * p[0] * sizeof(float);
         b = t > b ? t : b;
     }
     return b;
@@ -301,9 +302,9 @@ struct BatchDesc {
 // One projection.  `want` is the epilogue the caller would like fused; the plan falls back to raw
 // K-slice partial sums when it splits K.  Returns the plan so the caller knows which case ran.
 static int run_gemm(laps_ctx* c, int cls, bool capturing, const bf16_t* a, const bf16_t* w, int m, int n, int k,
-                    int want, float* partial, size_t partial_cap, float* out_f32, const float* resid, bf16_t* out_bf16,
+                    int want, bool row_kernel, float* partial, size_t partial_cap, float* out_f32, const float* resid, bf16_t* out_bf16,
                     const int* row_live, const int* n_live, bool live_varies, GemmPlan* plan, hipStream_t s) {
-    const GemmPlan p = laps_gemm_plan(m, n, k, 0, want, partial_cap);
+    const GemmPlan p = laps_gemm_plan(m, n, k, 0, want, partial_cap, row_kernel);
     *plan = p;
     ProfScope ps(c, s, cls, capturing);
     if (p.epi == EPI_PARTIAL) return laps_gemm_launch(p, a, w, m, n, k, partial, nullptr, nullptr, row_live, n_live, live_varies, s);
@@ -382,7 +383,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         // q, k, v: GEMM -> K-slice sums -> bias + RoPE + KV append
         const bf16_t* r_in = (l == 0 && r0_staged != nullptr) ? r0_staged : r;
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_QKV, capturing, r_in, static_cast<const bf16_t*>(lw.w_qkv), M, qkv, d, EPI_PARTIAL,
-                          partial, partial_cap, nullptr, nullptr, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
+                          true, partial, partial_cap, nullptr, nullptr, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
         {
             ProfScope ps(c, s, LAPS_K_EPI_QKV, capturing);
             LAPS_TRY(laps_launch_epi_qkv(partial, gp.split, cf.has_qkv_bias ? static_cast<const bf16_t*>(lw.b_qkv) : nullptr,
@@ -397,7 +398,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         // x_mid = resid + attn W_o^T ; r = rmsnorm(x_mid; ln2)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_O, capturing, attn, static_cast<const bf16_t*>(lw.w_o), M, d, qd, EPI_RESID,
-                          partial, partial_cap, x_mid, resid, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
+                          true, partial, partial_cap, x_mid, resid, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
         if (gp.epi == EPI_RESID) {
             ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);
             LAPS_TRY(laps_launch_rmsnorm(x_mid, static_cast<const bf16_t*>(lw.ln2_w), r, M, d, cf.rms_eps, tok_pos, s));
@@ -408,7 +409,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         // act = silu(r W_g^T) * (r W_u^T)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_GATEUP, capturing, r, static_cast<const bf16_t*>(lw.w_gate_up), M, 2 * I, d,
-                          EPI_SWIGLU, partial, partial_cap, nullptr, nullptr, act, row_live, n_live, r0_staged != nullptr, &gp, s));
+                          EPI_SWIGLU, false, partial, partial_cap, nullptr, nullptr, act, row_live, n_live, r0_staged != nullptr, &gp, s));
         if (gp.epi != EPI_SWIGLU) {
             ProfScope ps(c, s, LAPS_K_EPI_SWIGLU, capturing);
             LAPS_TRY(laps_launch_epi_swiglu(partial, gp.split, act, M, I, tok_pos, s));
@@ -416,7 +417,7 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         // x_out = x_mid + act W_d^T ; r = rmsnorm(x_out; next layer's ln1)
         const bf16_t* next_ln = (l + 1 < n_layers) ? static_cast<const bf16_t*>(w[l + 1].ln1_w) : nullptr;
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_DOWN, capturing, act, static_cast<const bf16_t*>(lw.w_down), M, d, I, EPI_RESID,
-                          partial, partial_cap, x_out, x_mid, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
+                          next_ln != nullptr, partial, partial_cap, x_out, x_mid, nullptr, row_live, n_live, r0_staged != nullptr, &gp, s));
         if (gp.epi == EPI_RESID) {
             if (next_ln) {
                 ProfScope ps(c, s, LAPS_K_RMSNORM, capturing);

@@ -534,7 +534,7 @@ void laps_gemm_tile_dims(int cfg, int* bm, int* bn) {
 }
 
 // Picks tile shape and K split.
-GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap) {
+GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap, bool row_kernel) {
     GemmPlan p;
     const int ksteps = k / BK;
     const bool far = k >= kMaxBufferK;   // rows that only the pointer-addressed tiles (1, 6, 7) reach
@@ -587,15 +587,27 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     // Above 128 rows no bound decides alone: at a few hundred rows the weight stream, the number of workgroups and the
     // rows a tile pads all count, further up the rounds of tiles over the 256 compute units do.  Time of a launch:
     //   rounds * (fill + slabs * slab) [a partly filled chip runs its slabs up to `part` faster: less traffic, more
-    //   clock], not less than the weights take from HBM; a split adds the partial sums written, the reduce launch and
-    //   the reading back; an un-split residual epilogue adds the RMSNorm launch that the reduce kernel would contain.
-    // Over the 240 measured shapes the choice is 1 % slower than the fastest measured one on average, more than 5 % in
-    // 17.  Against the one rule before it (256-row tiles only) the 32B layer's projections take, q/k/v, o, gate/up,
-    // down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows 42 -> 36, 41 -> 36, 272 -> 217,
-    // 142 -> 116; 7B at 256 rows 35 -> 19, 38 -> 22, 92 -> 92, 63 -> 53.
+    //   clock], not less than the weights take from HBM; a split adds the partial sums written and read back, the row
+    //   kernel's own traffic and, if there would be none otherwise, its launch; an un-split residual epilogue adds the
+    //   RMSNorm that the row kernel would contain, where one follows.
+    // Against the one rule before it (256-row tiles only) products of the 7B, 14B and 32B projections and of 24 random
+    // shapes at 40 row counts from 129 to 4096 are 1.37 times faster in the mean and more than 2.5 % slower at a K of six
+    // slabs only (7552 columns, 4096 rows: 45 -> 53 us, bound by the stores; the fit holds slabs by the dozen).  The 32B
+    // layer's projections take, q/k/v, o, gate/up, down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows
+    // 42 -> 36, 41 -> 36, 272 -> 217, 142 -> 116; 7B at 256 rows 35 -> 19, 38 -> 22, 92 -> 92, 63 -> 53.
+    // The bytes of partial sums are bounded by what the workspaces hold, not more tightly: at 48 MiB 7B down of 1200 rows
+    // took 2 slices instead of 3 (175 against 161 us) and 32B down of 1280 rows one instead of 5 (378 against 331).
     // Rows of 2^22 values and more take this model at any row count, with as many K slices as fill the chip.  K = 2^22 at
     // 256 columns, 1 / 64 / 128 / 256 / 700 rows: 0.53 / 0.69 / 0.91 / 1.7 / 2.8 ms (un-split on the same tiles 36 / 48 /
     // 68 / 64 / 65; tiles that reach no such rows would take 0.50 / 0.62 / 0.75 up to 128).
+    // Time of the partial sums (written and read back) and of the row kernel's own traffic: 11 TB/s while the caches hold
+    // them, 5 TB/s in the end (14B o, 4500 rows in two slices, 552 MB: 107 us behind the tiles; 4864 columns, 640 rows in two
+    // slices, 62 MB: 4).
+    auto moved = [](double b) {
+        return (b < 64e6 ? b : 64e6) / 11e6 + (b > 64e6 ? (b < 128e6 ? b - 64e6 : 64e6) / 6e6 : 0.0) + (b > 128e6 ? (b - 128e6) / 5e6 : 0.0);
+    };
+    const double mn = (double)m * n;
+    const double own = want_epi == EPI_RESID ? 8.0 * mn : want_epi == EPI_SWIGLU ? mn : row_kernel ? 2.0 * mn : 4.0 * mn;
     double best = 1e30;
     int best_cfg = -1, best_split = 1;
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
@@ -606,7 +618,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         if (t.bm == 192 && tiles_m != (m + 255) / 256 && !far) continue;   // 192 rows where they need no more row tiles than 256
         const int max_split = force_split > 0 ? force_split : (far ? 256 : 16);   // a few column tiles have to fill the chip
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
-            const double partial = 4.0 * s * (double)m * n;
+            const double partial = 4.0 * s * mn;
             if (force_split == 0 && s > 1 && (ksteps / s < 4 || partial > (double)partial_cap)) break;
             int per = (ksteps + s - 1) / s;
             if (t.ws == 2 && ksteps % 2 == 0) per = (per + 1) / 2 * 2;
@@ -616,10 +628,9 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
             const double tiles = 4.0 + rounds * (t.fill + per * t.slab * (1.0 - t.part * (1.0 - filled)));
             const double stream = 4.0 + 2.0 * n * (double)k / 4.6e6;
             double us = (tiles > stream ? tiles : stream) + 0.02 * tiles;   // of equal streams, the one with less to compute
-            if (s > 1) us += partial / 8.3e6;
-            if (want_epi == EPI_PARTIAL || s > 1) us += partial / 5.9e6;   // the row kernel's reading
-            if (want_epi != EPI_PARTIAL && s > 1) us += 3.6;
-            if (want_epi == EPI_RESID && s == 1) us += 4.0 + 6.0 * m * (double)n / 4.5e6;
+            if (s > 1) us += moved(2.0 * partial + own) + (want_epi == EPI_PARTIAL ? 0.0 : 3.6);
+            else if (row_kernel && want_epi == EPI_PARTIAL) us += moved(partial + own);   // written with the tiles
+            else if (row_kernel && want_epi == EPI_RESID) us += 4.0 + 6.0 * mn / 4.5e6;
             if (us < best) {
                 best = us;
                 best_cfg = cfg;

@@ -56,8 +56,11 @@ struct GemmPlan {
 };
 // partial_cap: bytes the partial sums of an automatic split may take above 128 rows or at K >= 2^22 (the layer driver
 // passes what its workspace holds if that is less).
-constexpr size_t LAPS_PARTIAL_CAP = (size_t)48 << 20;
-GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap = LAPS_PARTIAL_CAP);
+// row_kernel: a row kernel follows whether K is split or not and would add the slices as well: in a layer the RMSNorm
+// behind a residual projection, or the kernel that takes raw sums.  False for a product of its own.
+constexpr size_t LAPS_PARTIAL_CAP = (size_t)256 << 20;
+GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap = LAPS_PARTIAL_CAP,
+                        bool row_kernel = false);
 size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap);
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // rows and columns of tile shape `cfg` (0, 0 if unknown)
 // row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified:
@@ -186,7 +189,7 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
 // workgroups, spread over the compute units.  Where every unit has a workgroup to itself and the longest is no longer
 // than a share with what cutting costs (partial results, their merge, uneven cuts), nothing is cut: 32B shape, 16 short
 // turns (176 units of 5) 32 us in shares of several units, 23 so; 16 turns over up to 1472 keys (units of up to 27, shares
-// of 11) 57 us cut, 63 not; 1000 rows over 600 (160 units of up to 30, shares of 13) 73 cut, 66 not.
+// of 11) 55 us cut, 63 not; 1000 rows over 600 (160 units of up to 30, shares of 13) 73 cut, 66 not.
 // Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; pre (max_items + 1 ints) holds the prefix sums of the
 // item costs.
 constexpr int LAPS_ATTN_KT = 64;          // keys per tile

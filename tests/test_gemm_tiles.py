@@ -17,14 +17,26 @@ def plan(m, n, k, epi):
 
 
 @pytest.mark.parametrize("cfgf", [inputs.tiny_cfg, inputs.qwen7b_cfg, inputs.qwen14b_cfg, inputs.qwen32b_cfg])
-def test_partial_sums_of_an_automatic_split_stay_within_48_mib(cfgf):
+def test_partial_sums_of_an_automatic_split_stay_within_their_bound(cfgf):
+    """256 MiB, and no more than the workspace of a layer of these rows has room for."""
     c = cfgf(1)
     shapes = ((c.qkv_dim, c.hidden, PARTIAL), (c.hidden, c.q_dim, RESID), (2 * c.intermediate, c.hidden, SWIGLU),
               (c.hidden, c.intermediate, RESID))
-    for m in list(range(129, 800, 7)) + [1024, 2048, 4096, 12000]:
+    mc = api._ModelCfg(c.hidden, c.n_q_heads, c.n_kv_heads, c.head_dim, c.intermediate, 1, 16, 0, 1e6, 1e-6)
+    for m in list(range(129, 800, 7)) + [1024, 1200, 1280, 2048, 4096, 12000]:
+        room = api.lib().laps_workspace_bytes_for(C.byref(mc), C.c_int32(m), C.c_int32(1))
         for n, k, epi in shapes:
             p = plan(m, n, k, epi)
-            assert p["split"] == 1 or p["split"] * m * n * 4 <= 48 << 20, (m, n, k, p)
+            assert p["split"] == 1 or p["split"] * m * n * 4 <= min(room, 256 << 20), (m, n, k, p)
+
+
+@pytest.mark.parametrize("m,n,k,epi,slices", [(1200, 3584, 18944, RESID, 3), (1500, 3584, 18944, RESID, 3), (2048, 3584, 18944, RESID, 2),
+                                              (640, 5120, 27648, RESID, 4), (1280, 5120, 27648, RESID, 5), (1400, 5120, 27648, RESID, 2),
+                                              (2200, 5120, 27648, RESID, 4), (640, 4864, 7168, PARTIAL, 2), (1280, 3584, 11136, SWIGLU, 3)])
+def test_k_is_split_where_tiles_leave_the_chip_idle(m, n, k, epi, slices):
+    """Products whose fp32 partial sums are large but pay for themselves: fewer slices are slower, and sums of longer
+    chains less precise."""
+    assert plan(m, n, k, epi)["split"] >= slices
 
 
 # (rows, columns, K): 128x128 with odd / even slabs and K splits, 192x128 with one and two slices, 256x128 with odd /
@@ -74,7 +86,7 @@ def test_long_rows_fill_the_chip_and_keep_their_sums_short(m, n, k):
     for epi in (PARTIAL, RESID, SWIGLU):
         p = plan(m, n, k, epi)
         assert p["wgs"] >= 128 and p["k_per"] <= k // 16 and (p["split"] - 1) * p["k_per"] < k <= p["split"] * p["k_per"], p
-        assert p["split"] * m * n * 4 <= 48 << 20, p
+        assert p["split"] * m * n * 4 <= 256 << 20, p
 
 
 @pytest.mark.gpu
