@@ -8,7 +8,10 @@ which the request is memory-bound.  The paper does not say how a sample separate
   * T_comp(L, H) is the time of the matrix-core kernels (four projections per layer and attention) of one
     single-request pass through the stack, taken from the library's per-kernel-class event timers, over
     the samples with L >= `comp_min_len`, where those kernels are arithmetic-bound;
-  * T_mem(L, H) is the time the paged-KV kernels need to write L tokens and to read H tokens of every layer.
+  * T_mem(L, H) is the time the paged-KV kernels need to write L tokens and to read H tokens of every layer, on the
+    device: their launches are queued behind a pass through the stack, since a few microseconds of copying each would
+    otherwise be timed at the rate the host launches them, and what launches of a single token take is subtracted (the
+    term has no constant, and the layers' own kernels write and read the cache without launches for it).
 
 The paper's memory term has no constant for streaming the weights once per pass, which is what bounds a
 short batch on this GPU; `weight_floor_us` (the projection time of the smallest L) is reported beside the
@@ -27,10 +30,13 @@ from . import api
 GEMM_CLASSES = ("gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down")
 
 
-def _time_us(stream, fn, reps):
+def _time_us(stream, fn, reps, ahead=None):
+    """Microseconds per call; `ahead`: work that keeps the device busy while the calls are being enqueued."""
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     fn()
     stream.synchronize()
+    if ahead is not None:
+        ahead()
     e0.record(stream)
     for _ in range(reps):
         fn()
@@ -54,6 +60,22 @@ def collect_samples(ctx: api.LapsCtx, layers, new_lens, hist_lens, reps: int = 3
                          dtype=torch.float32).to(torch.bfloat16)
     ctx.workspace(max(new_lens), 1)
     zero = torch.zeros(1, dtype=torch.int32, device="cuda")
+    full = torch.tensor([0, max(new_lens)], dtype=torch.int32, device="cuda")
+    y_all = torch.empty_like(x_all)
+    ahead = lambda: ctx.laps_prefill_stack(layers, full, None, zero, pt, k_pools, v_pools, x_all, y_all, stream)
+    # KV I/O alone: write n tokens at position start, read n tokens from position 0, every layer
+    def kv_write(cu_n, start, n):
+        for l in range(n_layers):
+            ctx.laps_kv_scatter(cu_n, start, pt, kv_src[:n], kv_src[:n], k_pools[l], v_pools[l], stream)
+
+    def kv_read(cu_n, n):
+        for l in range(n_layers):
+            ctx.laps_kv_gather(cu_n, zero, pt, k_pools[l], v_pools[l], n, stream)
+
+    one = torch.tensor([0, 1], dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    w_launch = min(_time_us(stream, lambda: kv_write(one, zero, 1), reps, ahead) for _ in range(3))
+    r_launch = min(_time_us(stream, lambda: kv_read(one, 1), reps, ahead) for _ in range(3))
     out = []
     for H in hist_lens:
         for L in new_lens:
@@ -74,18 +96,12 @@ def collect_samples(ctx: api.LapsCtx, layers, new_lens, hist_lens, reps: int = 3
             gemm_us = sum(prof[k][0] for k in GEMM_CLASSES) * 1e3 / reps
             attn_us = prof["attn"][0] * 1e3 / reps
             total_us = _time_us(stream, run, reps)
-            # KV I/O alone: write L tokens at position H, read H tokens from position 0, every layer
-            def kv_write():
-                for l in range(n_layers):
-                    ctx.laps_kv_scatter(cu, pre, pt, kv_src[:L], kv_src[:L], k_pools[l], v_pools[l], stream)
-            w_us = _time_us(stream, kv_write, reps)
+            w_us = max(0.0, _time_us(stream, lambda: kv_write(cu, pre, L), reps, ahead) - w_launch)
             r_us = 0.0
             if H > 0:
                 cu_h = torch.tensor([0, H], dtype=torch.int32, device="cuda")
-                def kv_read():
-                    for l in range(n_layers):
-                        ctx.laps_kv_gather(cu_h, zero, pt, k_pools[l], v_pools[l], H, stream)
-                r_us = _time_us(stream, kv_read, reps)
+                torch.cuda.synchronize()
+                r_us = max(0.0, _time_us(stream, lambda: kv_read(cu_h, H), reps, ahead) - r_launch)
             out.append({"L": L, "H": H, "t_comp_us": gemm_us + attn_us, "gemm_us": gemm_us, "attn_us": attn_us,
                         "t_mem_us": w_us + r_us, "kv_write_us": w_us, "kv_read_us": r_us, "stack_us": total_us})
     return out
