@@ -195,11 +195,12 @@ int laps_prefill_stack(laps_ctx* ctx, const laps_layer_weights* w, int32_t n_seq
 /* ------------------------------------------------------------------ prefill forward without a workspace argument
  * For callers that cannot allocate device memory or may not call anything that does: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same computation, kernels and results as
- * laps_prefill_stack, with the workspace taken from a static device array inside the library
- * (laps_static_scratch_bytes() = 128 MiB per GPU, held from library load until the process ends; its address on the
- * context's device is resolved once, in laps_ctx_create).  The call itself allocates nothing, frees nothing and
- * never synchronises.  A batch whose workspace (laps_workspace_bytes) exceeds the array is rejected with LAPS_EINVAL
- * and a message naming both sizes: at the 32B layer shape that is a few hundred rows.  The context's device must be
+ * laps_prefill_stack, with the workspace taken from a static device array inside the library (129 MiB per GPU, held
+ * from library load until the process ends; its address on the context's device is resolved once, in
+ * laps_ctx_create).  The call itself allocates nothing, frees nothing and never synchronises.  A batch whose workspace
+ * (laps_workspace_bytes) exceeds laps_static_scratch_bytes() = 128 MiB by more than its attention work-item tables (a
+ * few KB; laps_attn_plan_info reports them; 1 MiB at most) is rejected with LAPS_EINVAL and a message naming both
+ * sizes: at the 32B layer shape that is a few hundred rows.  The context's device must be
  * current.  Every call on a GPU uses that GPU's one array (nothing in it has to start at zero: each region is
  * written before it is read within the call), so calls that overlap in time on one GPU - two streams, two threads,
  * two contexts - race on it and must be serialised by the caller; calls on one stream are ordered by the stream. */
@@ -244,8 +245,8 @@ int laps_graph_capture(laps_ctx* ctx, const laps_layer_weights* w, int32_t len_b
  * [n_rows, hidden], the sequences' rows packed in slot order, n_rows = the sum of the lengths
  * (0 <= n_rows <= depth*len_bucket, else LAPS_EINVAL).  x_rows_dev may be NULL with n_rows 0 when the caller
  * has written laps_graph_input() in place: those rows must then be complete before this call, which reads them.
- * Enqueues two kernels that prepare everything a replay needs besides the layers themselves: lengths, row
- * offsets and the attention's work-item table (one workgroup), then per row the token's position and cache slot,
+ * Enqueues one kernel that prepares everything a replay needs besides the layers themselves: lengths, row
+ * offsets and the attention's work-item table (one workgroup), beside it per row the token's position and cache slot,
  * the copy of its input, its RMSNorm with the first layer's gain, and the page-table copy.  A replay therefore
  * starts with the first projection; replaying again without staging repeats the same batch. */
 int laps_graph_stage(laps_graph* g, int32_t n_real, const int32_t* seq_len_dev, const int32_t* prefix_len_dev,

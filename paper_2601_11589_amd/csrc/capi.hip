@@ -526,10 +526,10 @@ extern "C" int laps_prefill_stack_static(laps_ctx* c, const laps_layer_weights* 
     }
     const size_t need = ws_layout(c->cfg, n_tokens, n_seq).total;
     const size_t tables = laps_attn_item_table_bytes(n_tokens, n_seq, c->cfg.n_q_heads / c->cfg.n_kv_heads);
-    if (need > LAPS_STATIC_SCRATCH_BYTES + (tables < LAPS_STATIC_TABLE_BYTES ? tables : LAPS_STATIC_TABLE_BYTES)) {
+    const size_t room = LAPS_STATIC_SCRATCH_BYTES + (tables < LAPS_STATIC_TABLE_BYTES ? tables : LAPS_STATIC_TABLE_BYTES);
+    if (need > room) {
         laps_set_error("prefill_stack_static: %d tokens x %d sequences need %zu bytes of workspace, the static scratch "
-                       "holds %zu; use laps_prefill_stack with a caller-owned workspace", n_tokens, n_seq, need,
-                       (size_t)LAPS_STATIC_SCRATCH_BYTES);
+                       "holds %zu of such a batch; use laps_prefill_stack with a caller-owned workspace", n_tokens, n_seq, need, room);
         return LAPS_EINVAL;
     }
     int dev = -1;
@@ -747,7 +747,7 @@ struct laps_graph {
     hipGraphExec_t exec;
 };
 
-// The two staging launches of a graph (see StageArgs): everything a replay needs besides the layers themselves.
+// The staging launch of a graph (see StageArgs): everything a replay needs besides the layers themselves.
 static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, const int* prefix_len, const int* page_table,
                               const float* x_rows, int n_rows, hipStream_t s) {
     const laps_model_cfg& cf = g->ctx->cfg;

@@ -2,6 +2,8 @@
 with the library's static device array as workspace.  Two calls in a row, the second on a smaller batch, each
 bit-equal to the existing entry point on the same inputs and fresh caches; a batch whose workspace exceeds the array
 is rejected."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -56,6 +58,10 @@ def test_static_scratch_entry_point_rejects_batches_beyond_the_array():
     pt = torch.zeros((1, n_tok // 16), dtype=torch.int32, device="cuda")
     kp, vp = ctx.new_pools(n_tok // 16, 1, zero=True)
     w = {k: torch.zeros(1, dtype=torch.bfloat16, device="cuda") for k in ("ln1", "w_qkv", "w_o", "ln2", "w_gate_up", "w_down")}
-    with pytest.raises(api.LapsError, match="static scratch"):
+    with pytest.raises(api.LapsError, match="static scratch") as e:
         ctx.laps_prefill_stack_static([w], cu, None, zero, pt, kp, vp, x, x)
+    # the message names the limit that was applied: 128 MiB and the batch's attention tables
+    out = (C.c_int64 * 6)()
+    assert api.lib().laps_attn_plan_info(1, n_tok, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, n_tok // 16, out) == 0
+    assert f"holds {(128 << 20) + out[4]}" in str(e.value)
     ctx.close()
