@@ -510,7 +510,7 @@ __global__ void kv_move_kernel(int n_seq, int n_tokens, const int* __restrict__ 
 
 // Staging of a captured bucket, one launch: workgroup 0 writes the batch's metadata, workgroup 1 + r prepares row r.  Every
 // row workgroup scans the slots' lengths itself instead of waiting for workgroup 0 (two launches, 4.8 + 9.4 us for 128
-// rows; one, 9 us; short re-prefill replay 285 -> 280, single turn 161 -> 156), and its input row is on the way meanwhile.
+// rows; one, 6.5 us; short re-prefill replay 285 -> 280, single turn 161 -> 156), and its input row is on the way meanwhile.
 //
 // The lengths the caller staged for the first n_real slots are clamped to [0, len_bucket], the other slots are empty, and
 // the sequences are packed one after the other (row_start = running sum of the clamped lengths, so the total never

@@ -219,7 +219,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const int lrow = lane & 31, lk = lane >> 5;
 
     // Slab copy assignment: 16-byte chunk c = tid + i*NT -> row c / CHUNKS = row0 + i * RPP, chunk kc.  RPP is a multiple
-    // of 16, so all rows of a thread share one swizzle and their LDS places differ by a constant.  The large tiles
+    // of 16, so all rows of a thread share one swizzle and their LDS places differ by a constant.  The 256-row tiles
     // address both operands through buffer descriptors: one 32-bit offset per operand and thread instead of a pointer per
     // row, which is what lets 256x256 hold two slabs in flight besides its 256 accumulators; A rows past M lie past the
     // descriptor's end and return zero without a request.
