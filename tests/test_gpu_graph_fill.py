@@ -34,17 +34,35 @@ def test_every_fill_of_a_graph_matches_the_uncaptured_path(setup, lens):
     ctx, layer, x, table, kp, vp, stream, graph = setup
     n, rows = len(lens), sum(lens)
     d = lambda a: torch.from_numpy(np.asarray(a, np.int32)).cuda()
+    live = torch.arange(BUCKET, device="cuda")[None] < torch.tensor(lens + [0] * (DEPTH - n), device="cuda")[:, None]   # [slot, token]
+
+    def poison():                                     # nothing of another fill, or of the other path, may pass for written
+        for pool in (kp[0], vp[0]):
+            pool.fill_(776.0)
+        torch.cuda.synchronize()
+
+    def written():                                    # [token, kv head, head_dim] of K and V; every other slot untouched
+        # pages 4 s .. 4 s + 3 hold slot s: K [page][head][16][hd], V [page][head][hd][16]
+        k = kp[0].view(DEPTH, 4, CFG.n_kv_heads, 16, CFG.head_dim).transpose(2, 3).reshape(DEPTH, BUCKET, CFG.n_kv_heads, CFG.head_dim)
+        v = vp[0].view(DEPTH, 4, CFG.n_kv_heads, CFG.head_dim, 16).permute(0, 1, 4, 2, 3).reshape(DEPTH, BUCKET, CFG.n_kv_heads, CFG.head_dim)
+        assert bool((k[~live] == 776.0).all()) and bool((v[~live] == 776.0).all())
+        assert not bool((k[live] == 776.0).all(-1).any()) and not bool((v[live] == 776.0).all(-1).any())
+        return k[live].double(), v[live].double()
+
+    poison()
     pre, out = d([0] * n), torch.empty((rows, CFG.hidden), device="cuda")
     graph.laps_graph_stage(n, d(lens), pre, table[:n].contiguous(), x[:rows].contiguous(), stream)
     graph.laps_graph_replay(stream)
     graph.laps_graph_read_output(rows, out, stream)
     torch.cuda.synchronize()
-    k_graph, v_graph = kp[0].clone(), vp[0].clone()
+    k_graph, v_graph = written()
+    poison()
     want = ctx.laps_prefill_layer(layer, d(np.concatenate([[0], np.cumsum(lens)])), None, pre, table[:n].contiguous(), kp[0], vp[0],
                                   x[:rows].contiguous())
     torch.cuda.synchronize()
     # other K splits on the un-captured side: fp32 sums in another order, re-rounded to bf16 operands four times in the
     # layer (2^-9 / sqrt(3) each, in part of the elements)
     assert float((out - want).norm() / want.norm()) < 4 * 2.0 ** -9 / 3 ** 0.5
-    assert float((k_graph.double() - kp[0].double()).norm() / kp[0].double().norm()) < 2.0 ** -9
-    assert float((v_graph.double() - vp[0].double()).norm() / vp[0].double().norm()) < 2.0 ** -9
+    k_want, v_want = written()
+    assert float((k_graph - k_want).norm() / k_want.norm()) < 2.0 ** -9
+    assert float((v_graph - v_want).norm() / v_want.norm()) < 2.0 ** -9
