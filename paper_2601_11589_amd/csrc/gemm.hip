@@ -190,7 +190,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     u32x4* As = reinterpret_cast<u32x4*>(smem);  // [2][BM][CHUNKS]
     u32x4* Bs = As + 2 * BM * CHUNKS;            // [2][BN][CHUNKS]
 
-    const int N = g.N, K = g.K;
+    const int K = g.K;
     const TileCoord tc = map_block(bid, tiles_m, tiles_n, g.split);
     const int m0 = tc.tm * BM, n0 = tc.tn * BN;
     const int kbeg = tc.ks * g.kps;

@@ -1,9 +1,12 @@
 """A captured graph of many rows at different fills: the GEMMs choose their tile width and deal out their tiles by the
-number of live rows they find on the device, so every fill has to give what the un-captured path gives."""
+number of live rows they find on the device, so every fill has to give what the un-captured path gives, and what the
+oracle gives for its first, middle and last sequence."""
 import numpy as np
 import pytest
 import torch
 
+from gpu_harness import MAX_ABS_TOL, REL_L2_TOL, errors, widen_layer
+from oracle import laps_oracle
 from paper_2601_11589_amd import api, inputs
 
 pytestmark = pytest.mark.gpu
@@ -56,6 +59,13 @@ def test_every_fill_of_a_graph_matches_the_uncaptured_path(setup, lens):
     graph.laps_graph_read_output(rows, out, stream)
     torch.cuda.synchronize()
     k_graph, v_graph = written()
+    cu, ids = np.concatenate([[0], np.cumsum(lens)]), sorted({0, n // 2, n - 1})
+    picked = np.concatenate([np.arange(cu[i], cu[i + 1]) for i in ids])
+    none = [[None] * len(ids)]
+    exact, *_ = laps_oracle.stack_forward(CFG, [widen_layer(inputs.make_layer_weights(CFG, 5, 0))], x.cpu().numpy()[picked].astype(np.float64),
+                                          [lens[i] for i in ids], none, none, False)
+    rel, mx = errors(out.cpu().numpy()[picked], exact)
+    assert rel < REL_L2_TOL and mx < MAX_ABS_TOL, (rel, mx)
     poison()
     want = ctx.laps_prefill_layer(layer, d(np.concatenate([[0], np.cumsum(lens)])), None, pre, table[:n].contiguous(), kp[0], vp[0],
                                   x[:rows].contiguous())
