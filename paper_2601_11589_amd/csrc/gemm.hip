@@ -440,7 +440,9 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
 // 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 220
 // of 256 x 256 take one: 997 against 700 us).  Widths WN_ (160 or 224), 256 and 128 are therefore one kernel, which takes
-// the width that the cost model gives the live rows; every workgroup comes to the same choice.
+// the width that the cost model gives the live rows; every workgroup comes to the same choice.  Built for raw sums and the
+// residual epilogue of N divisible by 160 (5120) or 224 (7168, 3584); SwiGLU and other N (7B q/k/v, 4608) keep the tile
+// planned for all rows.
 struct WidthCost {
     float fill[3], slabs[3], part[3];   // as TileDef, slabs = time of all K slabs on a full chip
 };
@@ -591,7 +593,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     //   kernel's own traffic and, if there would be none otherwise, its launch; an un-split residual epilogue adds the
     //   RMSNorm that the row kernel would contain, where one follows.
     // Against the one rule before it (256-row tiles only) products of the 7B, 14B and 32B projections and of 24 random
-    // shapes at 40 row counts from 129 to 4096 are 1.37 times faster in the mean and more than 2.5 % slower at a K of six
+    // shapes at 40 row counts from 129 to 4096 are 1.37 times faster in the mean and more than 3 % slower at a K of six
     // slabs only (7552 columns, 4096 rows: 45 -> 53 us, bound by the stores; the fit holds slabs by the dozen).  The 32B
     // layer's projections take, q/k/v, o, gate/up, down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows
     // 42 -> 36, 41 -> 36, 272 -> 217, 142 -> 116; 7B at 256 rows 35 -> 19, 38 -> 22, 92 -> 92, 63 -> 53.
