@@ -1,17 +1,24 @@
-// bf16 x bf16 -> fp32 GEMM on gfx950 MFMA (v_mfma_f32_32x32x16_bf16), LDS-staged tiles.
+// bf16 x bf16 -> fp32 GEMM on gfx950 MFMA, LDS-staged tiles.
 //
 //   C[M,N] = A[M,K] * W[N,K]^T        A: activations (row-major, K contiguous)
 //                                      W: weights in [out, in] order (row-major, K contiguous)
 //
 // Both operands are K-contiguous, so a lane's MFMA fragment (8 consecutive k of one row) is one
-// 16-byte read.  A workgroup owns a BM x BN output tile and one K slice.  The K loop moves 64-wide
-// slabs HBM -> registers -> LDS (two LDS buffers) and is software-pipelined by hand:
+// 16-byte read.  A workgroup owns a BM x BN output tile and one K slice, and walks it in slabs of 64.
+//
+// Two kinds of tile:
+//  * 128 rows (gemm_tile, v_mfma_f32_32x32x16_bf16): bound by what a compute unit takes in.  Slabs go HBM -> registers ->
+//    LDS, so that padding rows can be left out lane by lane and weights can bypass the caches.  Also the tiles of rows of
+//    2^22 values and more, which 32-bit offsets do not reach.
+//  * 192 and 256 rows (dma_tile, v_mfma_f32_16x16x32_bf16): bound by the power that the matrix cores and the operands' way
+//    to them draw on real data, so both are chosen for that.
+//
+// gemm_tile's K loop is software-pipelined by hand:
 //   * fragments of k-step kk+1 are read from LDS into a second register set before the MFMAs of
-//     k-step kk are issued, so LDS latency hides behind 8..16 MFMAs;
+//     k-step kk are issued, so LDS latency hides behind the MFMAs;
 //   * the registers holding slab kt+1 are written to the other LDS buffer in the middle of slab kt
 //     and immediately reloaded from HBM with slab kt+1+WS; WS = 2 sets of staging registers keep two
-//     slabs in flight (the large tiles gain 2-7 % over one: 2048 x 5120 x 27648 on 256x160 527 -> 494 us,
-//     2048 x 55296 x 5120 on 256x256 966 -> 951);
+//     slabs in flight;
 //   * the one barrier per slab sits in the middle of the last k-step's MFMAs and waits on LDS
 //     traffic only, never on the HBM loads in flight.
 // Epilogues: raw K-slice partial sums (split-K, reduced deterministically by the row kernels in
@@ -20,6 +27,8 @@
 // Workgroup ids are remapped so that each of the 8 XCDs (workgroups are dealt to them round-robin)
 // gets a contiguous range of tiles, walked M-fastest in groups of 8 row tiles: the workgroups
 // sharing a weight panel sit on one XCD and hit its L2.
+#include <type_traits>
+
 #include "laps_internal.h"
 
 namespace {
@@ -168,7 +177,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
 
 // Streaming weight loads and A rows through a buffer descriptor: the skinny tiles.  The 32-bit offsets of buffer
 // descriptors hold a tile of 256 rows up to K = 2^22; longer rows take the tiles that address every row by a pointer:
-// the 192-row ones and the one-slab variant of 128x64.
+// 192x256 and 192x128 here, and the one-slab variant of 128x64.
 constexpr int kMaxBufferK = 1 << 22;
 template <int BM, int BN, int WS>
 constexpr bool skinny_loads = BM <= 128 && !(BN == 64 && WS == 1);
@@ -176,8 +185,8 @@ constexpr bool skinny_loads = BM <= 128 && !(BN == 64 && WS == 1);
 // WS = number of register sets that stage slabs: WS slabs (A and W chunks alike - loads return in
 // issue order, so a shallower A stream would throttle the W stream) are in flight per workgroup.
 // With WS = 2 the K loop is unrolled so that every set index is static, and a K slice must hold a multiple of
-// two slabs; WS = 1 serves K of an odd number of slabs (and 192x128, whose second set costs the second workgroup's
-// registers).
+// two slabs; WS = 1 serves K of an odd number of slabs (and the pointer-addressed 192x128, whose second set costs the
+// second workgroup's registers).
 //
 // One tile of the rows_in live rows: workgroup `bid` of tiles_m * tiles_n * g.split.  late_live: NULL, or where the number
 // of live rows is found if it does not decide which tile this is (a single row tile): it is then read behind the first
@@ -198,7 +207,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const int KT = (kend - kbeg) / BK;
 
     constexpr bool NT = skinny_loads<BM, BN, WS>;
-    constexpr bool WIDE = BM == 256;
     const int tid = threadIdx.x;
     if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
         bool any = false;
@@ -219,32 +227,20 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const int lrow = lane & 31, lk = lane >> 5;
 
     // Slab copy assignment: 16-byte chunk c = tid + i*NT -> row c / CHUNKS = row0 + i * RPP, chunk kc.  RPP is a multiple
-    // of 16, so all rows of a thread share one swizzle and their LDS places differ by a constant.  The 256-row tiles
-    // address both operands through buffer descriptors: one 32-bit offset per operand and thread instead of a pointer per
-    // row, which is what lets 256x256 hold two slabs in flight besides its 256 accumulators; A rows past M lie past the
-    // descriptor's end and return zero without a request.
+    // of 16, so all rows of a thread share one swizzle and their LDS places differ by a constant.
     constexpr int RPP = T::NT / CHUNKS;
     static_assert(RPP % 16 == 0, "rows of a thread must share a swizzle");
     const int row0 = tid / CHUNKS, kc0 = tid % CHUNKS;
     const int dst0 = row0 * CHUNKS + swz(row0, kc0);
-    const u32x4* ag[WIDE ? 1 : T::A_LOADS];
-    const u32x4* bg[WIDE ? 1 : T::B_LOADS];
+    const u32x4* ag[T::A_LOADS];
+    const u32x4* bg[T::B_LOADS];
     u32x4 rrb[WS][T::B_LOADS];   // staged W slabs: slab j lives in set j % WS
-    const unsigned row_bytes = (unsigned)K * 2u;   // K <= kMaxBufferK: a tile of 256 rows stays below 2^31 bytes
-    __amdgpu_buffer_rsrc_t b_rsrc;
-    const unsigned off0 = (unsigned)row0 * row_bytes + (unsigned)kc0 * 16u;   // of either operand, from its slice's begin
-    if constexpr (WIDE) {
-        b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.W) + (size_t)n0 * K + kbeg, 0,
-                                                   (int)((unsigned)BN * row_bytes - (unsigned)kbeg * 2u), 0x00020000);
+    const unsigned row_bytes = (unsigned)K * 2u;   // of descriptors, where K < kMaxBufferK
+    const unsigned off0 = (unsigned)row0 * row_bytes + (unsigned)kc0 * 16u;
 #pragma unroll
-        for (int i = 0; i < T::B_LOADS; ++i)
-            rrb[0][i] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, off0, (unsigned)(i * RPP) * row_bytes, 0);
-    } else {
-#pragma unroll
-        for (int i = 0; i < T::B_LOADS; ++i) {
-            bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row0 + i * RPP) * K + kbeg) + kc0;
-            rrb[0][i] = STREAM ? __builtin_nontemporal_load(bg[i]) : *bg[i];
-        }
+    for (int i = 0; i < T::B_LOADS; ++i) {
+        bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row0 + i * RPP) * K + kbeg) + kc0;
+        rrb[0][i] = STREAM ? __builtin_nontemporal_load(bg[i]) : *bg[i];
     }
     int M = rows_in;
     if (late_live != nullptr) {
@@ -258,21 +254,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     // returns zero without a request and without the branch (and, in the prologue, the wait) that a condition
     // around each load cost.
     u32x4 rra[WS][T::A_LOADS];   // staged A slabs, same rule as rrb
-    unsigned a_off[WIDE ? 1 : T::A_LOADS];
-    const unsigned a_rows = WIDE ? (unsigned)(M - m0 < BM ? M - m0 : BM) : (unsigned)BM;
+    unsigned a_off[T::A_LOADS];
     const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(g.A) + (size_t)m0 * K, 0, NT || WIDE ? (int)(a_rows * row_bytes) : 0, 0x00020000);
-    if constexpr (WIDE) {
-        a_off[0] = off0 + (unsigned)kbeg * 2u;
-    } else {
+        const_cast<bf16_t*>(g.A) + (size_t)m0 * K, 0, NT ? (int)((unsigned)BM * row_bytes) : 0, 0x00020000);
 #pragma unroll
-        for (int i = 0; i < T::A_LOADS; ++i) {
-            const int row = row0 + i * RPP;
-            const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
-            ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc0;
-            const bool live = m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0);
-            a_off[i] = live ? off0 + (unsigned)(i * RPP) * row_bytes + (unsigned)kbeg * 2u : 0x80000000u;
-        }
+    for (int i = 0; i < T::A_LOADS; ++i) {
+        const int row = row0 + i * RPP;
+        const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
+        ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc0;
+        const bool live = m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0);
+        a_off[i] = live ? off0 + (unsigned)(i * RPP) * row_bytes + (unsigned)kbeg * 2u : 0x80000000u;
     }
     // fragment read offsets (in 16-byte chunks) inside one LDS buffer, per k-step
     int a_src[T::MI], b_src[T::NI];
@@ -301,15 +292,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     auto gload_one = [&](int i, int kt, int ws) {
         const int j = i - T::A_LOADS;
         if (i < T::A_LOADS) {
-            if constexpr (WIDE)   // the row goes into the lane's offset: it is what the range check sees
-                rra[ws][i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[0] + (unsigned)(i * RPP) * row_bytes,
-                                                                   clampk(kt) * (BK * 2), 0);
-            else if constexpr (NT)
+            if constexpr (NT)
                 rra[ws][i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], clampk(kt) * (BK * 2), 0);
             else
                 rra[ws][i] = ag[i][clampk(kt) * CHUNKS];
-        } else if constexpr (WIDE) {
-            rrb[ws][j] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, off0, (unsigned)(j * RPP) * row_bytes + clampk(kt) * (BK * 2), 0);
         } else {
             // weights are read once: streaming (non-temporal) loads keep them from evicting the A slabs,
             // which every workgroup on the CU and on the XCD re-reads, out of L1 / L2
@@ -414,6 +400,307 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     store_tile<T, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
+// ------------------------------------------------------------------ tiles of 192 and 256 rows
+// What bounds them on real data is power: the same kernel runs 1.15 times as fast on zeros.  Measured on normal(0, 1) x
+// normal(0, 0.02) operands:
+//  * v_mfma_f32_16x16x32_bf16 draws less than v_mfma_f32_32x32x16_bf16 (half the accumulator traffic per flop): 2.0-2.1
+//    against 1.76-1.85 PFLOP/s with registers alone;
+//  * slabs written into LDS by the load instruction itself, without staging registers and LDS stores;
+//  * a fragment held for several matrix instructions, and only one operand changed from each to the next (1 %).
+// 2048 x 55296 x 5120 with SwiGLU: 925 us through registers with 32x32x16, 865 with 16x16x32, 832 this way; 2048 x 5120 x
+// 27648: 500, 465, 445; 700 x 27648 x 5120: 204, 192, 180.
+// Slabs go in half slabs - the rows that one half of every wave's tile needs of A, and one half of B - through a ring of NS
+// of them (2.5 slabs on 256 x 256, the unit's 160 KB of LDS).  All fragments of a half slab (both k-steps of 32) are in
+// registers before its products begin, so its place in the ring is free half a slab after it was waited for.
+template <int BM, int BN, int WM, int WN>
+struct DmaTraits {
+    static constexpr int WTM = BM / WM, WTN = BN / WN;                   // wave tile
+    static constexpr int MI = WTM / 16, NI = WTN / 16;
+    static constexpr int HA = BM / 2, HB = BN / 2;                       // rows of a half slab
+    static constexpr int QA = HA / 4, QB = HB / 4;                       // rows that one wave loads
+    static constexpr int LA = (QA + 7) / 8, LB = (QB + 7) / 8;           // load instructions of a wave: 8 rows of 128 bytes
+    static constexpr int LOADS = LA + LB;
+    static constexpr int SLOT = (HA + HB) * BK * 2;                      // bytes
+    static constexpr bool TWO = BM * BN <= 192 * 128;                    // two workgroups on a compute unit
+    static constexpr int CAP = (TWO ? 80 : 160) * 1024;
+    static constexpr int NS = CAP / SLOT < 6 ? CAP / SLOT : 6;           // half slabs in LDS
+    static constexpr int LDS = NS * SLOT;
+    static_assert(WM * WN == 4 && QA % 8 == 0 && QB % 4 == 0, "four waves load whole groups of rows");
+    static_assert((WTM / 2) % 16 == 0 && (WTN / 2) % 16 == 0, "halves of whole sub-tiles");
+    static_assert((WTM / 2) % QA == 0 && (WTN / 2) % QB == 0, "the rows that a wave loads lie in one wave tile");
+};
+
+// LDS rows are 128 bytes; chunk c of row r is stored at chunk position c ^ key.  The 16 rows of a fragment have, two by
+// two, 8 different keys, so the 16 lanes that read the same chunk of them hit 16 different 16-byte columns of a 256-byte
+// bank line (SQ_LDS_BANK_CONFLICT reads 0).  Fragment row i of sub-tile s is row 16 s + i, or with PAIRED columns
+// 32 (s / 2) + 8 (i / 4) + 4 (s % 2) + i % 4.
+template <bool PAIRED>
+__device__ __forceinline__ int dma_key(int row) { return PAIRED ? ((row >> 1) & 1) | (((row >> 3) & 3) << 1) : (row >> 1) & 7; }
+
+// 16-byte accesses to the caller's arrays, which are aligned to their elements only
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+
+// The weights are the matrix instruction's first operand, so that a lane holds four consecutive columns (16 ni + 4 lk + r)
+// of row lane & 15 of a sub-tile.
+template <typename D, int EPI>
+__device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI], const GemmArgs& g, int M, int ks, int m0,
+                                               int n0, int wm, int wn, int lrow, int lk) {
+    const int N = g.N;
+    const int row0 = m0 + wm * D::WTM + lrow, col0 = n0 + wn * D::WTN;
+    if constexpr (EPI == EPI_PARTIAL) {
+        float* out = g.out_f32 + (size_t)ks * g.M * N + col0 + 4 * lk;
+#pragma unroll
+        for (int mi = 0; mi < D::MI; ++mi) {
+            const int m = row0 + mi * 16;
+            if (m >= M) continue;
+            f32x4_a4* dst = reinterpret_cast<f32x4_a4*>(out + (size_t)m * N);
+#pragma unroll
+            for (int ni = 0; ni < D::NI; ++ni) dst[ni * 4] = acc[mi][ni];
+        }
+    } else if constexpr (EPI == EPI_RESID) {
+        // resid may be the output array itself (every element is read by the thread that writes it), so the compiler
+        // keeps a load behind every store before it: the residual of sub-tile row mi + 1 is loaded before row mi is stored.
+        // Written element by element, a lane's results took as many memory round trips one after the other (o projection of
+        // the 32B layer, 2048 rows: 165 us; ahead: 102).
+        f32x4 rbuf[2][D::NI];
+        const float* res = g.resid + col0 + 4 * lk;
+        float* out = g.out_f32 + col0 + 4 * lk;
+        auto load = [&](int mi) {
+            const int m = row0 + mi * 16;
+            const f32x4_a4* src = reinterpret_cast<const f32x4_a4*>(res + (size_t)(m < M ? m : M - 1) * N);
+#pragma unroll
+            for (int ni = 0; ni < D::NI; ++ni) rbuf[mi & 1][ni] = src[ni * 4];
+        };
+        load(0);
+#pragma unroll
+        for (int mi = 0; mi < D::MI; ++mi) {
+            if (mi + 1 < D::MI) load(mi + 1);
+            const int m = row0 + mi * 16;
+            if (m >= M) continue;
+            f32x4_a4* dst = reinterpret_cast<f32x4_a4*>(out + (size_t)m * N);
+#pragma unroll
+            for (int ni = 0; ni < D::NI; ++ni) dst[ni * 4] = rbuf[mi & 1][ni] + acc[mi][ni];
+        }
+    } else {  // EPI_SWIGLU: sub-tiles 4j, 4j+1 hold gate columns, 4j+2, 4j+3 the matching up columns; PAIRED order: a lane
+              // holds columns 8 lk .. 8 lk + 7 of the 32 that two sub-tiles make
+        static_assert(EPI != EPI_SWIGLU || D::NI % 4 == 0, "SwiGLU epilogue pairs 32-column blocks");
+        const int half_n = N / 2;
+        bf16_t* out = g.out_bf16 + col0 / 2 + 8 * lk;
+#pragma unroll
+        for (int mi = 0; mi < D::MI; ++mi) {
+            const int m = row0 + mi * 16;
+            if (m >= M) continue;
+            u32x4_a2* dst = reinterpret_cast<u32x4_a2*>(out + (size_t)m * half_n);
+#pragma unroll
+            for (int j = 0; j < D::NI / 4; ++j) {
+                float y[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float gt = acc[mi][4 * j + e / 4][e % 4], up = acc[mi][4 * j + 2 + e / 4][e % 4];
+                    y[e] = gt / (1.f + __expf(-gt)) * up;
+                }
+                u32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(y[2 * e], y[2 * e + 1]);
+                dst[j * 4] = w;
+            }
+        }
+    }
+}
+
+// The matrix instructions are inline assembly: the builtin has separate accumulator operands in and out, and the register
+// allocator fills the loop with moves between them.  The compiler therefore does not know the wait states between them and
+// what else touches their accumulators: 2 after a vector instruction wrote one, 11 before one reads it.  Every accumulator
+// passes through a statement behind the wait, so that no access can be placed before it.
+template <typename D>
+__device__ __forceinline__ void acc_fence(f32x4 (&acc)[D::MI][D::NI]) {
+    asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+#pragma unroll
+    for (int mi = 0; mi < D::MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < D::NI; ++ni) {
+            if constexpr (D::TWO) asm volatile("" : "+v"(acc[mi][ni]));
+            else asm volatile("" : "+a"(acc[mi][ni]));
+        }
+}
+
+template <int V>
+constexpr std::integral_constant<int, V> I{};
+
+// all but the last N loads of this wave have landed and its LDS reads are done; so are the other waves'
+template <int N>
+__device__ __forceinline__ void dma_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+template <int BM, int BN, int WM, int WN, int EPI>
+__device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem, const int M, const int tiles_m,
+                                         const int tiles_n, const int bid) {
+    using D = DmaTraits<BM, BN, WM, WN>;
+    constexpr int MH = D::MI / 2, NH = D::NI / 2, NS = D::NS;
+    constexpr bool PAIRED = EPI == EPI_SWIGLU;
+    const int K = g.K;
+    const TileCoord tc = map_block(bid, tiles_m, tiles_n, g.split);
+    const int m0 = tc.tm * BM, n0 = tc.tn * BN;
+    const int kbeg = tc.ks * g.kps;
+    const int kend = (kbeg + g.kps < K) ? (kbeg + g.kps) : K;
+    const int KT = (kend - kbeg) / BK;
+    const int tid = threadIdx.x;
+    if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
+        bool any = false;
+        for (int r = tid; r < BM; r += 256) any |= (m0 + r < M) && g.row_live[m0 + r] >= 0;
+        int* flag = reinterpret_cast<int*>(smem);
+        const bool wave_any = __builtin_amdgcn_ballot_w64(any) != 0;
+        if ((tid & 63) == 0) flag[tid >> 6] = wave_any;
+        __syncthreads();
+        int live = 0;
+#pragma unroll
+        for (int w = 0; w < 256 / 64; ++w) live |= flag[w];
+        if (!live) return;
+        __syncthreads();
+    }
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int lrow = lane & 15, lk = lane >> 4;
+
+    const unsigned row_bytes = (unsigned)K * 2u;
+    const int rows = M - m0 < BM ? M - m0 : BM;
+    auto rsrc = [&](const bf16_t* base, unsigned bytes) {
+        const unsigned long long p = reinterpret_cast<unsigned long long>(base);
+        return i32x4{__builtin_amdgcn_readfirstlane((int)(unsigned)p), __builtin_amdgcn_readfirstlane((int)(p >> 32)),
+                     __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+    };
+    i32x4 ra = rsrc(g.A + (size_t)m0 * K, (unsigned)rows * row_bytes);
+    i32x4 rb = rsrc(g.W + (size_t)n0 * K, (unsigned)BN * row_bytes);
+    // offsets of a lane's chunks: half slab row q -> tile row (q / (WT/2)) * WT + half * WT/2 + q % (WT/2)
+    unsigned va[2][D::LA], vb[2][D::LB];
+    {
+        const int qa = wave * D::QA, qb = wave * D::QB;
+        const int ta = qa / (D::WTM / 2) * D::WTM + qa % (D::WTM / 2), tb = qb / (D::WTN / 2) * D::WTN + qb % (D::WTN / 2);
+        const int r = lane >> 3, c = lane & 7;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < D::LA; ++i)
+                va[h][i] = (unsigned)(ta + h * D::WTM / 2 + 8 * i + r) * row_bytes + (c ^ dma_key<false>(qa + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
+#pragma unroll
+            for (int i = 0; i < D::LB; ++i)
+                vb[h][i] = (unsigned)(tb + h * D::WTN / 2 + 8 * i + r) * row_bytes + (c ^ dma_key<PAIRED>(qb + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
+        }
+    }
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    const unsigned lds_a = lds0 + wave * D::QA * 128, lds_b = lds0 + D::HA * 128 + wave * D::QB * 128;
+    // load i of half slab (kt, A rows ha, B rows hb) into the slot at byte `slot`
+    auto dma = [&](int i, int ha, int hb, unsigned slot, int koff) {
+        if (i < D::LA) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                         ::"s"(lds_a + slot + i * 1024), "v"(va[ha][i]), "s"(ra), "s"(koff));
+        } else if (D::QB % 8 == 0 || i - D::LA < D::LB - 1) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                         ::"s"(lds_b + slot + (i - D::LA) * 1024), "v"(vb[hb][i - D::LA]), "s"(rb), "s"(koff));
+        } else {   // four rows: the first 32 lanes
+            asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_hi, 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\ts_mov_b32 exec_hi, -1"
+                         ::"s"(lds_b + slot + (i - D::LA) * 1024), "v"(vb[hb][i - D::LA]), "s"(rb), "s"(koff));
+        }
+    };
+
+    f32x4 acc[D::MI][D::NI];
+#pragma unroll
+    for (int mi = 0; mi < D::MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < D::NI; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 fa[2][D::MI], fb[2][D::NI];   // [k-step of 32]
+    const u32x4* L = reinterpret_cast<const u32x4*>(smem);
+    const int key = (lrow >> 1) & 7;
+    const int src_a = (wm * (D::WTM / 2) + lrow) * CHUNKS;
+    const int src_b = (D::HA + wn * (D::WTN / 2) + (PAIRED ? 8 * (lrow >> 2) + (lrow & 3) : lrow)) * CHUNKS;
+    auto read_a = [&](int h, int i, unsigned slot) {   // i < 2 MH: k-step i / MH
+        const int kk = i / MH, mi = i % MH;
+        fa[kk][h * MH + mi] = __builtin_bit_cast(bf16x8, L[slot / 16 + src_a + mi * 16 * CHUNKS + ((lk + kk * 4) ^ key)]);
+    };
+    auto read_b = [&](int h, int i, unsigned slot) {
+        const int kk = i / NH, ni = i % NH, row = PAIRED ? ni / 2 * 32 + ni % 2 * 4 : ni * 16;
+        fb[kk][h * NH + ni] = __builtin_bit_cast(bf16x8, L[slot / 16 + src_b + row * CHUNKS + ((lk + kk * 4) ^ key)]);
+    };
+
+    // Products of a slab: four quadrants of the wave's tile, each with one new half of A or B:
+    //   even slabs   A0B0 | read B1,  A0B1 | read A1,  A1B1 | read the next slab's A0,  A1B0 | read its B1
+    //   odd slabs    A0B1 | read B0,  A0B0 | read A1,  A1B0 | read the next slab's A0,  A1B1 | read its B0
+    // Half slab p is what quadrants 2p - 2 and 2p - 1 read: A half p % 2 and B half (p ^ (p >> 1)) & 1 of slab p / 2.  While
+    // half slab p is multiplied, p + 1 is read and p + NS is loaded into the place of p.
+#pragma unroll
+    for (int p = 0; p < NS; ++p)
+#pragma unroll
+        for (int i = 0; i < D::LOADS; ++i) dma(i, p & 1, (p ^ (p >> 1)) & 1, p * D::SLOT, (p / 2 < KT ? p / 2 : KT - 1) * (BK * 2));
+    dma_barrier<(NS - 1) * D::LOADS>();
+#pragma unroll
+    for (int i = 0; i < 2 * MH; ++i) read_a(0, i, 0);
+#pragma unroll
+    for (int i = 0; i < 2 * NH; ++i) read_b(0, i, 0);
+    acc_fence<D>(acc);
+    dma_barrier<(NS - 2) * D::LOADS>();
+
+    unsigned rd = D::SLOT, wr = 0;   // places of half slabs p + 1 and p
+    // One quadrant: rows half ma times columns half nb, both k-steps.  Spread over the first three quarters of its matrix
+    // instructions, so that the barrier finds the reads done: the fragments of half rh of A or B, and loads [l0, l1) of half
+    // slab p + NS (halves ha, hb).
+    auto quadrant = [&](auto ma, auto nb, auto rd_a, auto rh, auto l0, auto l1, auto ha, auto hb, int koff) {
+        constexpr int NM = 2 * MH * NH, SPAN = NM * 3 / 4;
+        constexpr int NR = rd_a() ? 2 * MH : 2 * NH, NL = l1() - l0(), OPS = NR + NL;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const int kk = i / (MH * NH), nr = i % (MH * NH) / MH;
+            const int mi = ma() * MH + (nr & 1 ? MH - 1 - i % MH : i % MH), ni = nb() * NH + nr;
+            if constexpr (D::TWO)
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(fb[kk][ni]), "v"(fa[kk][mi]));
+            else
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[mi][ni]) : "v"(fb[kk][ni]), "v"(fa[kk][mi]));
+            const int j0 = i < SPAN ? i * OPS / SPAN : OPS, j1 = i + 1 < SPAN ? (i + 1) * OPS / SPAN : OPS;
+#pragma unroll
+            for (int j = j0; j < j1; ++j) {
+                const int nl = j * NL / OPS;   // loads among the operations before j
+                if ((j + 1) * NL / OPS > nl) dma(l0() + nl, ha(), hb(), wr, koff);
+                else if (rd_a()) read_a(rh(), j - nl, rd);
+                else read_b(rh(), j - nl, rd);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto next = [&](unsigned s) { return s + D::SLOT == NS * D::SLOT ? 0u : s + D::SLOT; };
+    auto half_end = [&]() {
+        dma_barrier<(NS - 2) * D::LOADS>();
+        __builtin_amdgcn_sched_barrier(0);
+        wr = rd;
+        rd = next(rd);
+    };
+    // loads of half slab p + NS: slab (p + NS) / 2, the last one again in the tail
+    auto slab = [&](auto parity, int kt) {
+        constexpr int B = decltype(parity)::value;   // the columns half this slab begins with
+        constexpr int P0 = 2 * B, P1 = 2 * B + 1;    // p modulo 4
+        constexpr int N0 = (P0 + NS) & 3, N1 = (P1 + NS) & 3;
+        const int k0 = kt + NS / 2, k1 = kt + (1 + NS) / 2;
+        const int o0 = (k0 < KT ? k0 : KT - 1) * (BK * 2), o1 = (k1 < KT ? k1 : KT - 1) * (BK * 2);
+        constexpr int LH = D::LOADS / 2, H0 = (N0 ^ (N0 >> 1)) & 1, H1 = (N1 ^ (N1 >> 1)) & 1;
+        quadrant(I<0>, I<B>, I<0>, I<B ^ 1>, I<0>, I<LH>, I<(N0 & 1)>, I<H0>, o0);
+        quadrant(I<0>, I<B ^ 1>, I<1>, I<1>, I<LH>, I<D::LOADS>, I<(N0 & 1)>, I<H0>, o0);
+        half_end();
+        quadrant(I<1>, I<B ^ 1>, I<1>, I<0>, I<0>, I<LH>, I<(N1 & 1)>, I<H1>, o1);
+        quadrant(I<1>, I<B>, I<0>, I<B ^ 1>, I<LH>, I<D::LOADS>, I<(N1 & 1)>, I<H1>, o1);
+        half_end();
+    };
+    for (int kt = 0;;) {
+        slab(I<0>, kt);
+        if (++kt >= KT) break;
+        slab(I<1>, kt);
+        if (++kt >= KT) break;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load may land after this workgroup's LDS is another's
+    acc_fence<D>(acc);
+    store_dma_tile<D, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
+}
+
 // Rows past *n_live are padding: the tiles of the rows before them are dealt out as if there were no others.  (Tiles of all
 // M rows, the dead ones returning at once, leave whole XCDs idle, since each takes a contiguous range: gate/up of a
 // 4096-row graph with 2776 live rows 1880 us, this way 1390.)
@@ -435,6 +722,14 @@ __global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIM
         if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
     }
     gemm_tile<BM, BN, WM, WN, EPI, WS, STREAM>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x, late_live);
+}
+
+template <int BM, int BN, int WM, int WN, int EPI>
+__global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void dma_kernel(const GemmArgs g) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int M = live_rows(g), tiles_m = (M + BM - 1) / BM;
+    if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
+    dma_tile<BM, BN, WM, WN, EPI>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x);
 }
 
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
@@ -464,9 +759,9 @@ __global__ __launch_bounds__(256, 1) void gemm_width_kernel(const GemmArgs g, co
     }
     const int tiles_n = g.N / width[pick];
     if ((int)blockIdx.x >= tiles_m * tiles_n) return;
-    if (pick == 0) gemm_tile<256, W, 4, 1, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
-    else if (pick == 1) gemm_tile<256, 256, 2, 2, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
-    else gemm_tile<256, 128, 2, 2, EPI, 2, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    if (pick == 0) dma_tile<256, W, 4, 1, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+    else if (pick == 1) dma_tile<256, 256, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+    else dma_tile<256, 128, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
@@ -481,6 +776,20 @@ int launch_tile(const GemmArgs& a, hipStream_t s) {
     }
     const int grid = a.tiles_m * a.tiles_n * a.split;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(T::NT), T::LDS_BYTES, s, a);
+    LAPS_LAUNCH_CHECK();
+    return LAPS_OK;
+}
+
+template <int BM, int BN, int WM, int WN, int EPI>
+int launch_dma(const GemmArgs& a, hipStream_t s) {
+    constexpr int lds = DmaTraits<BM, BN, WM, WN>::LDS;
+    auto kern = dma_kernel<BM, BN, WM, WN, EPI>;
+    static bool attr_set = false;  // as in launch_tile
+    if (!attr_set) {
+        LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n * a.split), dim3(256), lds, s, a);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -510,7 +819,8 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 template <int W, int EPI>
 int launch_width(const GemmArgs& a, hipStream_t s) {
     constexpr int cfg[3] = {W == 160 ? 4 : 3, 2, 8};
-    constexpr int lds = Traits<256, 256, 2, 2>::LDS_BYTES;
+    constexpr int lds_w = DmaTraits<256, W, 4, 1>::LDS, lds_256 = DmaTraits<256, 256, 2, 2>::LDS, lds_128 = DmaTraits<256, 128, 2, 2>::LDS;
+    constexpr int lds = lds_w > lds_256 ? (lds_w > lds_128 ? lds_w : lds_128) : (lds_256 > lds_128 ? lds_256 : lds_128);
     auto kern = gemm_width_kernel<W, EPI>;
     static bool attr_set = false;  // as in launch_tile
     if (!attr_set) {
@@ -713,6 +1023,24 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     const bool alone = row_live == nullptr && n_live == nullptr;
     const bool cached = alone && m > (p.k_per_split < 32 * BK ? 16 : 48) && p.split > 1 && kTiles[p.cfg].bn < 256;
     const bool bypass = g.tiles_m == 1 && !cached;
+#define LAPS_DMA_CASE(cfg, ...)                                                                     \
+    case cfg:                                                                                       \
+        if (p.epi == EPI_PARTIAL) return launch_dma<__VA_ARGS__, EPI_PARTIAL>(g, s);                \
+        if (p.epi == EPI_RESID) return launch_dma<__VA_ARGS__, EPI_RESID>(g, s);                    \
+        if constexpr (DmaTraits<__VA_ARGS__>::NI % 4 == 0 && (DmaTraits<__VA_ARGS__>::NI / 2) % 2 == 0) \
+            return launch_dma<__VA_ARGS__, EPI_SWIGLU>(g, s);                                       \
+        break
+    if (k < kMaxBufferK) switch (p.cfg) {
+        LAPS_DMA_CASE(2, 256, 256, 2, 2);
+        LAPS_DMA_CASE(3, 256, 224, 4, 1);
+        LAPS_DMA_CASE(4, 256, 160, 4, 1);
+        LAPS_DMA_CASE(6, 192, 256, 2, 2);
+        LAPS_DMA_CASE(7, 192, 128, 2, 2);
+        LAPS_DMA_CASE(8, 256, 128, 2, 2);
+        LAPS_DMA_CASE(9, 256, 192, 4, 1);
+        default: break;
+    }
+#undef LAPS_DMA_CASE
 #define LAPS_TILE_CASE(cfg, BM, BN, WM, WN, EPI, WS) \
     case ((cfg) * 4 + (EPI)) * 8 + (WS):             \
         if (skinny_loads<BM, BN, WS> && bypass) return launch_tile<BM, BN, WM, WN, EPI, WS, skinny_loads<BM, BN, WS>>(g, s); \
@@ -728,26 +1056,6 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_PARTIAL, 2);
         LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_RESID, 1);
         LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_RESID, 2);
-        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_RESID, 1);
-        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_RESID, 2);
-        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_RESID, 1);
-        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_RESID, 2);
-        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(2, 256, 256, 2, 2, EPI_SWIGLU, 2);
-        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(9, 256, 192, 4, 1, EPI_SWIGLU, 2);
-        LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_RESID, 1);
-        LAPS_TILE_CASE(3, 256, 224, 4, 1, EPI_RESID, 2);
-        LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_RESID, 1);
-        LAPS_TILE_CASE(4, 256, 160, 4, 1, EPI_RESID, 2);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_PARTIAL, 1);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_PARTIAL, 2);
         LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_RESID, 1);
@@ -763,12 +1071,6 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_PARTIAL, 1);
         LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_RESID, 1);
         LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_RESID, 1);
-        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_RESID, 2);
-        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(8, 256, 128, 2, 2, EPI_SWIGLU, 2);
         default: break;
     }
 #undef LAPS_TILE_CASE
