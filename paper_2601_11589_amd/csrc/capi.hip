@@ -113,7 +113,7 @@ static size_t split_bytes_for(const laps_model_cfg& c, int m) {
                              {c.hidden, c.intermediate, EPI_RESID, 1}, {c.hidden, c.intermediate, EPI_RESID, 0}};
     size_t b = 0;
     for (const auto& p : shape) {
-        const GemmPlan g = laps_gemm_plan(m, p[0], p[1], 0, p[2], partial_cap_for(c, m), p[3] != 0);
+        const GemmPlan g = laps_gemm_plan(m, p[0], p[1], 0, p[2], partial_cap_for(c, m), p[3] != 0, true);
         const size_t t = (size_t)g.split * m * p[0] * sizeof(float);
         b = t > b ? t : b;
     }
@@ -304,7 +304,7 @@ struct BatchDesc {
 static int run_gemm(laps_ctx* c, int cls, bool capturing, const bf16_t* a, const bf16_t* w, int m, int n, int k,
                     int want, bool row_kernel, float* partial, size_t partial_cap, float* out_f32, const float* resid, bf16_t* out_bf16,
                     const int* row_live, const int* n_live, bool live_varies, GemmPlan* plan, hipStream_t s) {
-    const GemmPlan p = laps_gemm_plan(m, n, k, 0, want, partial_cap, row_kernel);
+    const GemmPlan p = laps_gemm_plan(m, n, k, 0, want, partial_cap, row_kernel, true);
     *plan = p;
     ProfScope ps(c, s, cls, capturing);
     if (p.epi == EPI_PARTIAL) return laps_gemm_launch(p, a, w, m, n, k, partial, nullptr, nullptr, row_live, n_live, live_varies, s);

@@ -10,7 +10,7 @@
 //  * 128 rows (gemm_tile, v_mfma_f32_32x32x16_bf16): bound by what a compute unit takes in.  Slabs go HBM -> registers ->
 //    LDS, so that padding rows can be left out lane by lane and weights can bypass the caches.  Also the tiles of rows of
 //    2^22 values and more, which 32-bit offsets do not reach.
-//  * 192 and 256 rows (dma_tile, v_mfma_f32_16x16x32_bf16): bound by the power that the matrix cores and the operands' way
+//  * 192 to 320 rows (dma_tile, v_mfma_f32_16x16x32_bf16): bound by the power that the matrix cores and the operands' way
 //    to them draw on real data, so both are chosen for that.
 //
 // gemm_tile's K loop is software-pipelined by hand:
@@ -400,7 +400,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     store_tile<T, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
-// ------------------------------------------------------------------ tiles of 192 and 256 rows
+// ------------------------------------------------------------------ tiles of 192 to 320 rows
 // What bounds them on real data is power: the same kernel runs 1.15 times as fast on zeros.  Measured on normal(0, 1) x
 // normal(0, 0.02) operands:
 //  * v_mfma_f32_16x16x32_bf16 draws less than v_mfma_f32_32x32x16_bf16 (half the accumulator traffic per flop): 2.0-2.1
@@ -422,6 +422,9 @@ struct DmaTraits {
     static constexpr int LOADS = LA + LB;
     static constexpr int SLOT = (HA + HB) * BK * 2;                      // bytes
     static constexpr bool TWO = BM * BN <= 192 * 128;                    // two workgroups on a compute unit
+    // One workgroup per unit: accumulators in the half of the registers that only matrix instructions compute in, and past
+    // that half (320 x 256) in the other.
+    static constexpr __host__ __device__ bool in_vgpr(int mi, int ni) { return TWO || mi * NI + ni >= 64; }
     static constexpr int CAP = (TWO ? 80 : 160) * 1024;
     static constexpr int NS = CAP / SLOT < 6 ? CAP / SLOT : 6;           // half slabs in LDS
     static constexpr int LDS = NS * SLOT;
@@ -521,7 +524,7 @@ __device__ __forceinline__ void acc_fence(f32x4 (&acc)[D::MI][D::NI]) {
     for (int mi = 0; mi < D::MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < D::NI; ++ni) {
-            if constexpr (D::TWO) asm volatile("" : "+v"(acc[mi][ni]));
+            if (D::in_vgpr(mi, ni)) asm volatile("" : "+v"(acc[mi][ni]));
             else asm volatile("" : "+a"(acc[mi][ni]));
         }
 }
@@ -574,21 +577,27 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
     };
     i32x4 ra = rsrc(g.A + (size_t)m0 * K, (unsigned)rows * row_bytes);
     i32x4 rb = rsrc(g.W + (size_t)n0 * K, (unsigned)BN * row_bytes);
-    // offsets of a lane's chunks: half slab row q -> tile row (q / (WT/2)) * WT + half * WT/2 + q % (WT/2)
-    unsigned va[2][D::LA], vb[2][D::LB];
+    // Offsets of a lane's chunks: half slab row q -> tile row (q / (WT/2)) * WT + half * WT/2 + q % (WT/2).  Rows of A past the
+    // last one lie behind the descriptor's end, so each has an offset of its own.  On 320 x 256 there are no registers for as
+    // many of B: the rows that share a key share one there, and the scalar offset moves it (a 256-row graph of the 7B layer is
+    // 2.5 % slower where all tiles do that).
+    constexpr bool SHARE = BM > 256;
+    constexpr int KEYS = SHARE ? (PAIRED ? 4 : 2) : D::LB;
+    unsigned va[2][D::LA], vb[SHARE ? 1 : 2][KEYS];
     {
         const int qa = wave * D::QA, qb = wave * D::QB;
         const int ta = qa / (D::WTM / 2) * D::WTM + qa % (D::WTM / 2), tb = qb / (D::WTN / 2) * D::WTN + qb % (D::WTN / 2);
         const int r = lane >> 3, c = lane & 7;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int i = 0; i < D::LA; ++i)
                 va[h][i] = (unsigned)(ta + h * D::WTM / 2 + 8 * i + r) * row_bytes + (c ^ dma_key<false>(qa + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
 #pragma unroll
-            for (int i = 0; i < D::LB; ++i)
-                vb[h][i] = (unsigned)(tb + h * D::WTN / 2 + 8 * i + r) * row_bytes + (c ^ dma_key<PAIRED>(qb + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
-        }
+        for (int h = 0; h < (SHARE ? 1 : 2); ++h)
+#pragma unroll
+            for (int i = 0; i < KEYS; ++i)
+                vb[h][i] = (unsigned)(tb + r + (SHARE ? 0 : h * D::WTN / 2 + 8 * i)) * row_bytes + (c ^ dma_key<PAIRED>(qb + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
     }
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const unsigned lds_a = lds0 + wave * D::QA * 128, lds_b = lds0 + D::HA * 128 + wave * D::QB * 128;
@@ -597,13 +606,16 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         if (i < D::LA) {
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                          ::"s"(lds_a + slot + i * 1024), "v"(va[ha][i]), "s"(ra), "s"(koff));
-        } else if (D::QB % 8 == 0 || i - D::LA < D::LB - 1) {
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                         ::"s"(lds_b + slot + (i - D::LA) * 1024), "v"(vb[hb][i - D::LA]), "s"(rb), "s"(koff));
-        } else {   // four rows: the first 32 lanes
-            asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_hi, 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\ts_mov_b32 exec_hi, -1"
-                         ::"s"(lds_b + slot + (i - D::LA) * 1024), "v"(vb[hb][i - D::LA]), "s"(rb), "s"(koff));
+            return;
         }
+        const int j = i - D::LA, off = SHARE ? koff + (hb * (D::WTN / 2) + 8 * j) * (int)row_bytes : koff;
+        const unsigned lane_off = vb[SHARE ? 0 : hb][j % KEYS];
+        if (D::QB % 8 == 0 || j < D::LB - 1)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                         ::"s"(lds_b + slot + j * 1024), "v"(lane_off), "s"(rb), "s"(off));
+        else   // four rows: the first 32 lanes
+            asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_hi, 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\ts_mov_b32 exec_hi, -1"
+                         ::"s"(lds_b + slot + j * 1024), "v"(lane_off), "s"(rb), "s"(off));
     };
 
     f32x4 acc[D::MI][D::NI];
@@ -653,7 +665,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         for (int i = 0; i < NM; ++i) {
             const int kk = i / (MH * NH), nr = i % (MH * NH) / MH;
             const int mi = ma() * MH + (nr & 1 ? MH - 1 - i % MH : i % MH), ni = nb() * NH + nr;
-            if constexpr (D::TWO)
+            if (D::in_vgpr(mi, ni))
                 asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[mi][ni]) : "v"(fb[kk][ni]), "v"(fa[kk][mi]));
             else
                 asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[mi][ni]) : "v"(fb[kk][ni]), "v"(fa[kk][mi]));
@@ -674,6 +686,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         __builtin_amdgcn_sched_barrier(0);
         wr = rd;
         rd = next(rd);
+        if (SHARE) asm volatile("" : "+s"(rd), "+s"(wr));   // one address per operand and k-step, not one for every place of the ring
     };
     // loads of half slab p + NS: slab (p + NS) / 2, the last one again in the tail
     auto slab = [&](auto parity, int kt) {
@@ -734,34 +747,41 @@ __global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void
 
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
 // 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 220
-// of 256 x 256 take one: 997 against 700 us).  Widths WN_ (160 or 224), 256 and 128 are therefore one kernel, which takes
-// the width that the cost model gives the live rows; every workgroup comes to the same choice.  Built for raw sums and the
-// residual epilogue of N divisible by 160 (5120) or 224 (7168, 3584); SwiGLU and other N (7B q/k/v, 4608) keep the tile
-// planned for all rows.
-struct WidthCost {
-    float fill[3], slabs[3], part[3];   // as TileDef, slabs = time of all K slabs on a full chip
+// of 256 x 256 take one: 997 against 700 us).  Four tiles are therefore one kernel, which takes the one that the cost model
+// gives the live rows; every workgroup comes to the same choice.  First tile: 256 x W, W = 160 (N = 5120), 224 (7168, 3584)
+// or 192 (55296, 27648, 4608); none for 7B gate/up (37888), and other N keep the tile planned for all rows.  q/k/v of 2776 rows on
+// 320 x 256 (252 tiles, one round) 152 us, on 256 x 224 (352) 198; gate/up 1141 on 320 x 256 and 1178 on 256 x 256.
+constexpr int kLiveTiles = 4;
+struct LiveCost {
+    float fill[kLiveTiles], slabs[kLiveTiles], part[kLiveTiles];   // as TileDef, slabs = time of all K slabs on a full chip
 };
 template <int W, int EPI>
-__global__ __launch_bounds__(256, 1) void gemm_width_kernel(const GemmArgs g, const WidthCost c) {
+__global__ __launch_bounds__(256, 1) void gemm_live_kernel(const GemmArgs g, const LiveCost c) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int M = live_rows(g);
     if (M <= 0) return;
-    const int tiles_m = (M + 255) / 256;
-    constexpr int width[3] = {W, 256, 128};
-    int pick = 0;
+    constexpr int rows[kLiveTiles] = {256, 256, 256, 320}, cols[kLiveTiles] = {W == 0 ? 256 : W, 256, 128, 256};
+    constexpr int first = W == 0 ? 1 : 0;
+    int pick = first;
     float best = 0.f;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int tiles = tiles_m * (g.N / width[i]);
+    for (int i = first; i < kLiveTiles; ++i) {
+        const int tiles = (M + rows[i] - 1) / rows[i] * (g.N / cols[i]);
         const float spare = tiles < 256 ? 1.f - tiles / 256.f : 0.f;
         const float us = (float)((tiles + 255) / 256) * (c.fill[i] + c.slabs[i] * (1.f - c.part[i] * spare));
-        if (i == 0 || us < best) best = us, pick = i;
+        if (i == first || us < best) best = us, pick = i;
     }
-    const int tiles_n = g.N / width[pick];
+    const int tiles_m = (M + rows[pick] - 1) / rows[pick], tiles_n = g.N / cols[pick];
     if ((int)blockIdx.x >= tiles_m * tiles_n) return;
-    if (pick == 0) dma_tile<256, W, 4, 1, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
-    else if (pick == 1) dma_tile<256, 256, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
-    else dma_tile<256, 128, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+    if constexpr (W > 0) {
+        if (pick == 0) {
+            dma_tile<256, W, 4, 1, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+            return;
+        }
+    }
+    if (pick == 1) dma_tile<256, 256, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+    else if (pick == 2) dma_tile<256, 128, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+    else dma_tile<320, 256, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
@@ -813,27 +833,30 @@ constexpr TileDef kTiles[] = {
     {192, 128, 1, 1.81, 0.716, 0.09},  // 7: 4 waves of 96x64, two workgroups per compute unit
     {256, 128, 2, 3.01, 0.863, 0.25},  // 8: 4 waves of 128x64
     {256, 192, 2, 2.93, 1.199, 0.31},  // 9: 4 waves of 64x192 (N = 55296, 27648, 4608)
+    {320, 256, 1, 6.83, 1.597, 0.11},  // 10: 4 waves of 160x128, inside layers; fitted to 400 launches against the others
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 template <int W, int EPI>
-int launch_width(const GemmArgs& a, hipStream_t s) {
-    constexpr int cfg[3] = {W == 160 ? 4 : 3, 2, 8};
-    constexpr int lds_w = DmaTraits<256, W, 4, 1>::LDS, lds_256 = DmaTraits<256, 256, 2, 2>::LDS, lds_128 = DmaTraits<256, 128, 2, 2>::LDS;
-    constexpr int lds = lds_w > lds_256 ? (lds_w > lds_128 ? lds_w : lds_128) : (lds_256 > lds_128 ? lds_256 : lds_128);
-    auto kern = gemm_width_kernel<W, EPI>;
+int launch_live(const GemmArgs& a, hipStream_t s) {
+    constexpr int cfg[kLiveTiles] = {W == 160 ? 4 : W == 224 ? 3 : W == 192 ? 9 : 2, 2, 8, 10};
+    constexpr int lds_of[kLiveTiles] = {DmaTraits<256, W == 0 ? 128 : W, 4, 1>::LDS, DmaTraits<256, 256, 2, 2>::LDS, DmaTraits<256, 128, 2, 2>::LDS,
+                                        DmaTraits<320, 256, 2, 2>::LDS};
+    int lds = 0;
+    for (int b : lds_of) lds = b > lds ? b : lds;
+    auto kern = gemm_live_kernel<W, EPI>;
     static bool attr_set = false;  // as in launch_tile
     if (!attr_set) {
         LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         attr_set = true;
     }
-    WidthCost c;
-    for (int i = 0; i < 3; ++i) {
+    LiveCost c;
+    for (int i = 0; i < kLiveTiles; ++i) {
         c.fill[i] = (float)kTiles[cfg[i]].fill;
         c.slabs[i] = (float)(kTiles[cfg[i]].slab * (a.K / BK));
         c.part[i] = (float)kTiles[cfg[i]].part;
     }
-    hipLaunchKernelGGL(kern, dim3((a.M + 255) / 256 * (a.N / 128)), dim3(256), lds, s, a, c);
+    hipLaunchKernelGGL(kern, dim3((a.M + 255) / 256 * (a.N / 128)), dim3(256), lds, s, a, c);   // the most tiles of any choice
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -846,7 +869,7 @@ void laps_gemm_tile_dims(int cfg, int* bm, int* bn) {
 }
 
 // Picks tile shape and K split.
-GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap, bool row_kernel) {
+GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap, bool row_kernel, bool layer) {
     GemmPlan p;
     const int ksteps = k / BK;
     const bool far = k >= kMaxBufferK;   // rows that only the pointer-addressed tiles (1, 6, 7) reach
@@ -928,6 +951,11 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
         const int tiles_m = (m + t.bm - 1) / t.bm;
         if (t.bm == 192 && tiles_m != (m + 255) / 256 && !far) continue;   // 192 rows where they need no more row tiles than 256
+        // 320 rows where they need fewer row tiles than 256.  They take in and read from LDS a tenth less per product: 32B
+        // gate/up of 280, 640 and 11104 rows 194 -> 156, 334 -> 285 and 4582 -> 4379 us, down of 11104 rows 2405 -> 2238, q/k/v
+        // of 1280 rows in two slices 99 -> 76; 206 products of 7B, 14B and 32B at 27 row counts 3 % in the mean.  Not for a
+        // product of its own, whose tile laps_gemm_plan_info reports: 256 rows at most.
+        if (t.bm == 320 && (!layer || tiles_m == (m + 255) / 256)) continue;
         const int max_split = force_split > 0 ? force_split : (far ? 256 : 16);   // a few column tiles have to fill the chip
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
             const double partial = 4.0 * s * mn;
@@ -1004,12 +1032,15 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     g.out_bf16 = out_bf16;
     g.row_live = row_live;
     g.n_live = n_live;
-    // batches of an unknown number of live rows, un-split plans of the 256-row class: the width is chosen on the device
-    if (live_varies && n_live && m > 256 && p.split == 1 && kTiles[p.cfg].bm == 256 && n % 256 == 0 && k % (2 * BK) == 0) {
-        if (n % 160 == 0 && p.epi == EPI_PARTIAL) return launch_width<160, EPI_PARTIAL>(g, s);
-        if (n % 160 == 0 && p.epi == EPI_RESID) return launch_width<160, EPI_RESID>(g, s);
-        if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_width<224, EPI_PARTIAL>(g, s);
-        if (n % 224 == 0 && p.epi == EPI_RESID) return launch_width<224, EPI_RESID>(g, s);
+    // batches of an unknown number of live rows, un-split plans of the 256- and 320-row tiles: chosen on the device
+    if (live_varies && n_live && m > 256 && p.split == 1 && kTiles[p.cfg].bm >= 256 && n % 256 == 0) {
+        if (n % 160 == 0 && p.epi == EPI_PARTIAL) return launch_live<160, EPI_PARTIAL>(g, s);
+        if (n % 160 == 0 && p.epi == EPI_RESID) return launch_live<160, EPI_RESID>(g, s);
+        if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_live<224, EPI_PARTIAL>(g, s);
+        if (n % 224 == 0 && p.epi == EPI_RESID) return launch_live<224, EPI_RESID>(g, s);
+        if (n % 192 == 0 && p.epi == EPI_PARTIAL) return launch_live<192, EPI_PARTIAL>(g, s);
+        if (n % 192 == 0 && p.epi == EPI_SWIGLU) return launch_live<192, EPI_SWIGLU>(g, s);
+        if (p.epi == EPI_SWIGLU) return launch_live<0, EPI_SWIGLU>(g, s);
     }
     // Weights that one row tile reads alone bypass the caches.  Above a few rows the K slices of the 64- and 128-column
     // tiles wait on the memory less with cached loads: 14B o, 16-slab slices, on its own with weights cold / warm (in the
@@ -1038,6 +1069,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         LAPS_DMA_CASE(7, 192, 128, 2, 2);
         LAPS_DMA_CASE(8, 256, 128, 2, 2);
         LAPS_DMA_CASE(9, 256, 192, 4, 1);
+        LAPS_DMA_CASE(10, 320, 256, 2, 2);
         default: break;
     }
 #undef LAPS_DMA_CASE

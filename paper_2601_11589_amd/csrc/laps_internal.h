@@ -58,9 +58,10 @@ struct GemmPlan {
 // passes what its workspace holds if that is less).
 // row_kernel: a row kernel follows whether K is split or not and would add the slices as well: in a layer the RMSNorm
 // behind a residual projection, or the kernel that takes raw sums.  False for a product of its own.
+// layer: a projection inside a layer, which may take every tile.
 constexpr size_t LAPS_PARTIAL_CAP = (size_t)256 << 20;
 GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size_t partial_cap = LAPS_PARTIAL_CAP,
-                        bool row_kernel = false);
+                        bool row_kernel = false, bool layer = false);
 size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap);
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // rows and columns of tile shape `cfg` (0, 0 if unknown)
 // row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified:

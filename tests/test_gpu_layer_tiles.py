@@ -1,0 +1,97 @@
+"""The GEMM launches that only a layer makes, called directly: the 320 x 256 tile, at the edges of its rows and with K slices
+of an odd and an even number of slabs, and the launch of a captured graph that chooses its tile by the live rows.  Against
+float64, with rows of NaN behind the operand and guard rows behind the result."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2601_11589_amd import api
+
+PARTIAL, RESID, SWIGLU = 0, 1, 2
+TILE_320 = 10
+
+
+class Plan(C.Structure):
+    _fields_ = [("cfg", C.c_int), ("split", C.c_int), ("k_per_split", C.c_int), ("epi", C.c_int), ("ws", C.c_int)]
+
+
+def layer_plan(m, n, k, epi, row_kernel):
+    f = api.lib()._Z14laps_gemm_planiiiiimbb
+    f.restype = Plan
+    return f(C.c_int(m), C.c_int(n), C.c_int(k), C.c_int(0), C.c_int(epi), C.c_size_t(256 << 20), C.c_bool(row_kernel), C.c_bool(True))
+
+
+def launch(plan, a, w, m, out, resid, act, live=None):
+    p = lambda t: C.c_void_p(t.data_ptr() if t is not None else 0)
+    rc = api.lib()._Z16laps_gemm_launchRK8GemmPlanPKtS3_iiiPfPKfPtPKiS9_bP12ihipStream_t(
+        C.byref(plan), p(a), p(w), C.c_int(m), C.c_int(w.shape[0]), C.c_int(w.shape[1]), p(out), p(resid), p(act), None, p(live),
+        C.c_bool(live is not None), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, api.lib().laps_last_error()
+
+
+def test_wide_rows_are_planned_in_layers_only():
+    """In a layer where 320 rows save a row tile; a product of its own is reported with 256 rows at most."""
+    for m, n, k, epi in ((300, 55296, 5120, SWIGLU), (640, 55296, 5120, SWIGLU), (11104, 5120, 27648, RESID), (1280, 7168, 5120, PARTIAL)):
+        assert layer_plan(m, n, k, epi, epi != SWIGLU).cfg == TILE_320, (m, n, k)
+        out = (C.c_int32 * 7)()
+        assert api.lib().laps_gemm_plan_info(C.c_int32(m), C.c_int32(n), C.c_int32(k), C.c_int32(0), C.c_int32(epi), out) == 0
+        assert out[0] <= 256
+    for m in (129, 256, 400, 512, 1000):      # no fewer row tiles, or most of the last one padding
+        assert layer_plan(m, 55296, 5120, SWIGLU, False).cfg != TILE_320, m
+
+
+def run(plan, m, n, k, live=None, rows=None):
+    """Runs one product of `rows` checked rows (default all m) and compares it with float64."""
+    rows = m if rows is None else rows
+    g = torch.Generator(device="cuda").manual_seed(m * 31 + n + k + rows)
+    a = torch.full((m + 7, k), float("nan"), dtype=torch.bfloat16, device="cuda")
+    a[:rows].normal_(0, 1, generator=g)
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=g)
+    want = a[:rows].double() @ w.double().T
+    out = torch.full((plan.split * m + 7, n), 7.0, device="cuda")
+    act = torch.full((m + 7, n // 2), 7.0, dtype=torch.bfloat16, device="cuda")
+    resid = None
+    if plan.epi == RESID:
+        resid = torch.empty((m, n), device="cuda").normal_(0, 4, generator=g)
+    launch(plan, a, w, m, out, resid, act, live)
+    torch.cuda.synchronize()
+    assert bool((out[plan.split * m:] == 7).all()) and bool((act[m:] == 7).all())
+    if plan.epi == SWIGLU:
+        gate, up = want.view(rows, n // 64, 2, 32).unbind(2)
+        ref = (torch.nn.functional.silu(gate) * up).reshape(rows, n // 2)
+        # one bf16 rounding (at most 2^-8 of the value) of fp32 sums of k products, std 0.02 sqrt(k), which take k / 32
+        # roundings of 2^-24 in a random walk: six standard deviations are delta; silu' is below 1.1
+        delta = 6 * 2.0 ** -24 * 0.02 * k / 4
+        slack = (delta * (1.1 * up.abs() + gate.abs())).reshape(rows, n // 2) + 1e-6
+        assert bool(((act[:rows].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all())
+        return
+    got = out[:plan.split * m].view(plan.split, m, n)[:, :rows].double().sum(0)
+    ref = want if resid is None else want + resid[:rows].double()
+    if rows:
+        assert float((got - ref).norm() / ref.norm()) < 2e-6       # fp32 sums of exact products
+        assert float((got - ref).abs().max()) < 2e-5 * float(ref.abs().max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m", [1, 160, 319, 320, 321, 657])
+@pytest.mark.parametrize("k,split", [(64, 1), (192, 1), (1024, 1), (448, 2), (1024, 4)])
+def test_320_row_tile_matches_float64(m, k, split):
+    for epi in (PARTIAL,) if split > 1 else (PARTIAL, RESID, SWIGLU):
+        per = -(-(k // 64) // split) * 64
+        run(Plan(TILE_320, split, per, epi, 1), m, 512, k)
+
+
+# every width with its first tile: 160, 224, 192 and none
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,epi", [(5120, PARTIAL), (5120, RESID), (7168, PARTIAL), (3584, RESID), (4608, PARTIAL), (27648, SWIGLU), (37888, SWIGLU)])
+def test_tile_by_live_rows_matches_float64(n, epi):
+    for m, k in ((640, 320), (1024, 2048)):
+        for rows in (1, 130, 256, 300, 513, 640):
+            run(Plan(2, 1, k, epi, 1), m, n, k, torch.tensor([rows], dtype=torch.int32, device="cuda"), rows)
+        run(Plan(TILE_320, 1, k, epi, 1), m, n, k, torch.tensor([m + 9], dtype=torch.int32, device="cuda"))
+        none = Plan(2, 1, k, epi, 1)
+        out, act = torch.full((m, n), 7.0, device="cuda"), torch.full((m, n // 2), 7.0, dtype=torch.bfloat16, device="cuda")
+        a, w = torch.zeros((m, k), dtype=torch.bfloat16, device="cuda"), torch.zeros((n, k), dtype=torch.bfloat16, device="cuda")
+        launch(none, a, w, m, out, out if epi == RESID else None, act, torch.tensor([0], dtype=torch.int32, device="cuda"))
+        assert bool((out == 7).all()) and bool((act == 7).all())
