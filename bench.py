@@ -615,7 +615,7 @@ def main():
                    "batches_per_step": short["n_batches"]},
         "latency_ms": {"p50": short["latency_ms_p50"], "p90": short["latency_ms_p90"]},
         # the dominant kernel: the gate/up projection with the fused SwiGLU epilogue on the streaming tile
-        "roofline": {"bound": "hbm", "kernel": "gemm_kernel<128,256,2,4,2,2,true> (gate/up + SwiGLU)",
+        "roofline": {"bound": "hbm", "kernel": "dma_kernel<128,256,1,4,2,true> (gate/up + SwiGLU)",
                      "achieved": gu["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gu["GBps"] / HBM_PEAK_GBS,
                      "traffic": traffic, "avg_launch_us": gu["avg_us"], "bytes_per_launch": gu["bytes_per_launch"],
                      "launches": gu["launches"]},

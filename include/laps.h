@@ -216,7 +216,7 @@ int laps_prefill_stack_static(laps_ctx* ctx, const laps_layer_weights* w, int32_
  * epilogue 0 = plain sums, 1 = residual add, 2 = SwiGLU, and split_k as in laps_gemm_bf16 (0 = automatic).  Inside a layer,
  * where a row kernel follows, the driver may split K otherwise.
  * out[7] = { tile rows, tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
- * split), slabs kept in flight per workgroup, workgroups }.
+ * split), slabs of 64 that every K slice holds a multiple of, workgroups }.
  * laps_attn_plan_info: the attention launch of a batch shape (n_tokens rows, n_seq sequences, page tables
  * max_pages wide).  out[6] = { query rows per workgroup, bound on the (sequence, row block) work items,
  * key-range splits (1 = none), fewest 64-key tiles a split is given, bytes of the work-item table, bytes of

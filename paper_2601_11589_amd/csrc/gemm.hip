@@ -7,13 +7,11 @@
 // 16-byte read.  A workgroup owns a BM x BN output tile and one K slice, and walks it in slabs of 64.
 //
 // Two kinds of tile:
-//  * 128 rows (gemm_tile, v_mfma_f32_32x32x16_bf16): bound by what a compute unit takes in.  Slabs go HBM -> registers ->
-//    LDS, so that padding rows can be left out lane by lane and weights can bypass the caches.  Also the tiles of rows of
-//    2^22 values and more, which 32-bit offsets do not reach.
-//  * 192 to 320 rows (dma_tile, v_mfma_f32_16x16x32_bf16): bound by the power that the matrix cores and the operands' way
-//    to them draw on real data, so both are chosen for that.
+//  * dma_tile (v_mfma_f32_16x16x32_bf16): slabs go straight into LDS; all tiles of rows of less than 2^22 values;
+//  * far_tile (v_mfma_f32_32x32x16_bf16): slabs go HBM -> registers -> LDS, every row has a pointer; the longer rows, which
+//    32-bit offsets do not reach.
 //
-// gemm_tile's K loop is software-pipelined by hand:
+// far_tile's K loop is software-pipelined by hand:
 //   * fragments of k-step kk+1 are read from LDS into a second register set before the MFMAs of
 //     k-step kk are issued, so LDS latency hides behind the MFMAs;
 //   * the registers holding slab kt+1 are written to the other LDS buffer in the middle of slab kt
@@ -104,8 +102,8 @@ struct GemmArgs {
     float* out_f32;        // EPI_PARTIAL: [split][M][N]; EPI_RESID: [M][N]
     const float* resid;    // EPI_RESID: [M][N] (may alias out_f32)
     bf16_t* out_bf16;      // EPI_SWIGLU: [M][N/2]
-    const int* row_live;   // [M] or NULL: rows with a negative entry are padding - skinny tiles skip their A loads,
-                           // every tile shape skips a row tile that holds nothing else (its output is then not written)
+    const int* row_live;   // [M] or NULL: rows with a negative entry are padding - they are not loaded, and a row tile that
+                           // holds nothing else is skipped (its output is then not written)
     const int* n_live;     // NULL, or where the number of leading rows that are not padding is found (at most M count)
 };
 
@@ -175,26 +173,20 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
     }
 }
 
-// Streaming weight loads and A rows through a buffer descriptor: the skinny tiles.  The 32-bit offsets of buffer
-// descriptors hold a tile of 256 rows up to K = 2^22; longer rows take the tiles that address every row by a pointer:
-// 192x256 and 192x128 here, and the one-slab variant of 128x64.
+// The 32-bit offsets of buffer descriptors hold a tile of 320 rows up to K = 2^22 (dma_tile); longer rows take tiles that
+// address every row by a pointer.
 constexpr int kMaxBufferK = 1 << 22;
-template <int BM, int BN, int WS>
-constexpr bool skinny_loads = BM <= 128 && !(BN == 64 && WS == 1);
 
 // WS = number of register sets that stage slabs: WS slabs (A and W chunks alike - loads return in
 // issue order, so a shallower A stream would throttle the W stream) are in flight per workgroup.
 // With WS = 2 the K loop is unrolled so that every set index is static, and a K slice must hold a multiple of
-// two slabs; WS = 1 serves K of an odd number of slabs (and the pointer-addressed 192x128, whose second set costs the
-// second workgroup's registers).
+// two slabs; WS = 1 serves K of an odd number of slabs (and 192x128, whose second set costs the second workgroup's
+// registers).
 //
-// One tile of the rows_in live rows: workgroup `bid` of tiles_m * tiles_n * g.split.  late_live: NULL, or where the number
-// of live rows is found if it does not decide which tile this is (a single row tile): it is then read behind the first
-// weight loads.
-// STREAM: nobody else reads this tile's weights (a single row tile), they bypass the caches.
-template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem, const int rows_in, const int tiles_m,
-                                          const int tiles_n, const int bid, const int* late_live) {
+// One tile of the rows_in live rows: workgroup `bid` of tiles_m * tiles_n * g.split.
+template <int BM, int BN, int WM, int WN, int EPI, int WS>
+__device__ __forceinline__ void far_tile(const GemmArgs& g, unsigned char* smem, const int M, const int tiles_m,
+                                         const int tiles_n, const int bid) {
     using T = Traits<BM, BN, WM, WN>;
     u32x4* As = reinterpret_cast<u32x4*>(smem);  // [2][BM][CHUNKS]
     u32x4* Bs = As + 2 * BM * CHUNKS;            // [2][BN][CHUNKS]
@@ -206,11 +198,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const int kend = (kbeg + g.kps < K) ? (kbeg + g.kps) : K;
     const int KT = (kend - kbeg) / BK;
 
-    constexpr bool NT = skinny_loads<BM, BN, WS>;
     const int tid = threadIdx.x;
     if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
         bool any = false;
-        for (int r = tid; r < BM; r += T::NT) any |= (m0 + r < rows_in) && g.row_live[m0 + r] >= 0;
+        for (int r = tid; r < BM; r += T::NT) any |= (m0 + r < M) && g.row_live[m0 + r] >= 0;
         // in the slab buffers, not in LDS of its own: two 192x128 workgroups take exactly a unit's 160 KB
         int* flag = reinterpret_cast<int*>(smem);
         const bool wave_any = __builtin_amdgcn_ballot_w64(any) != 0;
@@ -235,35 +226,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     const u32x4* ag[T::A_LOADS];
     const u32x4* bg[T::B_LOADS];
     u32x4 rrb[WS][T::B_LOADS];   // staged W slabs: slab j lives in set j % WS
-    const unsigned row_bytes = (unsigned)K * 2u;   // of descriptors, where K < kMaxBufferK
-    const unsigned off0 = (unsigned)row0 * row_bytes + (unsigned)kc0 * 16u;
 #pragma unroll
     for (int i = 0; i < T::B_LOADS; ++i) {
         bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row0 + i * RPP) * K + kbeg) + kc0;
-        rrb[0][i] = STREAM ? __builtin_nontemporal_load(bg[i]) : *bg[i];
+        rrb[0][i] = *bg[i];
     }
-    int M = rows_in;
-    if (late_live != nullptr) {
-        const int live = *late_live;
-        M = live < M ? live : M;
-        if (M <= 0) return;
-    }
-    // Skinny tiles: a CU keeps a bounded number of requests in flight, and the A slab's share of them
-    // (a third with 256 columns) is taken from the weight stream; rows past M and padding rows are
-    // therefore not loaded at all.  Their lanes address past the end of the A tile's buffer descriptor, which
-    // returns zero without a request and without the branch (and, in the prologue, the wait) that a condition
-    // around each load cost.
     u32x4 rra[WS][T::A_LOADS];   // staged A slabs, same rule as rrb
-    unsigned a_off[T::A_LOADS];
-    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(g.A) + (size_t)m0 * K, 0, NT ? (int)((unsigned)BM * row_bytes) : 0, 0x00020000);
 #pragma unroll
     for (int i = 0; i < T::A_LOADS; ++i) {
         const int row = row0 + i * RPP;
         const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
         ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc0;
-        const bool live = m0 + row < M && (g.row_live == nullptr || g.row_live[gr] >= 0);
-        a_off[i] = live ? off0 + (unsigned)(i * RPP) * row_bytes + (unsigned)kbeg * 2u : 0x80000000u;
     }
     // fragment read offsets (in 16-byte chunks) inside one LDS buffer, per k-step
     int a_src[T::MI], b_src[T::NI];
@@ -291,17 +264,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     // copy op i of the slab pipeline: i < A_LOADS moves an A chunk, else a W chunk held in set `ws`
     auto gload_one = [&](int i, int kt, int ws) {
         const int j = i - T::A_LOADS;
-        if (i < T::A_LOADS) {
-            if constexpr (NT)
-                rra[ws][i] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], clampk(kt) * (BK * 2), 0);
-            else
-                rra[ws][i] = ag[i][clampk(kt) * CHUNKS];
-        } else {
-            // weights are read once: streaming (non-temporal) loads keep them from evicting the A slabs,
-            // which every workgroup on the CU and on the XCD re-reads, out of L1 / L2
-            const u32x4* src = bg[j] + clampk(kt) * CHUNKS;
-            rrb[ws][j] = STREAM ? __builtin_nontemporal_load(src) : *src;
-        }
+        if (i < T::A_LOADS) rra[ws][i] = ag[i][clampk(kt) * CHUNKS];
+        else rrb[ws][j] = bg[j][clampk(kt) * CHUNKS];
     };
     auto lstore_one = [&](int i, int buf, int ws) {
         if (i < T::A_LOADS) As[buf * BM * CHUNKS + dst0 + i * RPP * CHUNKS] = rra[ws][i];
@@ -400,15 +364,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, unsigned char* smem
     store_tile<T, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
-// ------------------------------------------------------------------ tiles of 192 to 320 rows
-// What bounds them on real data is power: the same kernel runs 1.15 times as fast on zeros.  Measured on normal(0, 1) x
-// normal(0, 0.02) operands:
+// ------------------------------------------------------------------ slabs straight into LDS
+// What bounds the tiles of 192 and more rows on real data is power: the same kernel runs 1.15 times as fast on zeros.
+// Measured on normal(0, 1) x normal(0, 0.02) operands:
 //  * v_mfma_f32_16x16x32_bf16 draws less than v_mfma_f32_32x32x16_bf16 (half the accumulator traffic per flop): 2.0-2.1
 //    against 1.76-1.85 PFLOP/s with registers alone;
 //  * slabs written into LDS by the load instruction itself, without staging registers and LDS stores;
 //  * a fragment held for several matrix instructions, and only one operand changed from each to the next (1 %).
+// Up to 128 rows the weights' stream bounds, and the loads that bypass the registers can bypass the caches as well.
 // 2048 x 55296 x 5120 with SwiGLU: 925 us through registers with 32x32x16, 865 with 16x16x32, 832 this way; 2048 x 5120 x
-// 27648: 500, 465, 445; 700 x 27648 x 5120: 204, 192, 180.
+// 27648: 500, 465, 445; 700 x 27648 x 5120: 204, 192, 180.  Up to 128 rows, weights cold, through registers and this way: 32B
+// gate/up at 64 / 128 rows 98 -> 92 / 110 -> 104, q/k/v in 4 slices at 8 / 64 / 128 rows 15.7 -> 13.4 / 19.3 -> 16.4 / 22.0 ->
+// 21.0, o in 5 at 8 / 96 rows 12.3 -> 10.6 / 16.7 -> 15.5, down in 12 at 64 / 128 rows 51.5 -> 47.9 / 58.9 -> 54.
 // Slabs go in half slabs - the rows that one half of every wave's tile needs of A, and one half of B - through a ring of NS
 // of them (2.5 slabs on 256 x 256, the unit's 160 KB of LDS).  All fragments of a half slab (both k-steps of 32) are in
 // registers before its products begin, so its place in the ring is free half a slab after it was waited for.
@@ -538,9 +505,12 @@ __device__ __forceinline__ void dma_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int BM, int BN, int WM, int WN, int EPI>
-__device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem, const int M, const int tiles_m,
-                                         const int tiles_n, const int bid) {
+// One tile of the rows_in live rows: workgroup `bid` of tiles_m * tiles_n * g.split.  late_live: NULL, or where the number
+// of live rows is found if it does not decide which tile this is (a single row tile): it is then read behind the first
+// weight loads.
+template <int BM, int BN, int WM, int WN, int EPI, bool STREAM>
+__device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem, const int rows_in, const int tiles_m,
+                                         const int tiles_n, const int bid, const int* late_live) {
     using D = DmaTraits<BM, BN, WM, WN>;
     constexpr int MH = D::MI / 2, NH = D::NI / 2, NS = D::NS;
     constexpr bool PAIRED = EPI == EPI_SWIGLU;
@@ -553,14 +523,14 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
     const int tid = threadIdx.x;
     if (g.row_live != nullptr) {  // a row tile made of padding only has nothing to compute (and nothing reads its output)
         bool any = false;
-        for (int r = tid; r < BM; r += 256) any |= (m0 + r < M) && g.row_live[m0 + r] >= 0;
+        for (int r = tid; r < BM; r += 256) any |= (m0 + r < rows_in) && g.row_live[m0 + r] >= 0;
         int* flag = reinterpret_cast<int*>(smem);
         const bool wave_any = __builtin_amdgcn_ballot_w64(any) != 0;
         if ((tid & 63) == 0) flag[tid >> 6] = wave_any;
         __syncthreads();
         int live = 0;
 #pragma unroll
-        for (int w = 0; w < 256 / 64; ++w) live |= flag[w];
+        for (int w = 0; w < 4; ++w) live |= flag[w];
         if (!live) return;
         __syncthreads();
     }
@@ -569,16 +539,16 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
     const int lrow = lane & 15, lk = lane >> 4;
 
     const unsigned row_bytes = (unsigned)K * 2u;
-    const int rows = M - m0 < BM ? M - m0 : BM;
     auto rsrc = [&](const bf16_t* base, unsigned bytes) {
         const unsigned long long p = reinterpret_cast<unsigned long long>(base);
         return i32x4{__builtin_amdgcn_readfirstlane((int)(unsigned)p), __builtin_amdgcn_readfirstlane((int)(p >> 32)),
                      __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
     };
-    i32x4 ra = rsrc(g.A + (size_t)m0 * K, (unsigned)rows * row_bytes);
-    i32x4 rb = rsrc(g.W + (size_t)n0 * K, (unsigned)BN * row_bytes);
+    i32x4 ra, rb = rsrc(g.W + (size_t)n0 * K, (unsigned)BN * row_bytes);
+    int a_bytes, b_bytes = rb[2];
     // Offsets of a lane's chunks: half slab row q -> tile row (q / (WT/2)) * WT + half * WT/2 + q % (WT/2).  Rows of A past the
-    // last one lie behind the descriptor's end, so each has an offset of its own.  On 320 x 256 there are no registers for as
+    // last one lie behind the descriptor's end and padding rows are sent there: no request is made for them (a unit keeps a
+    // bounded number in flight, and A takes a third of it on 128 x 256).  So each row of A has an offset of its own.  On 320 x 256 there are no registers for as
     // many of B: the rows that share a key share one there, and the scalar offset moves it (a 256-row graph of the 7B layer is
     // 2.5 % slower where all tiles do that).
     constexpr bool SHARE = BM > 256;
@@ -591,8 +561,11 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int i = 0; i < D::LA; ++i)
-                va[h][i] = (unsigned)(ta + h * D::WTM / 2 + 8 * i + r) * row_bytes + (c ^ dma_key<false>(qa + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
+            for (int i = 0; i < D::LA; ++i) {
+                const int row = ta + h * D::WTM / 2 + 8 * i + r;
+                va[h][i] = (unsigned)row * row_bytes + (c ^ dma_key<false>(qa + 8 * i + r)) * 16 + (unsigned)kbeg * 2u;
+                if (g.row_live != nullptr && m0 + row < rows_in && g.row_live[m0 + row] < 0) va[h][i] = 0xf0000000u;
+            }
 #pragma unroll
         for (int h = 0; h < (SHARE ? 1 : 2); ++h)
 #pragma unroll
@@ -610,7 +583,10 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         }
         const int j = i - D::LA, off = SHARE ? koff + (hb * (D::WTN / 2) + 8 * j) * (int)row_bytes : koff;
         const unsigned lane_off = vb[SHARE ? 0 : hb][j % KEYS];
-        if (D::QB % 8 == 0 || j < D::LB - 1)
+        if (STREAM && (D::QB % 8 == 0 || j < D::LB - 1))
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                         ::"s"(lds_b + slot + j * 1024), "v"(lane_off), "s"(rb), "s"(off));
+        else if (D::QB % 8 == 0 || j < D::LB - 1)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                          ::"s"(lds_b + slot + j * 1024), "v"(lane_off), "s"(rb), "s"(off));
         else   // four rows: the first 32 lanes
@@ -642,10 +618,39 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
     //   odd slabs    A0B1 | read B0,  A0B0 | read A1,  A1B0 | read the next slab's A0,  A1B1 | read its B0
     // Half slab p is what quadrants 2p - 2 and 2p - 1 read: A half p % 2 and B half (p ^ (p >> 1)) & 1 of slab p / 2.  While
     // half slab p is multiplied, p + 1 is read and p + NS is loaded into the place of p.
+    int M = rows_in;
+    if (STREAM) {
 #pragma unroll
-    for (int p = 0; p < NS; ++p)
+        for (int i = D::LA; i < D::LOADS; ++i) dma(i, 0, 0, 0, 0);
+        if (late_live != nullptr) {
+            const int live = *late_live;
+            M = live < M ? live : M;
+            if (M <= 0) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // as at the end
+                return;
+            }
+        }
+    }
+    ra = rsrc(g.A + (size_t)m0 * K, (unsigned)(M - m0 < BM ? M - m0 : BM) * row_bytes);
+    a_bytes = ra[2];
+    // Slabs past the last one are loaded from descriptors of no bytes, which takes no request (with the last slab again in
+    // their place q/k/v of 128 rows took 22.5 us instead of 21.0, down 58 instead of 54).  Not where power bounds: there the
+    // loads of the last slab again cost nothing, and a 4096-row graph took 0.7 % longer without them.
+    auto until = [&](int k) {
+        if (STREAM) {
+            ra[2] = k < KT ? a_bytes : 0;
+            rb[2] = k < KT ? b_bytes : 0;
+        }
+        return (k < KT ? k : KT - 1) * (BK * 2);
+    };
 #pragma unroll
-        for (int i = 0; i < D::LOADS; ++i) dma(i, p & 1, (p ^ (p >> 1)) & 1, p * D::SLOT, (p / 2 < KT ? p / 2 : KT - 1) * (BK * 2));
+    for (int i = 0; i < (STREAM ? D::LA : D::LOADS); ++i) dma(i, 0, 0, 0, 0);
+#pragma unroll
+    for (int p = 1; p < NS; ++p) {
+        const int koff = until(p / 2);
+#pragma unroll
+        for (int i = 0; i < D::LOADS; ++i) dma(i, p & 1, (p ^ (p >> 1)) & 1, p * D::SLOT, koff);
+    }
     dma_barrier<(NS - 1) * D::LOADS>();
 #pragma unroll
     for (int i = 0; i < 2 * MH; ++i) read_a(0, i, 0);
@@ -688,17 +693,16 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         rd = next(rd);
         if (SHARE) asm volatile("" : "+s"(rd), "+s"(wr));   // one address per operand and k-step, not one for every place of the ring
     };
-    // loads of half slab p + NS: slab (p + NS) / 2, the last one again in the tail
     auto slab = [&](auto parity, int kt) {
         constexpr int B = decltype(parity)::value;   // the columns half this slab begins with
         constexpr int P0 = 2 * B, P1 = 2 * B + 1;    // p modulo 4
-        constexpr int N0 = (P0 + NS) & 3, N1 = (P1 + NS) & 3;
-        const int k0 = kt + NS / 2, k1 = kt + (1 + NS) / 2;
-        const int o0 = (k0 < KT ? k0 : KT - 1) * (BK * 2), o1 = (k1 < KT ? k1 : KT - 1) * (BK * 2);
-        constexpr int LH = D::LOADS / 2, H0 = (N0 ^ (N0 >> 1)) & 1, H1 = (N1 ^ (N1 >> 1)) & 1;
+        constexpr int N0 = (P0 + NS) & 3, N1 = (P1 + NS) & 3, H0 = (N0 ^ (N0 >> 1)) & 1, H1 = (N1 ^ (N1 >> 1)) & 1;
+        constexpr int LH = D::LOADS / 2;
+        const int o0 = until(kt + NS / 2);           // half slab p + NS lies in slab (p + NS) / 2
         quadrant(I<0>, I<B>, I<0>, I<B ^ 1>, I<0>, I<LH>, I<(N0 & 1)>, I<H0>, o0);
         quadrant(I<0>, I<B ^ 1>, I<1>, I<1>, I<LH>, I<D::LOADS>, I<(N0 & 1)>, I<H0>, o0);
         half_end();
+        const int o1 = until(kt + (1 + NS) / 2);
         quadrant(I<1>, I<B ^ 1>, I<1>, I<0>, I<0>, I<LH>, I<(N1 & 1)>, I<H1>, o1);
         quadrant(I<1>, I<B>, I<0>, I<B ^ 1>, I<LH>, I<D::LOADS>, I<(N1 & 1)>, I<H1>, o1);
         half_end();
@@ -723,26 +727,25 @@ __device__ __forceinline__ int live_rows(const GemmArgs& g) {
     return live < g.M ? live : g.M;
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
-__global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIMD)) void gemm_kernel(const GemmArgs g) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    int M = g.M, tiles_m = g.tiles_m;
-    const int* late_live = g.n_live;
-    if (tiles_m > 1) {
-        late_live = nullptr;
-        M = live_rows(g);
-        tiles_m = (M + BM - 1) / BM;
-        if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
-    }
-    gemm_tile<BM, BN, WM, WN, EPI, WS, STREAM>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x, late_live);
-}
-
-template <int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void dma_kernel(const GemmArgs g) {
+template <int BM, int BN, int WM, int WN, int EPI, int WS>
+__global__ __launch_bounds__(WM* WN * 64, (Traits<BM, BN, WM, WN>::WAVES_PER_SIMD)) void far_kernel(const GemmArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int M = live_rows(g), tiles_m = (M + BM - 1) / BM;
     if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
-    dma_tile<BM, BN, WM, WN, EPI>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x);
+    far_tile<BM, BN, WM, WN, EPI, WS>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x);
+}
+
+// STREAM: nobody else reads this tile's weights (a single row tile), they bypass the caches.
+template <int BM, int BN, int WM, int WN, int EPI, bool STREAM>
+__global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void dma_kernel(const GemmArgs g) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (STREAM) {   // the live rows do not decide which tile this is
+        dma_tile<BM, BN, WM, WN, EPI, true>(g, smem, g.M, 1, g.tiles_n, blockIdx.x, g.n_live);
+        return;
+    }
+    const int M = live_rows(g), tiles_m = (M + BM - 1) / BM;
+    if (M <= 0 || (int)blockIdx.x >= tiles_m * g.tiles_n * g.split) return;
+    dma_tile<BM, BN, WM, WN, EPI, false>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x, nullptr);
 }
 
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
@@ -775,60 +778,62 @@ __global__ __launch_bounds__(256, 1) void gemm_live_kernel(const GemmArgs g, con
     if ((int)blockIdx.x >= tiles_m * tiles_n) return;
     if constexpr (W > 0) {
         if (pick == 0) {
-            dma_tile<256, W, 4, 1, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+            dma_tile<256, W, 4, 1, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
             return;
         }
     }
-    if (pick == 1) dma_tile<256, 256, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
-    else if (pick == 2) dma_tile<256, 128, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
-    else dma_tile<320, 256, 2, 2, EPI>(g, smem, M, tiles_m, tiles_n, blockIdx.x);
+    if (pick == 1) dma_tile<256, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else if (pick == 2) dma_tile<256, 128, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else dma_tile<320, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int WS, bool STREAM>
-int launch_tile(const GemmArgs& a, hipStream_t s) {
-    using T = Traits<BM, BN, WM, WN>;
-    auto kern = gemm_kernel<BM, BN, WM, WN, EPI, WS, STREAM>;
-    static bool attr_set = false;  // per instantiation; idempotent, so a race only repeats the call
-    if (!attr_set) {
-        LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     T::LDS_BYTES));
-        attr_set = true;
-    }
-    const int grid = a.tiles_m * a.tiles_n * a.split;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(T::NT), T::LDS_BYTES, s, a);
-    LAPS_LAUNCH_CHECK();
-    return LAPS_OK;
-}
-
-template <int BM, int BN, int WM, int WN, int EPI>
-int launch_dma(const GemmArgs& a, hipStream_t s) {
-    constexpr int lds = DmaTraits<BM, BN, WM, WN>::LDS;
-    auto kern = dma_kernel<BM, BN, WM, WN, EPI>;
-    static bool attr_set = false;  // as in launch_tile
-    if (!attr_set) {
+int launch_gemm(void (*kern)(const GemmArgs), bool* attr_set, int threads, int lds, const GemmArgs& a, hipStream_t s) {
+    if (!*attr_set) {   // per kernel; idempotent, so a race only repeats the call
         LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        attr_set = true;
+        *attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n * a.split), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n * a.split), dim3(threads), lds, s, a);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
+}
+
+template <int BM, int BN, int WM, int WN, int EPI, int WS>
+int launch_far(const GemmArgs& a, hipStream_t s) {
+    static bool attr_set = false;
+    return launch_gemm(far_kernel<BM, BN, WM, WN, EPI, WS>, &attr_set, Traits<BM, BN, WM, WN>::NT, Traits<BM, BN, WM, WN>::LDS_BYTES, a, s);
+}
+
+template <int BM, int BN, int WM, int WN, int EPI, bool STREAM>
+int launch_dma(const GemmArgs& a, hipStream_t s) {
+    static bool attr_set = false;
+    return launch_gemm(dma_kernel<BM, BN, WM, WN, EPI, STREAM>, &attr_set, 256, DmaTraits<BM, BN, WM, WN>::LDS, a, s);
+}
+
+template <int BM, int BN, int WM, int WN, bool STREAM>
+int launch_dma_epi(int epi, const GemmArgs& a, hipStream_t s) {
+    using D = DmaTraits<BM, BN, WM, WN>;
+    if (epi == EPI_PARTIAL) return launch_dma<BM, BN, WM, WN, EPI_PARTIAL, STREAM>(a, s);
+    if (epi == EPI_RESID) return launch_dma<BM, BN, WM, WN, EPI_RESID, STREAM>(a, s);
+    if constexpr (D::NI % 4 == 0) return launch_dma<BM, BN, WM, WN, EPI_SWIGLU, STREAM>(a, s);
+    laps_set_error("gemm: no SwiGLU on a tile of %d columns", BN);
+    return LAPS_EINVAL;
 }
 
 struct TileDef {
     int bm, bn;
-    int ws;            // slabs kept in flight per workgroup where the K slices allow it
+    int ws;            // slabs that a K slice holds a multiple of where K allows it
     double fill, slab, part;   // cost model of launches above 128 rows, see laps_gemm_plan
 };
 // index = GemmPlan::cfg.  The cost columns are a fit over 4800 launches (all tiles and K splits on the 7B, 14B and 32B
 // projections at 24 row counts from 129 to 8192, weights cold; rms error 7 %): microseconds a workgroup takes besides its
 // slabs, microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.
 constexpr TileDef kTiles[] = {
-    {128, 128, 2, 1.11, 0.521, 0.06},  // 0: 4 waves of 64x64, two workgroups per compute unit
+    {128, 128, 2, 1.11, 0.521, 0.06},  // 0: 4 waves of 64x64 (32x64 up to 64 rows), two workgroups per compute unit
     {128, 64, 2, 1.20, 0.350, 0.00},   // 1: 4 waves of 64x32, for n % 128 != 0
     {256, 256, 2, 5.25, 1.430, 0.25},  // 2: 4 waves of 128x128
     {256, 224, 2, 5.19, 1.234, 0.24},  // 3: 4 waves of 64x224 (N = 7168 -> 32 column tiles)
     {256, 160, 2, 4.38, 0.985, 0.24},  // 4: 4 waves of 64x160 (N = 5120 -> 32 column tiles)
-    {128, 256, 2, 2.44, 0.904, 0.21},  // 5: 8 waves of 64x64: the streaming tile, A slab shared by 256 columns
+    {128, 256, 2, 2.44, 0.904, 0.21},  // 5: 4 waves of 128x64 (64x64 up to 64 rows): the streaming tile, A slab shared by 256 columns
     {192, 256, 2, 5.75, 1.160, 0.20},  // 6: 4 waves of 96x128
     {192, 128, 1, 1.81, 0.716, 0.09},  // 7: 4 waves of 96x64, two workgroups per compute unit
     {256, 128, 2, 3.01, 0.863, 0.25},  // 8: 4 waves of 128x64
@@ -845,7 +850,7 @@ int launch_live(const GemmArgs& a, hipStream_t s) {
     int lds = 0;
     for (int b : lds_of) lds = b > lds ? b : lds;
     auto kern = gemm_live_kernel<W, EPI>;
-    static bool attr_set = false;  // as in launch_tile
+    static bool attr_set = false;  // as in launch_gemm
     if (!attr_set) {
         LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         attr_set = true;
@@ -878,7 +883,6 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         if (split > ksteps) split = ksteps;
         if (split < 1) split = 1;
         int per = (ksteps + split - 1) / split;
-        // with 2 slabs in flight every K slice must hold a multiple of 2 slabs
         p.ws = 1;
         if (kTiles[cfg].ws == 2 && ksteps % 2 == 0 && !(far && cfg == 1)) {
             per = (per + 1) / 2 * 2;
@@ -894,26 +898,28 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         // Bandwidth-bound.  A CU keeps a bounded number of requests in flight, and the A slab that every
         // workgroup re-reads per K step (L2 hits) takes its share of them from the weight stream: a
         // 256-column tile halves the A share of a 128-column one, which decides the wide projections
-        // (gate/up: 5.3 against 4.4 TB/s of weights).  A narrow
+        // (32B gate/up of 128 rows: 104 against 126 us).  A narrow
         // projection (q/k/v, o: 20-28 tiles of 256 columns) never gets near that limit; it pays for the
         // K split that has to fill the chip - every slice writes m*n fp32 partial sums that a reduce
         // kernel reads back - and for the short pipeline of each slice.  128-column tiles need half the
-        // split; they win where the 256-column slices would be shorter than 24 K slabs (measured with
-        // cold weights at m = 128: q/k/v 33.8 -> 26.7 us, o 29.0 -> 22.4, 7B-shaped down 43.8 -> 37.4;
-        // the 32B down projection, 36 slabs per slice, is even and stays on 256 columns).  At most 256
+        // split; they win where the 256-column slices would be shorter than 24 K slabs (cold
+        // weights, m = 128: q/k/v 22.2 -> 21.3 us, o with the row kernel 30.2 -> 26.2, 7B down 43.0 -> 39.9;
+        // the 32B down projection, 36 slabs per slice, stays on 256 columns: 61.2 against 65.8).  At most 256
         // workgroups either way: a streaming kernel with 257 leaves one CU with twice the work.
         auto auto_split = [&](int c) {
-            const int min_steps = c == 5 ? 8 : 16;   // K slabs per slice below which the pipeline is all prologue
+            // K slabs per slice below which the pipeline is all prologue; where raw sums are read by a row kernel anyhow, 8
+            // (7B q/k/v at 8 / 128 rows: 4 slices of 14 slabs 8.7 / 15.1 us, 7 of 8 7.6 / 12.6)
+            const int min_steps = c == 5 || want_epi == EPI_PARTIAL ? 8 : 16;
             int sp = 256 / (n / kTiles[c].bn);
             const int cap = (ksteps + min_steps / 2) / min_steps;
             sp = sp > cap ? cap : sp;
             return sp < 1 ? 1 : sp;
         };
         int cfg;
-        if (n % 256 == 0 && (n % 128 != 0 || ksteps / auto_split(5) >= 24)) cfg = 5;
+        if (n % 256 == 0 && ksteps / auto_split(5) >= 24) cfg = 5;
         else cfg = (n % 128 == 0) ? 0 : 1;
         // SwiGLU on 129..256 tiles of 128 columns: un-split, and so fused, where 256 columns would need two K slices
-        // and the row kernel (14B gate/up at 8 / 64 / 128 rows 56 / 65 / 75 -> 49 / 57 / 66 us with that kernel)
+        // and the row kernel (14B gate/up at 8 / 64 / 128 rows 46 / 57 / 66 -> 43 / 50 / 62 us with that kernel)
         if (cfg == 5 && want_epi == EPI_SWIGLU && force_split == 0 && auto_split(5) > 1 && auto_split(0) == 1 && n % 128 == 0) cfg = 0;
         if (cfg == 1 && want_epi == EPI_SWIGLU) want_epi = EPI_PARTIAL;
         const int split = force_split > 0 ? force_split : auto_split(cfg);
@@ -1042,70 +1048,58 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         if (n % 192 == 0 && p.epi == EPI_SWIGLU) return launch_live<192, EPI_SWIGLU>(g, s);
         if (p.epi == EPI_SWIGLU) return launch_live<0, EPI_SWIGLU>(g, s);
     }
-    // Weights that one row tile reads alone bypass the caches.  Above a few rows the K slices of the 64- and 128-column
-    // tiles wait on the memory less with cached loads: 14B o, 16-slab slices, on its own with weights cold / warm (in the
-    // memory-side cache), bypassing against cached: 16 rows 16.7 / 16.1 against 17.1 / 15.7 us, 128 rows 25.1 / 25.1
-    // against 22.5 / 18.8; down, 36-slab slices: 32 rows 31.2 / 29.9 against 33.1 / 28.9, 64 rows 34.3 / 33.4 against 34.6 /
-    // 29.3, 128 rows 40.2 / 40.4 against 39.1 / 31.6.  Inside a layer that is lost again, since the weights then push out
-    // what the kernels around them find in the caches (14B, 64-row graph: 178.2 us cached, 174.8 bypassing; 32B, 128 rows:
-    // even), so only a product of its own (no batch whose live rows are given) takes it.  Un-split and 256-column launches
-    // lose by it (14B gate/up, 8 / 64 rows, cold: 46.8 / 55.1 against 50.4 / 58.7; 32B down, 8 / 128: 51.7 / 65.9 against
-    // 56.4 / 68.5).
-    const bool alone = row_live == nullptr && n_live == nullptr;
-    const bool cached = alone && m > (p.k_per_split < 32 * BK ? 16 : 48) && p.split > 1 && kTiles[p.cfg].bn < 256;
-    const bool bypass = g.tiles_m == 1 && !cached;
-#define LAPS_DMA_CASE(cfg, ...)                                                                     \
-    case cfg:                                                                                       \
-        if (p.epi == EPI_PARTIAL) return launch_dma<__VA_ARGS__, EPI_PARTIAL>(g, s);                \
-        if (p.epi == EPI_RESID) return launch_dma<__VA_ARGS__, EPI_RESID>(g, s);                    \
-        if constexpr (DmaTraits<__VA_ARGS__>::NI % 4 == 0 && (DmaTraits<__VA_ARGS__>::NI / 2) % 2 == 0) \
-            return launch_dma<__VA_ARGS__, EPI_SWIGLU>(g, s);                                       \
+    if (k >= kMaxBufferK) {
+#define LAPS_FAR_CASE(cfg, BM, BN, WS)                                                          \
+    case (cfg) * 8 + (WS):                                                                      \
+        if (p.epi == EPI_PARTIAL) return launch_far<BM, BN, 2, 2, EPI_PARTIAL, WS>(g, s);       \
+        if (p.epi == EPI_RESID) return launch_far<BM, BN, 2, 2, EPI_RESID, WS>(g, s);           \
+        if constexpr (BN % 128 == 0) return launch_far<BM, BN, 2, 2, EPI_SWIGLU, WS>(g, s);     \
         break
-    if (k < kMaxBufferK) switch (p.cfg) {
-        LAPS_DMA_CASE(2, 256, 256, 2, 2);
-        LAPS_DMA_CASE(3, 256, 224, 4, 1);
-        LAPS_DMA_CASE(4, 256, 160, 4, 1);
-        LAPS_DMA_CASE(6, 192, 256, 2, 2);
-        LAPS_DMA_CASE(7, 192, 128, 2, 2);
-        LAPS_DMA_CASE(8, 256, 128, 2, 2);
-        LAPS_DMA_CASE(9, 256, 192, 4, 1);
-        LAPS_DMA_CASE(10, 320, 256, 2, 2);
-        default: break;
-    }
+        switch (p.cfg * 8 + p.ws) {
+            LAPS_FAR_CASE(1, 128, 64, 1);
+            LAPS_FAR_CASE(6, 192, 256, 1);
+            LAPS_FAR_CASE(6, 192, 256, 2);
+            LAPS_FAR_CASE(7, 192, 128, 1);
+            default: break;
+        }
+#undef LAPS_FAR_CASE
+    } else {
+        // Weights that one row tile reads alone bypass the caches (32B, 128 rows: gate/up 114 us through them, 104 bypassing,
+        // down 64 and 54, q/k/v 21.8 and 21.0); several row tiles that share them lose by it (2048 rows, q/k/v 109 cached, 116
+        // bypassing).  A product of its own (no batch whose live rows are given) may find its weights in the memory-side cache
+        // the next time: where that holds them and K is split over narrow tiles, they stay in the caches above 48 rows (weights
+        // cold / warm, cached against bypassing: 14B down 48 rows 32.9 / 29.2 against 30.9 / 30.2, 64 rows 33.9 / 29.9 against
+        // 32.7 / 32.0, 128 rows 39.7 / 32.3 against 40.0 / 40.1, 160 rows 42.5 / 33.8 against 42.5 / 42.7; o 128 rows 23.2 / 18.8
+        // against 25.1 / 25.0; 32B down of 283 MB, 160 rows 74.7 against 68.8).
+        // Up to 64 rows the tiles of 64 rows spare the LDS reads and the products of as many rows of nothing.
+        const bool alone = row_live == nullptr && n_live == nullptr;
+        const bool keep = alone && m > 48 && p.split > 1 && kTiles[p.cfg].bn < 256 && 2.0 * n * k <= 256e6;
+        const bool bypass = g.tiles_m == 1 && !keep;
+#define LAPS_DMA_CASE(cfg, BM, BN, WM, WN)                                                       \
+    case cfg:                                                                                    \
+        if (bypass) return launch_dma_epi<BM, BN, WM, WN, true>(p.epi, g, s);                    \
+        return launch_dma_epi<BM, BN, WM, WN, false>(p.epi, g, s)
+        if (m <= 64) switch (p.cfg) {
+            LAPS_DMA_CASE(0, 64, 128, 2, 2);
+            LAPS_DMA_CASE(5, 64, 256, 1, 4);
+            default: break;
+        }
+        switch (p.cfg) {
+            LAPS_DMA_CASE(0, 128, 128, 2, 2);
+            LAPS_DMA_CASE(1, 128, 64, 2, 2);
+            LAPS_DMA_CASE(2, 256, 256, 2, 2);
+            LAPS_DMA_CASE(3, 256, 224, 4, 1);
+            LAPS_DMA_CASE(4, 256, 160, 4, 1);
+            LAPS_DMA_CASE(5, 128, 256, 1, 4);
+            LAPS_DMA_CASE(6, 192, 256, 2, 2);
+            LAPS_DMA_CASE(7, 192, 128, 2, 2);
+            LAPS_DMA_CASE(8, 256, 128, 2, 2);
+            LAPS_DMA_CASE(9, 256, 192, 4, 1);
+            LAPS_DMA_CASE(10, 320, 256, 2, 2);
+            default: break;
+        }
 #undef LAPS_DMA_CASE
-#define LAPS_TILE_CASE(cfg, BM, BN, WM, WN, EPI, WS) \
-    case ((cfg) * 4 + (EPI)) * 8 + (WS):             \
-        if (skinny_loads<BM, BN, WS> && bypass) return launch_tile<BM, BN, WM, WN, EPI, WS, skinny_loads<BM, BN, WS>>(g, s); \
-        return launch_tile<BM, BN, WM, WN, EPI, WS, false>(g, s)
-    switch ((p.cfg * 4 + p.epi) * 8 + p.ws) {
-        LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_RESID, 1);
-        LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_RESID, 2);
-        LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(0, 128, 128, 2, 2, EPI_SWIGLU, 2);
-        LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_RESID, 1);
-        LAPS_TILE_CASE(1, 128, 64, 2, 2, EPI_RESID, 2);
-        LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_RESID, 1);
-        LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_RESID, 2);
-        LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(5, 128, 256, 2, 4, EPI_SWIGLU, 2);
-        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_PARTIAL, 2);
-        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_RESID, 1);
-        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_RESID, 2);
-        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_SWIGLU, 1);
-        LAPS_TILE_CASE(6, 192, 256, 2, 2, EPI_SWIGLU, 2);
-        LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_PARTIAL, 1);
-        LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_RESID, 1);
-        LAPS_TILE_CASE(7, 192, 128, 2, 2, EPI_SWIGLU, 1);
-        default: break;
     }
-#undef LAPS_TILE_CASE
     laps_set_error("gemm: no kernel for tile %d with epilogue %d", p.cfg, p.epi);
     return LAPS_EINVAL;
 }

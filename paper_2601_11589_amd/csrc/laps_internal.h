@@ -52,7 +52,7 @@ struct GemmPlan {
     int split;        // K slices
     int k_per_split;  // multiple of 64
     int epi;          // epilogue the launch will apply: the requested one if split == 1, else EPI_PARTIAL
-    int ws;           // weight slabs kept in flight per workgroup (register sets): 1 or 2
+    int ws;           // slabs that every K slice holds a multiple of: 1 or 2
 };
 // partial_cap: bytes the partial sums of an automatic split may take above 128 rows or at K >= 2^22 (the layer driver
 // passes what its workspace holds if that is less).
@@ -64,8 +64,8 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
                         bool row_kernel = false, bool layer = false);
 size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap);
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // rows and columns of tile shape `cfg` (0, 0 if unknown)
-// row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified:
-// the skinny tiles do not load them (they compute with zeros), and a row tile of padding only is skipped.
+// row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified: they are
+// not loaded, and a row tile of padding only is skipped.
 // n_live: NULL, or a device int: rows at and past it are padding (batches whose padding is all at the end).
 // live_varies: the launch will be replayed with other values of *n_live (a captured graph).
 int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m, int n, int k, float* out_f32,

@@ -1,6 +1,7 @@
-"""The GEMM launches that only a layer makes, called directly: the 320 x 256 tile, at the edges of its rows and with K slices
-of an odd and an even number of slabs, and the launch of a captured graph that chooses its tile by the live rows.  Against
-float64, with rows of NaN behind the operand and guard rows behind the result."""
+"""The GEMM launches called directly: the 320 x 256 tile that only layers take, the launch of a captured graph that chooses its
+tile by the live rows, the tiles up to 128 rows with live rows told late, and padding rows; at the edges of the tiles' rows and
+with K slices of an odd and an even number of slabs.  Against float64, with rows of NaN behind the operand and guard rows
+behind the result."""
 import ctypes as C
 
 import pytest
@@ -95,3 +96,39 @@ def test_tile_by_live_rows_matches_float64(n, epi):
         a, w = torch.zeros((m, k), dtype=torch.bfloat16, device="cuda"), torch.zeros((n, k), dtype=torch.bfloat16, device="cuda")
         launch(none, a, w, m, out, out if epi == RESID else None, act, torch.tensor([0], dtype=torch.int32, device="cuda"))
         assert bool((out == 7).all()) and bool((act == 7).all())
+
+# Up to 64 rows on tiles of 64 rows, then 128: edges of both, weights bypassing the caches (rows given as live) and through them
+# (a product of its own), with live rows told late and K slices of one and several slabs
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,n", [(0, 256), (5, 512), (1, 192)])
+@pytest.mark.parametrize("m", [1, 16, 63, 64, 65, 128])
+def test_tiles_up_to_128_rows_match_float64(cfg, n, m):
+    for k, split in ((64, 1), (192, 1), (1024, 1), (448, 2), (1024, 4)):
+        per = -(-(k // 64) // split) * 64
+        for epi in (PARTIAL,) if split > 1 else (PARTIAL, RESID) + ((SWIGLU,) if cfg != 1 else ()):
+            run(Plan(cfg, split, per, epi, 1), m, n, k)
+            for rows in {1, (m + 1) // 2, m}:
+                run(Plan(cfg, split, per, epi, 1), m, n, k, torch.tensor([rows], dtype=torch.int32, device="cuda"), rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,m,n", [(0, 100, 256), (5, 40, 512), (2, 300, 512), (10, 320, 512)])
+def test_padding_rows_between_sequences_are_left_out(cfg, m, n):
+    """Rows that row_live marks as padding hold NaN: they reach no other row, and a row tile of padding only is not written."""
+    k = 320
+    g = torch.Generator(device="cuda").manual_seed(m)
+    live = torch.rand(m, device="cuda", generator=g) < 0.6
+    live[256:] = False
+    a = torch.empty((m, k), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    a[~live] = float("nan")
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=g)
+    out = torch.full((m, n), 7.0, device="cuda")
+    flags = torch.where(live, 3, -1).to(torch.int32)
+    p = lambda t: C.c_void_p(t.data_ptr())
+    assert api.lib()._Z16laps_gemm_launchRK8GemmPlanPKtS3_iiiPfPKfPtPKiS9_bP12ihipStream_t(
+        C.byref(Plan(cfg, 1, k, PARTIAL, 1)), p(a), p(w), C.c_int(m), C.c_int(n), C.c_int(k), p(out), None, None, p(flags), None,
+        C.c_bool(False), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    want = a[live].double() @ w.double().T
+    assert float((out[live].double() - want).norm() / want.norm()) < 2e-6
+    if cfg == 2:
+        assert bool((out[256:] == 7).all())
