@@ -829,7 +829,13 @@ static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_
             return;
         }
     }
-    *mt = (total_rows > 128L * n_seq) ? 2 : 1;  // average rows per sequence above one 128-row block
+    // Few key tiles: 256-row blocks pay for their pipelined loop (three stages to fill and drain) and for the rows that fill
+    // no block, so 128-row ones take all launches of up to 4 tiles, and up to the split's 8 those that fit the chip at once.
+    // Attention alone with its scheduling kernel, 256- against 128-row blocks: 32B, 16 / 32 / 64 prompts of 64 tokens 21.7 / 35.9
+    // / 63.1 against 17.9 / 27.5 / 42.6 us, one of 440 27.5 against 22.5, 8 turns of 64 over 200 keys 24.1 against 19.3; 7B, 64
+    // prompts 37.3 against 35.2, but 64 turns over 380 keys 63.4 against 68.3.
+    const bool few = max_kv_tiles <= 4 || (max_kv_tiles < 2 * MIN_TILES_PER_SPLIT && items1 * n_kv <= 512);
+    *mt = (!few && total_rows > 128L * n_seq) ? 2 : 1;  // average rows per sequence above one 128-row block
     const int rows_per_wg = 128 * *mt;
     // every sequence contributes ceil(rows/rows_per_wg) blocks: at most rows/rows_per_wg + 1
     *max_items = (int)(total_rows / rows_per_wg) + n_seq;
