@@ -1,0 +1,66 @@
+"""The attention of page tables a few key tiles wide (64 keys, 4 pages each): 128-row blocks up to 4 tiles, and up to 7 for
+launches whose blocks fit the chip at once; 256-row blocks from there on.  The rule on the host, and both sides of each of its
+edges against float64."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_11589_amd import api, inputs
+from test_gpu_attention_shares import reference
+
+# (model, new tokens, cached tokens, pages of the table, query rows per workgroup)
+EDGES = [
+    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 130] * 10, 16, 128),       # 4 tiles, more blocks than the chip holds
+    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 193] * 10, 17, 256),       # 5 tiles, as many blocks
+    (inputs.qwen32b_cfg, [64] * 16, [384, 0, 1, 200] * 4, 28, 128),         # 7 tiles, 448 blocks
+    (inputs.qwen32b_cfg, [64] * 16, [385, 0, 1, 200] * 4, 29, 256),         # 8 tiles
+    (inputs.qwen32b_cfg, [1] * 8 + [63, 64] * 8, [0, 15] * 4 + [3, 384] * 8, 28, 128),
+    (inputs.qwen7b_cfg, [256, 129, 1, 77], [0, 127, 255, 64], 16, 128),     # blocks of 18 tokens, the last of few rows
+    (inputs.tiny_cfg, [65] * 140, [0, 63, 190, 191, 1] * 28, 16, 128),      # head dimension 64
+    (inputs.tiny_cfg, [65] * 140, [0, 63, 191, 192, 1] * 28, 17, 256),
+    (inputs.tiny_cfg, [65] * 120, [383] * 119 + [0], 28, 128),              # 480 blocks of head dimension 64
+]
+
+
+def rows_per_workgroup(cfg, new, pages):
+    out = (C.c_int64 * 6)()
+    assert api.lib().laps_attn_plan_info(len(new), sum(new), cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, pages, out) == 0
+    return out[0], out[2]
+
+
+@pytest.mark.parametrize("case", range(len(EDGES)))
+def test_blocks_of_a_few_key_tiles(case):
+    cfgf, new, pre, pages, rows = EDGES[case]
+    assert max(-(-(n + h) // 16) for n, h in zip(new, pre)) <= pages
+    assert rows_per_workgroup(cfgf(1), new, pages) == (rows, 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(EDGES)))
+def test_attention_of_a_few_key_tiles_matches_float64(case):
+    cfgf, new, pre, pages, _ = EDGES[case]
+    cfg = cfgf(1)
+    ctx = api.LapsCtx(cfg, 64)
+    g = torch.Generator(device="cuda").manual_seed(31 + case)
+    cu = np.concatenate([[0], np.cumsum(new)])
+    table, n_pages = inputs.make_page_table(5, new, pre)
+    table = np.pad(table, ((0, 0), (0, pages - table.shape[1])), constant_values=-1)
+    draw = lambda shape, std=1.0: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).cuda()
+    q = draw((int(cu[-1]), cfg.q_dim), 2.5)
+    kp, vp = draw((n_pages, cfg.n_kv_heads, 16, cfg.head_dim)), draw((n_pages, cfg.n_kv_heads, cfg.head_dim, 16))
+    run = lambda: ctx.laps_attention(d(cu), None, d(pre), d(table), kp, vp, q).double().view(-1, cfg.n_q_heads, cfg.head_dim)
+    got = run()
+    assert torch.equal(got, run())
+    for i, (n, h) in enumerate(zip(new, pre)):
+        rows = slice(int(cu[i]), int(cu[i]) + n)
+        ids = d(table[i, :(n + h + 15) // 16]).long()
+        k = kp[ids].transpose(1, 2).reshape(-1, cfg.n_kv_heads, cfg.head_dim)[:n + h].double()
+        v = vp[ids].permute(0, 3, 1, 2).reshape(-1, cfg.n_kv_heads, cfg.head_dim)[:n + h].double()
+        want = reference(cfg, q[rows].double().view(n, cfg.n_q_heads, cfg.head_dim), k, v, h)
+        err = (got[rows] - want).flatten(1).norm(dim=1)
+        # probabilities and result are bf16 (2^-9 relative each, rms 1.7e-3 together); a token's heads share one norm
+        assert bool((err <= 8e-3 * want.flatten(1).norm(dim=1)).all()), (i, float((err / want.flatten(1).norm(dim=1)).max()))
+    ctx.close()
