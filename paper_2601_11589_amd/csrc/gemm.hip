@@ -131,7 +131,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[T::MI][T::NI], co
         // keeps a load behind every store before it; written element by element, a lane's 80..256 results take as many
         // memory round trips one after the other (45-70 us per launch whatever the size).  The residual of sub-tile
         // i + 1 is therefore loaded before sub-tile i is stored: one round trip per sub-tile of 16, overlapped.
-        // o projection of the 32B layer, 2048 rows: 165 -> 102 us; a 227 x 256 x 256 product: 45 -> 15 us.
+        // o projection of the 32B layer, 2048 rows, when it ran on these tiles: 165 -> 102 us; a 227 x 256 x 256 product: 45 -> 15.
         constexpr int NS = T::MI * T::NI;
         float rbuf[2][16];
         auto row = [&](int i, int r) { return m0 + wm * T::WTM + (i / T::NI) * 32 + 8 * (r / 4) + 4 * lk + (r % 4); };
@@ -720,7 +720,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
 
 // Rows past *n_live are padding: the tiles of the rows before them are dealt out as if there were no others.  (Tiles of all
 // M rows, the dead ones returning at once, leave whole XCDs idle, since each takes a contiguous range: gate/up of a
-// 4096-row graph with 2776 live rows 1880 us, this way 1390.)
+// 4096-row graph with 2776 live rows 1880 us, this way 1390, both with slabs through registers.)
 __device__ __forceinline__ int live_rows(const GemmArgs& g) {
     if (g.n_live == nullptr) return g.M;
     const int live = *g.n_live;
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void
 
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
 // 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 220
-// of 256 x 256 take one: 997 against 700 us).  Four tiles are therefore one kernel, which takes the one that the cost model
+// of 256 x 256 take one: 997 against 700 us with slabs through registers).  Four tiles are therefore one kernel, which takes the one that the cost model
 // gives the live rows; every workgroup comes to the same choice.  First tile: 256 x W, W = 160 (N = 5120), 224 (7168, 3584)
 // or 192 (55296, 27648, 4608); none for 7B gate/up (37888), and other N keep the tile planned for all rows.  q/k/v of 2776 rows on
 // 320 x 256 (252 tiles, one round) 152 us, on 256 x 224 (352) 198; gate/up 1141 on 320 x 256 and 1178 on 256 x 256.
@@ -826,7 +826,9 @@ struct TileDef {
 };
 // index = GemmPlan::cfg.  The cost columns are a fit over 4800 launches (all tiles and K splits on the 7B, 14B and 32B
 // projections at 24 row counts from 129 to 8192, weights cold; rms error 7 %): microseconds a workgroup takes besides its
-// slabs, microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.
+// slabs, microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.  Fitted
+// with slabs through registers; the choices stand: what they cost against the best plan of each product, measured with slabs
+// straight into LDS, is under 1 % in the mean.
 constexpr TileDef kTiles[] = {
     {128, 128, 2, 1.11, 0.521, 0.06},  // 0: 4 waves of 64x64 (32x64 up to 64 rows), two workgroups per compute unit
     {128, 64, 2, 1.20, 0.350, 0.00},   // 1: 4 waves of 64x32, for n % 128 != 0
@@ -931,7 +933,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     //   clock], not less than the weights take from HBM; a split adds the partial sums written and read back, the row
     //   kernel's own traffic and, if there would be none otherwise, its launch; an un-split residual epilogue adds the
     //   RMSNorm that the row kernel would contain, where one follows.
-    // Against the one rule before it (256-row tiles only) products of the 7B, 14B and 32B projections and of 24 random
+    // Against the one rule before it (256-row tiles only; slabs through registers on both sides) products of the 7B, 14B and 32B projections and of 24 random
     // shapes at 40 row counts from 129 to 4096 are 1.37 times faster in the mean and more than 3 % slower at a K of six
     // slabs only (7552 columns, 4096 rows: 45 -> 53 us, bound by the stores; the fit holds slabs by the dozen).  The 32B
     // layer's projections take, q/k/v, o, gate/up, down: 573 rows 59 -> 47, 50 -> 47, 395 -> 320, 205 -> 164 us; 300 rows
