@@ -326,7 +326,7 @@ def run_long(ctx, layers, cfg, steps, warmup):
     n, kk = gemm_shapes(cfg)["gemm_gateup"]
     ms, cnt = prof["gemm_gateup"]
     fl = 2.0 * T * n * kk * cfg.n_layers          # all chunks of all prompts, real rows only
-    res["roofline"] = {"bound": "mfma", "kernel": "gemm (gate/up projection, 256x256 tile)", "achieved": fl / (ms * 1e-3) / 1e12,
+    res["roofline"] = {"bound": "mfma", "kernel": "gemm (gate/up projection, 320x256 tile)", "achieved": fl / (ms * 1e-3) / 1e12,
                        "peak": MFMA_BF16_PEAK_TFS, "unit": "TFLOP/s", "frac": fl / (ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFS,
                        "traffic": None, "avg_launch_us": ms / cnt * 1e3, "launches": cnt}
     ms_all = sum(prof[k][0] for k in gemm_shapes(cfg))
