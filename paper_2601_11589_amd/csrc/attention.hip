@@ -48,11 +48,11 @@ __device__ __forceinline__ int swz16(int row, int c) { return c ^ (row & 15); }
 
 // NW waves per workgroup, one 32-row query tile per wave: rows per workgroup = 32 * NW.  With NW = 8
 // two waves share a SIMD, so one wave's softmax (VALU, exp) overlaps the other's MFMAs.
-// key tiles per split (lower bound) and the split geometry shared by the attention and the merge kernel
+// key tiles per split (lower bound, attn_blocking) and the split geometry shared by the attention and the merge kernel
 constexpr int MIN_TILES_PER_SPLIT = 4;
-__device__ __forceinline__ void split_geometry(int kv_end, int n_split, int* eff, int* per) {
+__device__ __forceinline__ void split_geometry(int kv_end, int n_split, int min_tiles, int* eff, int* per) {
     const int nt = (kv_end + KT - 1) / KT;
-    int e = nt / MIN_TILES_PER_SPLIT;
+    int e = min_tiles == 1 ? nt : nt / MIN_TILES_PER_SPLIT;   // 1 or that: no division
     e = e < 1 ? 1 : (e > n_split ? n_split : e);
     *eff = e;
     *per = (nt + e - 1) / e;
@@ -74,7 +74,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
                                                         const int* __restrict__ tile_start,
                                                         const int* __restrict__ item_seq, int n_seq, int n_q,
                                                         int n_kv, float scale_log2e, int n_pool_pages, int n_tokens,
-                                                        int max_items, const int4* __restrict__ bounds) {
+                                                        int max_items, int min_tiles,
+                                                        const int4* __restrict__ bounds) {
     constexpr int NTHR = NW * 64;
     constexpr int CPR = HD / 8;            // 16-byte chunks per K row
     constexpr int CPP = HD * 2;            // 16-byte chunks per page (K and V alike)
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
     int kv_begin = 0, kv_end = kv_end_all, eff = 1;
     if (SPLIT) {
         int per;
-        split_geometry(kv_end_all, (int)gridDim.z, &eff, &per);
+        split_geometry(kv_end_all, (int)gridDim.z, min_tiles, &eff, &per);
         const int z = blockIdx.z;
         if (z >= eff || z * per * KT >= kv_end_all) return;   // this split has no keys: the merge skips it too
         kv_begin = z * per * KT;
@@ -671,7 +672,7 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     bf16_t* __restrict__ out, const float* __restrict__ part_o, const float* __restrict__ part_ml,
     const int* __restrict__ row_start, const int* __restrict__ new_len, const int* __restrict__ prefix_len,
     const int* __restrict__ tile_start, const int* __restrict__ item_seq, int n_seq, int n_q, int n_kv, int n_split,
-    int max_pages, int n_tokens) {
+    int min_tiles, int max_pages, int n_tokens) {
     constexpr int ROWS = 128;
     __shared__ float red_m[MERGE_GROUPS][ROWS];
     __shared__ float red_l[MERGE_GROUPS][ROWS];
@@ -688,7 +689,7 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     const int last_row_wg = (R0 + ROWS < n_rows ? R0 + ROWS : n_rows) - 1;
     const int kv_end_all = H + last_row_wg / G + 1;
     int eff, per;
-    split_geometry(kv_end_all, n_split, &eff, &per);
+    split_geometry(kv_end_all, n_split, min_tiles, &eff, &per);
     if (eff == 1) return;   // the attention kernel wrote the final rows itself (uniform over the workgroup)
     const int nt = (kv_end_all + KT - 1) / KT;
     const int used = (nt + per - 1) / per < eff ? (nt + per - 1) / per : eff;   // splits that had keys
@@ -752,7 +753,7 @@ int launch_attn(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
     hipLaunchKernelGGL((attn_kernel<HD, NW, false, false>), dim3(max_items, n_kv), dim3(NW * 64), 0, s, q, out, nullptr,
                        nullptr, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq,
-                       n_seq, n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, nullptr);
+                       n_seq, n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, 0, nullptr);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -766,7 +767,7 @@ int launch_attn_persistent(const bf16_t* q, bf16_t* out, float* part, int n_wgs,
     float* part_ml = part + (size_t)2 * n_wgs * LAPS_ATTN_LONG_ROWS * HD;
     hipLaunchKernelGGL((attn_kernel<HD, 8, false, true>), dim3(n_wgs), dim3(512), 0, s, q, out, part, part_ml, k_pool, v_pool,
                        row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, n_q, n_kv,
-                       scale_log2e, n_pool_pages, n_tokens, max_items, bounds);
+                       scale_log2e, n_pool_pages, n_tokens, max_items, 0, bounds);
     LAPS_LAUNCH_CHECK();
     hipLaunchKernelGGL((attn_merge_cut_kernel<HD>), dim3(n_wgs - 1, 4), dim3(LAPS_ATTN_LONG_ROWS), 0, s, out, part, part_ml,
                        row_start, new_len, tile_start, item_seq, bounds, n_wgs, n_seq, n_q, n_kv, n_tokens);
@@ -777,7 +778,7 @@ int launch_attn_persistent(const bf16_t* q, bf16_t* out, float* part, int n_wgs,
 template <int HD>
 int launch_attn_split(const bf16_t* q, bf16_t* out, float* part, const bf16_t* k_pool, const bf16_t* v_pool,
                       const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
-                      int max_pages, const int* tile_start, const int* item_seq, int n_seq, int max_items, int n_split,
+                      int max_pages, const int* tile_start, const int* item_seq, int n_seq, int max_items, int n_split, int min_tiles,
                       int n_q, int n_kv, int n_pool_pages, int n_tokens, hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
     const size_t blocks = (size_t)max_items * n_kv * n_split;
@@ -785,10 +786,10 @@ int launch_attn_split(const bf16_t* q, bf16_t* out, float* part, const bf16_t* k
     float* part_ml = part + blocks * 128 * HD;
     hipLaunchKernelGGL((attn_kernel<HD, 4, true, false>), dim3(max_items, n_kv, n_split), dim3(256), 0, s, q, out, part_o, part_ml,
                        k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq,
-                       n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, nullptr);
+                       n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, min_tiles, nullptr);
     LAPS_LAUNCH_CHECK();
     hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(max_items, n_kv, HD / 4), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
-                       row_start, new_len, prefix_len, tile_start, item_seq, n_seq, n_q, n_kv, n_split, max_pages, n_tokens);
+                       row_start, new_len, prefix_len, tile_start, item_seq, n_seq, n_q, n_kv, n_split, min_tiles, max_pages, n_tokens);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -812,15 +813,20 @@ size_t laps_attn_partial_bytes(int hd, int max_pages) {
 // (sequence, row block) work items, and the number of key-range splits.  Depends only on shapes known to
 // the host (a captured graph must replay with the same grid whatever the lengths staged into it).
 static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* mt, int* max_items,
-                          int* n_split) {
+                          int* n_split, int* min_tiles) {
     const long total_rows = (long)n_tokens * group;
     const long items1 = total_rows / 128 + n_seq;      // bound with 128-row blocks
     const int max_kv_tiles = (max_pages * LAPS_PAGE + KT - 1) / KT;
     *n_split = 1;
+    *min_tiles = MIN_TILES_PER_SPLIT;
     if (items1 * n_kv < kSplitBelowBlocks && max_kv_tiles >= 2 * MIN_TILES_PER_SPLIT) {
         const int blocks0 = (int)items1 * n_kv;
+        // A turn or two of few tokens leave most compute units idle however fine the split: a workgroup per key tile where
+        // all of them fit one round (14B, 7 rows over 900 keys, with the rest of its one-layer graph: splits of at least
+        // 4 / 2 / 1 tiles 148.3 / 145.5 / 143.6 us).  Not for more: 32B, 2 turns of 32 over 2000 keys 26.3 / 28.3 / 28.2.
+        if ((long)blocks0 * max_kv_tiles <= 256) *min_tiles = 1;
         int ns = (kSplitTargetBlocks + blocks0 - 1) / blocks0;
-        ns = ns < max_kv_tiles / MIN_TILES_PER_SPLIT ? ns : max_kv_tiles / MIN_TILES_PER_SPLIT;
+        ns = ns < max_kv_tiles / *min_tiles ? ns : max_kv_tiles / *min_tiles;
         ns = ns < kSplitMax ? ns : kSplitMax;
         if (ns > 1) {
             *n_split = ns;
@@ -844,9 +850,8 @@ static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_
 void laps_attn_plan(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* rows_per_wg, int* max_items,
                     int* n_split, int* min_tiles_per_split) {
     int mt = 1;
-    attn_blocking(n_seq, n_tokens, group, n_kv, max_pages, &mt, max_items, n_split);
+    attn_blocking(n_seq, n_tokens, group, n_kv, max_pages, &mt, max_items, n_split, min_tiles_per_split);
     *rows_per_wg = 128 * mt;
-    *min_tiles_per_split = MIN_TILES_PER_SPLIT;
 }
 
 // Work-item table for laps_launch_attention; depends on the batch only, so a layer stack builds it once.
@@ -876,8 +881,8 @@ void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, in
 constexpr int MIN_TILES_PERSIST = 20;
 constexpr int GRID_CUT_COST = 20;   // what cutting costs against the grid: the merge launch comes on top
 int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes) {
-    int mt, max_items, n_split;
-    attn_blocking(n_seq, n_tokens, group, n_kv, max_pages, &mt, &max_items, &n_split);
+    int mt, max_items, n_split, min_tiles;
+    attn_blocking(n_seq, n_tokens, group, n_kv, max_pages, &mt, &max_items, &n_split, &min_tiles);
     const long tiles = (max_pages * (long)LAPS_PAGE + KT - 1) / KT;
     if (mt != 2 || n_split != 1 || tiles < MIN_TILES_PERSIST) return 0;
     const size_t slot = (size_t)LAPS_ATTN_LONG_ROWS * (hd + 2) * sizeof(float);
@@ -901,8 +906,8 @@ int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, co
                           const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
                           int max_pages, int n_seq, int n_tokens, const int* tile_start, const int* item_seq,
                           float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s) {
-    int mt, max_items, n_split;
-    attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split);
+    int mt, max_items, n_split, min_tiles;
+    attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split, &min_tiles);
     const int n_wgs = partial ? laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes) : 0;
     if (n_wgs > 0) {
         int* pre;
@@ -917,8 +922,8 @@ int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, co
             laps_set_error("attention: key-split launch needs the partial-result workspace");
             return LAPS_EINVAL;
         }
-        if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, n_q, n_kv, n_pool_pages, n_tokens, s);
-        if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     if (hd == 128) {
         if (mt == 2) return launch_attn<128, 8>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);

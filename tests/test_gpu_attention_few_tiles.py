@@ -1,6 +1,7 @@
 """The attention of page tables a few key tiles wide (64 keys, 4 pages each): 128-row blocks up to 4 tiles, and up to 7 for
-launches whose blocks fit the chip at once; 256-row blocks from there on.  The rule on the host, and both sides of each of its
-edges against float64."""
+launches whose blocks fit the chip at once; 256-row blocks from there on.  From 8 tiles on, few blocks are split over the
+keys: one tile per workgroup where all of them fit one round of the 256 compute units, else four at least.  The rules on the
+host, and both sides of each of their edges against float64."""
 import ctypes as C
 
 import numpy as np
@@ -10,31 +11,38 @@ import torch
 from paper_2601_11589_amd import api, inputs
 from test_gpu_attention_shares import reference
 
-# (model, new tokens, cached tokens, pages of the table, query rows per workgroup)
+# (model, new tokens, cached tokens, pages of the table, (query rows per workgroup, splits of the keys, least tiles of a split))
 EDGES = [
-    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 130] * 10, 16, 128),       # 4 tiles, more blocks than the chip holds
-    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 193] * 10, 17, 256),       # 5 tiles, as many blocks
-    (inputs.qwen32b_cfg, [64] * 16, [384, 0, 1, 200] * 4, 28, 128),         # 7 tiles, 448 blocks
-    (inputs.qwen32b_cfg, [64] * 16, [385, 0, 1, 200] * 4, 29, 256),         # 8 tiles
-    (inputs.qwen32b_cfg, [1] * 8 + [63, 64] * 8, [0, 15] * 4 + [3, 384] * 8, 28, 128),
-    (inputs.qwen7b_cfg, [256, 129, 1, 77], [0, 127, 255, 64], 16, 128),     # blocks of 18 tokens, the last of few rows
-    (inputs.tiny_cfg, [65] * 140, [0, 63, 190, 191, 1] * 28, 16, 128),      # head dimension 64
-    (inputs.tiny_cfg, [65] * 140, [0, 63, 191, 192, 1] * 28, 17, 256),
-    (inputs.tiny_cfg, [65] * 120, [383] * 119 + [0], 28, 128),              # 480 blocks of head dimension 64
+    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 130] * 10, 16, (128, 1, 4)),       # 4 tiles, more blocks than the chip holds
+    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 193] * 10, 17, (256, 1, 4)),       # 5 tiles, as many blocks
+    (inputs.qwen32b_cfg, [64] * 16, [384, 0, 1, 200] * 4, 28, (128, 1, 4)),         # 7 tiles, 448 blocks
+    (inputs.qwen32b_cfg, [64] * 16, [385, 0, 1, 200] * 4, 29, (256, 1, 4)),         # 8 tiles
+    (inputs.qwen32b_cfg, [1] * 8 + [63, 64] * 8, [0, 15] * 4 + [3, 384] * 8, 28, (128, 1, 4)),
+    (inputs.qwen7b_cfg, [256, 129, 1, 77], [0, 127, 255, 64], 16, (128, 1, 4)),     # blocks of 18 tokens, the last of few rows
+    (inputs.tiny_cfg, [65] * 140, [0, 63, 190, 191, 1] * 28, 16, (128, 1, 4)),      # head dimension 64
+    (inputs.tiny_cfg, [65] * 140, [0, 63, 191, 192, 1] * 28, 17, (256, 1, 4)),
+    (inputs.tiny_cfg, [65] * 120, [383] * 119 + [0], 28, (128, 1, 4)),              # 480 blocks of head dimension 64
+    (inputs.qwen14b_cfg, [7], [900], 57, (128, 15, 1)),
+    (inputs.qwen32b_cfg, [8], [2040], 128, (128, 32, 1)),                   # 8 blocks x 32 tiles
+    (inputs.qwen32b_cfg, [8], [2041], 129, (128, 8, 4)),                    # 8 x 33
+    (inputs.qwen7b_cfg, [9], [4087], 256, (128, 64, 1)),                    # 4 x 64, as many splits as there may be
+    (inputs.qwen32b_cfg, [3, 5], [600, 0], 38, (128, 10, 1)),               # the second sequence is one split's
+    (inputs.tiny_cfg, [100], [1900], 125, (128, 32, 1)),                    # rows that see no key of the last splits
+    (inputs.tiny_cfg, [200, 64, 1], [321, 448, 511], 33, (128, 9, 1)),
 ]
 
 
-def rows_per_workgroup(cfg, new, pages):
+def blocking(cfg, new, pages):
     out = (C.c_int64 * 6)()
     assert api.lib().laps_attn_plan_info(len(new), sum(new), cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, pages, out) == 0
-    return out[0], out[2]
+    return out[0], out[2], out[3]
 
 
 @pytest.mark.parametrize("case", range(len(EDGES)))
 def test_blocks_of_a_few_key_tiles(case):
-    cfgf, new, pre, pages, rows = EDGES[case]
+    cfgf, new, pre, pages, want = EDGES[case]
     assert max(-(-(n + h) // 16) for n, h in zip(new, pre)) <= pages
-    assert rows_per_workgroup(cfgf(1), new, pages) == (rows, 1)
+    assert blocking(cfgf(1), new, pages) == want
 
 
 @pytest.mark.gpu
