@@ -25,6 +25,7 @@
 // Workgroup ids are remapped so that each of the 8 XCDs (workgroups are dealt to them round-robin)
 // gets a contiguous range of tiles, walked M-fastest in groups of 8 row tiles: the workgroups
 // sharing a weight panel sit on one XCD and hit its L2.
+#include <algorithm>
 #include <type_traits>
 
 #include "laps_internal.h"
@@ -909,11 +910,16 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         // the 32B down projection, 36 slabs per slice, stays on 256 columns: 61.2 against 65.8).  At most 256
         // workgroups either way: a streaming kernel with 257 leaves one CU with twice the work.
         auto auto_split = [&](int c) {
-            // K slabs per slice below which the pipeline is all prologue; where raw sums are read by a row kernel anyhow, 8
-            // (7B q/k/v at 8 / 128 rows: 4 slices of 14 slabs 8.7 / 15.1 us, 7 of 8 7.6 / 12.6)
-            const int min_steps = c == 5 || want_epi == EPI_PARTIAL ? 8 : 16;
-            int sp = 256 / (n / kTiles[c].bn);
-            const int cap = (ksteps + min_steps / 2) / min_steps;
+            // Slices of 16 slabs or more: below, the pipeline is all prologue.  8 where a row kernel reads raw sums anyhow (q/k/v
+            // in the 7B layer at 8 / 128 rows: 4 slices of 14 slabs 8.7 / 15.1 us, 7 of 8 7.6 / 12.6).  Raw sums of a product of
+            // its own are its result if K is one slice, and cost a launch and a workspace if not (3584 columns, K = 768, 128
+            // rows: one slice 11.1, two 13.1); where 16 slabs split K already, up to 4 slices of 8 pay, and more until they fill
+            // half the chip (48 rows: 512 x 2560 3 slices 12.4, 5 8.9; 2048 x 3584 4 slices 12.0, 7 10.8; 7168 x 1920, 64 rows,
+            // 2 slices 17.1, 4 14.2; but 4608 x 3584 4 slices 14.2, 7 16.1).
+            const int tiles = n / kTiles[c].bn, fine = (ksteps + 4) / 8;
+            int sp = 256 / tiles, cap = (ksteps + 8) / 16;
+            if (c == 5 || (want_epi == EPI_PARTIAL && row_kernel)) cap = fine;
+            else if (want_epi == EPI_PARTIAL && cap > 1) cap = std::max(cap, std::min(fine, std::max(4, 128 / tiles)));
             sp = sp > cap ? cap : sp;
             return sp < 1 ? 1 : sp;
         };
@@ -997,7 +1003,7 @@ size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap) {   // m
     // upper bound over the epilogue kinds the layer driver may request
     size_t b = 0;
     for (int e = 0; e < 3; ++e) {
-        const GemmPlan p = laps_gemm_plan(m, n, k, 0, e, partial_cap);
+        const GemmPlan p = laps_gemm_plan(m, n, k, 0, e, partial_cap, e == EPI_PARTIAL, true);   // raw sums: q/k/v
         const size_t t = p.split > 1 ? (size_t)p.split * m * n * sizeof(float) : 0;
         b = t > b ? t : b;
     }

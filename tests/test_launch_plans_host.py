@@ -74,6 +74,21 @@ def test_forced_k_splits_are_clamped_to_whole_slices():
                 assert (p["k_per"] // 64) % p["ws"] == 0 and ((k - (p["split"] - 1) * p["k_per"]) // 64) % p["ws"] == 0
 
 
+@pytest.mark.parametrize("m", [1, 8, 64, 128])
+def test_products_of_their_own_up_to_128_rows_keep_long_k_slices(m):
+    """No row kernel reads the sums of a product of its own: K below 24 slabs stays one launch that needs no workspace, and
+    from there on slices hold about 16 slabs, or 8 while there are no more than 4 or they fill no more than 128 compute units."""
+    for n in (64, 192, 512, 3584, 4608, 7168, 8192):
+        for steps in list(range(1, 40)) + [56, 64, 80]:
+            p = gemm_plan(m, n, steps * 64)
+            if p["bn"] == 256:
+                continue
+            need = api.lib().laps_gemm_workspace_bytes(C.c_int32(m), C.c_int32(n), C.c_int32(steps * 64), C.c_int32(0))
+            if steps < 24:
+                assert p["split"] == 1 and need == 0, (n, steps, p, need)
+            assert p["split"] <= max(1, (steps + 8) // 16) or (p["split"] <= (steps + 4) // 8 and (p["split"] <= 4 or p["wgs"] <= 128)), (n, steps, p)
+
+
 def test_plan_info_rejects_unsupported_shapes():
     lib = api.lib()
     out = (C.c_int32 * 7)()
