@@ -7,9 +7,10 @@
 // 16-byte read.  A workgroup owns a BM x BN output tile and one K slice, and walks it in slabs of 64.
 //
 // Two kinds of tile:
-//  * dma_tile (v_mfma_f32_16x16x32_bf16): slabs go straight into LDS; all tiles of rows of less than 2^22 values;
+//  * dma_tile (v_mfma_f32_16x16x32_bf16): slabs go straight into LDS; operands of 16-byte alignment and rows of less than
+//    2^22 values;
 //  * far_tile (v_mfma_f32_32x32x16_bf16): slabs go HBM -> registers -> LDS, every row has a pointer; the longer rows, which
-//    32-bit offsets do not reach.
+//    32-bit offsets do not reach, and operands that are aligned to their elements only.
 //
 // far_tile's K loop is software-pipelined by hand:
 //   * fragments of k-step kk+1 are read from LDS into a second register set before the MFMAs of
@@ -59,6 +60,10 @@ struct Traits {
     static_assert(BM * CHUNKS % NT == 0 && BN * CHUNKS % NT == 0, "tile rows must divide over threads");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA");
 };
+
+// 16-byte accesses to the caller's arrays, which are aligned to their elements only
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 
 struct TileCoord {
     int tm, tn, ks;
@@ -224,12 +229,12 @@ __device__ __forceinline__ void far_tile(const GemmArgs& g, unsigned char* smem,
     static_assert(RPP % 16 == 0, "rows of a thread must share a swizzle");
     const int row0 = tid / CHUNKS, kc0 = tid % CHUNKS;
     const int dst0 = row0 * CHUNKS + swz(row0, kc0);
-    const u32x4* ag[T::A_LOADS];
-    const u32x4* bg[T::B_LOADS];
+    const u32x4_a2* ag[T::A_LOADS];
+    const u32x4_a2* bg[T::B_LOADS];
     u32x4 rrb[WS][T::B_LOADS];   // staged W slabs: slab j lives in set j % WS
 #pragma unroll
     for (int i = 0; i < T::B_LOADS; ++i) {
-        bg[i] = reinterpret_cast<const u32x4*>(g.W + (size_t)(n0 + row0 + i * RPP) * K + kbeg) + kc0;
+        bg[i] = reinterpret_cast<const u32x4_a2*>(g.W + (size_t)(n0 + row0 + i * RPP) * K + kbeg) + kc0;
         rrb[0][i] = *bg[i];
     }
     u32x4 rra[WS][T::A_LOADS];   // staged A slabs, same rule as rrb
@@ -237,7 +242,7 @@ __device__ __forceinline__ void far_tile(const GemmArgs& g, unsigned char* smem,
     for (int i = 0; i < T::A_LOADS; ++i) {
         const int row = row0 + i * RPP;
         const int gr = (m0 + row < M) ? (m0 + row) : (M - 1);  // clamp: rows past M are never stored
-        ag[i] = reinterpret_cast<const u32x4*>(g.A + (size_t)gr * K + kbeg) + kc0;
+        ag[i] = reinterpret_cast<const u32x4_a2*>(g.A + (size_t)gr * K + kbeg) + kc0;
     }
     // fragment read offsets (in 16-byte chunks) inside one LDS buffer, per k-step
     int a_src[T::MI], b_src[T::NI];
@@ -408,9 +413,6 @@ struct DmaTraits {
 template <bool PAIRED>
 __device__ __forceinline__ int dma_key(int row) { return PAIRED ? ((row >> 1) & 1) | (((row >> 3) & 3) << 1) : (row >> 1) & 7; }
 
-// 16-byte accesses to the caller's arrays, which are aligned to their elements only
-typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 // The weights are the matrix instruction's first operand, so that a lane holds four consecutive columns (16 ni + 4 lk + r)
@@ -1046,8 +1048,11 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     g.out_bf16 = out_bf16;
     g.row_live = row_live;
     g.n_live = n_live;
+    // Loads straight into LDS are given 16-byte pieces that lie on 16-byte bounds: rows are whole multiples of 128 bytes, so
+    // the bases decide.  (5120 x 5120 at 8 / 128 / 2048 rows, weights cold: 22 / 25 / 92 us, with weights 2 bytes off 26 / 30 / 155.)
+    const bool aligned = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w)) & 15) == 0;
     // batches of an unknown number of live rows, un-split plans of the 256- and 320-row tiles: chosen on the device
-    if (live_varies && n_live && m > 256 && p.split == 1 && kTiles[p.cfg].bm >= 256 && n % 256 == 0) {
+    if (aligned && live_varies && n_live && m > 256 && p.split == 1 && kTiles[p.cfg].bm >= 256 && n % 256 == 0) {
         if (n % 160 == 0 && p.epi == EPI_PARTIAL) return launch_live<160, EPI_PARTIAL>(g, s);
         if (n % 160 == 0 && p.epi == EPI_RESID) return launch_live<160, EPI_RESID>(g, s);
         if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_live<224, EPI_PARTIAL>(g, s);
@@ -1056,14 +1061,23 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         if (n % 192 == 0 && p.epi == EPI_SWIGLU) return launch_live<192, EPI_SWIGLU>(g, s);
         if (p.epi == EPI_SWIGLU) return launch_live<0, EPI_SWIGLU>(g, s);
     }
-    if (k >= kMaxBufferK) {
+    if (k >= kMaxBufferK || !aligned) {
+        int cfg = p.cfg, ws = p.ws;
+        if (k < kMaxBufferK) {   // the plan's K slices on the widest pointer-addressed tile that fills the chip or divides n
+            const bool wide = n % 256 == 0 && (long)((m + 191) / 192) * (n / 256) * p.split >= 256;
+            cfg = wide ? 6 : n % 128 == 0 ? 7 : 1;
+            ws = 1;
+            g.tiles_m = (m + kTiles[cfg].bm - 1) / kTiles[cfg].bm;
+            g.tiles_n = n / kTiles[cfg].bn;
+        }
+        if (cfg == 1 && p.epi == EPI_SWIGLU) return launch_far<128, 64, 4, 1, EPI_SWIGLU, 1>(g, s);   // pairs in a wave of 64 columns
 #define LAPS_FAR_CASE(cfg, BM, BN, WS)                                                          \
     case (cfg) * 8 + (WS):                                                                      \
         if (p.epi == EPI_PARTIAL) return launch_far<BM, BN, 2, 2, EPI_PARTIAL, WS>(g, s);       \
         if (p.epi == EPI_RESID) return launch_far<BM, BN, 2, 2, EPI_RESID, WS>(g, s);           \
         if constexpr (BN % 128 == 0) return launch_far<BM, BN, 2, 2, EPI_SWIGLU, WS>(g, s);     \
         break
-        switch (p.cfg * 8 + p.ws) {
+        switch (cfg * 8 + ws) {
             LAPS_FAR_CASE(1, 128, 64, 1);
             LAPS_FAR_CASE(6, 192, 256, 1);
             LAPS_FAR_CASE(6, 192, 256, 2);
