@@ -60,9 +60,10 @@ __device__ __forceinline__ void split_geometry(int kv_end, int n_split, int min_
 
 // Two waves per SIMD in every variant (second launch-bound argument): with 4 waves per workgroup that is two
 // resident workgroups per compute unit, which the key-streaming launches need to cover the memory latency.
+// HALVES: the 4-wave loop forms its probabilities and row sums by half tiles, as the 8-wave loop does: the same bits.
 // PERSIST: a fixed number of workgroups, each walking its share of the batch (laps_dev_attn_bounds); a share may begin
 // and end inside a unit, whose parts then go through partial results like the splits.
-template <int HD, int NW, bool SPLIT, bool PERSIST>
+template <int HD, int NW, bool SPLIT, bool PERSIST, bool HALVES = false>
 __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         const bf16_t* __restrict__ k_pool,
@@ -293,6 +294,62 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
             o[g % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(vb, g), pf[g / (2 * NI)][(g / NI) & 1], o[g % NI], 0, 0, 0);
     };
 
+    // the same by half tiles of 32 keys (the 8-wave loop, HALVES)
+    [[maybe_unused]] auto mask_half = [&](int j0, int h, f32x16& sc) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int a = i >> 2, b = i & 3;
+            const int key = j0 + h * 32 + 16 * (a >> 1) + 8 * lh + 4 * (a & 1) + b;
+            sc[i] = (key <= limit) ? sc[i] : -INFINITY;
+        }
+    };
+    // Row sums come from the matrix cores as well: a fragment of ones times P^T gives, in every register of the
+    // result, the sum over the fragment's keys of the probabilities as the second product sees them (rounded to
+    // bf16), complete in both lanes of a row.  It is added to l_run where the same probabilities are added to O.
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    [[maybe_unused]] auto softmax_half = [&](f32x16& sc, bf16x8 (&pf)[2]) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[i]);
+        mx = fmaxf(mx, from_partner(mx));
+        const float m_sub = pick_reference(mx);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            bf16x8 pk;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                pk[e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[8 * u + e], scale_log2e, -m_sub));
+            pf[u] = pk;
+        }
+    };
+    [[maybe_unused]] auto pv_half = [&](int vb, int h, bf16x8 (&pf)[2]) {
+#pragma unroll
+        for (int g = 0; g < 2 * NI; ++g)
+            o[g % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(vb, (2 * h + g / NI) * NI + g % NI), pf[g / NI],
+                                                                o[g % NI], 0, 0, 0);
+        f32x16 ls;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) ls[i] = 0.f;
+        ls = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[0], ls, 0, 0, 0);
+        ls = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[1], ls, 0, 0, 0);
+        l_run += ls[0];
+    };
+    // moves the reference to m_new after the matrix work of a half step (the probabilities just formed already
+    // use it; O and l_run, which hold the half tiles before, follow here)
+    [[maybe_unused]] auto move_reference = [&]() {
+        if (moved) {
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[ni][i] *= alpha;
+            m_run = m_new;
+        }
+    };
+
     const auto exists = [&](int j) { return j < kv_end; };
     if constexpr (NW == 8) {
         // Long prompts.  The loop is software-pipelined three deep over 32-key half tiles: in step w the matrix
@@ -333,60 +390,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
 #pragma unroll
             for (int kk = 0; kk < KSTEPS; ++kk)
                 sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(kb, 2 * kk + h), qf[kk], sc, 0, 0, 0);
-        };
-        auto mask_half = [&](int j0, int h, f32x16& sc) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int a = i >> 2, b = i & 3;
-                const int key = j0 + h * 32 + 16 * (a >> 1) + 8 * lh + 4 * (a & 1) + b;
-                sc[i] = (key <= limit) ? sc[i] : -INFINITY;
-            }
-        };
-        // Row sums come from the matrix cores as well: a fragment of ones times P^T gives, in every register of the
-        // result, the sum over the fragment's keys of the probabilities as the second product sees them (rounded to
-        // bf16), complete in both lanes of a row.  It is added to l_run where the same probabilities are added to O.
-        bf16x8 ones;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
-        auto softmax_half = [&](f32x16& sc, bf16x8 (&pf)[2]) {
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[i]);
-            mx = fmaxf(mx, from_partner(mx));
-            const float m_sub = pick_reference(mx);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                bf16x8 pk;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    pk[e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[8 * u + e], scale_log2e, -m_sub));
-                pf[u] = pk;
-            }
-        };
-        auto pv_half = [&](int vb, int h, bf16x8 (&pf)[2]) {
-#pragma unroll
-            for (int g = 0; g < 2 * NI; ++g)
-                o[g % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(vb, (2 * h + g / NI) * NI + g % NI), pf[g / NI],
-                                                                    o[g % NI], 0, 0, 0);
-            f32x16 ls;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) ls[i] = 0.f;
-            ls = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[0], ls, 0, 0, 0);
-            ls = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[1], ls, 0, 0, 0);
-            l_run += ls[0];
-        };
-        // moves the reference to m_new after the matrix work of a half step (the probabilities just formed already
-        // use it; O and l_run, which hold the half tiles before, follow here)
-        auto move_reference = [&]() {
-            if (moved) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha;
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[ni][i] *= alpha;
-                m_run = m_new;
-            }
         };
         // one half step.  (kb, hq): buffer and half of the scores to form into s_nxt; s_cur -> pf_cur; (vb, hv):
         // buffer and half of the V tile that goes with pf_prev
@@ -536,10 +539,21 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
                 f32x16 sc[2];
                 bf16x8 pf[2][2];
                 qk_tile(buf, sc);
-                if (j0 + KT - 1 > vis_min) mask_tile(j0, sc);
-                softmax_tile(sc, pf);
-                softmax_finish();
-                pv_tile(buf, pf);
+                if constexpr (HALVES) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (j0 + 32 * h > vis_max) continue;
+                        if (j0 + 32 * h + 31 > vis_min) mask_half(j0, h, sc[h]);
+                        softmax_half(sc[h], pf[h]);
+                        move_reference();
+                        pv_half(buf, h, pf[h]);
+                    }
+                } else {
+                    if (j0 + KT - 1 > vis_min) mask_tile(j0, sc);
+                    softmax_tile(sc, pf);
+                    softmax_finish();
+                    pv_tile(buf, pf);
+                }
             }
             __syncthreads();
         }
@@ -547,8 +561,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
 
     // ---- normalise and store: lane owns row r; register i of sub-tile ni is head_dim index
     //      ni*32 + 8*(i/4) + 4*(lane/32) + i%4
-    // the pipelined loop holds complete row sums, the plain one a lane's share
-    const float l_tot = (NW == 8) ? l_run : l_run + __shfl_xor(l_run, 32, 64);
+    // row sums by half tiles are complete, the plain loop's are a lane's share
+    const float l_tot = (NW == 8 || HALVES) ? l_run : l_run + __shfl_xor(l_run, 32, 64);
     if (!whole) {
         // partial result of this key range: accumulator as [4-float chunk][row] so that the 32 rows of a half
         // wave write consecutive 16-byte pieces; (running max, row sum) per row
@@ -745,13 +759,13 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     *reinterpret_cast<u32x2*>(op + 4 * c) = o2;
 }
 
-template <int HD, int NW>
+template <int HD, int NW, bool HALVES = false>
 int launch_attn(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool, const int* row_start,
                 const int* new_len, const int* prefix_len, const int* page_table, int max_pages, const int* tile_start,
                 const int* item_seq, int n_seq, int max_items, int n_q, int n_kv, int n_pool_pages, int n_tokens,
                 hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
-    hipLaunchKernelGGL((attn_kernel<HD, NW, false, false>), dim3(max_items, n_kv), dim3(NW * 64), 0, s, q, out, nullptr,
+    hipLaunchKernelGGL((attn_kernel<HD, NW, false, false, HALVES>), dim3(max_items, n_kv), dim3(NW * 64), 0, s, q, out, nullptr,
                        nullptr, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq,
                        n_seq, n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, 0, nullptr);
     LAPS_LAUNCH_CHECK();
@@ -925,12 +939,18 @@ int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, co
         if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
         if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
+    // 128-row blocks that would be 256-row ones over more key tiles: summed up as those do, so that the width of the page table
+    // does not show in the result (the sums of rounded probabilities are also the ones that match the second product:
+    // 32B prompts of 64 tokens 1.79e-3 from 64 bits, with sums of unrounded ones 1.81e-3; the same time)
+    const bool halves = (long)n_tokens * (n_q / n_kv) > 128L * n_seq;
     if (hd == 128) {
         if (mt == 2) return launch_attn<128, 8>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (halves) return launch_attn<128, 4, true>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
         return launch_attn<128, 4>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     if (hd == 64) {
         if (mt == 2) return launch_attn<64, 8>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (halves) return launch_attn<64, 4, true>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
         return launch_attn<64, 4>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     laps_set_error("attention: head_dim %d not supported (64 or 128)", hd);

@@ -1,7 +1,8 @@
 """The attention of page tables a few key tiles wide (64 keys, 4 pages each): 128-row blocks up to 4 tiles, and up to 7 for
 launches whose blocks fit the chip at once; 256-row blocks from there on.  From 8 tiles on, few blocks are split over the
 keys: one tile per workgroup where all of them fit one round of the 256 compute units, else four at least.  The rules on the
-host, and both sides of each of their edges against float64."""
+host, and both sides of each of their edges against float64, and the same bits from 128- and
+256-row blocks."""
 import ctypes as C
 
 import numpy as np
@@ -45,13 +46,10 @@ def test_blocks_of_a_few_key_tiles(case):
     assert blocking(cfgf(1), new, pages) == want
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("case", range(len(EDGES)))
-def test_attention_of_a_few_key_tiles_matches_float64(case):
-    cfgf, new, pre, pages, _ = EDGES[case]
+def operands(case, seed, pages):
+    cfgf, new, pre, _, _ = EDGES[case]
     cfg = cfgf(1)
-    ctx = api.LapsCtx(cfg, 64)
-    g = torch.Generator(device="cuda").manual_seed(31 + case)
+    g = torch.Generator(device="cuda").manual_seed(seed + case)
     cu = np.concatenate([[0], np.cumsum(new)])
     table, n_pages = inputs.make_page_table(5, new, pre)
     table = np.pad(table, ((0, 0), (0, pages - table.shape[1])), constant_values=-1)
@@ -59,6 +57,30 @@ def test_attention_of_a_few_key_tiles_matches_float64(case):
     d = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).cuda()
     q = draw((int(cu[-1]), cfg.q_dim), 2.5)
     kp, vp = draw((n_pages, cfg.n_kv_heads, 16, cfg.head_dim)), draw((n_pages, cfg.n_kv_heads, cfg.head_dim, 16))
+    return cfg, new, pre, cu, d, table, kp, vp, q
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case,pages", [(0, 17), (2, 29), (6, 17), (8, 29)])
+def test_blocks_of_128_and_256_rows_give_the_same_bits(case, pages):
+    """A page table a page wider takes the launch to the other kind of block."""
+    cfgf, new, _, narrow, _ = EDGES[case]
+    assert blocking(cfgf(1), new, narrow)[0] == 128 and blocking(cfgf(1), new, pages)[0] == 256
+    out = []
+    for p in (narrow, pages):
+        cfg, new, pre, cu, d, table, kp, vp, q = operands(case, 77, p)
+        ctx = api.LapsCtx(cfg, 64)
+        out.append(ctx.laps_attention(d(cu), None, d(pre), d(table), kp, vp, q))
+        torch.cuda.synchronize()
+        ctx.close()
+    assert torch.equal(*out)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(EDGES)))
+def test_attention_of_a_few_key_tiles_matches_float64(case):
+    cfg, new, pre, cu, d, table, kp, vp, q = operands(case, 31, EDGES[case][3])
+    ctx = api.LapsCtx(cfg, 64)
     run = lambda: ctx.laps_attention(d(cu), None, d(pre), d(table), kp, vp, q).double().view(-1, cfg.n_q_heads, cfg.head_dim)
     got = run()
     assert torch.equal(got, run())
