@@ -850,11 +850,18 @@ static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_
         }
     }
     // Few key tiles: 256-row blocks pay for their pipelined loop (three stages to fill and drain) and for the rows that fill
-    // no block, so 128-row ones take all launches of up to 4 tiles, and up to the split's 8 those that fit the chip at once.
-    // Attention alone with its scheduling kernel, 256- against 128-row blocks: 32B, 16 / 32 / 64 prompts of 64 tokens 21.7 / 35.9
-    // / 63.1 against 17.9 / 27.5 / 42.6 us, one of 440 27.5 against 22.5, 8 turns of 64 over 200 keys 24.1 against 19.3; 7B, 64
-    // prompts 37.3 against 35.2, but 64 turns over 380 keys 63.4 against 68.3.
-    const bool few = max_kv_tiles <= 4 || (max_kv_tiles < 2 * MIN_TILES_PER_SPLIT && items1 * n_kv <= 512);
+    // no block; 128-row blocks pay by reading the keys twice and without the pipeline.  Up to the split's 8 tiles 128 rows are
+    // the faster ones where each block has a compute unit (256- against 128-row blocks, attention with its scheduling kernel:
+    // 32B, 8 turns of 64 in 440 keys 29.2 and 24.3 us, a prompt of 440 27.5 and 23.6).  With more blocks than units 5 to 7 tiles
+    // are the pipeline's (12 turns of 100 in 440 keys 31.5 and 35.0).  Up to 4 tiles 128 rows win where they spare a quarter of
+    // the rows (40 turns of 64 in 256 keys 40.5 and 31.5) or take more than one round of two blocks a unit: ragged turns by
+    // 1.08 to 1.25 (47 turns of 33 to 64 over up to 100 keys 42.3 and 33.8); lost are batches of equal lengths that fill rounds
+    // of 256-row blocks exactly (7B, 64 turns of 64 in 256 keys 49.7 and 52.0).  Between, ragged batches gain or lose 3 %, equal
+    // ones lose up to 10 %.  Up to 2 tiles 128 rows always win (64 prompts of 64 tokens 44.0 and 37.4).
+    const long blocks1 = items1 * n_kv;
+    const bool spares = total_rows > 256L * n_seq && total_rows <= 384L * n_seq;   // 3 blocks of 128 rows instead of 2 of 256
+    const bool few = max_kv_tiles <= 2 || (max_kv_tiles <= 4 && (spares || blocks1 > 512)) ||
+                     (max_kv_tiles < 2 * MIN_TILES_PER_SPLIT && blocks1 <= 256);
     *mt = (!few && total_rows > 128L * n_seq) ? 2 : 1;  // average rows per sequence above one 128-row block
     const int rows_per_wg = 128 * *mt;
     // every sequence contributes ceil(rows/rows_per_wg) blocks: at most rows/rows_per_wg + 1

@@ -1,8 +1,8 @@
-"""The attention of page tables a few key tiles wide (64 keys, 4 pages each): 128-row blocks up to 4 tiles, and up to 7 for
-launches whose blocks fit the chip at once; 256-row blocks from there on.  From 8 tiles on, few blocks are split over the
-keys: one tile per workgroup where all of them fit one round of the 256 compute units, else four at least.  The rules on the
-host, and both sides of each of their edges against float64, and the same bits from 128- and
-256-row blocks."""
+"""The attention of page tables a few key tiles wide (64 keys, 4 pages each): 128-row blocks up to 2 tiles, up to 4 where they
+spare a quarter of the rows or are more than two a compute unit, and up to 7 for launches of a block per compute unit at most; 256-row blocks
+else.  From 8 tiles on, few blocks are split over the keys: one tile per workgroup where all of them fit one round of the 256
+compute units, else four at least.  The rules on the host, both sides of each of their edges against float64, and the same bits
+from 128- and 256-row blocks."""
 import ctypes as C
 
 import numpy as np
@@ -14,15 +14,22 @@ from test_gpu_attention_shares import reference
 
 # (model, new tokens, cached tokens, pages of the table, (query rows per workgroup, splits of the keys, least tiles of a split))
 EDGES = [
-    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 130] * 10, 16, (128, 1, 4)),       # 4 tiles, more blocks than the chip holds
+    (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 130] * 10, 16, (128, 1, 4)),       # 4 tiles, 1120 blocks, 320 rows a sequence
     (inputs.qwen32b_cfg, [64] * 40, [0, 192, 17, 193] * 10, 17, (256, 1, 4)),       # 5 tiles, as many blocks
-    (inputs.qwen32b_cfg, [64] * 16, [384, 0, 1, 200] * 4, 28, (128, 1, 4)),         # 7 tiles, 448 blocks
+    (inputs.qwen32b_cfg, [76] * 15, [0, 180, 17, 130, 52] * 3, 16, (128, 1, 4)),    # 472 blocks, 380 rows a sequence
+    (inputs.qwen32b_cfg, [77] * 15, [0, 179, 17, 130, 51] * 3, 16, (256, 1, 4)),    # 385
+    (inputs.qwen7b_cfg, [64] * 28, [0, 192, 136, 5] * 7, 16, (256, 1, 4)),          # 4 tiles, 504 blocks, 448 rows a sequence
+    (inputs.qwen7b_cfg, [64] * 29, [0, 192, 136, 5] * 7 + [70], 16, (128, 1, 4)),   # 520 blocks
+    (inputs.qwen32b_cfg, [64] * 8, [384, 0, 1, 200] * 2, 28, (128, 1, 4)),          # 7 tiles, 224 blocks
+    (inputs.qwen32b_cfg, [64] * 8, [385, 0, 1, 200] * 2, 29, (128, 2, 4)),          # 8 tiles
+    (inputs.qwen32b_cfg, [64] * 16, [384, 0, 1, 200] * 4, 28, (256, 1, 4)),         # 7 tiles, 448 blocks
     (inputs.qwen32b_cfg, [64] * 16, [385, 0, 1, 200] * 4, 29, (256, 1, 4)),         # 8 tiles
-    (inputs.qwen32b_cfg, [1] * 8 + [63, 64] * 8, [0, 15] * 4 + [3, 384] * 8, 28, (128, 1, 4)),
+    (inputs.qwen32b_cfg, [1] * 4 + [63, 64] * 4, [0, 15] * 2 + [3, 384] * 4, 28, (128, 1, 4)),
     (inputs.qwen7b_cfg, [256, 129, 1, 77], [0, 127, 255, 64], 16, (128, 1, 4)),     # blocks of 18 tokens, the last of few rows
-    (inputs.tiny_cfg, [65] * 140, [0, 63, 190, 191, 1] * 28, 16, (128, 1, 4)),      # head dimension 64
-    (inputs.tiny_cfg, [65] * 140, [0, 63, 191, 192, 1] * 28, 17, (256, 1, 4)),
-    (inputs.tiny_cfg, [65] * 120, [383] * 119 + [0], 28, (128, 1, 4)),              # 480 blocks of head dimension 64
+    (inputs.tiny_cfg, [65] * 120, [0, 63, 62, 31, 1] * 24, 8, (128, 1, 4)),         # head dimension 64, 2 tiles, 482 blocks
+    (inputs.tiny_cfg, [65] * 120, [0, 63, 64, 31, 1] * 24, 9, (256, 1, 4)),         # 3 tiles
+    (inputs.tiny_cfg, [65] * 60, [383] * 59 + [0], 28, (128, 1, 4)),                # 242 blocks of head dimension 64
+    (inputs.tiny_cfg, [65] * 68, [383] * 67 + [0], 28, (256, 1, 4)),                # 274
     (inputs.qwen14b_cfg, [7], [900], 57, (128, 15, 1)),
     (inputs.qwen32b_cfg, [8], [2040], 128, (128, 32, 1)),                   # 8 blocks x 32 tiles
     (inputs.qwen32b_cfg, [8], [2041], 129, (128, 8, 4)),                    # 8 x 33
@@ -61,7 +68,7 @@ def operands(case, seed, pages):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case,pages", [(0, 17), (2, 29), (6, 17), (8, 29)])
+@pytest.mark.parametrize("case,pages", [(0, 17), (2, 17), (5, 17), (12, 9)])
 def test_blocks_of_128_and_256_rows_give_the_same_bits(case, pages):
     """A page table a page wider takes the launch to the other kind of block."""
     cfgf, new, _, narrow, _ = EDGES[case]
