@@ -835,10 +835,14 @@ static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_
     *min_tiles = MIN_TILES_PER_SPLIT;
     if (items1 * n_kv < kSplitBelowBlocks && max_kv_tiles >= 2 * MIN_TILES_PER_SPLIT) {
         const int blocks0 = (int)items1 * n_kv;
-        // A turn or two of few tokens leave most compute units idle however fine the split: a workgroup per key tile where
-        // all of them fit one round (14B, 7 rows over 900 keys, with the rest of its one-layer graph: splits of at least
-        // 4 / 2 / 1 tiles 148.3 / 145.5 / 143.6 us).  Not for more: 32B, 2 turns of 32 over 2000 keys 26.3 / 28.3 / 28.2.
-        if ((long)blocks0 * max_kv_tiles <= 256) *min_tiles = 1;
+        // A turn or two of few tokens leave most compute units idle however fine the split: a workgroup per key tile where all
+        // of them fit one round, as wide as the page table is, and the rows of their partial results are few.  Attention with
+        // its scheduling kernel, splits of at least 4 tiles and of one: 7B, a turn of 7 over 900 / 2000 / 4000 keys 17.5 / 16.7 /
+        // 18.4 and 13.2 / 13.4 / 16.7; 14B, 7 rows over 900 keys with the rest of its one-layer graph 148.3 and 143.6 (a table of
+        // 129 pages and more leaves that at 4 tiles).  Not for more workgroups (32B, 2 turns of 32 over 2000 keys 26.3 / 28.2) or
+        // rows (7B, a turn of 16 over 4000 keys, 64 x 112 rows, 19.5 / 20.4; tiny model, 64 x 128, 14.5 / 14.8; 48 x 128 still
+        // 15.2 / 13.8).
+        if ((long)blocks0 * max_kv_tiles <= 256 && total_rows * max_kv_tiles <= 6400) *min_tiles = 1;
         int ns = (kSplitTargetBlocks + blocks0 - 1) / blocks0;
         ns = ns < max_kv_tiles / *min_tiles ? ns : max_kv_tiles / *min_tiles;
         ns = ns < kSplitMax ? ns : kSplitMax;

@@ -1,8 +1,8 @@
 """The attention of page tables a few key tiles wide (64 keys, 4 pages each): 128-row blocks up to 2 tiles, up to 4 where they
-spare a quarter of the rows or are more than two a compute unit, and up to 7 for launches of a block per compute unit at most; 256-row blocks
-else.  From 8 tiles on, few blocks are split over the keys: one tile per workgroup where all of them fit one round of the 256
-compute units, else four at least.  The rules on the host, both sides of each of their edges against float64, and the same bits
-from 128- and 256-row blocks."""
+spare a quarter of the rows or are more than two a compute unit, and up to 7 for launches of a block per compute unit at most;
+256-row blocks else.  From 8 tiles on, few blocks are split over the keys: one tile per workgroup where all of them fit one
+round of the 256 compute units and have at most 6400 rows of partial results, else four at least.  The rules on the host, both
+sides of each of their edges against float64, and the same bits from 128- and 256-row blocks."""
 import ctypes as C
 
 import numpy as np
@@ -34,6 +34,8 @@ EDGES = [
     (inputs.qwen32b_cfg, [8], [2040], 128, (128, 32, 1)),                   # 8 blocks x 32 tiles
     (inputs.qwen32b_cfg, [8], [2041], 129, (128, 8, 4)),                    # 8 x 33
     (inputs.qwen7b_cfg, [9], [4087], 256, (128, 64, 1)),                    # 4 x 64, as many splits as there may be
+    (inputs.qwen7b_cfg, [16], [3000], 189, (128, 48, 1)),                   # 112 rows x 48
+    (inputs.qwen7b_cfg, [16], [4080], 256, (128, 16, 4)),                   # 112 x 64
     (inputs.qwen32b_cfg, [3, 5], [600, 0], 38, (128, 10, 1)),               # the second sequence is one split's
     (inputs.tiny_cfg, [100], [1900], 125, (128, 32, 1)),                    # rows that see no key of the last splits
     (inputs.tiny_cfg, [200, 64, 1], [321, 448, 511], 33, (128, 9, 1)),
