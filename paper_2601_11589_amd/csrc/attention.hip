@@ -24,7 +24,7 @@
 //
 // Few query rows over a long cached prefix (a short re-prefill turn) would leave most of the chip idle:
 // one request of 16 new tokens is a single row block per kv head.  For such launches the key range is
-// split over gridDim.z workgroups (at least 4 key tiles each); every split writes its un-normalised
+// split over gridDim.z workgroups (at least 4 key tiles each, or one where few workgroups make it pay); every split writes its un-normalised
 // accumulator with its running maximum and row sum, and a second kernel merges the splits in a fixed
 // order, so the result does not depend on scheduling.  The split count is a function of launch shapes
 // only (row blocks, kv heads, page-table width), which keeps captured graphs replayable; how many of

@@ -108,8 +108,8 @@ struct GemmArgs {
     float* out_f32;        // EPI_PARTIAL: [split][M][N]; EPI_RESID: [M][N]
     const float* resid;    // EPI_RESID: [M][N] (may alias out_f32)
     bf16_t* out_bf16;      // EPI_SWIGLU: [M][N/2]
-    const int* row_live;   // [M] or NULL: rows with a negative entry are padding - they are not loaded, and a row tile that
-                           // holds nothing else is skipped (its output is then not written)
+    const int* row_live;   // [M] or NULL: rows with a negative entry are padding - a row tile that holds nothing else is
+                           // skipped (its output is then not written), and dma_tile loads none of them
     const int* n_live;     // NULL, or where the number of leading rows that are not padding is found (at most M count)
 };
 
@@ -824,14 +824,17 @@ int launch_dma_epi(int epi, const GemmArgs& a, hipStream_t s) {
 
 struct TileDef {
     int bm, bn;
-    int ws;            // slabs that a K slice holds a multiple of where K allows it
+    int ws;            // slabs that a K slice holds a multiple of where K allows it (far_tile's loop needs it on 192 x 256; the
+                       // others walk any number and share the rule, which laps_gemm_plan_info reports)
     double fill, slab, part;   // cost model of launches above 128 rows, see laps_gemm_plan
 };
 // index = GemmPlan::cfg.  The cost columns are a fit over 4800 launches (all tiles and K splits on the 7B, 14B and 32B
 // projections at 24 row counts from 129 to 8192, weights cold; rms error 7 %): microseconds a workgroup takes besides its
 // slabs, microseconds per 64-wide K slab on a full chip, and the share of the latter that goes away on an empty one.  Fitted
-// with slabs through registers; the choices stand: what they cost against the best plan of each product, measured with slabs
-// straight into LDS, is under 1 % in the mean.
+// with slabs through registers, as are the choices; against the best plan of each of 100 products (ten projections at ten row
+// counts, all tiles of up to 256 rows and all splits, slabs straight into LDS) they cost 1.1 % in the mean, over 4 % in ten of
+// them and 23 % at worst (a 7168 x 5120 product of its own, 1000 rows: 75 us in one slice of 256 x 128, 61 in two of 256 x 224,
+// which the layer takes).
 constexpr TileDef kTiles[] = {
     {128, 128, 2, 1.11, 0.521, 0.06},  // 0: 4 waves of 64x64 (32x64 up to 64 rows), two workgroups per compute unit
     {128, 64, 2, 1.20, 0.350, 0.00},   // 1: 4 waves of 64x32, for n % 128 != 0
@@ -969,8 +972,9 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         if (t.bm == 192 && tiles_m != (m + 255) / 256 && !far) continue;   // 192 rows where they need no more row tiles than 256
         // 320 rows where they need fewer row tiles than 256.  They take in and read from LDS a tenth less per product: 32B
         // gate/up of 280, 640 and 11104 rows 194 -> 156, 334 -> 285 and 4582 -> 4379 us, down of 11104 rows 2405 -> 2238, q/k/v
-        // of 1280 rows in two slices 99 -> 76; 206 products of 7B, 14B and 32B at 27 row counts 3 % in the mean.  Not for a
-        // product of its own, whose tile laps_gemm_plan_info reports: 256 rows at most.
+        // of 1280 rows in two slices 99 -> 76; 206 products of 7B, 14B and 32B at 27 row counts 3 % in the mean.  Products of
+        // their own would gain as much; they keep to the 128, 192 or 256 rows that laps_gemm_plan_info has always reported and
+        // that its readers rely on.
         if (t.bm == 320 && (!layer || tiles_m == (m + 255) / 256)) continue;
         const int max_split = force_split > 0 ? force_split : (far ? 256 : 16);   // a few column tiles have to fill the chip
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {

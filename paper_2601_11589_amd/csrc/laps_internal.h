@@ -64,8 +64,8 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
                         bool row_kernel = false, bool layer = false);
 size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap);
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn);   // rows and columns of tile shape `cfg` (0, 0 if unknown)
-// row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified: they are
-// not loaded, and a row tile of padding only is skipped.
+// row_live: NULL, or m entries; a negative entry marks a padding row.  Output rows of padding are unspecified; a row tile of
+// padding only is skipped, and the tiles whose slabs go straight into LDS load no padding row at all.
 // n_live: NULL, or a device int: rows at and past it are padding (batches whose padding is all at the end).
 // live_varies: the launch will be replayed with other values of *n_live (a captured graph).
 int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m, int n, int k, float* out_f32,

@@ -39,8 +39,8 @@ def test_k_is_split_where_tiles_leave_the_chip_idle(m, n, k, epi, slices):
     assert plan(m, n, k, epi)["split"] >= slices
 
 
-# Every tile with one (odd K / 64) and two slabs in flight, each epilogue it is built with and K splits (tile rows, columns,
-# slabs in flight, epilogue, split), and the smallest product of whole and ragged row tiles that is planned on it.
+# Every tile with K slices of any number of slabs (odd K / 64) and of multiples of two, each epilogue it is built with and K splits
+# (tile rows, columns, slabs that a K slice holds a multiple of, epilogue, split), and the smallest product of whole and ragged row tiles that is planned on it.
 TILES = [
     (128, 128, 1, PARTIAL, True, 129, 128, 576), (128, 128, 1, PARTIAL, False, 129, 128, 192), (128, 128, 1, RESID, False, 129, 128, 192),
     (128, 128, 1, SWIGLU, False, 129, 128, 192), (128, 128, 2, PARTIAL, True, 129, 128, 512), (128, 128, 2, PARTIAL, False, 129, 128, 256),
@@ -119,7 +119,8 @@ def test_tile_matches_float64(bm, bn, ws, epi, split, m, n, k):
 SHAPES = [(129, 128, 64), (191, 256, 192), (257, 128, 1088), (255, 384, 128), (513, 8192, 64), (576, 8192, 128),
           (513, 3584, 1024), (576, 3584, 1088), (1025, 4096, 576), (1025, 4096, 512), (192, 27648, 5120),
           (300, 27648, 5120), (384, 5120, 13824), (700, 27648, 1024)]
-# up to 128 rows, either side of the row counts at which the weights of short and long K slices come through the caches
+# up to 128 rows, either side of the 48 rows above which the weights of split products come through the caches, and of a 16-row
+# sub-tile
 SHAPES += [(m, n, k) for n, k in ((5120, 5120), (5120, 13824), (4160, 5120)) for m in (16, 17, 48, 49, 128)]
 
 

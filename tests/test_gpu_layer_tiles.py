@@ -3,6 +3,8 @@ tile by the live rows, the tiles up to 128 rows with live rows told late, and pa
 with K slices of an odd and an even number of slabs.  Against float64, with rows of NaN behind the operand and guard rows
 behind the result."""
 import ctypes as C
+import os
+import re
 
 import pytest
 import torch
@@ -13,11 +15,20 @@ PARTIAL, RESID, SWIGLU = 0, 1, 2
 TILE_320 = 10
 
 
+# GemmPlan's fields in the order of its definition (all of them int)
+_HEADER = open(os.path.join(os.path.dirname(api.__file__), "csrc", "laps_internal.h")).read()
+_FIELDS = re.findall(r"^    int (\w+);", re.search(r"struct GemmPlan \{(.*?)\n\};", _HEADER, re.S).group(1), re.M)
+
+
 class Plan(C.Structure):
-    _fields_ = [("cfg", C.c_int), ("split", C.c_int), ("k_per_split", C.c_int), ("epi", C.c_int), ("ws", C.c_int)]
+    _fields_ = [(name, C.c_int) for name in _FIELDS]
+
+    def __init__(self, cfg, split, k_per_split, epi, ws):
+        super().__init__(cfg=cfg, split=split, k_per_split=k_per_split, epi=epi, ws=ws)
 
 
 def layer_plan(m, n, k, epi, row_kernel):
+    """The plan a layer's driver makes.  (The symbols called here carry their argument types: a changed signature is not found.)"""
     f = api.lib()._Z14laps_gemm_planiiiiimbb
     f.restype = Plan
     return f(C.c_int(m), C.c_int(n), C.c_int(k), C.c_int(0), C.c_int(epi), C.c_size_t(256 << 20), C.c_bool(row_kernel), C.c_bool(True))

@@ -54,7 +54,7 @@ def test_projection_at_real_shape_matches_fp64_matmul(ctx32, name, m):
     n, k = SHAPES[name]
     info = ctx32.laps_gemm_plan_info(m, n, k, 0, 0)
     print(f"[stage] {name} m={m}: tile {info['bm']}x{info['bn']}, {info['split']} K slices of {info['k_per_split']}, "
-          f"{info['ws']} slabs in flight, {info['workgroups']} workgroups", flush=True)
+          f"multiples of {info['ws']} slabs, {info['workgroups']} workgroups", flush=True)
     if m <= 128:      # the streaming tiles: 256 columns for the wide / long-K projections, 128 for the narrow ones
         assert info["bm"] == 128 and info["bn"] == (256 if name in ("gate_up", "down") else 128) and info["ws"] == 2
     else:
