@@ -1097,7 +1097,6 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         // cold / warm, cached against bypassing: 14B down 48 rows 32.9 / 29.2 against 30.9 / 30.2, 64 rows 33.9 / 29.9 against
         // 32.7 / 32.0, 128 rows 39.7 / 32.3 against 40.0 / 40.1, 160 rows 42.5 / 33.8 against 42.5 / 42.7; o 128 rows 23.2 / 18.8
         // against 25.1 / 25.0; 32B down of 283 MB, 160 rows 74.7 against 68.8).
-        // Up to 64 rows the tiles of 64 rows spare the LDS reads and the products of as many rows of nothing.
         const bool alone = row_live == nullptr && n_live == nullptr;
         const bool keep = alone && m > 48 && p.split > 1 && kTiles[p.cfg].bn < 256 && 2.0 * n * k <= 256e6;
         const bool bypass = g.tiles_m == 1 && !keep;
@@ -1105,6 +1104,14 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     case cfg:                                                                                    \
         if (bypass) return launch_dma_epi<BM, BN, WM, WN, true>(p.epi, g, s);                    \
         return launch_dma_epi<BM, BN, WM, WN, false>(p.epi, g, s)
+        // Up to 64 rows the tiles of 64 rows spare the LDS reads and the products of as many rows of nothing.  65 to 128 rows are
+        // two of them where 128 columns leave compute units for twice the workgroups: a unit takes in 64 rows of A beside the
+        // weights instead of 128.  Through registers / 128 rows this way / 64: 2560 x 1024 at 80 / 128 rows 12.1 / 12.1 / 10.0 and
+        // 13.3 / 14.5 / 11.1 us, 3584 x 3584 in 4 slices, 128 rows, 18.6 / 18.8 / 15.9, 14336 x 1024 14.3 / 14.9 / 12.1.
+        if (p.cfg == 0 && m > 64 && m <= 128 && 2 * g.tiles_n * p.split <= 256) {
+            g.tiles_m = 2;
+            return launch_dma_epi<64, 128, 2, 2, false>(p.epi, g, s);
+        }
         if (m <= 64) switch (p.cfg) {
             LAPS_DMA_CASE(0, 64, 128, 2, 2);
             LAPS_DMA_CASE(5, 64, 256, 1, 4);

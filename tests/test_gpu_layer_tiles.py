@@ -108,11 +108,12 @@ def test_tile_by_live_rows_matches_float64(n, epi):
         launch(none, a, w, m, out, out if epi == RESID else None, act, torch.tensor([0], dtype=torch.int32, device="cuda"))
         assert bool((out == 7).all()) and bool((act == 7).all())
 
-# Up to 64 rows on tiles of 64 rows, then 128: edges of both, weights bypassing the caches (rows given as live) and through them
+# Up to 64 rows on tiles of 64 rows, then 128, or two of 64 where 128 columns make at most 128 workgroups (not the 129 tiles of
+# 16512 columns, nor 2 and more slices of 16384): edges of both, weights bypassing the caches (rows given as live) and through them
 # (a product of its own), with live rows told late and K slices of one and several slabs
 @pytest.mark.gpu
-@pytest.mark.parametrize("cfg,n", [(0, 256), (5, 512), (1, 192)])
-@pytest.mark.parametrize("m", [1, 16, 63, 64, 65, 128])
+@pytest.mark.parametrize("cfg,n", [(0, 256), (0, 16384), (0, 16512), (5, 512), (1, 192)])
+@pytest.mark.parametrize("m", [1, 16, 63, 64, 65, 97, 128])
 def test_tiles_up_to_128_rows_match_float64(cfg, n, m):
     for k, split in ((64, 1), (192, 1), (1024, 1), (448, 2), (1024, 4)):
         per = -(-(k // 64) // split) * 64
