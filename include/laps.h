@@ -259,6 +259,9 @@ const float* laps_graph_output(const laps_graph* g);
 float* laps_graph_input(laps_graph* g);
 /* Enqueues a device-to-device copy of output rows [0, n_rows) into dst_dev (fp32 [n_rows, hidden]). */
 int laps_graph_read_output(const laps_graph* g, int32_t n_rows, float* dst_dev, void* stream);
+/* 1 if all work enqueued on stream `before` has run, so that what is enqueued on `stream` next need not wait for it; 0 if
+ * some has not, if either stream is being captured, or if the runtime cannot say. */
+int laps_stream_idle(void* before, void* stream);
 size_t laps_graph_device_bytes(const laps_graph* g); /* staging + workspace held by this graph */
 void laps_graph_destroy(laps_graph* g);
 

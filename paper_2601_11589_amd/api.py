@@ -110,11 +110,12 @@ def _after_current(stream):
     """Orders `stream` behind torch's current stream.  What a wrapper allocates (outputs, workspace) and what the
     caller has just filled (page tables, lengths, inputs) belongs to the current stream; the library enqueues on
     `stream`, which does not wait for another stream by itself - a page table read before it is written steers the
-    K/V append to wherever the stale entries point.  One event record + wait, nothing when the two are the same."""
+    K/V append to wherever the stale entries point.  One event record + wait; nothing when the two are the same, or when
+    the current stream has run all it was given (each event wait holds the device up for a few us)."""
     if stream is None:
         return
     cur = torch.cuda.current_stream()
-    if cur.cuda_stream != stream.cuda_stream:
+    if cur.cuda_stream != stream.cuda_stream and not lib().laps_stream_idle(C.c_void_p(cur.cuda_stream), C.c_void_p(stream.cuda_stream)):
         stream.wait_stream(cur)
 
 
