@@ -401,6 +401,9 @@ struct DmaTraits {
     static constexpr int CAP = (TWO ? 80 : 160) * 1024;
     static constexpr int NS = CAP / SLOT < 6 ? CAP / SLOT : 6;           // half slabs in LDS
     static constexpr int LDS = NS * SLOT;
+    // The last column tile may reach past N.  Not on 320 x 256, whose offsets of B lie partly in the scalar offset, which the
+    // descriptor's bound does not see.
+    static constexpr bool RAGGED = BM <= 256;
     static_assert(WM * WN == 4 && QA % 8 == 0 && QB % 4 == 0, "four waves load whole groups of rows");
     static_assert((WTM / 2) % 16 == 0 && (WTN / 2) % 16 == 0, "halves of whole sub-tiles");
     static_assert((WTM / 2) % QA == 0 && (WTN / 2) % QB == 0, "the rows that a wave loads lie in one wave tile");
@@ -417,11 +420,14 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 // The weights are the matrix instruction's first operand, so that a lane holds four consecutive columns (16 ni + 4 lk + r)
 // of row lane & 15 of a sub-tile.
-template <typename D, int EPI>
+// GUARD: the tile reaches past column N.  (A test in front of every load and store of whole tiles too keeps the loads from
+// being issued together: a layer of 227 rows of the tiny model 41.5 -> 44.0 us.)
+template <typename D, int EPI, bool GUARD>
 __device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI], const GemmArgs& g, int M, int ks, int m0,
                                                int n0, int wm, int wn, int lrow, int lk) {
     const int N = g.N;
     const int row0 = m0 + wm * D::WTM + lrow, col0 = n0 + wn * D::WTN;
+    const auto inside = [&](int ni) { return !GUARD || col0 + ni * 16 < N; };   // wave-uniform; N is a multiple of 64
     if constexpr (EPI == EPI_PARTIAL) {
         float* out = g.out_f32 + (size_t)ks * g.M * N + col0 + 4 * lk;
 #pragma unroll
@@ -430,7 +436,8 @@ __device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI],
             if (m >= M) continue;
             f32x4_a4* dst = reinterpret_cast<f32x4_a4*>(out + (size_t)m * N);
 #pragma unroll
-            for (int ni = 0; ni < D::NI; ++ni) dst[ni * 4] = acc[mi][ni];
+            for (int ni = 0; ni < D::NI; ++ni)
+                if (inside(ni)) dst[ni * 4] = acc[mi][ni];
         }
     } else if constexpr (EPI == EPI_RESID) {
         // resid may be the output array itself (every element is read by the thread that writes it), so the compiler
@@ -444,7 +451,8 @@ __device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI],
             const int m = row0 + mi * 16;
             const f32x4_a4* src = reinterpret_cast<const f32x4_a4*>(res + (size_t)(m < M ? m : M - 1) * N);
 #pragma unroll
-            for (int ni = 0; ni < D::NI; ++ni) rbuf[mi & 1][ni] = src[ni * 4];
+            for (int ni = 0; ni < D::NI; ++ni)
+                if (inside(ni)) rbuf[mi & 1][ni] = src[ni * 4];
         };
         load(0);
 #pragma unroll
@@ -454,7 +462,8 @@ __device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI],
             if (m >= M) continue;
             f32x4_a4* dst = reinterpret_cast<f32x4_a4*>(out + (size_t)m * N);
 #pragma unroll
-            for (int ni = 0; ni < D::NI; ++ni) dst[ni * 4] = rbuf[mi & 1][ni] + acc[mi][ni];
+            for (int ni = 0; ni < D::NI; ++ni)
+                if (inside(ni)) dst[ni * 4] = rbuf[mi & 1][ni] + acc[mi][ni];
         }
     } else {  // EPI_SWIGLU: sub-tiles 4j, 4j+1 hold gate columns, 4j+2, 4j+3 the matching up columns; PAIRED order: a lane
               // holds columns 8 lk .. 8 lk + 7 of the 32 that two sub-tiles make
@@ -468,6 +477,7 @@ __device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI],
             u32x4_a2* dst = reinterpret_cast<u32x4_a2*>(out + (size_t)m * half_n);
 #pragma unroll
             for (int j = 0; j < D::NI / 4; ++j) {
+                if (!inside(4 * j)) continue;
                 float y[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -547,7 +557,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         return i32x4{__builtin_amdgcn_readfirstlane((int)(unsigned)p), __builtin_amdgcn_readfirstlane((int)(p >> 32)),
                      __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
     };
-    i32x4 ra, rb = rsrc(g.W + (size_t)n0 * K, (unsigned)BN * row_bytes);
+    i32x4 ra, rb = rsrc(g.W + (size_t)n0 * K, (unsigned)(D::RAGGED && g.N - n0 < BN ? g.N - n0 : BN) * row_bytes);
     int a_bytes, b_bytes = rb[2];
     // Offsets of a lane's chunks: half slab row q -> tile row (q / (WT/2)) * WT + half * WT/2 + q % (WT/2).  Rows of A past the
     // last one lie behind the descriptor's end and padding rows are sent there: no request is made for them (a unit keeps a
@@ -718,7 +728,8 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load may land after this workgroup's LDS is another's
     acc_fence<D>(acc);
-    store_dma_tile<D, EPI>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
+    if (D::RAGGED && __builtin_expect(n0 + BN > g.N, 0)) store_dma_tile<D, EPI, true>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
+    else store_dma_tile<D, EPI, false>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
 // Rows past *n_live are padding: the tiles of the rows before them are dealt out as if there were no others.  (Tiles of all
@@ -752,42 +763,47 @@ __global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void
 }
 
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
-// 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 220
-// of 256 x 256 take one: 997 against 700 us with slabs through registers).  Four tiles are therefore one kernel, which takes the one that the cost model
-// gives the live rows; every workgroup comes to the same choice.  First tile: 256 x W, W = 160 (N = 5120), 224 (7168, 3584)
-// or 192 (55296, 27648, 4608); none for 7B gate/up (37888), and other N keep the tile planned for all rows.  q/k/v of 2776 rows on
-// 320 x 256 (252 tiles, one round) 152 us, on 256 x 224 (352) 198; gate/up 1141 on 320 x 256 and 1178 on 256 x 256.
-constexpr int kLiveTiles = 4;
+// 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 253
+// of 256 x 224 take one: 997 against 700 us with slabs through registers on 256 x 256; 612 on 256 x 256 and 581 on 256 x 224
+// now).  The tiles of one workgroup a unit are therefore one kernel, which takes the one that the cost model gives the live
+// rows; every workgroup comes to the same choice.  The last column tile may reach past N, so that every width serves every N.
+// q/k/v of 2776 rows on 320 x 256 (252 tiles, one round) 152 us, on 256 x 224 (352) 198; gate/up 1141 on 320 x 256 and 1178 on
+// 256 x 256; 7B o on 256 x 160 (253 tiles) 81, on 256 x 224 (176) 93.
+constexpr int kLiveTiles = 7;
+constexpr int kLiveRows[kLiveTiles] = {256, 256, 256, 320, 192, 256, 256}, kLiveCols[kLiveTiles] = {256, 128, 192, 256, 256, 224, 160};
+constexpr int live_tiles(int epi) { return epi == EPI_SWIGLU ? 5 : 7; }   // no gate / up pairs in a wave of the last two
 struct LiveCost {
     float fill[kLiveTiles], slabs[kLiveTiles], part[kLiveTiles];   // as TileDef, slabs = time of all K slabs on a full chip
 };
-template <int W, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(256, 1) void gemm_live_kernel(const GemmArgs g, const LiveCost c) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int M = live_rows(g);
     if (M <= 0) return;
-    constexpr int rows[kLiveTiles] = {256, 256, 256, 320}, cols[kLiveTiles] = {W == 0 ? 256 : W, 256, 128, 256};
-    constexpr int first = W == 0 ? 1 : 0;
-    int pick = first;
+    int pick = 0;
     float best = 0.f;
 #pragma unroll
-    for (int i = first; i < kLiveTiles; ++i) {
-        const int tiles = (M + rows[i] - 1) / rows[i] * (g.N / cols[i]);
+    for (int i = 0; i < live_tiles(EPI); ++i) {
+        const int tiles = (M + kLiveRows[i] - 1) / kLiveRows[i] * ((g.N + kLiveCols[i] - 1) / kLiveCols[i]);
         const float spare = tiles < 256 ? 1.f - tiles / 256.f : 0.f;
         const float us = (float)((tiles + 255) / 256) * (c.fill[i] + c.slabs[i] * (1.f - c.part[i] * spare));
-        if (i == first || us < best) best = us, pick = i;
+        if (i == 0 || us < best) best = us, pick = i;
     }
-    const int tiles_m = (M + rows[pick] - 1) / rows[pick], tiles_n = g.N / cols[pick];
+    int rows = kLiveRows[0], cols = kLiveCols[0];
+#pragma unroll
+    for (int i = 1; i < live_tiles(EPI); ++i)
+        if (pick == i) rows = kLiveRows[i], cols = kLiveCols[i];
+    const int tiles_m = (M + rows - 1) / rows, tiles_n = (g.N + cols - 1) / cols;
     if ((int)blockIdx.x >= tiles_m * tiles_n) return;
-    if constexpr (W > 0) {
-        if (pick == 0) {
-            dma_tile<256, W, 4, 1, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
-            return;
-        }
+    if constexpr (EPI != EPI_SWIGLU) {
+        if (pick == 5) return dma_tile<256, 224, 4, 1, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+        if (pick == 6) return dma_tile<256, 160, 4, 1, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
     }
-    if (pick == 1) dma_tile<256, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
-    else if (pick == 2) dma_tile<256, 128, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
-    else dma_tile<320, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    if (pick == 0) dma_tile<256, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else if (pick == 1) dma_tile<256, 128, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else if (pick == 2) dma_tile<256, 192, 4, 1, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else if (pick == 3) dma_tile<320, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
+    else dma_tile<192, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
 }
 
 int launch_gemm(void (*kern)(const GemmArgs), bool* attr_set, int threads, int lds, const GemmArgs& a, hipStream_t s) {
@@ -850,26 +866,31 @@ constexpr TileDef kTiles[] = {
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
-template <int W, int EPI>
+template <int EPI>
 int launch_live(const GemmArgs& a, hipStream_t s) {
-    constexpr int cfg[kLiveTiles] = {W == 160 ? 4 : W == 224 ? 3 : W == 192 ? 9 : 2, 2, 8, 10};
-    constexpr int lds_of[kLiveTiles] = {DmaTraits<256, W == 0 ? 128 : W, 4, 1>::LDS, DmaTraits<256, 256, 2, 2>::LDS, DmaTraits<256, 128, 2, 2>::LDS,
-                                        DmaTraits<320, 256, 2, 2>::LDS};
-    int lds = 0;
-    for (int b : lds_of) lds = b > lds ? b : lds;
-    auto kern = gemm_live_kernel<W, EPI>;
-    static bool attr_set = false;  // as in launch_gemm
-    if (!attr_set) {
-        LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        attr_set = true;
-    }
+    constexpr int cfg[kLiveTiles] = {2, 8, 9, 10, 6, 3, 4};   // in the order of kLiveRows, kLiveCols
+    constexpr int lds_of[kLiveTiles] = {DmaTraits<256, 256, 2, 2>::LDS, DmaTraits<256, 128, 2, 2>::LDS, DmaTraits<256, 192, 4, 1>::LDS,
+                                        DmaTraits<320, 256, 2, 2>::LDS, DmaTraits<192, 256, 2, 2>::LDS, DmaTraits<256, 224, 4, 1>::LDS,
+                                        DmaTraits<256, 160, 4, 1>::LDS};
+    int lds = 0, most = 0;   // the most tiles of any choice
     LiveCost c;
+    for (int i = 0; i < live_tiles(EPI); ++i) {
+        lds = lds_of[i] > lds ? lds_of[i] : lds;
+        const int tiles = (a.M + kLiveRows[i] - 1) / kLiveRows[i] * ((a.N + kLiveCols[i] - 1) / kLiveCols[i]);
+        most = tiles > most ? tiles : most;
+    }
     for (int i = 0; i < kLiveTiles; ++i) {
         c.fill[i] = (float)kTiles[cfg[i]].fill;
         c.slabs[i] = (float)(kTiles[cfg[i]].slab * (a.K / BK));
         c.part[i] = (float)kTiles[cfg[i]].part;
     }
-    hipLaunchKernelGGL(kern, dim3((a.M + 255) / 256 * (a.N / 128)), dim3(256), lds, s, a, c);   // the most tiles of any choice
+    auto kern = gemm_live_kernel<EPI>;
+    static bool attr_set = false;  // as in launch_gemm
+    if (!attr_set) {
+        LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(most), dim3(256), lds, s, a, c);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -966,23 +987,33 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     int best_cfg = -1, best_split = 1;
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
-        if (n % t.bn != 0 || (cfg == 1 && n % 128 == 0) || (far && cfg != 1 && cfg != 6 && cfg != 7)) continue;
+        // Inside layers the last column tile may reach past n (not on 320 x 256, see DmaTraits), and 192 rows may need more row
+        // tiles than 256; products of their own keep to what laps_gemm_plan_info has always reported.  Both have to be ahead on
+        // paper by more than the model errs where they lost: 8.5 and 2 % (32B q/k/v of 1280 rows 8 % ahead, 95 -> 99 us).  Row
+        // kernel included, weights cold, before and with them: 7B gate/up of 200 / 256 / 512 rows 77.4 / 82.3 / 160.2 -> 68.6 / 73.9
+        // (198 tiles of 256 x 192 where 256 columns make 148) / 135.2 (192 x 256), q/k/v of 1847 rows 74.0 -> 68.3, o of 1536 rows
+        // 60.1 -> 56.8; of ten projections at 17 row counts 14 plans change, none for a slower one.
+        const bool ragged = n % t.bn != 0;
+        if (ragged && (!layer || far || t.bm > 256)) continue;
+        if ((cfg == 1 && n % 128 == 0) || (far && cfg != 1 && cfg != 6 && cfg != 7)) continue;
         if (want_epi == EPI_SWIGLU && (cfg == 1 || cfg == 3 || cfg == 4)) continue;   // no gate / up pairs in a wave
         const int tiles_m = (m + t.bm - 1) / t.bm;
-        if (t.bm == 192 && tiles_m != (m + 255) / 256 && !far) continue;   // 192 rows where they need no more row tiles than 256
         // 320 rows where they need fewer row tiles than 256.  They take in and read from LDS a tenth less per product: 32B
         // gate/up of 280, 640 and 11104 rows 194 -> 156, 334 -> 285 and 4582 -> 4379 us, down of 11104 rows 2405 -> 2238, q/k/v
         // of 1280 rows in two slices 99 -> 76; 206 products of 7B, 14B and 32B at 27 row counts 3 % in the mean.  Products of
         // their own would gain as much; they keep to the 128, 192 or 256 rows that laps_gemm_plan_info has always reported and
         // that its readers rely on.
         if (t.bm == 320 && (!layer || tiles_m == (m + 255) / 256)) continue;
+        const bool more_192 = t.bm == 192 && tiles_m != (m + 255) / 256;
+        if (more_192 && !layer && !far) continue;
+        const double margin = ragged ? 1.085 : more_192 && !far ? 1.02 : 1.0;
         const int max_split = force_split > 0 ? force_split : (far ? 256 : 16);   // a few column tiles have to fill the chip
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
             const double partial = 4.0 * s * mn;
             if (force_split == 0 && s > 1 && (ksteps / s < 4 || partial > (double)partial_cap)) break;
             int per = (ksteps + s - 1) / s;
             if (t.ws == 2 && ksteps % 2 == 0) per = (per + 1) / 2 * 2;
-            const long wgs = (long)tiles_m * (n / t.bn) * s;
+            const long wgs = (long)tiles_m * ((n + t.bn - 1) / t.bn) * s;
             const long rounds = (wgs + 255) / 256;
             const double filled = wgs < 256 ? wgs / 256.0 : 1.0;
             const double tiles = 4.0 + rounds * (t.fill + per * t.slab * (1.0 - t.part * (1.0 - filled)));
@@ -991,6 +1022,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
             if (s > 1) us += moved(2.0 * partial + own) + (want_epi == EPI_PARTIAL ? 0.0 : 3.6);
             else if (row_kernel && want_epi == EPI_PARTIAL) us += moved(partial + own);   // written with the tiles
             else if (row_kernel && want_epi == EPI_RESID) us += 4.0 + 6.0 * mn / 4.5e6;
+            us *= margin;
             if (us < best) {
                 best = us;
                 best_cfg = cfg;
@@ -1021,7 +1053,9 @@ size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap) {   // m
 int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m, int n, int k, float* out_f32,
                      const float* resid, bf16_t* out_bf16, const int* row_live, const int* n_live, bool live_varies,
                      hipStream_t s) {
-    if (m < 1 || n < 64 || k < BK || k % BK != 0 || p.cfg < 0 || p.cfg >= kNumTiles || n % kTiles[p.cfg].bn != 0) {
+    // the last column tile may reach past n where slabs go straight into LDS (DmaTraits::RAGGED)
+    const bool ragged_ok = k < kMaxBufferK && n % 64 == 0 && p.cfg >= 0 && p.cfg < kNumTiles && kTiles[p.cfg].bm <= 256;
+    if (m < 1 || n < 64 || k < BK || k % BK != 0 || p.cfg < 0 || p.cfg >= kNumTiles || (n % kTiles[p.cfg].bn != 0 && !ragged_ok)) {
         laps_set_error("gemm: unsupported shape m=%d n=%d k=%d for tile %d", m, n, k, p.cfg);
         return LAPS_EINVAL;
     }
@@ -1046,7 +1080,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     g.split = p.split;
     g.kps = p.k_per_split;
     g.tiles_m = (m + kTiles[p.cfg].bm - 1) / kTiles[p.cfg].bm;
-    g.tiles_n = n / kTiles[p.cfg].bn;
+    g.tiles_n = (n + kTiles[p.cfg].bn - 1) / kTiles[p.cfg].bn;
     g.out_f32 = out_f32;
     g.resid = resid;
     g.out_bf16 = out_bf16;
@@ -1055,15 +1089,11 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     // Loads straight into LDS are given 16-byte pieces that lie on 16-byte bounds: rows are whole multiples of 128 bytes, so
     // the bases decide.  (5120 x 5120 at 8 / 128 / 2048 rows, weights cold: 22 / 25 / 92 us, with weights 2 bytes off 26 / 30 / 155.)
     const bool aligned = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w)) & 15) == 0;
-    // batches of an unknown number of live rows, un-split plans of the 256- and 320-row tiles: chosen on the device
-    if (aligned && live_varies && n_live && m > 256 && p.split == 1 && kTiles[p.cfg].bm >= 256 && n % 256 == 0) {
-        if (n % 160 == 0 && p.epi == EPI_PARTIAL) return launch_live<160, EPI_PARTIAL>(g, s);
-        if (n % 160 == 0 && p.epi == EPI_RESID) return launch_live<160, EPI_RESID>(g, s);
-        if (n % 224 == 0 && p.epi == EPI_PARTIAL) return launch_live<224, EPI_PARTIAL>(g, s);
-        if (n % 224 == 0 && p.epi == EPI_RESID) return launch_live<224, EPI_RESID>(g, s);
-        if (n % 192 == 0 && p.epi == EPI_PARTIAL) return launch_live<192, EPI_PARTIAL>(g, s);
-        if (n % 192 == 0 && p.epi == EPI_SWIGLU) return launch_live<192, EPI_SWIGLU>(g, s);
-        if (p.epi == EPI_SWIGLU) return launch_live<0, EPI_SWIGLU>(g, s);
+    // batches of an unknown number of live rows, un-split plans of the tiles of one workgroup a unit: chosen on the device
+    if (aligned && live_varies && n_live && m > 256 && k < kMaxBufferK && p.split == 1 && kTiles[p.cfg].bm >= 192 && p.cfg != 7 && n % 256 == 0) {
+        if (p.epi == EPI_PARTIAL) return launch_live<EPI_PARTIAL>(g, s);
+        if (p.epi == EPI_RESID) return launch_live<EPI_RESID>(g, s);
+        return launch_live<EPI_SWIGLU>(g, s);
     }
     if (k >= kMaxBufferK || !aligned) {
         int cfg = p.cfg, ws = p.ws;

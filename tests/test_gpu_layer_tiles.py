@@ -144,3 +144,42 @@ def test_padding_rows_between_sequences_are_left_out(cfg, m, n):
     assert float((out[live].double() - want).norm() / want.norm()) < 2e-6
     if cfg == 2:
         assert bool((out[256:] == 7).all())
+
+
+def test_ragged_columns_are_planned_in_layers_only():
+    """A last column tile past n where it fills the chip better; a product of its own keeps to widths that divide n."""
+    for m, n, k, epi, cfg in ((256, 37888, 3584, SWIGLU, 9), (2776, 5120, 27648, RESID, 3), (1847, 4608, 3584, PARTIAL, 4)):
+        p = layer_plan(m, n, k, epi, epi != SWIGLU)
+        assert p.cfg == cfg and p.split == 1, (m, n, k, p.cfg, p.split)
+        out = (C.c_int32 * 7)()
+        assert api.lib().laps_gemm_plan_info(C.c_int32(m), C.c_int32(n), C.c_int32(k), C.c_int32(0), C.c_int32(epi), out) == 0
+        assert n % out[1] == 0
+    f = api.lib()._Z14laps_gemm_planiiiiimbb      # and never where 32-bit offsets do not reach
+    f.restype = Plan
+    for n in (192, 320, 640):
+        p = f(C.c_int(700), C.c_int(n), C.c_int(1 << 22), C.c_int(0), C.c_int(PARTIAL), C.c_size_t(256 << 20), C.c_bool(True), C.c_bool(True))
+        assert p.cfg in (1, 6, 7) and n % {1: 64, 6: 256, 7: 128}[p.cfg] == 0
+
+
+# tile index -> columns; the last column tile holds 64 columns, all but 64, and (two and a bit) a whole one and 64
+WIDTHS = {0: 128, 2: 256, 3: 224, 4: 160, 6: 256, 7: 128, 8: 128, 9: 192}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", sorted(WIDTHS))
+@pytest.mark.parametrize("m", [129, 300])
+def test_last_column_tile_past_n_matches_float64(cfg, m):
+    width = WIDTHS[cfg]
+    for n in sorted({64, -(-width // 64) * 64 - 64, -(-width // 64) * 64 + 64, 2 * width // 64 * 64 + 64}):
+        if n % width == 0:
+            continue
+        for k, split in ((64, 1), (192, 1), (1024, 1), (448, 2), (1024, 4)):
+            for epi in (PARTIAL,) if split > 1 else (PARTIAL, RESID) + ((SWIGLU,) if cfg not in (3, 4) else ()):
+                run(Plan(cfg, split, -(-(k // 64) // split) * 64, epi, 1), m, n, k)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,epi", [(5120, RESID), (3584, RESID), (4608, PARTIAL), (27648, SWIGLU)])
+def test_tile_by_live_rows_of_large_batches_matches_float64(n, epi):
+    for rows in (1111, 1847, 2776, 3000):      # 256 x 160, 256 x 224, 256 x 192 and others, the last column tile past n or not
+        run(Plan(2, 1, 1024, epi, 1), 3000, n, 1024, torch.tensor([rows], dtype=torch.int32, device="cuda"), rows)
