@@ -293,12 +293,6 @@ struct BatchDesc {
     int ws_pages = kAnyPages;   // page-table width the workspace was laid out for
 };
 
-#define LAPS_TRY(x)                 \
-    do {                            \
-        int rc_ = (x);              \
-        if (rc_ != LAPS_OK) return rc_; \
-    } while (0)
-
 // One projection.  `want` is the epilogue the caller would like fused; the plan falls back to raw
 // K-slice partial sums when it splits K.  Returns the plan so the caller knows which case ran.
 static int run_gemm(laps_ctx* c, int cls, bool capturing, const bf16_t* a, const bf16_t* w, int m, int n, int k,

@@ -31,6 +31,11 @@ void laps_set_error(const char* fmt, ...);
             return LAPS_EHIP;                                                                  \
         }                                                                                      \
     } while (0)
+#define LAPS_TRY(x)                 \
+    do {                            \
+        int rc_ = (x);              \
+        if (rc_ != LAPS_OK) return rc_; \
+    } while (0)
 #define LAPS_LAUNCH_CHECK()                                                                    \
     do {                                                                                       \
         hipError_t e_ = hipGetLastError();                                                     \
