@@ -68,12 +68,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         const bf16_t* __restrict__ k_pool,
                                                         const bf16_t* __restrict__ v_pool,
-                                                        const int* __restrict__ row_start,
-                                                        const int* __restrict__ new_len,
-                                                        const int* __restrict__ prefix_len,
+                                                        const int4* __restrict__ desc,
                                                         const int* __restrict__ page_table, int max_pages,
-                                                        const int* __restrict__ tile_start,
-                                                        const int* __restrict__ item_seq, int n_seq, int n_q,
+                                                        const int* __restrict__ tile_start, int n_seq, int n_q,
                                                         int n_kv, float scale_log2e, int n_pool_pages, int n_tokens,
                                                         int max_items, int min_tiles,
                                                         const int4* __restrict__ bounds) {
@@ -89,15 +86,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
     __shared__ __align__(16) u32x4 Ks[2][KT * CPR];   // double buffered: one barrier per tile
     __shared__ __align__(16) u32x4 Vs[2][HD * 8];
 
-    const int n_items_all = tile_start[n_seq], G = n_q / n_kv;
+    const int G = n_q / n_kv;
     // one unit: (item, kv head), key tiles [t0, t1) of it if PERSIST; slot: where a cut unit's result goes
     auto unit = [&](const int item, const int kvh, const int t0, const int t1, const int slot) __attribute__((always_inline)) {
-    if (item >= n_items_all) return;
-    const int seq = item_seq[item];
-    const int qtile = item - tile_start[seq];
-    const int L = new_len[seq], H = laps_dev_clamp_prefix(prefix_len[seq], L, max_pages);
+    const int4 it = desc[2 * item];
+    const int seq = it.x, qtile = it.y, L = it.z, H = it.w, rs = desc[2 * item + 1].x;
+    if (seq < 0) return;
     // row offsets come from the caller's device array: rows outside the batch are never touched, whatever it holds
-    const int rs = row_start[seq];
     if (rs < 0 || L > n_tokens - rs) return;
     const int n_rows = L * G;
     const int kv_len = H + L;
@@ -607,7 +602,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
         // consecutive shares (mostly the same kv head) on one XCD
         const int w = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
         const int4 b = bounds[w], e = bounds[w + 1];
-        const int n_items = n_items_all < max_items ? n_items_all : max_items;
+        const int n_items_all = tile_start[n_seq], n_items = n_items_all < max_items ? n_items_all : max_items;
         int kvh = b.x, item = b.y, t = b.z, slot = 2 * w;
         while (kvh < n_kv && (kvh != e.x || item != e.y || t < e.z)) {
             const bool last = kvh == e.x && item == e.y;
@@ -626,8 +621,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
 template <int HD>
 __global__ __launch_bounds__(LAPS_ATTN_LONG_ROWS) void attn_merge_cut_kernel(
     bf16_t* __restrict__ out, const float* __restrict__ part_o, const float* __restrict__ part_ml,
-    const int* __restrict__ row_start, const int* __restrict__ new_len, const int* __restrict__ tile_start,
-    const int* __restrict__ item_seq, const int4* __restrict__ bounds, int n_wgs, int n_seq, int n_q, int n_kv, int n_tokens) {
+    const int4* __restrict__ desc, const int4* __restrict__ bounds, int n_wgs, int n_q, int n_kv, int n_tokens) {
     constexpr int ROWS = LAPS_ATTN_LONG_ROWS;
     constexpr int NC = HD / 16;   // 4-float chunks per thread
     const int w = blockIdx.x + 1;
@@ -636,10 +630,10 @@ __global__ __launch_bounds__(LAPS_ATTN_LONG_ROWS) void attn_merge_cut_kernel(
     const int4 before = bounds[w - 1];
     const bool same = before.x == here.x && before.y == here.y;
     if (same && before.z > 0) return;             // the unit's first cut merges it
-    const int seq = item_seq[here.y], G = n_q / n_kv, L = new_len[seq];
-    const int rs = row_start[seq];
+    const int4 it = desc[2 * here.y];
+    const int G = n_q / n_kv, L = it.z, rs = desc[2 * here.y + 1].x;
     if (rs < 0 || L > n_tokens - rs) return;      // as in attn_kernel
-    const int row = threadIdx.x, row_id = (here.y - tile_start[seq]) * ROWS + row;
+    const int row = threadIdx.x, row_id = it.y * ROWS + row;
     if (row_id >= L * G) return;
     f32x4 acc[NC];
 #pragma unroll
@@ -677,27 +671,23 @@ __global__ __launch_bounds__(LAPS_ATTN_LONG_ROWS) void attn_merge_cut_kernel(
 }
 
 // Merges the key-range splits of attn_kernel<.., SPLIT = true> in a fixed order: out = sum_z 2^(m_z - M) O_z /
-// sum_z 2^(m_z - M) l_z with M = max_z m_z.  A workgroup covers the 128 rows of one work item and one 4-float
-// slice of head_dim; its four groups of 128 threads take the splits z = g, g + 4, g + 8, ... (more loads in flight than one
+// sum_z 2^(m_z - M) l_z with M = max_z m_z.  A workgroup covers the 128 rows of one work item and CH 4-float
+// slices of head_dim; its four groups of 128 threads take the splits z = g, g + 4, g + 8, ... (more loads in flight than one
 // thread per row could issue) and their four partial sums are added in the order g = 0, 1, 2, 3.
 constexpr int MERGE_GROUPS = 4;
-template <int HD>
+constexpr int MERGE_SMALL = 512;   // workgroups
+template <int HD, int CH>
 __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     bf16_t* __restrict__ out, const float* __restrict__ part_o, const float* __restrict__ part_ml,
-    const int* __restrict__ row_start, const int* __restrict__ new_len, const int* __restrict__ prefix_len,
-    const int* __restrict__ tile_start, const int* __restrict__ item_seq, int n_seq, int n_q, int n_kv, int n_split,
-    int min_tiles, int max_pages, int n_tokens) {
+    const int4* __restrict__ desc, int n_q, int n_kv, int n_split, int min_tiles, int n_tokens) {
     constexpr int ROWS = 128;
     __shared__ float red_m[MERGE_GROUPS][ROWS];
     __shared__ float red_l[MERGE_GROUPS][ROWS];
-    __shared__ f32x4 red_o[MERGE_GROUPS][ROWS];
-    const int item = blockIdx.x;
-    if (item >= tile_start[n_seq]) return;
-    const int seq = item_seq[item], qtile = item - tile_start[seq], kvh = blockIdx.y;
-    const int G = n_q / n_kv;
-    const int L = new_len[seq], H = laps_dev_clamp_prefix(prefix_len[seq], L, max_pages);   // as in attn_kernel
-    const int rs = row_start[seq];
-    if (rs < 0 || L > n_tokens - rs) return;                                          // as in attn_kernel
+    __shared__ f32x4 red_o[CH][MERGE_GROUPS][ROWS];
+    const int item = blockIdx.x, kvh = blockIdx.y;
+    const int4 it = desc[2 * item];
+    const int qtile = it.y, G = n_q / n_kv, L = it.z, H = it.w, rs = desc[2 * item + 1].x;
+    if (it.x < 0 || rs < 0 || L > n_tokens - rs) return;                              // as in attn_kernel
     const int n_rows = L * G, R0 = qtile * ROWS;
     if (R0 >= n_rows) return;
     const int last_row_wg = (R0 + ROWS < n_rows ? R0 + ROWS : n_rows) - 1;
@@ -722,51 +712,56 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     float m_all = red_m[0][row];
 #pragma unroll
     for (int k = 1; k < MERGE_GROUPS; ++k) m_all = fmaxf(m_all, red_m[k][row]);
-    const int c = blockIdx.z;   // one 4-float chunk of head_dim per workgroup
-    const f32x4* po = reinterpret_cast<const f32x4*>(part_o) + (blk0 * (size_t)(HD / 4) + c) * ROWS + row;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const int c0 = blockIdx.z * CH;
+    const f32x4* po = reinterpret_cast<const f32x4*>(part_o) + (blk0 * (size_t)(HD / 4) + c0) * ROWS + row;
+    f32x4 acc[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     float l_g = 0.f;
     if (live) {
 #pragma unroll 4
         for (int z = g; z < used; z += MERGE_GROUPS) {
             const float w = __builtin_amdgcn_exp2f(pm[(size_t)z * 2 * ROWS] - m_all);
-            const f32x4 v = po[(size_t)z * (HD / 4) * ROWS];
+            f32x4 v[CH];
+#pragma unroll
+            for (int c = 0; c < CH; ++c) v[c] = po[((size_t)z * (HD / 4) + c) * ROWS];
             l_g = __builtin_fmaf(w, pm[(size_t)z * 2 * ROWS + ROWS], l_g);
-            acc.x = __builtin_fmaf(w, v.x, acc.x);
-            acc.y = __builtin_fmaf(w, v.y, acc.y);
-            acc.z = __builtin_fmaf(w, v.z, acc.z);
-            acc.w = __builtin_fmaf(w, v.w, acc.w);
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[c][e] = __builtin_fmaf(w, v[c][e], acc[c][e]);
         }
     }
     red_l[g][row] = l_g;
-    red_o[g][row] = acc;
-    __syncthreads();
-    if (g != 0 || !live) return;
-    float l_all = red_l[0][row];
-    f32x4 o4 = red_o[0][row];
 #pragma unroll
-    for (int k = 1; k < MERGE_GROUPS; ++k) {
-        l_all += red_l[k][row];
-        const f32x4 t = red_o[k][row];
-        o4.x += t.x; o4.y += t.y; o4.z += t.z; o4.w += t.w;
-    }
+    for (int c = 0; c < CH; ++c) red_o[c][g][row] = acc[c];
+    __syncthreads();
+    // group g finishes the slices g, g + 4, ...
+    if (g >= CH || !live) return;
+    float l_all = red_l[0][row];
+#pragma unroll
+    for (int k = 1; k < MERGE_GROUPS; ++k) l_all += red_l[k][row];
     const float inv = 1.f / l_all;
     const int tq = row_id / G, gq = row_id - tq * G;
     bf16_t* op = out + ((size_t)rs + tq) * (size_t)(n_q * HD) + (size_t)(kvh * G + gq) * HD;
-    u32x2 o2;
-    o2.x = pack_bf16x2(o4.x * inv, o4.y * inv);
-    o2.y = pack_bf16x2(o4.z * inv, o4.w * inv);
-    *reinterpret_cast<u32x2*>(op + 4 * c) = o2;
+    for (int c = g; c < CH; c += MERGE_GROUPS) {
+        f32x4 o4 = red_o[c][0][row];
+#pragma unroll
+        for (int k = 1; k < MERGE_GROUPS; ++k) o4 += red_o[c][k][row];
+        u32x2 o2;
+        o2.x = pack_bf16x2(o4.x * inv, o4.y * inv);
+        o2.y = pack_bf16x2(o4.z * inv, o4.w * inv);
+        *reinterpret_cast<u32x2*>(op + 4 * (c0 + c)) = o2;
+    }
 }
 
 template <int HD, int NW, bool HALVES = false>
-int launch_attn(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool, const int* row_start,
-                const int* new_len, const int* prefix_len, const int* page_table, int max_pages, const int* tile_start,
-                const int* item_seq, int n_seq, int max_items, int n_q, int n_kv, int n_pool_pages, int n_tokens,
+int launch_attn(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool, const int4* desc,
+                const int* page_table, int max_pages, const int* tile_start, int n_seq, int max_items, int n_q, int n_kv, int n_pool_pages, int n_tokens,
                 hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
     hipLaunchKernelGGL((attn_kernel<HD, NW, false, false, HALVES>), dim3(max_items, n_kv), dim3(NW * 64), 0, s, q, out, nullptr,
-                       nullptr, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq,
+                       nullptr, k_pool, v_pool, desc, page_table, max_pages, tile_start,
                        n_seq, n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, 0, nullptr);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
@@ -774,36 +769,42 @@ int launch_attn(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t
 
 template <int HD>
 int launch_attn_persistent(const bf16_t* q, bf16_t* out, float* part, int n_wgs, const int4* bounds, const bf16_t* k_pool,
-                           const bf16_t* v_pool, const int* row_start, const int* new_len, const int* prefix_len,
-                           const int* page_table, int max_pages, const int* tile_start, const int* item_seq, int n_seq,
+                           const bf16_t* v_pool, const int4* desc,
+                           const int* page_table, int max_pages, const int* tile_start, int n_seq,
                            int max_items, int n_q, int n_kv, int n_pool_pages, int n_tokens, hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
     float* part_ml = part + (size_t)2 * n_wgs * LAPS_ATTN_LONG_ROWS * HD;
     hipLaunchKernelGGL((attn_kernel<HD, 8, false, true>), dim3(n_wgs), dim3(512), 0, s, q, out, part, part_ml, k_pool, v_pool,
-                       row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, n_q, n_kv,
+                       desc, page_table, max_pages, tile_start, n_seq, n_q, n_kv,
                        scale_log2e, n_pool_pages, n_tokens, max_items, 0, bounds);
     LAPS_LAUNCH_CHECK();
     hipLaunchKernelGGL((attn_merge_cut_kernel<HD>), dim3(n_wgs - 1, 4), dim3(LAPS_ATTN_LONG_ROWS), 0, s, out, part, part_ml,
-                       row_start, new_len, tile_start, item_seq, bounds, n_wgs, n_seq, n_q, n_kv, n_tokens);
+                       desc, bounds, n_wgs, n_q, n_kv, n_tokens);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
 
 template <int HD>
 int launch_attn_split(const bf16_t* q, bf16_t* out, float* part, const bf16_t* k_pool, const bf16_t* v_pool,
-                      const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
-                      int max_pages, const int* tile_start, const int* item_seq, int n_seq, int max_items, int n_split, int min_tiles,
+                      const int4* desc, const int* page_table,
+                      int max_pages, const int* tile_start, int n_seq, int max_items, int n_split, int min_tiles,
                       int n_q, int n_kv, int n_pool_pages, int n_tokens, hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
     const size_t blocks = (size_t)max_items * n_kv * n_split;
     float* part_o = part;
     float* part_ml = part + blocks * 128 * HD;
     hipLaunchKernelGGL((attn_kernel<HD, 4, true, false>), dim3(max_items, n_kv, n_split), dim3(256), 0, s, q, out, part_o, part_ml,
-                       k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq,
+                       k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq,
                        n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, min_tiles, nullptr);
     LAPS_LAUNCH_CHECK();
-    hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(max_items, n_kv, HD / 4), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
-                       row_start, new_len, prefix_len, tile_start, item_seq, n_seq, n_q, n_kv, n_split, min_tiles, max_pages, n_tokens);
+    // slices of head_dim a workgroup merges: one where all of them are on the chip at once, four from there on
+    if ((long)max_items * n_kv * (HD / 4) <= MERGE_SMALL) {
+        hipLaunchKernelGGL((attn_merge_kernel<HD, 1>), dim3(max_items, n_kv, HD / 4), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
+                       desc, n_q, n_kv, n_split, min_tiles, n_tokens);
+    } else {
+        hipLaunchKernelGGL((attn_merge_kernel<HD, 4>), dim3(max_items, n_kv, HD / 16), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
+                       desc, n_q, n_kv, n_split, min_tiles, n_tokens);
+    }
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -884,12 +885,14 @@ static size_t item_table_ints(int max_tokens, int max_seqs, int group) {   // it
     return (((size_t)max_tokens * group / 128 + max_seqs + 2) + 3) / 4 * 4;
 }
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group) {
-    return 2 * item_table_ints(max_tokens, max_seqs, group) * sizeof(int) + (LAPS_ATTN_MAX_WGS + 1) * sizeof(int4);
+    const size_t n = item_table_ints(max_tokens, max_seqs, group);
+    return 2 * n * sizeof(int) + (LAPS_ATTN_MAX_WGS + 1 + 2 * n) * sizeof(int4);
 }
-void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds) {
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc) {
     const size_t n = item_table_ints(n_tokens, n_seq, group);
     *pre = item_seq + n;
     *bounds = reinterpret_cast<int4*>(item_seq + 2 * n);
+    *desc = *bounds + LAPS_ATTN_MAX_WGS + 1;
 }
 
 // The persistent kernel takes un-split launches of 256-row blocks where units differ enough in length for equal shares to
@@ -934,35 +937,35 @@ int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, co
     int mt, max_items, n_split, min_tiles;
     attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split, &min_tiles);
     const int n_wgs = partial ? laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes) : 0;
+    int* pre;
+    int4 *bounds, *desc;
+    laps_attn_item_tables(const_cast<int*>(item_seq), n_tokens, n_seq, n_q / n_kv, &pre, &bounds, &desc);
     if (n_wgs > 0) {
-        int* pre;
-        int4* bounds;
-        laps_attn_item_tables(const_cast<int*>(item_seq), n_tokens, n_seq, n_q / n_kv, &pre, &bounds);
         auto launch = hd == 128 ? launch_attn_persistent<128> : launch_attn_persistent<64>;
-        return launch(q, out, partial, n_wgs, bounds, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages,
-                      tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        return launch(q, out, partial, n_wgs, bounds, k_pool, v_pool, desc, page_table, max_pages,
+                      tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     if (n_split > 1) {
         if (!partial) {
             laps_set_error("attention: key-split launch needs the partial-result workspace");
             return LAPS_EINVAL;
         }
-        if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
-        if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_split, min_tiles, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     // 128-row blocks that would be 256-row ones over more key tiles: summed up as those do, so that the width of the page table
     // does not show in the result (the sums of rounded probabilities are also the ones that match the second product:
     // 32B prompts of 64 tokens 1.79e-3 from 64 bits, with sums of unrounded ones 1.81e-3; the same time)
     const bool halves = (long)n_tokens * (n_q / n_kv) > 128L * n_seq;
     if (hd == 128) {
-        if (mt == 2) return launch_attn<128, 8>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
-        if (halves) return launch_attn<128, 4, true>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
-        return launch_attn<128, 4>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (mt == 2) return launch_attn<128, 8>(q, out, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (halves) return launch_attn<128, 4, true>(q, out, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        return launch_attn<128, 4>(q, out, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     if (hd == 64) {
-        if (mt == 2) return launch_attn<64, 8>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
-        if (halves) return launch_attn<64, 4, true>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
-        return launch_attn<64, 4>(q, out, k_pool, v_pool, row_start, new_len, prefix_len, page_table, max_pages, tile_start, item_seq, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (mt == 2) return launch_attn<64, 8>(q, out, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (halves) return launch_attn<64, 4, true>(q, out, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
+        return launch_attn<64, 4>(q, out, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     laps_set_error("attention: head_dim %d not supported (64 or 128)", hd);
     return LAPS_EINVAL;

@@ -326,7 +326,7 @@ static BeginArgs begin_args(const laps_ctx* c, const BatchDesc& b, unsigned char
     a.tok_slot = reinterpret_cast<int*>(ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(ws + L.item_seq);
-    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds);
+    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc);
     a.d = cf.hidden;
     a.eps = cf.rms_eps;
     return a;
@@ -772,7 +772,7 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
     a.tok_slot = reinterpret_cast<int*>(g->ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(g->ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(g->ws + L.item_seq);
-    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds);
+    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc);
     a.x_in = g->x_in;
     a.ln_w = g->ln1_first;
     a.r0 = g->r0;

@@ -89,7 +89,7 @@ struct BeginArgs {
     int n_seq, n_rows, max_pages, n_pool_pages;
     int group, rows_per_wg, max_items, n_kv, attn_wgs;          // attention blocking; attn_wgs as laps_attn_persistent_wgs
     int *new_len, *tok_pos, *tok_slot, *tile_start, *item_seq, *attn_pre;
-    int4* attn_bounds;
+    int4 *attn_bounds, *attn_desc;
     const float* x;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -127,7 +127,7 @@ struct StageArgs {
     int *seq_len_out, *prefix_out, *row_start_out, *page_table_out;   // the graph's staging block
     int *new_len_out, *tok_pos, *tok_slot, *tile_start, *item_seq;    // the graph's workspace
     int* attn_pre;
-    int4* attn_bounds;
+    int4 *attn_bounds, *attn_desc;
     float* x_in;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -185,6 +185,27 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
     const int room = max_pages * LAPS_PAGE - new_len;
     h = h < room ? h : room;
     return h > 0 ? h : 0;
+}
+
+// What a workgroup of the attention needs to know of a work item, two int4 an item: (sequence, row block, new tokens, cached
+// tokens) and (first row, -, -, -); the items past the batch's last one have a sequence of -1.  One scalar load instead of
+// the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a link.  Runs in ONE workgroup of 256 threads after
+// laps_dev_attn_sched.
+static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
+                                                          const int* __restrict__ row_start, int n_seq, int group,
+                                                          int rows_per_wg, int max_pages, const int* tile_start,
+                                                          int max_items, int4* __restrict__ desc) {
+    __syncthreads();   // tile_start was written by other threads of this workgroup
+    for (int i = threadIdx.x; i < n_seq; i += 256) {
+        const int L = new_len[i], H = laps_dev_clamp_prefix(prefix_len[i], L, max_pages);
+        const int first = tile_start[i], v = (L * group + rows_per_wg - 1) / rows_per_wg;
+        const int4 where = make_int4(row_start[i], 0, 0, 0);
+        for (int k = 0; k < v && first + k < max_items; ++k) {
+            desc[2 * (first + k)] = make_int4(i, k, L, H);
+            desc[2 * (first + k) + 1] = where;
+        }
+    }
+    for (int k = tile_start[n_seq] + threadIdx.x; k < max_items; k += 256) desc[2 * k] = make_int4(-1, 0, 0, 0);
 }
 
 // Equal shares of a batch's attention for `n_wgs` workgroups (the persistent long-prompt kernel).  A unit is one
@@ -276,9 +297,9 @@ static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restric
 // calls for splitting the key range; it may be NULL only if max_pages * 16 < 512.  partial_bytes must be that of the table's shares.
 // tile_start: n_seq + 1 ints; item_seq: laps_attn_item_table_bytes (sequence of every row-block work item).
 size_t laps_attn_partial_bytes(int hd, int max_pages);   // 0 when page tables this narrow never split
-// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel.
+// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel and the items' descriptions.
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group);
-void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds);
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc);
 // Workgroups of the persistent long-prompt kernel for a launch shape with partial_bytes of room for the results of cut
 // units (two slots per workgroup); 0: the launch does not use it.
 int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes);
