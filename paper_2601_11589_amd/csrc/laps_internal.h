@@ -192,20 +192,17 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
 // the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a link.  Runs in ONE workgroup of 256 threads after
 // laps_dev_attn_sched.
 static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
-                                                          const int* __restrict__ row_start, int n_seq, int group,
-                                                          int rows_per_wg, int max_pages, const int* tile_start,
-                                                          int max_items, int4* __restrict__ desc) {
-    __syncthreads();   // tile_start was written by other threads of this workgroup
-    for (int i = threadIdx.x; i < n_seq; i += 256) {
-        const int L = new_len[i], H = laps_dev_clamp_prefix(prefix_len[i], L, max_pages);
-        const int first = tile_start[i], v = (L * group + rows_per_wg - 1) / rows_per_wg;
-        const int4 where = make_int4(row_start[i], 0, 0, 0);
-        for (int k = 0; k < v && first + k < max_items; ++k) {
-            desc[2 * (first + k)] = make_int4(i, k, L, H);
-            desc[2 * (first + k) + 1] = where;
-        }
+                                                          const int* __restrict__ row_start, int n_seq, int max_pages,
+                                                          const int* tile_start, const int* item_seq, int max_items,
+                                                          int4* __restrict__ desc) {
+    __syncthreads();   // tile_start and item_seq were written by other threads of this workgroup
+    const int total = tile_start[n_seq];
+    for (int k = threadIdx.x; k < max_items; k += 256) {
+        const bool any = k < total;
+        const int i = any ? item_seq[k] : 0, L = new_len[i];
+        desc[2 * k] = any ? make_int4(i, k - tile_start[i], L, laps_dev_clamp_prefix(prefix_len[i], L, max_pages)) : make_int4(-1, 0, 0, 0);
+        desc[2 * k + 1] = make_int4(row_start[i], 0, 0, 0);
     }
-    for (int k = tile_start[n_seq] + threadIdx.x; k < max_items; k += 256) desc[2 * k] = make_int4(-1, 0, 0, 0);
 }
 
 // Equal shares of a batch's attention for `n_wgs` workgroups (the persistent long-prompt kernel).  A unit is one
@@ -268,11 +265,12 @@ static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restric
     for (int w = threadIdx.x; w <= n_wgs; w += 256) {
         int4 b = make_int4(n_kv, 0, 0, 0);   // the end
         const int u = (w * used + n_wgs - 1) / n_wgs;   // share w begins where the u-th of `used` equal ones does
-        const long x = u < used ? cost * u / used : cost;
+        // 64-bit quotients take a microsecond
+        const long x = u >= used ? cost : cost < (1 << 22) ? (long)((unsigned)cost * (unsigned)u / (unsigned)used) : cost * u / used;
         if (!cut) {
             if (u < units) b = make_int4(u / n_items, u % n_items, 0, 0);
         } else if (x < cost) {
-            const int head = (int)(x / per_head), rem = (int)(x - (long)head * per_head);
+            const int head = cost < (1 << 22) ? (int)((unsigned)x / (unsigned)per_head) : (int)(x / per_head), rem = (int)(x - (long)head * per_head);
             int lo = 0, hi = n_items;   // item with pre[item] <= rem < pre[item + 1]
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
