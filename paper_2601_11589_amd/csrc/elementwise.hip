@@ -2,6 +2,8 @@
 // layer's element-wise steps (residual + next RMSNorm, RoPE + KV append, SwiGLU), weight packing
 // and KV cache moves.  All are bandwidth-trivial next to the GEMMs; they use one workgroup per
 // row with 16-byte accesses.
+#include <type_traits>
+
 #include "laps_internal.h"
 
 namespace {
@@ -68,11 +70,12 @@ constexpr int ROW_MAXV = 8192 / 4 / ROW_THREADS;
 template <int MAXV>
 struct RowRegs {
     f32x4 v[MAXV];
-    __device__ __forceinline__ void load(const f32x4* __restrict__ xr, int d) {
+    u32x2 gain[MAXV];   // loaded with the row: behind the reduction they would be a second round trip
+    __device__ __forceinline__ void load(const f32x4* __restrict__ xr, const bf16_t* __restrict__ w, int d) {
 #pragma unroll
         for (int j = 0; j < MAXV; ++j) {
             const int i = threadIdx.x + j * ROW_THREADS;
-            if (i < d / 4) v[j] = xr[i];
+            if (i < d / 4) v[j] = xr[i], gain[j] = reinterpret_cast<const u32x2*>(w)[i];
         }
     }
     __device__ __forceinline__ void store(f32x4* __restrict__ dst, int d) const {
@@ -82,20 +85,18 @@ struct RowRegs {
             if (i < d / 4) dst[i] = v[j];
         }
     }
-    __device__ __forceinline__ void norm(const bf16_t* __restrict__ w, bf16_t* __restrict__ out_row, int d, float eps,
-                                         float* red) const {
+    __device__ __forceinline__ void norm(bf16_t* __restrict__ out_row, int d, float eps, float* red) const {
         float ss = 0.f;
 #pragma unroll
         for (int j = 0; j < MAXV; ++j)
             if (threadIdx.x + j * ROW_THREADS < d / 4) ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
         const float inv = rsqrtf(block_sum(ss, red) / (float)d + eps);
         u32x2* orow = reinterpret_cast<u32x2*>(out_row);
-        const u32x2* wr = reinterpret_cast<const u32x2*>(w);
 #pragma unroll
         for (int j = 0; j < MAXV; ++j) {
             const int i = threadIdx.x + j * ROW_THREADS;
             if (i < d / 4) {
-                const u32x2 g = wr[i];
+                const u32x2 g = gain[j];
                 u32x2 o;
                 o.x = pack_bf16x2(v[j].x * inv * __uint_as_float(g.x << 16), v[j].y * inv * __uint_as_float(g.x & 0xffff0000u));
                 o.y = pack_bf16x2(v[j].z * inv * __uint_as_float(g.y << 16), v[j].w * inv * __uint_as_float(g.y & 0xffff0000u));
@@ -113,8 +114,8 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_kernel(const float* __res
     const size_t row = blockIdx.x;
     if (row_live && row_live[row] < 0) return;  // padding row: nothing reads its output
     RowRegs<MAXV> r;
-    r.load(reinterpret_cast<const f32x4*>(x + row * d), d);
-    r.norm(w, out + row * d, d, eps, red);
+    r.load(reinterpret_cast<const f32x4*>(x + row * d), w, d);
+    r.norm(out + row * d, d, eps, red);
 }
 
 // ------------------------------------------------------------------ begin of an un-captured batch
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
     }
     const int row = blockIdx.x - 1;
     RowRegs<MAXV> r;
-    r.load(reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.d), a.d);
+    r.load(reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.d), a.ln_w, a.d);
     if (threadIdx.x == 0) {
         int pos, slot;
         token_meta(row, a.n_seq, a.row_start, a.seq_len, a.prefix_len, a.page_table, a.max_pages, a.n_pool_pages, &pos, &slot);
@@ -153,13 +154,42 @@ __global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
     }
     __syncthreads();
     if (row_pos < 0) return;   // padding row: nothing reads its normed row
-    r.norm(a.ln_w, a.r0 + (size_t)row * a.d, a.d, a.eps, red);
+    r.norm(a.r0 + (size_t)row * a.d, a.d, a.eps, red);
+}
+
+// ------------------------------------------------------------------ K-slice sums
+// The row kernels behind a split K are latency: the partial sums have left the caches of the XCDs that wrote them, a round
+// trip takes about a microsecond, and a loop over the slices that adds each as it comes makes a chain of them (residual and
+// norm of 128 rows of the 32B shape: 12 slices 7.7 us, 5 slices 6.0; q/k/v in 4 slices 5.2).  They load SLICES slices for
+// everything a thread holds before they add any; slices past the last one are the last one again, not added.
+template <int SLICES, int N, typename Load>
+__device__ __forceinline__ void add_slices(f32x4 (&acc)[N], int split, Load load) {
+    for (int s0 = 0; s0 < split; s0 += SLICES) {
+        f32x4 p[SLICES][N];
+#pragma unroll
+        for (int k = 0; k < SLICES; ++k)
+#pragma unroll
+            for (int j = 0; j < N; ++j) p[k][j] = load(s0 + k < split ? s0 + k : split - 1, j);
+#pragma unroll
+        for (int k = 0; k < SLICES; ++k)
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const f32x4 sum = acc[j] + p[k][j];
+                acc[j] = s0 + k < split ? sum : acc[j];
+            }
+    }
+}
+// Slices to load at once: all up to 8, equal shares of more.
+static int slices_at_once(int split) {
+    const int rounds = (split + 7) / 8;
+    return (split + rounds - 1) / rounds;
 }
 
 // ------------------------------------------------------------------ sum K slices + residual (+ RMSNorm)
-// x_out[row] = resid[row] (or 0 if resid is null) + sum_s partial[s][row]; optionally
-// r_out[row] = rmsnorm(x_out[row]) in bf16.  One workgroup of 512 threads per row; the row stays in
-// registers between the two passes (d <= 4 * 512 * MAXV).
+// x_out[row] = resid[row] (or 0 if resid is null) + sum_s partial[s][row]; with NORM also
+// r_out[row] = rmsnorm(x_out[row]) in bf16.  Workgroups of 512 threads, MAXV pieces of four values each: one a row
+// where the norm follows (the row stays in registers between the two passes, d <= 4 * 512 * MAXV), else one a piece
+// (grid: rows x pieces), so that a few rows keep more compute units busy.
 constexpr int RESID_THREADS = 512;
 
 __device__ __forceinline__ float block_sum512(float v, float* red) {
@@ -174,7 +204,7 @@ __device__ __forceinline__ float block_sum512(float v, float* red) {
     return t;
 }
 
-template <int MAXV>
+template <int MAXV, int SLICES, bool NORM>
 __global__ __launch_bounds__(RESID_THREADS) void epi_resid_kernel(const float* __restrict__ partial, int split,
                                                                    size_t slice_stride, const float* __restrict__ resid,
                                                                    float* __restrict__ x_out,
@@ -184,44 +214,35 @@ __global__ __launch_bounds__(RESID_THREADS) void epi_resid_kernel(const float* _
     __shared__ float red[RESID_THREADS / 64];
     const size_t row = blockIdx.x;
     if (row_live && row_live[row] < 0) return;  // padding row
-    const int nv = d / 4;
+    const int nv = d / 4, first = (NORM ? 0 : blockIdx.y * RESID_THREADS) + threadIdx.x;
+    int at[MAXV];   // a thread past the row's end loads its last piece again and stores nothing
     f32x4 v[MAXV];
+    u32x2 gain[MAXV];
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+        at[j] = first + j * RESID_THREADS < nv ? first + j * RESID_THREADS : nv - 1;
+        v[j] = resid ? reinterpret_cast<const f32x4*>(resid + row * d)[at[j]] : f32x4{0.f, 0.f, 0.f, 0.f};
+        if (NORM) gain[j] = reinterpret_cast<const u32x2*>(ln_w)[at[j]];
+    }
+    const float* p = partial + row * d;
+    add_slices<SLICES>(v, split, [&](int sl, int j) { return reinterpret_cast<const f32x4*>(p + sl * slice_stride)[at[j]]; });
     float ss = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXV; ++j) {
-        const int i = threadIdx.x + j * RESID_THREADS;
-        if (i < nv) {
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-            if (resid) a = reinterpret_cast<const f32x4*>(resid + row * d)[i];
-            const f32x4* p = reinterpret_cast<const f32x4*>(partial + row * d) + i;
-            const size_t st = slice_stride / 4;
-            int s = 0;
-            for (; s + 4 <= split; s += 4) {  // four independent loads in flight, summed in slice order
-                const f32x4 p0 = p[(size_t)s * st], p1 = p[(size_t)(s + 1) * st], p2 = p[(size_t)(s + 2) * st],
-                            p3 = p[(size_t)(s + 3) * st];
-                a += p0;
-                a += p1;
-                a += p2;
-                a += p3;
-            }
-            for (; s < split; ++s) a += p[(size_t)s * st];
-            reinterpret_cast<f32x4*>(x_out + row * d)[i] = a;
-            v[j] = a;
-            ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
-        }
+        if (first + j * RESID_THREADS >= nv) continue;
+        reinterpret_cast<f32x4*>(x_out + row * d)[at[j]] = v[j];
+        ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
     }
-    if (ln_w == nullptr) return;
-    const float inv = rsqrtf(block_sum512(ss, red) / (float)d + eps);
-    const u32x2* wr = reinterpret_cast<const u32x2*>(ln_w);
+    if constexpr (NORM) {
+        const float inv = rsqrtf(block_sum512(ss, red) / (float)d + eps);
 #pragma unroll
-    for (int j = 0; j < MAXV; ++j) {
-        const int i = threadIdx.x + j * RESID_THREADS;
-        if (i < nv) {
-            const u32x2 g = wr[i];
+        for (int j = 0; j < MAXV; ++j) {
+            if (first + j * RESID_THREADS >= nv) continue;
+            const u32x2 g = gain[j];
             u32x2 o;
             o.x = pack_bf16x2(v[j].x * inv * __uint_as_float(g.x << 16), v[j].y * inv * __uint_as_float(g.x & 0xffff0000u));
             o.y = pack_bf16x2(v[j].z * inv * __uint_as_float(g.y << 16), v[j].w * inv * __uint_as_float(g.y & 0xffff0000u));
-            reinterpret_cast<u32x2*>(r_out + row * d)[i] = o;
+            reinterpret_cast<u32x2*>(r_out + row * d)[at[j]] = o;
         }
     }
 }
@@ -238,7 +259,7 @@ __global__ __launch_bounds__(RESID_THREADS) void epi_resid_kernel(const float* _
 // rows 5.1 / 5.4 us turned over and 4.0 / 4.0 one by one, 128 rows 6.2 / 5.5 and 5.2 / 4.2, 192 rows 7.6 / 5.6 and 8.3 / 5.6.
 constexpr int V_ROWS = 16;
 constexpr int TURN_ABOVE = 128;   // rows
-template <int HD, bool TURN>
+template <int HD, bool TURN, int SLICES>
 __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __restrict__ partial, int split,
                                                                size_t slice_stride, const bf16_t* __restrict__ bias,
                                                                const int* __restrict__ tok_pos,
@@ -262,16 +283,30 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
         }
         __syncthreads();
         const int col = (n_q + n_kv + g) * HD + 4 * c;
+        constexpr int NP = V_ROWS / PASS;
+        const float* p[NP];
+        f32x4 acc[NP];
 #pragma unroll
-        for (int i = 0; i < V_ROWS / PASS; ++i) {
+        for (int i = 0; i < NP; ++i) {
+            const int row = r0 + threadIdx.x / F4 + i * PASS;
+            p[i] = partial + (size_t)(row < rows ? row : rows - 1) * width + col;
+            acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        float b[4] = {0.f, 0.f, 0.f, 0.f};
+        if (bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) b[e] = bf16_to_f32(bias[col + e]);
+        }
+        const bool any = __syncthreads_or(threadIdx.x < V_ROWS && vslot[threadIdx.x] >= 0);
+        if (!any) return;   // padding rows only
+        add_slices<SLICES>(acc, split, [&](int sl, int i) { return *reinterpret_cast<const f32x4*>(p[i] + sl * slice_stride); });
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
             const int rr = threadIdx.x / F4 + i * PASS;
-            if (vslot[rr] < 0) continue;
-            const float* p = partial + (size_t)(r0 + rr) * width + col;
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-            for (int s = 0; s < split; ++s) a += *reinterpret_cast<const f32x4*>(p + s * slice_stride);
+            f32x4 a = acc[i];
             if (bias) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[e] += bf16_to_f32(bias[col + e]);
+                for (int e = 0; e < 4; ++e) a[e] += b[e];
             }
             u32x2 w;
             w.x = pack_bf16x2(a.x, a.y);
@@ -315,25 +350,31 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
         }
         return;
     }
-    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-    const float* p = partial + row * width;
-    for (int s = 0; s < split; ++s) {
-        a += *reinterpret_cast<const f32x4*>(p + s * slice_stride + c0);
-        b += *reinterpret_cast<const f32x4*>(p + s * slice_stride + c1);
+    // positions past the table are the caller's error; clamp so that the read stays in bounds
+    const float2* cs = rope + (size_t)(pos < max_pos ? pos : max_pos - 1) * half + j;
+    float2 turn[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) turn[e] = cs[e];
+    float bias_a[4] = {0.f, 0.f, 0.f, 0.f}, bias_b[4] = {0.f, 0.f, 0.f, 0.f};
+    if (bias) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias_a[e] = bf16_to_f32(bias[c0 + e]), bias_b[e] = bf16_to_f32(bias[c1 + e]);
     }
+    f32x4 ab[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    const float* p = partial + row * width;
+    add_slices<SLICES>(ab, split, [&](int sl, int h) { return *reinterpret_cast<const f32x4*>(p + sl * slice_stride + (h ? c1 : c0)); });
+    f32x4 a = ab[0], b = ab[1];
     if (bias) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            a[e] += bf16_to_f32(bias[c0 + e]);
-            b[e] += bf16_to_f32(bias[c1 + e]);
+            a[e] += bias_a[e];
+            b[e] += bias_b[e];
         }
     }
     if (TURN || head < n_q + n_kv) {
-        // positions past the table are the caller's error; clamp so that the read stays in bounds
-        const float2* cs = rope + (size_t)(pos < max_pos ? pos : max_pos - 1) * half + j;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float2 t = cs[e];
+            const float2 t = turn[e];
             const float ra = a[e] * t.x - b[e] * t.y;
             const float rb = b[e] * t.x + a[e] * t.y;
             a[e] = ra;
@@ -364,6 +405,7 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
 
 // ------------------------------------------------------------------ sum K slices + SwiGLU
 // Packed gate/up columns: block b of 64 columns = gate cols [32b, 32b+32) then up cols [32b, 32b+32).
+template <int SLICES>
 __global__ __launch_bounds__(ROW_THREADS) void epi_swiglu_kernel(const float* __restrict__ partial, int split,
                                                                   size_t slice_stride, bf16_t* __restrict__ act,
                                                                   int inter, const int* __restrict__ row_live) {
@@ -376,12 +418,10 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_swiglu_kernel(const float* __
         const int c = c4 * 4;
         const int blk = c / 32, in = c % 32;
         const size_t gcol = (size_t)blk * 64 + in;
-        f32x4 g = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < split; ++s) {
-            const float* p = partial + s * slice_stride + row * width;
-            g += *reinterpret_cast<const f32x4*>(p + gcol);
-            u += *reinterpret_cast<const f32x4*>(p + gcol + 32);
-        }
+        f32x4 gu[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        const float* p = partial + row * width + gcol;
+        add_slices<SLICES>(gu, split, [&](int sl, int h) { return *reinterpret_cast<const f32x4*>(p + sl * slice_stride + 32 * h); });
+        const f32x4 g = gu[0], u = gu[1];
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = g[e] / (1.f + __expf(-g[e])) * u[e];
@@ -579,7 +619,7 @@ __global__ __launch_bounds__(ROW_THREADS) void stage_kernel(const StageArgs a) {
         if (src == copy_to) copy_to = nullptr;
     }
     RowRegs<ROW_MAXV> r;
-    r.load(src, a.d);
+    r.load(src, a.ln_w, a.d);
     if (t == 0) where[2] = 0;
     int run = staged_scan(a, lo, hi, &mine, sums);   // its barrier orders the line above before the lines below
     if (row >= run && row < run + mine)
@@ -615,7 +655,7 @@ __global__ __launch_bounds__(ROW_THREADS) void stage_kernel(const StageArgs a) {
     }
     if (copy_to) r.store(copy_to, a.d);
     if (!live) return;   // padding row: nothing reads its normed row
-    r.norm(a.ln_w, a.r0 + (size_t)row * a.d, a.d, a.eps, red);
+    r.norm(a.r0 + (size_t)row * a.d, a.d, a.eps, red);
 }
 
 }  // namespace
@@ -653,16 +693,28 @@ int laps_launch_rmsnorm(const float* x, const bf16_t* w, bf16_t* out, int rows, 
 int laps_launch_epi_resid(const float* partial, int split, const float* resid, float* x_out, const bf16_t* ln_w,
                           bf16_t* r_out, int rows, int d, float eps, const int* row_live, hipStream_t s) {
     const size_t stride = (size_t)rows * d;
-    if (d <= 4 * RESID_THREADS * 1)
-        hipLaunchKernelGGL(epi_resid_kernel<1>, dim3(rows), dim3(RESID_THREADS), 0, s, partial, split, stride, resid,
-                           x_out, ln_w, r_out, d, eps, row_live);
-    else if (d <= 4 * RESID_THREADS * 4)
-        hipLaunchKernelGGL(epi_resid_kernel<4>, dim3(rows), dim3(RESID_THREADS), 0, s, partial, split, stride, resid,
-                           x_out, ln_w, r_out, d, eps, row_live);
-    else {
+    const int pieces = (d / 4 + RESID_THREADS - 1) / RESID_THREADS, at_once = slices_at_once(split);
+    if (pieces > 4) {
         laps_set_error("row width %d too large for the fused residual + norm kernel (max %d)", d, 4 * RESID_THREADS * 4);
         return LAPS_EINVAL;
     }
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rows, ln_w ? 1 : pieces), dim3(RESID_THREADS), 0, s, partial, split, stride, resid, x_out,
+                           ln_w, r_out, d, eps, row_live);
+    };
+    auto with = [&](auto slices) {
+        constexpr int S = decltype(slices)::value;
+        if (!ln_w) go(epi_resid_kernel<1, S, false>);
+        else if (pieces == 1) go(epi_resid_kernel<1, S, true>);
+        else if (pieces == 2) go(epi_resid_kernel<2, S, true>);
+        else if (pieces == 3) go(epi_resid_kernel<3, S, true>);
+        else go(epi_resid_kernel<4, S, true>);
+    };
+    if (at_once <= 1) with(std::integral_constant<int, 1>{});
+    else if (at_once <= 2) with(std::integral_constant<int, 2>{});
+    else if (at_once <= 4) with(std::integral_constant<int, 4>{});
+    else if (at_once <= 6) with(std::integral_constant<int, 6>{});
+    else with(std::integral_constant<int, 8>{});
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -674,8 +726,16 @@ int laps_launch_epi_qkv(const float* partial, int split, const bf16_t* bias, con
     const bool turn = rows > TURN_ABOVE;
     const int chunks = ((n_q + (turn ? 1 : 2) * n_kv) * (hd / 8) + ROW_THREADS - 1) / ROW_THREADS;
     const dim3 grid = turn ? dim3(rows * chunks + (rows + V_ROWS - 1) / V_ROWS * n_kv) : dim3(rows, chunks);
-    auto kern = turn ? (hd == 128 ? epi_qkv_kernel<128, true> : epi_qkv_kernel<64, true>)   // head_dim is one of the two
-                     : (hd == 128 ? epi_qkv_kernel<128, false> : epi_qkv_kernel<64, false>);   // (check_cfg)
+    const int at_once = slices_at_once(split);
+    auto pick = [&](auto slices) {   // head_dim is one of the two (check_cfg)
+        constexpr int S = decltype(slices)::value;
+        return turn ? (hd == 128 ? epi_qkv_kernel<128, true, S> : epi_qkv_kernel<64, true, S>)
+                    : (hd == 128 ? epi_qkv_kernel<128, false, S> : epi_qkv_kernel<64, false, S>);
+    };
+    auto kern = at_once <= 1   ? pick(std::integral_constant<int, 1>{})
+                : at_once <= 2 ? pick(std::integral_constant<int, 2>{})
+                : at_once <= 4 ? pick(std::integral_constant<int, 4>{})
+                               : pick(std::integral_constant<int, 8>{});
     hipLaunchKernelGGL(kern, grid, dim3(ROW_THREADS), 0, s, partial, split, stride, bias, tok_pos, tok_slot, rope,
                        max_pos, q_out, k_pool, v_pool, n_q, n_kv, rows, chunks);
     LAPS_LAUNCH_CHECK();
@@ -685,7 +745,7 @@ int laps_launch_epi_qkv(const float* partial, int split, const bf16_t* bias, con
 int laps_launch_epi_swiglu(const float* partial, int split, bf16_t* act, int rows, int inter, const int* row_live,
                            hipStream_t s) {
     const size_t stride = (size_t)rows * 2 * inter;
-    hipLaunchKernelGGL(epi_swiglu_kernel, dim3(rows, (inter / 4 + ROW_THREADS - 1) / ROW_THREADS), dim3(ROW_THREADS), 0,
+    hipLaunchKernelGGL(split <= 2 ? epi_swiglu_kernel<2> : epi_swiglu_kernel<4>, dim3(rows, (inter / 4 + ROW_THREADS - 1) / ROW_THREADS), dim3(ROW_THREADS), 0,
                        s, partial, split, stride, act, inter, row_live);
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
