@@ -13,7 +13,8 @@ LIB = os.path.join(HERE, "liblaps.so")
 SOURCES = ["gemm.hip", "elementwise.hip", "attention.hip", "capi.hip", "planner.cpp", "latency_model.cpp", "awd.cpp", "pool_ctrl.cpp", "window.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 VALU forms are switched off for all device code
-DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                "-mllvm", "-amdgpu-kernarg-preload-count=16"]   # the first arguments arrive in registers: 0.1 us a short kernel
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-result"]
 
 
