@@ -317,8 +317,7 @@ static BeginArgs begin_args(const laps_ctx* c, const BatchDesc& b, unsigned char
     a.max_pages = b.max_pages;
     a.n_pool_pages = c->pool_pages;
     a.group = cf.n_q_heads / cf.n_kv_heads;
-    int n_split = 0, min_tiles = 0;
-    laps_attn_plan(b.n_seq, b.n_tokens, a.group, cf.n_kv_heads, b.max_pages, &a.rows_per_wg, &a.max_items, &n_split, &min_tiles);
+    laps_attn_plan(b.n_seq, b.n_tokens, a.group, cf.n_kv_heads, b.max_pages, &a.rows_per_wg, &a.max_items, &a.n_split, &a.min_tiles);
     a.n_kv = cf.n_kv_heads;
     a.attn_wgs = laps_attn_persistent_wgs(b.n_seq, b.n_tokens, a.group, cf.n_kv_heads, cf.head_dim, b.max_pages, L.total - L.partial);
     a.new_len = reinterpret_cast<int*>(ws + L.new_len);
@@ -326,7 +325,7 @@ static BeginArgs begin_args(const laps_ctx* c, const BatchDesc& b, unsigned char
     a.tok_slot = reinterpret_cast<int*>(ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(ws + L.item_seq);
-    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc);
+    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc, &a.attn_blocks);
     a.d = cf.hidden;
     a.eps = cf.rms_eps;
     return a;
@@ -759,8 +758,7 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
     a.max_pages = g->max_pages;
     a.n_pool_pages = g->ctx->pool_pages;
     a.group = cf.n_q_heads / cf.n_kv_heads;
-    int n_split = 0, min_tiles = 0;
-    laps_attn_plan(g->depth, M, a.group, cf.n_kv_heads, g->max_pages, &a.rows_per_wg, &a.max_items, &n_split, &min_tiles);
+    laps_attn_plan(g->depth, M, a.group, cf.n_kv_heads, g->max_pages, &a.rows_per_wg, &a.max_items, &a.n_split, &a.min_tiles);
     a.n_kv = cf.n_kv_heads;
     a.attn_wgs = laps_attn_persistent_wgs(g->depth, M, a.group, cf.n_kv_heads, cf.head_dim, g->max_pages, L.total - L.partial);
     a.seq_len_out = g->seq_len;
@@ -772,7 +770,7 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
     a.tok_slot = reinterpret_cast<int*>(g->ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(g->ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(g->ws + L.item_seq);
-    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc);
+    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc, &a.attn_blocks);
     a.x_in = g->x_in;
     a.ln_w = g->ln1_first;
     a.r0 = g->r0;

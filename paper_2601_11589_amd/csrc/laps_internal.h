@@ -88,8 +88,9 @@ struct BeginArgs {
     const int *row_start, *seq_len, *prefix_len, *page_table;   // seq_len may be NULL
     int n_seq, n_rows, max_pages, n_pool_pages;
     int group, rows_per_wg, max_items, n_kv, attn_wgs;          // attention blocking; attn_wgs as laps_attn_persistent_wgs
+    int n_split, min_tiles;                                     // as laps_attn_plan
     int *new_len, *tok_pos, *tok_slot, *tile_start, *item_seq, *attn_pre;
-    int4 *attn_bounds, *attn_desc;
+    int4 *attn_bounds, *attn_desc, *attn_blocks;
     const float* x;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -124,10 +125,11 @@ struct StageArgs {
     int n_real, n_rows, depth, len_bucket, max_pages, n_pool_pages;
     int group, rows_per_wg, max_items;              // attention blocking of the graph's shape
     int n_kv, attn_wgs;                             // workgroups of the persistent attention kernel (0: not used)
+    int n_split, min_tiles;                         // as laps_attn_plan
     int *seq_len_out, *prefix_out, *row_start_out, *page_table_out;   // the graph's staging block
     int *new_len_out, *tok_pos, *tok_slot, *tile_start, *item_seq;    // the graph's workspace
     int* attn_pre;
-    int4 *attn_bounds, *attn_desc;
+    int4 *attn_bounds, *attn_desc, *attn_blocks;
     float* x_in;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -188,7 +190,7 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
 }
 
 // What a workgroup of the attention needs to know of a work item, two int4 an item: (sequence, row block, new tokens, cached
-// tokens) and (first row, -, -, -); the items past the batch's last one have a sequence of -1.  One scalar load instead of
+// tokens) and (first row; with split key ranges also the item's first part, its parts, -); the items past the batch's last one have a sequence of -1.  One scalar load instead of
 // the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a link.  Runs in ONE workgroup of 256 threads after
 // laps_dev_attn_sched.
 static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
@@ -205,6 +207,52 @@ static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict_
     }
 }
 
+constexpr int LAPS_ATTN_KT = 64;          // keys per tile
+
+// Key-range splits of a batch whose (item, kv head) blocks leave compute units idle: parts of equal numbers of key tiles over
+// all items, as long as makes LAPS_ATTN_SPLIT_WGS workgroups of the batch's tiles, at least min_tiles.  Equal numbers of parts an
+// item, tried before, made the longest item's parts decide: 32B, turns of 17 to 32 tokens over 512 to 4096 keys, parts of up to 9
+// tiles where all parts together are 4 tiles for every place on the chip.
+// blocks: two int4 a part, (sequence, row block, new tokens, cached tokens) and (first row, its number among the item's parts, key
+// tiles of a part, the item's parts); a sequence of -1 past the last one, max_items * n_split in all, which the parts never exceed.
+// Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; max_items < 256.
+constexpr int LAPS_ATTN_SPLIT_WGS = 512;   // two workgroups a compute unit
+static __device__ __forceinline__ void laps_dev_attn_split(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
+                                                           const int* __restrict__ row_start, int n_seq, int group, int n_kv,
+                                                           int rows_per_wg, int max_pages, const int* tile_start, const int* item_seq,
+                                                           int max_items, int n_split, int min_tiles, int4* desc, int4* blocks,
+                                                           int* sums) {
+    __syncthreads();   // desc was written by other threads of this workgroup
+    const int k = threadIdx.x, cap = max_items * n_split;
+    const int n_items = tile_start[n_seq] < max_items ? tile_start[n_seq] : max_items;
+    const bool any = k < n_items;
+    int4 it = make_int4(-1, 0, 0, 0);
+    int nt = 0;
+    if (any) {
+        const int i = item_seq[k], L = new_len[i], H = laps_dev_clamp_prefix(prefix_len[i], L, max_pages), q = k - tile_start[i];
+        const int last = ((q + 1) * rows_per_wg < L * group ? (q + 1) * rows_per_wg : L * group) - 1;
+        it = make_int4(i, q, L, H);
+        nt = (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT;
+    }
+    int total, used, parts, first;
+    laps_dev_scan(nt, sums, &total);
+    const int places = LAPS_ATTN_SPLIT_WGS / n_kv > 1 ? LAPS_ATTN_SPLIT_WGS / n_kv : 1;
+    for (int per = (total + places - 1) / places > min_tiles ? (total + places - 1) / places : min_tiles;; per += 1 + per / 8) {
+        parts = (nt + per - 1) / per;   // one each in the end: n_items <= cap
+        first = laps_dev_scan(parts, sums, &used) - parts;
+        if (used <= cap) break;
+    }
+    if (any) {
+        const int each = (nt + parts - 1) / parts, real = (nt + each - 1) / each, rs = row_start[it.x];
+        desc[2 * k + 1] = make_int4(rs, first, real, 0);
+        for (int z = 0; z < parts; ++z) {
+            blocks[2 * (first + z)] = z < real ? it : make_int4(-1, 0, 0, 0);
+            blocks[2 * (first + z) + 1] = make_int4(rs, z, each, real);
+        }
+    }
+    for (int x = used + k; x < cap; x += 256) blocks[2 * x] = make_int4(-1, 0, 0, 0);
+}
+
 // Equal shares of a batch's attention for `n_wgs` workgroups (the persistent long-prompt kernel).  A unit is one
 // (kv head, work item) pair and costs its key tiles plus COST0 (its prologue and epilogue; 1 to 10 tried, 4 is best or even); the units
 // of all kv heads, one head after the other, are cut into equal lengths.  bounds[w] = (kv head, item, first tile) is
@@ -216,7 +264,6 @@ static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict_
 // of 11) 55 us cut, 63 not; 1000 rows over 600 (160 units of up to 30, shares of 13) 73 cut, 66 not.
 // Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; pre (max_items + 1 ints) holds the prefix sums of the
 // item costs.
-constexpr int LAPS_ATTN_KT = 64;          // keys per tile
 constexpr int LAPS_ATTN_LONG_ROWS = 256;  // query rows per work item of the long-prompt kernel
 constexpr int LAPS_ATTN_MAX_WGS = 256;    // one workgroup per compute unit
 constexpr int LAPS_ATTN_COST0 = 4;        // in key tiles (about 2 us), as CUT_COST
@@ -295,9 +342,10 @@ static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restric
 // calls for splitting the key range; it may be NULL only if max_pages * 16 < 512.  partial_bytes must be that of the table's shares.
 // tile_start: n_seq + 1 ints; item_seq: laps_attn_item_table_bytes (sequence of every row-block work item).
 size_t laps_attn_partial_bytes(int hd, int max_pages);   // 0 when page tables this narrow never split
-// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel and the items' descriptions.
+// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel, the items' descriptions and
+// the parts of split key ranges.
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group);
-void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc);
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc, int4** blocks);
 // Workgroups of the persistent long-prompt kernel for a launch shape with partial_bytes of room for the results of cut
 // units (two slots per workgroup); 0: the launch does not use it.
 int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes);
