@@ -111,6 +111,7 @@ struct GemmArgs {
     const int* row_live;   // [M] or NULL: rows with a negative entry are padding - a row tile that holds nothing else is
                            // skipped (its output is then not written), and dma_tile loads none of them
     const int* n_live;     // NULL, or where the number of leading rows that are not padding is found (at most M count)
+    int cols;              // columns of W and of the output that the tiles cover; N apart from them is the outputs' row length
 };
 
 // Writes a workgroup's accumulators with the requested epilogue.  Accumulator layout of the 32x32 MFMA:
@@ -427,7 +428,7 @@ __device__ __forceinline__ void store_dma_tile(const f32x4 (&acc)[D::MI][D::NI],
                                                int n0, int wm, int wn, int lrow, int lk) {
     const int N = g.N;
     const int row0 = m0 + wm * D::WTM + lrow, col0 = n0 + wn * D::WTN;
-    const auto inside = [&](int ni) { return !GUARD || col0 + ni * 16 < N; };   // wave-uniform; N is a multiple of 64
+    const auto inside = [&](int ni) { return !GUARD || col0 + ni * 16 < g.cols; };   // wave-uniform; cols is a multiple of 64
     if constexpr (EPI == EPI_PARTIAL) {
         float* out = g.out_f32 + (size_t)ks * g.M * N + col0 + 4 * lk;
 #pragma unroll
@@ -557,7 +558,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
         return i32x4{__builtin_amdgcn_readfirstlane((int)(unsigned)p), __builtin_amdgcn_readfirstlane((int)(p >> 32)),
                      __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
     };
-    i32x4 ra, rb = rsrc(g.W + (size_t)n0 * K, (unsigned)(D::RAGGED && g.N - n0 < BN ? g.N - n0 : BN) * row_bytes);
+    i32x4 ra, rb = rsrc(g.W + (size_t)n0 * K, (unsigned)(D::RAGGED && g.cols - n0 < BN ? g.cols - n0 : BN) * row_bytes);
     int a_bytes, b_bytes = rb[2];
     // Offsets of a lane's chunks: half slab row q -> tile row (q / (WT/2)) * WT + half * WT/2 + q % (WT/2).  Rows of A past the
     // last one lie behind the descriptor's end and padding rows are sent there: no request is made for them (a unit keeps a
@@ -732,7 +733,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g, unsigned char* smem,
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load may land after this workgroup's LDS is another's
     acc_fence<D>(acc);
-    if (D::RAGGED && __builtin_expect(n0 + BN > g.N, 0)) store_dma_tile<D, EPI, true>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
+    if (D::RAGGED && __builtin_expect(n0 + BN > g.cols, 0)) store_dma_tile<D, EPI, true>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
     else store_dma_tile<D, EPI, false>(acc, g, M, tc.ks, m0, n0, wm, wn, lrow, lk);
 }
 
@@ -810,6 +811,32 @@ __global__ __launch_bounds__(256, 1) void gemm_live_kernel(const GemmArgs g, con
     else dma_tile<192, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, tiles_n, blockIdx.x, nullptr);
 }
 
+// Whole rounds of big tiles over the compute units, and the columns that they leave in smaller tiles behind them: a last round
+// of a few big tiles takes as long as a full one.  `big` workgroups of 256 x 256 (320 x 256 if tall) on g, the others on h, the
+// columns behind g's; small: 0 = 128 x 128, 1 = 192 x 128, 2 = 256 x 128, one workgroup a unit beside the big tiles' registers.
+// What a few tiles in the last round cost, SwiGLU, K = 5120: 1847 rows of 55296 columns, 1296 tiles of 320 x 256 in 5.06 rounds,
+// 772 us; 1278 of them and 90 of 128 x 128 724.  1024 rows of 37888 columns, K = 3584, 592 tiles of 256 x 256 239 us; 512 and 240
+// of 192 x 128 202.  The sums are the same bits: every tile walks K alike.
+constexpr int kMixRows[3] = {128, 192, 256};
+template <int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_mix_kernel(const GemmArgs g, const GemmArgs h, const int big, const int tall, const int small) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int M = live_rows(g), bid = blockIdx.x;
+    if (M <= 0) return;
+    if (bid < big) {
+        const int rows = tall ? 320 : 256, tiles_m = (M + rows - 1) / rows;
+        if (bid >= tiles_m * g.tiles_n) return;
+        if (tall) dma_tile<320, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, g.tiles_n, bid, nullptr);
+        else dma_tile<256, 256, 2, 2, EPI, false>(g, smem, M, tiles_m, g.tiles_n, bid, nullptr);
+        return;
+    }
+    const int rows = small == 0 ? kMixRows[0] : small == 1 ? kMixRows[1] : kMixRows[2], tiles_m = (M + rows - 1) / rows;
+    if (bid - big >= tiles_m * h.tiles_n) return;
+    if (small == 0) dma_tile<128, 128, 2, 2, EPI, false>(h, smem, M, tiles_m, h.tiles_n, bid - big, nullptr);
+    else if (small == 1) dma_tile<192, 128, 2, 2, EPI, false>(h, smem, M, tiles_m, h.tiles_n, bid - big, nullptr);
+    else dma_tile<256, 128, 2, 2, EPI, false>(h, smem, M, tiles_m, h.tiles_n, bid - big, nullptr);
+}
+
 int launch_gemm(void (*kern)(const GemmArgs), bool* attr_set, int threads, int lds, const GemmArgs& a, hipStream_t s) {
     if (!*attr_set) {   // per kernel; idempotent, so a race only repeats the call
         LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
@@ -870,6 +897,15 @@ constexpr TileDef kTiles[] = {
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
+// The tiles behind whole rounds of big ones, alone on their compute unit: cost as above, without `part`.  Fitted to the choices of
+// 84 products (gate/up of the three models at 14 row counts, the others of 32B at six, 7 to 10 ways each): against the best
+// plain tile 1.023 times as fast in the mean and none slower; the best of all ways is 0.2 % away.
+struct MixDef {
+    int cfg;
+    double fill, slab;
+};
+constexpr MixDef kMix[3] = {{0, 4.0, 0.40}, {7, 4.0, 0.75}, {8, 4.0, 0.80}};   // in the order of kMixRows
+
 template <int EPI>
 int launch_live(const GemmArgs& a, hipStream_t s) {
     constexpr int cfg[kLiveTiles] = {2, 8, 9, 10, 6, 3, 4};   // in the order of kLiveRows, kLiveCols
@@ -899,6 +935,38 @@ int launch_live(const GemmArgs& a, hipStream_t s) {
     return LAPS_OK;
 }
 
+// Column tiles of 256 that whole rounds of the big tiles take.
+int mix_columns(int tiles_m, int n) { return (int)((long)tiles_m * (n / 256) / 256 * 256 / tiles_m); }
+
+template <int EPI>
+int launch_mix(const GemmArgs& a, bool tall, int small, hipStream_t s) {
+    const int lds_big = tall ? DmaTraits<320, 256, 2, 2>::LDS : DmaTraits<256, 256, 2, 2>::LDS;
+    constexpr int lds_small[3] = {DmaTraits<128, 128, 2, 2>::LDS, DmaTraits<192, 128, 2, 2>::LDS, DmaTraits<256, 128, 2, 2>::LDS};
+    constexpr int lds_most = DmaTraits<256, 256, 2, 2>::LDS > DmaTraits<320, 256, 2, 2>::LDS ? DmaTraits<256, 256, 2, 2>::LDS : DmaTraits<320, 256, 2, 2>::LDS;
+    static_assert(lds_small[2] <= lds_most && lds_small[1] <= lds_most, "the attribute below covers every tile");
+    GemmArgs g = a, h = a;
+    g.tiles_n = mix_columns(a.tiles_m, a.N);
+    g.cols = g.tiles_n * 256;
+    h.cols = a.N - g.cols;
+    h.tiles_n = (h.cols + 127) / 128;
+    h.tiles_m = (a.M + kMixRows[small] - 1) / kMixRows[small];
+    h.W = a.W + (size_t)g.cols * a.K;
+    if (a.out_f32) h.out_f32 = a.out_f32 + g.cols;
+    if (a.resid) h.resid = a.resid + g.cols;
+    if (a.out_bf16) h.out_bf16 = a.out_bf16 + g.cols / 2;
+    auto kern = gemm_mix_kernel<EPI>;
+    static bool attr_set = false;  // as in launch_gemm
+    if (!attr_set) {
+        LAPS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_most));
+        attr_set = true;
+    }
+    const int big = g.tiles_m * g.tiles_n;
+    hipLaunchKernelGGL(kern, dim3(big + h.tiles_m * h.tiles_n), dim3(256), lds_big > lds_small[small] ? lds_big : lds_small[small], s, g, h, big,
+                       (int)tall, small);
+    LAPS_LAUNCH_CHECK();
+    return LAPS_OK;
+}
+
 }  // namespace
 
 void laps_gemm_tile_dims(int cfg, int* bm, int* bn) {
@@ -922,6 +990,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
             p.ws = 2;
         }
         p.cfg = cfg;
+        p.rest = 0;
         p.k_per_split = per * BK;
         p.split = (ksteps + per - 1) / per;
         p.epi = (p.split == 1) ? want_epi : EPI_PARTIAL;
@@ -988,7 +1057,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     const double mn = (double)m * n;
     const double own = want_epi == EPI_RESID ? 8.0 * mn : want_epi == EPI_SWIGLU ? mn : row_kernel ? 2.0 * mn : 4.0 * mn;
     double best = 1e30;
-    int best_cfg = -1, best_split = 1;
+    int best_cfg = -1, best_split = 1, best_rest = 0;
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
         // Inside layers the last column tile may reach past n (not on 320 x 256, see DmaTraits), and 192 rows may need more row
@@ -1031,6 +1100,23 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
                 best = us;
                 best_cfg = cfg;
                 best_split = s;
+                best_rest = 0;
+            }
+            // Whole rounds only, and smaller tiles in one round behind them, where that is 2 % ahead.
+            if (s != 1 || far || ragged || (cfg != 2 && cfg != 10) || wgs <= 256 || wgs % 256 == 0) continue;
+            const int columns = mix_columns(tiles_m, n), left = n - columns * 256;
+            if (columns < 1) continue;
+            for (const MixDef& x : kMix) {
+                const int rows = kTiles[x.cfg].bm;
+                if ((long)((m + rows - 1) / rows) * ((left + 127) / 128) > 256) continue;
+                const double mixed = 4.0 + (wgs / 256) * (t.fill + per * t.slab) + x.fill + per * x.slab;
+                const double total = 1.02 * (us + 1.02 * (mixed > stream ? mixed : stream) - 1.02 * tiles);
+                if (tiles > stream && total < best) {
+                    best = total;
+                    best_cfg = cfg;
+                    best_split = 1;
+                    best_rest = 1 + x.cfg;
+                }
             }
         }
     }
@@ -1038,7 +1124,9 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         want_epi = EPI_PARTIAL;
         return finish(1, force_split > 0 ? force_split : 1);
     }
-    return finish(best_cfg, best_split);
+    p = finish(best_cfg, best_split);
+    p.rest = p.split == 1 ? best_rest : 0;
+    return p;
 }
 
 size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap) {   // m <= 128
@@ -1090,6 +1178,7 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
     g.out_bf16 = out_bf16;
     g.row_live = row_live;
     g.n_live = n_live;
+    g.cols = n;
     // Loads straight into LDS are given 16-byte pieces that lie on 16-byte bounds: rows are whole multiples of 128 bytes, so
     // the bases decide.  (5120 x 5120 at 8 / 128 / 2048 rows, weights cold: 22 / 25 / 92 us, with weights 2 bytes off 26 / 30 / 155.)
     const bool aligned = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w)) & 15) == 0;
@@ -1098,6 +1187,19 @@ int laps_gemm_launch(const GemmPlan& p, const bf16_t* a, const bf16_t* w, int m,
         if (p.epi == EPI_PARTIAL) return launch_live<EPI_PARTIAL>(g, s);
         if (p.epi == EPI_RESID) return launch_live<EPI_RESID>(g, s);
         return launch_live<EPI_SWIGLU>(g, s);
+    }
+    if (p.rest != 0 && aligned && k < kMaxBufferK) {
+        int small = -1;
+        for (int i = 0; i < 3; ++i)
+            if (kMix[i].cfg == p.rest - 1) small = i;
+        if (small < 0 || (p.cfg != 2 && p.cfg != 10) || p.split != 1 || n % 256 != 0 || mix_columns(g.tiles_m, n) < 1 ||
+            mix_columns(g.tiles_m, n) >= n / 256) {
+            laps_set_error("gemm: no tile %d behind whole rounds of tile %d (m=%d n=%d)", p.rest - 1, p.cfg, m, n);
+            return LAPS_EINVAL;
+        }
+        if (p.epi == EPI_PARTIAL) return launch_mix<EPI_PARTIAL>(g, p.cfg == 10, small, s);
+        if (p.epi == EPI_RESID) return launch_mix<EPI_RESID>(g, p.cfg == 10, small, s);
+        return launch_mix<EPI_SWIGLU>(g, p.cfg == 10, small, s);
     }
     if (k >= kMaxBufferK || !aligned) {
         int cfg = p.cfg, ws = p.ws;

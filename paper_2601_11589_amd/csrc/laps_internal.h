@@ -58,6 +58,7 @@ struct GemmPlan {
     int k_per_split;  // multiple of 64
     int epi;          // epilogue the launch will apply: the requested one if split == 1, else EPI_PARTIAL
     int ws;           // slabs that every K slice holds a multiple of: 1 or 2
+    int rest;         // 0, or 1 + the tile shape of the columns that whole rounds of `cfg` over the compute units leave
 };
 // partial_cap: bytes the partial sums of an automatic split may take above 128 rows or at K >= 2^22 (the layer driver
 // passes what its workspace holds if that is less).

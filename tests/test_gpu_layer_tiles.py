@@ -183,3 +183,48 @@ def test_last_column_tile_past_n_matches_float64(cfg, m):
 def test_tile_by_live_rows_of_large_batches_matches_float64(n, epi):
     for rows in (1111, 1847, 2776, 3000):      # 256 x 160, 256 x 224, 256 x 192 and others, the last column tile past n or not
         run(Plan(2, 1, 1024, epi, 1), 3000, n, 1024, torch.tensor([rows], dtype=torch.int32, device="cuda"), rows)
+
+
+# whole rounds of big tiles and the columns behind them in smaller ones
+def mixed(cfg, rest, k, epi):
+    p = Plan(cfg, 1, k, epi, 1)
+    p.rest = 1 + rest
+    return p
+
+
+def test_columns_behind_whole_rounds_are_planned_in_smaller_tiles():
+    for m, n, k, epi, cfg, rest in ((1847, 55296, 5120, SWIGLU, 10, 0), (1024, 37888, 3584, SWIGLU, 2, 7), (1200, 55296, 5120, SWIGLU, 10, 8)):
+        p = layer_plan(m, n, k, epi, epi != SWIGLU)
+        assert (p.cfg, p.split, p.rest) == (cfg, 1, 1 + rest), (m, n, k, p.cfg, p.rest)
+    for m in range(129, 5000, 53):       # whatever is planned fits: big tiles fill rounds, the others make at most one
+        for n, k, epi in ((55296, 5120, SWIGLU), (27648, 5120, SWIGLU), (37888, 3584, SWIGLU), (5120, 27648, RESID), (7168, 5120, PARTIAL)):
+            p = layer_plan(m, n, k, epi, epi != SWIGLU)
+            if p.rest == 0:
+                continue
+            rows = {0: 128, 7: 192, 8: 256}[p.rest - 1]
+            tiles_m = -(-m // {2: 256, 10: 320}[p.cfg])
+            columns = tiles_m * (n // 256) // 256 * 256 // tiles_m
+            assert p.split == 1 and 1 <= columns < n // 256 and -(-m // rows) * (n - columns * 256) // 128 <= 256, (m, n, p.cfg, p.rest)
+    assert layer_plan(70000, 256, 5120, PARTIAL, True).rest == 0      # more row tiles than a round holds
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,m,n", [(2, 257, 33024), (2, 700, 22272), (10, 321, 33024), (10, 961, 16640), (2, 513, 22016)])
+@pytest.mark.parametrize("rest", [0, 7, 8])
+def test_columns_behind_whole_rounds_match_float64(cfg, m, n, rest):
+    for k in (64, 192):
+        for epi in (PARTIAL, RESID, SWIGLU):
+            run(mixed(cfg, rest, k, epi), m, n, k)
+    # fewer live rows than an un-captured launch was made for: rows of NaN behind them reach nothing
+    k, g = 192, torch.Generator(device="cuda").manual_seed(m + n)
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=g)
+    for rows in (1, m - 130, m):
+        a = torch.full((m, k), float("nan"), dtype=torch.bfloat16, device="cuda")
+        a[:rows].normal_(0, 1, generator=g)
+        out, live = torch.full((m, n), 7.0, device="cuda"), torch.tensor([rows], dtype=torch.int32, device="cuda")
+        p = lambda t: C.c_void_p(t.data_ptr())
+        assert api.lib()._Z16laps_gemm_launchRK8GemmPlanPKtS3_iiiPfPKfPtPKiS9_bP12ihipStream_t(
+            C.byref(mixed(cfg, rest, k, PARTIAL)), p(a), p(w), C.c_int(m), C.c_int(n), C.c_int(k), p(out), None, None, None, p(live),
+            C.c_bool(False), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        want = a[:rows].double() @ w.double().T
+        assert float((out[:rows].double() - want).norm() / want.norm()) < 2e-6
