@@ -199,7 +199,7 @@ int laps_prefill_stack(laps_ctx* ctx, const laps_layer_weights* w, int32_t n_seq
  * from library load until the process ends; its address on the context's device is resolved once, in
  * laps_ctx_create).  The call itself allocates nothing, frees nothing and never synchronises.  A batch whose workspace
  * (laps_workspace_bytes) exceeds laps_static_scratch_bytes() = 128 MiB by more than its attention work-item tables (a
- * few KB; laps_attn_plan_info reports them; 1 MiB at most) is rejected with LAPS_EINVAL and a message naming both
+ * few tens of KB; laps_attn_plan_info reports them; 1 MiB at most) is rejected with LAPS_EINVAL and a message naming both
  * sizes: at the 32B layer shape that is a few hundred rows.  The context's device must be
  * current.  Every call on a GPU uses that GPU's one array (nothing in it has to start at zero: each region is
  * written before it is read within the call), so calls that overlap in time on one GPU - two streams, two threads,
@@ -216,10 +216,12 @@ int laps_prefill_stack_static(laps_ctx* ctx, const laps_layer_weights* w, int32_
  * epilogue 0 = plain sums, 1 = residual add, 2 = SwiGLU, and split_k as in laps_gemm_bf16 (0 = automatic).  Inside a layer,
  * where a row kernel follows, the driver may split K otherwise.
  * out[7] = { tile rows, tile columns, K slices, K elements per slice, epilogue the kernel applies (0 when K is
- * split), slabs of 64 that every K slice holds a multiple of, workgroups }.
+ * split), slabs of 64 that every K slice holds a multiple of, workgroups }.  Where the tiles fill the compute units a whole
+ * number of times and a few are left, the columns of those may be computed in smaller tiles; tile and workgroups are reported
+ * as if there were none.
  * laps_attn_plan_info: the attention launch of a batch shape (n_tokens rows, n_seq sequences, page tables
  * max_pages wide).  out[6] = { query rows per workgroup, bound on the (sequence, row block) work items,
- * key-range splits (1 = none), fewest 64-key tiles a split is given, bytes of the work-item table, bytes of
+ * key-range splits per item that there are workgroups for (1 = none), fewest 64-key tiles a split is given, bytes of the work-item table, bytes of
  * the key-split partial results (0 if tables this narrow never split) }.
  * EINVAL on NULL or unsupported shapes. */
 int laps_gemm_plan_info(int32_t m, int32_t n, int32_t k, int32_t split_k, int32_t epilogue, int32_t* out);

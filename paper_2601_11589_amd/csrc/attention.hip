@@ -23,12 +23,13 @@
 // exponentials subtract follows the row maximum lazily, so that O is rescaled rarely.
 //
 // Few query rows over a long cached prefix (a short re-prefill turn) would leave most of the chip idle:
-// one request of 16 new tokens is a single row block per kv head.  For such launches the key range is
-// split over gridDim.z workgroups (at least 4 key tiles each, or one where few workgroups make it pay); every split writes its un-normalised
-// accumulator with its running maximum and row sum, and a second kernel merges the splits in a fixed
-// order, so the result does not depend on scheduling.  The split count is a function of launch shapes
-// only (row blocks, kv heads, page-table width), which keeps captured graphs replayable; how many of
-// the splits a given sequence really uses is decided on the device from its length.
+// one request of 16 new tokens is a single row block per kv head.  For such launches the key ranges of
+// the row blocks are split into parts of equal length over the whole batch (laps_dev_attn_split; at least 4
+// key tiles each, or one where few workgroups make it pay); every part writes its un-normalised accumulator
+// with its running maximum and row sum, and a second kernel merges the parts of a block in key order, so
+// the result does not depend on scheduling.  The number of workgroups is a function of launch shapes only
+// (row blocks, kv heads, page-table width), which keeps captured graphs replayable; which part a workgroup
+// takes, if any, is worked out on the device from the batch's lengths.
 //
 // Many query rows over page tables that allow long prefixes (chunks of long prompts, mixed batches, groups of turns) make
 // blocks of very different lengths.  Such launches run the 8-wave loop in a fixed number of workgroups, each of which walks
@@ -48,7 +49,7 @@ __device__ __forceinline__ int swz16(int row, int c) { return c ^ (row & 15); }
 
 // NW waves per workgroup, one 32-row query tile per wave: rows per workgroup = 32 * NW.  With NW = 8
 // two waves share a SIMD, so one wave's softmax (VALU, exp) overlaps the other's MFMAs.
-constexpr int MIN_TILES_PER_SPLIT = 4;   // key tiles per split (lower bound, attn_blocking)
+constexpr int MIN_TILES_PER_SPLIT = 4;   // key tiles per part of a split key range (lower bound, attn_blocking)
 
 // Two waves per SIMD in every variant (second launch-bound argument): with 4 waves per workgroup that is two
 // resident workgroups per compute unit, which the key-streaming launches need to cover the memory latency.
@@ -808,7 +809,7 @@ size_t laps_attn_partial_bytes(int hd, int max_pages) {
 }
 
 // Query-row blocking for a batch: rows per workgroup (128 or 256), an upper bound on the number of
-// (sequence, row block) work items, and the number of key-range splits.  Depends only on shapes known to
+// (sequence, row block) work items, and the parts of split key ranges that there are workgroups for, per item.  Depends only on shapes known to
 // the host (a captured graph must replay with the same grid whatever the lengths staged into it).
 static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* mt, int* max_items,
                           int* n_split, int* min_tiles) {
@@ -819,7 +820,7 @@ static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_
     *min_tiles = MIN_TILES_PER_SPLIT;
     if (items1 * n_kv < kSplitBelowBlocks && max_kv_tiles >= 2 * MIN_TILES_PER_SPLIT) {
         const int blocks0 = (int)items1 * n_kv;
-        // A turn or two of few tokens leave most compute units idle however fine the split: a workgroup per key tile where all
+        // A turn or two of few tokens (one or two items: parts of equal length are equal parts of an item) leave most compute units idle however fine the split: a workgroup per key tile where all
         // of them fit one round, as wide as the page table is, and the rows of their partial results are few.  Attention with
         // its scheduling kernel, splits of at least 4 tiles and of one: 7B, a turn of 7 over 900 / 2000 / 4000 keys 17.5 / 16.7 /
         // 18.4 and 13.2 / 13.4 / 16.7; 14B, 7 rows over 900 keys with the rest of its one-layer graph 148.3 and 143.6 (a table of

@@ -29,7 +29,7 @@ extern "C" const char* laps_version(void) { return "laps-gfx950 0.1"; }
 // of the process.  In host code the array's name is only a handle for hipGetSymbolAddress; the address the
 // kernels are given is the one resolved below, per device, with that device current.
 #define LAPS_STATIC_SCRATCH_BYTES ((size_t)128 << 20)
-// The attention's work-item tables (a few KB) come on top, so that what they take is not missing from the 128 MiB.
+// The attention's work-item tables (a few tens of KB) come on top, so that what they take is not missing from the 128 MiB.
 #define LAPS_STATIC_TABLE_BYTES ((size_t)1 << 20)
 static __device__ __align__(256) unsigned char scratch[LAPS_STATIC_SCRATCH_BYTES + LAPS_STATIC_TABLE_BYTES];
 

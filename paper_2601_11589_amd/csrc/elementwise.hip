@@ -251,15 +251,16 @@ __global__ __launch_bounds__(RESID_THREADS) void epi_resid_kernel(const float* _
 }
 
 // ------------------------------------------------------------------ sum K slices + bias + RoPE + KV append
-// One token row and a chunk of its work items (grid: row x chunk; TURN: workgroups [0, rows * chunks)).  Work item = four consecutive rotate-half
-// pairs (j..j+3, j+hd/2..j+hd/2+3) of one head: two 16-byte loads per K slice.  q goes to q_out[row], k and v to the
+// One token row and a chunk of its work items (grid: row x chunk; TURN: workgroups [0, rows * chunks)).  Work item = four
+// consecutive rotate-half pairs (j..j+3, j+hd/2..j+hd/2+3) of one head: two 16-byte loads per K slice.  q goes to q_out[row], k and v to the
 // token's slot in the paged pools.
 // TURN: v has workgroups of its own behind these, one kv head of 16 rows each.  A page keeps v as [head_dim][16 tokens],
 // so 8 rows whose tokens lie side by side in an aligned half of a page are turned over in LDS and written as 16 bytes
 // per head_dim index; others go one by one.  Written one by one throughout, the 2-byte stores at a 32-byte stride are a
 // third of the kernel's time in large batches: 32B shape, 2048 rows 30 us, turned over 19; 11104 rows 190 and 92 (478 MB,
-// 5.2 TB/s).  Small ones are all latency, and the two barriers of the way through LDS add to it: 32B / 7B shape, 32
-// rows 5.1 / 5.4 us turned over and 4.0 / 4.0 one by one, 128 rows 6.2 / 5.5 and 5.2 / 4.2, 192 rows 7.6 / 5.6 and 8.3 / 5.6.
+// 5.2 TB/s).  Small ones are all latency, and the two barriers of the way through LDS add to it: 32B / 7B shape, slices added
+// as they came, 32 rows 5.1 / 5.4 us turned over and 4.0 / 4.0 one by one, 128 rows 6.2 / 5.5 and 5.2 / 4.2, 192 rows 7.6 /
+// 5.6 and 8.3 / 5.6; loading all slices first takes as much off either.
 constexpr int V_ROWS = 16;
 constexpr int TURN_ABOVE = 128;   // rows
 template <int HD, bool TURN, int SLICES>

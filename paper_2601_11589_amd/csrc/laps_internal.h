@@ -191,9 +191,9 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
 }
 
 // What a workgroup of the attention needs to know of a work item, two int4 an item: (sequence, row block, new tokens, cached
-// tokens) and (first row; with split key ranges also the item's first part, its parts, -); the items past the batch's last one have a sequence of -1.  One scalar load instead of
-// the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a link.  Runs in ONE workgroup of 256 threads after
-// laps_dev_attn_sched.
+// tokens) and (first row; with split key ranges also the item's first part, its parts, -); the items past the batch's last one
+// have a sequence of -1.  One scalar load instead of the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a
+// link.  Runs in ONE workgroup of 256 threads after laps_dev_attn_sched.
 static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
                                                           const int* __restrict__ row_start, int n_seq, int max_pages,
                                                           const int* tile_start, const int* item_seq, int max_items,
