@@ -121,7 +121,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_kernel(const float* __res
 // ------------------------------------------------------------------ begin of an un-captured batch
 // Workgroup 0: clamped lengths and the attention's work-item table (and shares).  Workgroup 1 + r: row r's position and
 // cache slot and its first RMSNorm.  All of it is latency: three launches one after the other took 4.7 + 8.1 + 7.4 us
-// ahead of 573 rows of the 32B shape, this one 11.7 (2048 rows: 29 and 19).
+// ahead of 573 rows of the 32B shape, this one 10.3 (2048 rows: 29 and 18).
 template <int MAXV>
 __global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
     __shared__ int sums[ROW_THREADS / 64];
@@ -555,7 +555,7 @@ __global__ void kv_move_kernel(int n_seq, int n_tokens, const int* __restrict__ 
 
 // Staging of a captured bucket, one launch: workgroup 0 writes the batch's metadata, workgroup 1 + r prepares row r.  Every
 // row workgroup scans the slots' lengths itself instead of waiting for workgroup 0 (two launches, 4.8 + 9.4 us for 128
-// rows; one, 6.5 us; short re-prefill replay 285 -> 280, single turn 161 -> 156), and its input row is on the way meanwhile.
+// rows; one, 5.9 us; short re-prefill replay 285 -> 280, single turn 161 -> 156), and its input row is on the way meanwhile.
 //
 // The lengths the caller staged for the first n_real slots are clamped to [0, len_bucket], the other slots are empty, and
 // the sequences are packed one after the other (row_start = running sum of the clamped lengths, so the total never
