@@ -1009,7 +1009,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         // the 32B down projection, 36 slabs per slice, stays on 256 columns: 61.2 against 65.8).  At most 256
         // workgroups either way: a streaming kernel with 257 leaves one CU with twice the work.
         auto auto_split = [&](int c) {
-            // Slices of 16 slabs or more: below, the pipeline is all prologue.  8 where a row kernel reads raw sums anyhow (q/k/v
+            // Slices of 16 slabs or more: below, the pipeline is all prologue.  8 where a row kernel reads the sums anyhow (q/k/v
             // in the 7B layer at 8 / 128 rows: 4 slices of 14 slabs 8.7 / 15.1 us, 7 of 8 7.6 / 12.6).  Raw sums of a product of
             // its own are its result if K is one slice, and cost a launch and a workspace if not (3584 columns, K = 768, 128
             // rows: one slice 11.1, two 13.1); where 16 slabs split K already, up to 4 slices of 8 pay, and more until they fill
@@ -1017,7 +1017,19 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
             // 2 slices 17.1, 4 14.2; but 4608 x 3584 4 slices 14.2, 7 16.1).
             const int tiles = n / kTiles[c].bn, fine = (ksteps + 4) / 8;
             int sp = 256 / tiles, cap = (ksteps + 8) / 16;
-            if (c == 5 || (want_epi == EPI_PARTIAL && row_kernel)) cap = fine;
+            const bool read_anyhow = want_epi != EPI_SWIGLU && row_kernel, many = m >= 96;
+            // Above 64 rows two tiles of 64 in half the slices (laps_gemm_launch) where those are 3 or more of up to 20 slabs: with
+            // the row kernel, 7B q/k/v at 72 / 96 / 128 rows in 7 slices 15.6 / 18.3 / 20.7, in 3 15.2 / 16.5 / 18.1; 3584 x 5120 in 8
+            // 15.9 / 18.1 / 21.0, in 4 16.2 / 17.8 / 18.8 (so 19 below 96 rows); slices of 27, 32B o, 21.2 / 23.1 / 24.8, in 6 of 14
+            // 20.0 / 22.3 / 25.2.
+            const int halves = std::min(128 / tiles, fine);
+            if (c == 0 && m > 64 && read_anyhow && halves >= 3 && ksteps <= (many ? 20 : 19) * halves) return halves;
+            // Residual products split at 16 slabs already: finer slices are read by the same row kernel.  Half as many again and
+            // more: 2048 x 2048 at 8 / 64 / 128 rows 10.7 / 13.1 / 13.5 in 2, 8.5 / 10.6 / 11.7 in 4; 7B o up to 64 rows 1 us a layer.
+            // Fewer pay from 96 rows on: 6144 x 4096 at 8 / 72 / 96 / 128 rows 14.5 / 19.8 / 21.6 / 24.4 in 4, 15.3 / 20.2 / 21.5 /
+            // 23.6 in 5; 32B o at 96 / 128 rows 22.7 / 26.0 in 5, 22.3 / 25.2 in 6.
+            const bool finer = want_epi == EPI_PARTIAL || (cap > 1 && (many || 2 * std::min(sp, fine) >= 3 * std::min(sp, cap)));
+            if (c == 5 || (read_anyhow && finer)) cap = fine;
             else if (want_epi == EPI_PARTIAL && cap > 1) cap = std::max(cap, std::min(fine, std::max(4, 128 / tiles)));
             sp = sp > cap ? cap : sp;
             return sp < 1 ? 1 : sp;
@@ -1133,9 +1145,11 @@ size_t laps_gemm_partial_bytes(int m, int n, int k, size_t partial_cap) {   // m
     // upper bound over the epilogue kinds the layer driver may request
     size_t b = 0;
     for (int e = 0; e < 3; ++e) {
-        const GemmPlan p = laps_gemm_plan(m, n, k, 0, e, partial_cap, e == EPI_PARTIAL, true);   // raw sums: q/k/v
-        const size_t t = p.split > 1 ? (size_t)p.split * m * n * sizeof(float) : 0;
-        b = t > b ? t : b;
+        for (int follows = 0; follows < 2; ++follows) {   // a row kernel
+            const GemmPlan p = laps_gemm_plan(m, n, k, 0, e, partial_cap, follows != 0, true);
+            const size_t t = p.split > 1 ? (size_t)p.split * m * n * sizeof(float) : 0;
+            b = t > b ? t : b;
+        }
     }
     // QKV always goes through the partial buffer (its epilogue is a separate kernel)
     const size_t one = (size_t)m * n * sizeof(float);
