@@ -926,8 +926,16 @@ extern "C" int laps_stream_idle(void* before, void* stream) {
         }
         if (st != hipStreamCaptureStatusNone) return 0;
     }
+    // Asked in a thread that keeps to the runtime's default mode, the query breaks whatever stream is being captured in the
+    // global mode, by this thread or another one.  An event would not: it is enqueued on these two streams alone.
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
     const hipError_t e = hipStreamQuery(pair[1]);
     if (e != hipSuccess) (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     return e == hipSuccess;
 }
 
