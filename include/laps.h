@@ -221,7 +221,7 @@ int laps_prefill_stack_static(laps_ctx* ctx, const laps_layer_weights* w, int32_
  * as if there were none.
  * laps_attn_plan_info: the attention launch of a batch shape (n_tokens rows, n_seq sequences, page tables
  * max_pages wide).  out[6] = { query rows per workgroup, bound on the (sequence, row block) work items,
- * key-range splits per item that there are workgroups for (1 = none), fewest 64-key tiles a split is given, bytes of the work-item table, bytes of
+ * key-range splits of an item at most (1 = none), fewest 64-key tiles a split is given, bytes of the work-item table, bytes of
  * the key-split partial results (0 if tables this narrow never split) }.
  * EINVAL on NULL or unsupported shapes. */
 int laps_gemm_plan_info(int32_t m, int32_t n, int32_t k, int32_t split_k, int32_t epilogue, int32_t* out);

@@ -24,10 +24,10 @@
 //
 // Few query rows over a long cached prefix (a short re-prefill turn) would leave most of the chip idle:
 // one request of 16 new tokens is a single row block per kv head.  For such launches the key ranges of
-// the row blocks are split into parts of equal length over the whole batch (laps_dev_attn_split; at least 4
-// key tiles each, or one where few workgroups make it pay); every part writes its un-normalised accumulator
-// with its running maximum and row sum, and a second kernel merges the parts of a block in key order, so
-// the result does not depend on scheduling.  The number of workgroups is a function of launch shapes only
+// each row block are split into parts of equal length (laps_dev_attn_split; at least 4 key tiles each, or one
+// where few workgroups make it pay); every part writes its un-normalised accumulator with its running maximum
+// and row sum, and a second kernel merges the parts of a block in key order, so the result depends neither on
+// scheduling nor on the lengths of other sequences.  The number of workgroups is a function of launch shapes only
 // (row blocks, kv heads, page-table width), which keeps captured graphs replayable; which part a workgroup
 // takes, if any, is worked out on the device from the batch's lengths.
 //
@@ -809,7 +809,7 @@ size_t laps_attn_partial_bytes(int hd, int max_pages) {
 }
 
 // Query-row blocking for a batch: rows per workgroup (128 or 256), an upper bound on the number of
-// (sequence, row block) work items, and the parts of split key ranges that there are workgroups for, per item.  Depends only on shapes known to
+// (sequence, row block) work items, and the most parts an item's key range is split into.  Depends only on shapes known to
 // the host (a captured graph must replay with the same grid whatever the lengths staged into it).
 static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* mt, int* max_items,
                           int* n_split, int* min_tiles) {
@@ -820,7 +820,7 @@ static void attn_blocking(int n_seq, int n_tokens, int group, int n_kv, int max_
     *min_tiles = MIN_TILES_PER_SPLIT;
     if (items1 * n_kv < kSplitBelowBlocks && max_kv_tiles >= 2 * MIN_TILES_PER_SPLIT) {
         const int blocks0 = (int)items1 * n_kv;
-        // A turn or two of few tokens (one or two items: parts of equal length are equal parts of an item) leave most compute units idle however fine the split: a workgroup per key tile where all
+        // A turn or two of few tokens leave most compute units idle however fine the split: a workgroup per key tile where all
         // of them fit one round, as wide as the page table is, and the rows of their partial results are few.  Attention with
         // its scheduling kernel, splits of at least 4 tiles and of one: 7B, a turn of 7 over 900 / 2000 / 4000 keys 17.5 / 16.7 /
         // 18.4 and 13.2 / 13.4 / 16.7; 14B, 7 rows over 900 keys with the rest of its one-layer graph 148.3 and 143.6 (a table of

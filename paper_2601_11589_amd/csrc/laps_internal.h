@@ -210,16 +210,16 @@ static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict_
 
 constexpr int LAPS_ATTN_KT = 64;          // keys per tile
 
-// Key-range splits of a batch whose (item, kv head) blocks leave compute units idle: parts of equal numbers of key tiles over
-// all items, as long as makes LAPS_ATTN_SPLIT_WGS workgroups of the batch's tiles, at least min_tiles.  Equal numbers of parts an
-// item, tried before, made the longest item's parts decide: 32B, turns of 17 to 32 tokens over 512 to 4096 keys, parts of up to 9
-// tiles where all parts together are 4 tiles for every place on the chip.
+// Key-range splits of a batch whose (item, kv head) blocks leave compute units idle: an item's key tiles go out in parts of
+// equal length, at least min_tiles each and n_split of them at most.  Where an item is cut follows from its own length and the
+// launch's shape alone, so that the bits of a request do not depend on the lengths it is batched with.  (Parts of equal length
+// over the whole batch would spare the longest item's parts, 32B, turns of 17 to 32 tokens over 512 to 4096 keys, up to 9 tiles
+// where all parts together are 4 tiles for every place on the chip: a layer's graph 252 -> 247 us.)
 // blocks: two int4 a part, (sequence, row block, new tokens, cached tokens) and (first row, its number among the item's parts, key
-// tiles of a part, the item's parts); a sequence of -1 past the last one, max_items * n_split in all, which the parts never exceed.
+// tiles of a part, the item's parts); a sequence of -1 past the last one, max_items * n_split in all.
 // Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; max_items < 256.
-constexpr int LAPS_ATTN_SPLIT_WGS = 512;   // two workgroups a compute unit
 static __device__ __forceinline__ void laps_dev_attn_split(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
-                                                           const int* __restrict__ row_start, int n_seq, int group, int n_kv,
+                                                           const int* __restrict__ row_start, int n_seq, int group,
                                                            int rows_per_wg, int max_pages, const int* tile_start, const int* item_seq,
                                                            int max_items, int n_split, int min_tiles, int4* desc, int4* blocks,
                                                            int* sums) {
@@ -228,27 +228,22 @@ static __device__ __forceinline__ void laps_dev_attn_split(const int* __restrict
     const int n_items = tile_start[n_seq] < max_items ? tile_start[n_seq] : max_items;
     const bool any = k < n_items;
     int4 it = make_int4(-1, 0, 0, 0);
-    int nt = 0;
+    int each = 0, parts = 0, used;
     if (any) {
         const int i = item_seq[k], L = new_len[i], H = laps_dev_clamp_prefix(prefix_len[i], L, max_pages), q = k - tile_start[i];
         const int last = ((q + 1) * rows_per_wg < L * group ? (q + 1) * rows_per_wg : L * group) - 1;
         it = make_int4(i, q, L, H);
-        nt = (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT;
+        const int nt = (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT, most = nt / min_tiles < n_split ? nt / min_tiles : n_split;
+        each = most > 1 ? (nt + most - 1) / most : nt;
+        parts = (nt + each - 1) / each;   // none of them empty
     }
-    int total, used, parts, first;
-    laps_dev_scan(nt, sums, &total);
-    const int places = LAPS_ATTN_SPLIT_WGS / n_kv > 1 ? LAPS_ATTN_SPLIT_WGS / n_kv : 1;
-    for (int per = (total + places - 1) / places > min_tiles ? (total + places - 1) / places : min_tiles;; per += 1 + per / 8) {
-        parts = (nt + per - 1) / per;   // one each in the end: n_items <= cap
-        first = laps_dev_scan(parts, sums, &used) - parts;
-        if (used <= cap) break;
-    }
+    const int first = laps_dev_scan(parts, sums, &used) - parts;
     if (any) {
-        const int each = (nt + parts - 1) / parts, real = (nt + each - 1) / each, rs = row_start[it.x];
-        desc[2 * k + 1] = make_int4(rs, first, real, 0);
+        const int rs = row_start[it.x];
+        desc[2 * k + 1] = make_int4(rs, first, parts, 0);
         for (int z = 0; z < parts; ++z) {
-            blocks[2 * (first + z)] = z < real ? it : make_int4(-1, 0, 0, 0);
-            blocks[2 * (first + z) + 1] = make_int4(rs, z, each, real);
+            blocks[2 * (first + z)] = it;
+            blocks[2 * (first + z) + 1] = make_int4(rs, z, each, parts);
         }
     }
     for (int x = used + k; x < cap; x += 256) blocks[2 * x] = make_int4(-1, 0, 0, 0);

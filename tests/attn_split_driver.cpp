@@ -1,6 +1,6 @@
 // Runs the device code that cuts a batch's attention into parts of its key ranges on the CPU, with the coroutines of the
 // driver next to it.  Reads batches from stdin, one line of numbers each:
-//   n_split min_tiles n_kv group max_pages rows_per_wg max_items n_seq  new_len[n_seq]  prefix_len[n_seq]
+//   n_split min_tiles group max_pages rows_per_wg max_items n_seq  new_len[n_seq]  prefix_len[n_seq]
 // and prints, a line per batch: eight numbers per item of the table, then eight per part, both with a guard entry behind.
 #define main shares_main
 #include "attn_shares_driver.cpp"
@@ -15,7 +15,7 @@ void split_main() {
     laps_dev_attn_sched(b.new_len.data(), b.n_seq, b.group, b.rows_per_wg, b.tile_start.data(), b.item_seq.data(), b.max_items, sums);
     laps_dev_attn_desc(b.new_len.data(), b.prefix_len.data(), row_start.data(), b.n_seq, b.max_pages, b.tile_start.data(),
                        b.item_seq.data(), b.max_items, desc.data());
-    laps_dev_attn_split(b.new_len.data(), b.prefix_len.data(), row_start.data(), b.n_seq, b.group, b.n_kv, b.rows_per_wg, b.max_pages,
+    laps_dev_attn_split(b.new_len.data(), b.prefix_len.data(), row_start.data(), b.n_seq, b.group, b.rows_per_wg, b.max_pages,
                         b.tile_start.data(), b.item_seq.data(), b.max_items, n_split, min_tiles, desc.data(), parts.data(), sums);
     done[threadIdx.x] = true;
     barrier();
@@ -27,8 +27,8 @@ void print(const std::vector<int4>& table) {
 
 int main() {
     std::vector<std::vector<char>> stack(kThreads, std::vector<char>(64 << 10));
-    while (std::scanf("%d %d %d %d %d %d %d %d", &n_split, &min_tiles, &b.n_kv, &b.group, &b.max_pages, &b.rows_per_wg, &b.max_items,
-                      &b.n_seq) == 8) {
+    while (std::scanf("%d %d %d %d %d %d %d", &n_split, &min_tiles, &b.group, &b.max_pages, &b.rows_per_wg, &b.max_items,
+                      &b.n_seq) == 7) {
         b.new_len.resize(b.n_seq);
         b.prefix_len.resize(b.n_seq);
         for (int& v : b.new_len)
