@@ -767,6 +767,16 @@ __global__ __launch_bounds__(256, (DmaTraits<BM, BN, WM, WN>::TWO ? 2 : 1)) void
     dma_tile<BM, BN, WM, WN, EPI, false>(g, smem, M, tiles_m, g.tiles_n, blockIdx.x, nullptr);
 }
 
+// Plans that the fit of kTiles' cost columns has not seen have to lead on paper by more than it errs on them.  Measured against
+// the plan without them, products of the 7B, 14B and 32B projections and of 19 other weights (1536 x 8960 to 57344 x 8192), 129
+// to 11104 rows, then of 20 weights and 60 row counts that the lines were not drawn with:
+//   a last column tile past n: 1.01 to 1.22 times as fast (61 products); 1.02 to 1.45 of the others (90), one 0.98;
+//   192 rows where they need more row tiles than 256: 0.995 to 1.23 from a lead of 6 % on (52), 0.93 to 1.10 below (30: 2560
+//   columns, K = 9728, 1138 rows 61.7 -> 66.7 us); 1.01 to 1.36 of the others (45), one 0.97;
+//   whole rounds and smaller tiles behind them: 0.993 to 1.29 from 4 % on, 0.95 to 1.03 below; 0.99 to 1.30 of the others (276),
+//   three of them, 2304 and 3072 columns of more than 7000 rows, 0.977 to 0.986.
+constexpr double kRaggedMargin = 1.085, kMore192Margin = 1.06, kMixMargin = 1.04;
+
 // A captured graph is launched for all its rows, and the tile that fills the chip for them (down projection, 4096 rows:
 // 512 tiles of 256 x 160 in two rounds) is not the one for the rows a batch has (2776: 352 tiles in two rounds where 253
 // of 256 x 224 take one: 997 against 700 us with slabs through registers on 256 x 256; 612 on 256 x 256 and 581 on 256 x 224
@@ -789,9 +799,11 @@ __global__ __launch_bounds__(256, 1) void gemm_live_kernel(const GemmArgs g, con
     float best = 0.f;
 #pragma unroll
     for (int i = 0; i < live_tiles(EPI); ++i) {
-        const int tiles = (M + kLiveRows[i] - 1) / kLiveRows[i] * ((g.N + kLiveCols[i] - 1) / kLiveCols[i]);
+        const int tiles_m = (M + kLiveRows[i] - 1) / kLiveRows[i], tiles = tiles_m * ((g.N + kLiveCols[i] - 1) / kLiveCols[i]);
         const float spare = tiles < 256 ? 1.f - tiles / 256.f : 0.f;
-        const float us = (float)((tiles + 255) / 256) * (c.fill[i] + c.slabs[i] * (1.f - c.part[i] * spare));
+        float us = (float)((tiles + 255) / 256) * (c.fill[i] + c.slabs[i] * (1.f - c.part[i] * spare));
+        if (g.N % kLiveCols[i] != 0) us *= (float)kRaggedMargin;   // as in laps_gemm_plan
+        else if (kLiveRows[i] == 192 && tiles_m != (M + 255) / 256) us *= (float)kMore192Margin;
         if (i == 0 || us < best) best = us, pick = i;
     }
     int rows = kLiveRows[0], cols = kLiveCols[0];
@@ -897,14 +909,14 @@ constexpr TileDef kTiles[] = {
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
-// The tiles behind whole rounds of big ones, alone on their compute unit: cost as above, without `part`.  Fitted to the choices of
-// 84 products (gate/up of the three models at 14 row counts, the others of 32B at six, 7 to 10 ways each): against the best
-// plain tile 1.023 times as fast in the mean and none slower; the best of all ways is 0.2 % away.
+// The tiles behind whole rounds of big ones, alone on their compute unit: cost as above, without `part`.  Fitted to 467 products
+// (the first ones above kRaggedMargin), which they meet within 4 % (rms).  The first constants, from 84 products, had 128 x 128 at
+// half its time: 14B down of 3396 rows, 256 x 160 in 1.75 rounds, 402 -> 414 us.
 struct MixDef {
     int cfg;
     double fill, slab;
 };
-constexpr MixDef kMix[3] = {{0, 4.0, 0.40}, {7, 4.0, 0.75}, {8, 4.0, 0.80}};   // in the order of kMixRows
+constexpr MixDef kMix[3] = {{0, 8.0, 0.60}, {7, 6.0, 0.80}, {8, 2.0, 1.00}};   // in the order of kMixRows
 
 template <int EPI>
 int launch_live(const GemmArgs& a, hipStream_t s) {
@@ -1073,11 +1085,9 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
     for (int cfg = 0; cfg < kNumTiles; ++cfg) {
         const TileDef& t = kTiles[cfg];
         // Inside layers the last column tile may reach past n (not on 320 x 256, see DmaTraits), and 192 rows may need more row
-        // tiles than 256; products of their own keep to what laps_gemm_plan_info has always reported.  Both have to be ahead on
-        // paper by more than the model errs where they lost: 8.5 and 2 % (32B q/k/v of 1280 rows 8 % ahead, 95 -> 99 us).  Row
-        // kernel included, weights cold, before and with them: 7B gate/up of 200 / 256 / 512 rows 77.4 / 82.3 / 160.2 -> 68.6 / 73.9
-        // (198 tiles of 256 x 192 where 256 columns make 148) / 135.2 (192 x 256), q/k/v of 1847 rows 74.0 -> 68.3, o of 1536 rows
-        // 60.1 -> 56.8; of ten projections at 17 row counts 14 plans change, none for a slower one.
+        // tiles than 256; products of their own keep to what laps_gemm_plan_info has always reported.  Row kernel included,
+        // weights cold, before and with them: 7B gate/up of 200 / 256 rows 77.4 / 82.3 -> 68.6 / 73.9 (198 tiles of 256 x 192
+        // where 256 columns make 148), q/k/v of 1847 rows 74.0 -> 68.3, o of 1536 rows 60.1 -> 56.8.
         const bool ragged = n % t.bn != 0;
         if (ragged && (!layer || far || t.bm > 256)) continue;
         if ((cfg == 1 && n % 128 == 0) || (far && cfg != 1 && cfg != 6 && cfg != 7)) continue;
@@ -1091,7 +1101,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
         if (t.bm == 320 && (!layer || tiles_m == (m + 255) / 256)) continue;
         const bool more_192 = t.bm == 192 && tiles_m != (m + 255) / 256;
         if (more_192 && !layer && !far) continue;
-        const double margin = ragged ? 1.085 : more_192 && !far ? 1.02 : 1.0;
+        const double margin = ragged ? kRaggedMargin : more_192 && !far ? kMore192Margin : 1.0;
         const int max_split = force_split > 0 ? force_split : (far ? 256 : 16);   // a few column tiles have to fill the chip
         for (int s = force_split > 0 ? force_split : 1; s <= max_split; ++s) {
             const double partial = 4.0 * s * mn;
@@ -1114,7 +1124,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
                 best_split = s;
                 best_rest = 0;
             }
-            // Whole rounds only, and smaller tiles in one round behind them, where that is 2 % ahead.
+            // Whole rounds only, and smaller tiles in one round behind them.
             if (s != 1 || far || ragged || (cfg != 2 && cfg != 10) || wgs <= 256 || wgs % 256 == 0) continue;
             const int columns = mix_columns(tiles_m, n), left = n - columns * 256;
             if (columns < 1) continue;
@@ -1122,7 +1132,7 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
                 const int rows = kTiles[x.cfg].bm;
                 if ((long)((m + rows - 1) / rows) * ((left + 127) / 128) > 256) continue;
                 const double mixed = 4.0 + (wgs / 256) * (t.fill + per * t.slab) + x.fill + per * x.slab;
-                const double total = 1.02 * (us + 1.02 * (mixed > stream ? mixed : stream) - 1.02 * tiles);
+                const double total = kMixMargin * (us + 1.02 * (mixed > stream ? mixed : stream) - 1.02 * tiles);
                 if (tiles > stream && total < best) {
                     best = total;
                     best_cfg = cfg;
