@@ -182,10 +182,23 @@ __device__ __forceinline__ void add_slices(f32x4 (&acc)[N], int split, Load load
             }
     }
 }
-// Slices to load at once: all up to 8, equal shares of more.
-static int slices_at_once(int split) {
+// Slices to load at once: all up to 8, equal shares of more, each number with a kernel of its own: the kernel of the next larger
+// one loads the last slice again (with their products, 5 slices of the o projection of 33 to 128 rows and 7 of q/k/v take 1 % less
+// than with kernels for 6 and 8).
+template <typename F>
+static void with_slices(int split, F go) {
     const int rounds = (split + 7) / 8;
-    return (split + rounds - 1) / rounds;
+    switch ((split + rounds - 1) / rounds) {
+        case 0:
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 3: return go(std::integral_constant<int, 3>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        case 5: return go(std::integral_constant<int, 5>{});
+        case 6: return go(std::integral_constant<int, 6>{});
+        case 7: return go(std::integral_constant<int, 7>{});
+        default: return go(std::integral_constant<int, 8>{});
+    }
 }
 
 // ------------------------------------------------------------------ sum K slices + residual (+ RMSNorm)
@@ -275,17 +288,21 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
     constexpr int half = HD / 2, per_head = half / 4;
     const int width = (n_q + 2 * n_kv) * HD;
     __shared__ __align__(16) bf16_t vt[V_ROWS * (HD + 8)];
-    __shared__ int vslot[V_ROWS];
+    __shared__ int vslot[V_ROWS], vany;
     const int n_qk = rows * chunks;
     if (TURN && (int)blockIdx.x >= n_qk) {
         constexpr int ROW = HD + 8, F4 = HD / 4, PASS = ROW_THREADS / F4;   // rows per pass
         const int vb = blockIdx.x - n_qk, g = vb % n_kv, r0 = (vb / n_kv) * V_ROWS;
         const int c = threadIdx.x % F4;
-        if (threadIdx.x < V_ROWS) {
+        if (threadIdx.x < 64) {   // wave 0
             const int row = r0 + threadIdx.x;
-            vslot[threadIdx.x] = (row < rows && tok_pos[row] >= 0) ? tok_slot[row] : -1;
+            const int slot = threadIdx.x < V_ROWS && row < rows && tok_pos[row] >= 0 ? tok_slot[row] : -1;
+            if (threadIdx.x < V_ROWS) vslot[threadIdx.x] = slot;
+            const bool any = __builtin_amdgcn_ballot_w64(slot >= 0) != 0;
+            if (threadIdx.x == 0) vany = any;
         }
         __syncthreads();
+        if (!vany) return;   // padding rows only
         const int col = (n_q + n_kv + g) * HD + 4 * c;
         constexpr int NP = V_ROWS / PASS;
         const float* p[NP];
@@ -301,8 +318,6 @@ __global__ __launch_bounds__(ROW_THREADS) void epi_qkv_kernel(const float* __res
 #pragma unroll
             for (int e = 0; e < 4; ++e) b[e] = bf16_to_f32(bias[col + e]);
         }
-        const bool any = __syncthreads_or(threadIdx.x < V_ROWS && vslot[threadIdx.x] >= 0);
-        if (!any) return;   // padding rows only
         add_slices<SLICES>(acc, split, [&](int sl, int i) { return *reinterpret_cast<const f32x4*>(p[i] + sl * slice_stride); });
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
@@ -700,7 +715,7 @@ int laps_launch_rmsnorm(const float* x, const bf16_t* w, bf16_t* out, int rows, 
 int laps_launch_epi_resid(const float* partial, int split, const float* resid, float* x_out, const bf16_t* ln_w,
                           bf16_t* r_out, int rows, int d, float eps, const int* row_live, hipStream_t s) {
     const size_t stride = (size_t)rows * d;
-    const int pieces = (d / 4 + RESID_THREADS - 1) / RESID_THREADS, at_once = slices_at_once(split);
+    const int pieces = (d / 4 + RESID_THREADS - 1) / RESID_THREADS;
     if (pieces > 4) {
         laps_set_error("row width %d too large for the fused residual + norm kernel (max %d)", d, 4 * RESID_THREADS * 4);
         return LAPS_EINVAL;
@@ -709,19 +724,14 @@ int laps_launch_epi_resid(const float* partial, int split, const float* resid, f
         hipLaunchKernelGGL(kern, dim3(rows, ln_w ? 1 : pieces), dim3(RESID_THREADS), 0, s, partial, split, stride, resid, x_out,
                            ln_w, r_out, d, eps, row_live);
     };
-    auto with = [&](auto slices) {
+    with_slices(split, [&](auto slices) {
         constexpr int S = decltype(slices)::value;
         if (!ln_w) go(epi_resid_kernel<1, S, false>);
         else if (pieces == 1) go(epi_resid_kernel<1, S, true>);
         else if (pieces == 2) go(epi_resid_kernel<2, S, true>);
         else if (pieces == 3) go(epi_resid_kernel<3, S, true>);
         else go(epi_resid_kernel<4, S, true>);
-    };
-    if (at_once <= 1) with(std::integral_constant<int, 1>{});
-    else if (at_once <= 2) with(std::integral_constant<int, 2>{});
-    else if (at_once <= 4) with(std::integral_constant<int, 4>{});
-    else if (at_once <= 6) with(std::integral_constant<int, 6>{});
-    else with(std::integral_constant<int, 8>{});
+    });
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -733,18 +743,13 @@ int laps_launch_epi_qkv(const float* partial, int split, const bf16_t* bias, con
     const bool turn = rows > TURN_ABOVE;
     const int chunks = ((n_q + (turn ? 1 : 2) * n_kv) * (hd / 8) + ROW_THREADS - 1) / ROW_THREADS;
     const dim3 grid = turn ? dim3(rows * chunks + (rows + V_ROWS - 1) / V_ROWS * n_kv) : dim3(rows, chunks);
-    const int at_once = slices_at_once(split);
-    auto pick = [&](auto slices) {   // head_dim is one of the two (check_cfg)
+    with_slices(split, [&](auto slices) {   // head_dim is one of the two (check_cfg)
         constexpr int S = decltype(slices)::value;
-        return turn ? (hd == 128 ? epi_qkv_kernel<128, true, S> : epi_qkv_kernel<64, true, S>)
-                    : (hd == 128 ? epi_qkv_kernel<128, false, S> : epi_qkv_kernel<64, false, S>);
-    };
-    auto kern = at_once <= 1   ? pick(std::integral_constant<int, 1>{})
-                : at_once <= 2 ? pick(std::integral_constant<int, 2>{})
-                : at_once <= 4 ? pick(std::integral_constant<int, 4>{})
-                               : pick(std::integral_constant<int, 8>{});
-    hipLaunchKernelGGL(kern, grid, dim3(ROW_THREADS), 0, s, partial, split, stride, bias, tok_pos, tok_slot, rope,
-                       max_pos, q_out, k_pool, v_pool, n_q, n_kv, rows, chunks);
+        auto kern = turn ? (hd == 128 ? epi_qkv_kernel<128, true, S> : epi_qkv_kernel<64, true, S>)
+                         : (hd == 128 ? epi_qkv_kernel<128, false, S> : epi_qkv_kernel<64, false, S>);
+        hipLaunchKernelGGL(kern, grid, dim3(ROW_THREADS), 0, s, partial, split, stride, bias, tok_pos, tok_slot, rope,
+                           max_pos, q_out, k_pool, v_pool, n_q, n_kv, rows, chunks);
+    });
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
@@ -752,8 +757,11 @@ int laps_launch_epi_qkv(const float* partial, int split, const bf16_t* bias, con
 int laps_launch_epi_swiglu(const float* partial, int split, bf16_t* act, int rows, int inter, const int* row_live,
                            hipStream_t s) {
     const size_t stride = (size_t)rows * 2 * inter;
-    hipLaunchKernelGGL(split <= 2 ? epi_swiglu_kernel<2> : epi_swiglu_kernel<4>, dim3(rows, (inter / 4 + ROW_THREADS - 1) / ROW_THREADS), dim3(ROW_THREADS), 0,
-                       s, partial, split, stride, act, inter, row_live);
+    with_slices(split, [&](auto slices) {
+        constexpr int S = decltype(slices)::value;
+        hipLaunchKernelGGL(epi_swiglu_kernel<S>, dim3(rows, (inter / 4 + ROW_THREADS - 1) / ROW_THREADS), dim3(ROW_THREADS), 0, s, partial,
+                           split, stride, act, inter, row_live);
+    });
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
 }
