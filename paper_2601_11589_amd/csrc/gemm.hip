@@ -1029,18 +1029,24 @@ GemmPlan laps_gemm_plan(int m, int n, int k, int force_split, int want_epi, size
             // 2 slices 17.1, 4 14.2; but 4608 x 3584 4 slices 14.2, 7 16.1).
             const int tiles = n / kTiles[c].bn, fine = (ksteps + 4) / 8;
             int sp = 256 / tiles, cap = (ksteps + 8) / 16;
-            const bool read_anyhow = want_epi != EPI_SWIGLU && row_kernel, many = m >= 96;
-            // Above 64 rows two tiles of 64 in half the slices (laps_gemm_launch) where those are 3 or more of up to 20 slabs: with
-            // the row kernel, 7B q/k/v at 72 / 96 / 128 rows in 7 slices 15.6 / 18.3 / 20.7, in 3 15.2 / 16.5 / 18.1; 3584 x 5120 in 8
-            // 15.9 / 18.1 / 21.0, in 4 16.2 / 17.8 / 18.8 (so 19 below 96 rows); slices of 27, 32B o, 21.2 / 23.1 / 24.8, in 6 of 14
-            // 20.0 / 22.3 / 25.2.
+            const bool read_anyhow = want_epi != EPI_SWIGLU && row_kernel;
+            // Above 64 rows two tiles of 64 in half the slices (laps_gemm_launch) where those are 3 or more, and the shorter the fewer
+            // rows of A one tile would take in: up to 12 + m / 12 slabs.  With the row kernel, 32 products of 1536 to 7168 columns and
+            // K = 1536 to 8192 at 7 row counts from 66 to 128: no pair that this takes is behind the one tile (7B q/k/v at 80 / 96 / 128
+            // rows in 7 slices 17.5 / 18.9 / 21.4, in 3 17.0 / 17.9 / 19.1; 3584 x 5120, 20 slabs, at 66 / 96 / 128 rows in 8 16.6 / 19.4 /
+            // 22.3, in 4 17.3 / 18.8 / 20.4), and all of them are within 1 % of the best in the mean (one tile 3.6).
             const int halves = std::min(128 / tiles, fine);
-            if (c == 0 && m > 64 && read_anyhow && halves >= 3 && ksteps <= (many ? 20 : 19) * halves) return halves;
-            // Residual products split at 16 slabs already: finer slices are read by the same row kernel.  Half as many again and
-            // more: 2048 x 2048 at 8 / 64 / 128 rows 10.7 / 13.1 / 13.5 in 2, 8.5 / 10.6 / 11.7 in 4; 7B o up to 64 rows 1 us a layer.
-            // Fewer pay from 96 rows on: 6144 x 4096 at 8 / 72 / 96 / 128 rows 14.5 / 19.8 / 21.6 / 24.4 in 4, 15.3 / 20.2 / 21.5 /
-            // 23.6 in 5; 32B o at 96 / 128 rows 22.7 / 26.0 in 5, 22.3 / 25.2 in 6.
-            const bool finer = want_epi == EPI_PARTIAL || (cap > 1 && (many || 2 * std::min(sp, fine) >= 3 * std::min(sp, cap)));
+            if (c == 0 && m > 64 && read_anyhow && halves >= 3 && 12 * ksteps <= (144 + m) * halves) return halves;
+            // Residual products up to 64 rows split at 16 slabs already: finer slices are read by the same row kernel, and pay where the
+            // longest is shorter by a third (same products, 1 to 64 rows: 0.99 to 1.28 times as fast, 2048 x 2048 at 8 / 64 rows 11.0 /
+            // 13.1 us in 2, 8.7 / 10.7 in 4; 16 slabs in 12 lose, 5120 x 4096 13.4 / 17.4 in 4 and 14.1 / 17.9 in 6).  Above 64 rows they
+            // lose (4096 x 6144 at 72 / 128 rows 18.9 / 23.6 in 6, 19.5 / 25.1 in 8) or are even (32B o, 128 rows, alone 24.8 in 5 and
+            // 25.1 in 6, in a graph of four layers 1 us the other way round).
+            const auto longest = [&](int split) {
+                const int per = (ksteps + split - 1) / split;
+                return ksteps % 2 == 0 ? (per + 1) / 2 * 2 : per;
+            };
+            const bool finer = want_epi == EPI_PARTIAL || (cap > 1 && m <= 64 && 3 * longest(std::min(sp, fine)) <= 2 * longest(std::min(sp, cap)));
             if (c == 5 || (read_anyhow && finer)) cap = fine;
             else if (want_epi == EPI_PARTIAL && cap > 1) cap = std::max(cap, std::min(fine, std::max(4, 128 / tiles)));
             sp = sp > cap ? cap : sp;
