@@ -199,9 +199,9 @@ int laps_prefill_stack(laps_ctx* ctx, const laps_layer_weights* w, int32_t n_seq
  * from library load until the process ends; its address on the context's device is resolved once, in
  * laps_ctx_create).  The call itself allocates nothing, frees nothing and never synchronises.  A batch whose workspace
  * (laps_workspace_bytes) exceeds laps_static_scratch_bytes() = 128 MiB by more than its attention work-item tables (a
- * few tens of KB; laps_attn_plan_info reports them; 1 MiB at most) is rejected with LAPS_EINVAL and a message naming both
- * sizes: at the 32B layer shape that is a few hundred rows.  The context's device must be
- * current.  Every call on a GPU uses that GPU's one array (nothing in it has to start at zero: each region is
+ * few KB, tens of KB for thousands of rows; laps_attn_plan_info reports them; 1 MiB at most) is rejected with
+ * LAPS_EINVAL and a message naming both sizes: at the 32B layer shape that is a few hundred rows.  The context's device
+ * must be current.  Every call on a GPU uses that GPU's one array (nothing in it has to start at zero: each region is
  * written before it is read within the call), so calls that overlap in time on one GPU - two streams, two threads,
  * two contexts - race on it and must be serialised by the caller; calls on one stream are ordered by the stream. */
 size_t laps_static_scratch_bytes(void);

@@ -23,8 +23,8 @@
 // exponentials subtract follows the row maximum lazily, so that O is rescaled rarely.
 //
 // Few query rows over a long cached prefix (a short re-prefill turn) would leave most of the chip idle:
-// one request of 16 new tokens is a single row block per kv head.  For such launches the key ranges of
-// each row block are split into parts of equal length (laps_dev_attn_split; at least 4 key tiles each, or one
+// one request of 16 new tokens is a single row block per kv head.  For such launches the key range of
+// each row block is split into parts of equal length (laps_dev_attn_desc; at least 4 key tiles each, or one
 // where few workgroups make it pay); every part writes its un-normalised accumulator with its running maximum
 // and row sum, and a second kernel merges the parts of a block in key order, so the result depends neither on
 // scheduling nor on the lengths of other sequences.  The number of workgroups is a function of launch shapes only
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
     // one unit: (item, kv head), key tiles [t0, t1) of it if PERSIST; slot: where a cut unit's result goes
     auto unit = [&](const int item, const int kvh, const int t0, const int t1, const int slot) __attribute__((always_inline)) {
     const int4 it = desc[2 * item];
-    const int4 at = desc[2 * item + 1];   // SPLIT: `item` is a part of one, and this says which
+    const int4 at = desc[2 * item + 1];
     const int seq = it.x, qtile = it.y, L = it.z, H = it.w, rs = at.x;
     if (seq < 0) return;
     // row offsets come from the caller's device array: rows outside the batch are never touched, whatever it holds
@@ -98,14 +98,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
     const int kv_end_all = H + last_row_wg / G + 1;  // keys visible to the last row of this block
     int kv_begin = 0, kv_end = kv_end_all;
     if (SPLIT) {
-        kv_begin = at.y * at.z * KT;
+        if ((int)blockIdx.z >= at.y) return;   // the item has fewer parts
+        kv_begin = blockIdx.z * at.z * KT;
         kv_end = kv_begin + at.z * KT < kv_end_all ? kv_begin + at.z * KT : kv_end_all;
     }
     if (PERSIST) {
         kv_begin = t0 * KT;
         kv_end = t1 < (kv_end_all + KT - 1) / KT ? t1 * KT : kv_end_all;
     }
-    const bool whole = SPLIT ? at.w == 1 : (!PERSIST || (kv_begin == 0 && kv_end == kv_end_all));
+    const bool whole = SPLIT ? at.y == 1 : (!PERSIST || (kv_begin == 0 && kv_end == kv_end_all));
     const int* pt = page_table + (size_t)seq * max_pages;
     const size_t tok0 = (size_t)rs;
     const int q_stride = n_q * HD;
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_kernel(const bf16_t* __restri
         // partial result of this key range: accumulator as [4-float chunk][row] so that the 32 rows of a half
         // wave write consecutive 16-byte pieces; (running max, row sum) per row
         if (row_id < n_rows) {
-            const size_t blk = PERSIST ? (size_t)slot : (size_t)item * n_kv + kvh;
+            const size_t blk = PERSIST ? (size_t)slot : ((size_t)item * n_kv + kvh) * gridDim.z + blockIdx.z;
             const int row = wave * 32 + lm;
             f32x4* po = reinterpret_cast<f32x4*>(part_o) + blk * (size_t)(HD / 4) * ROWS;
 #pragma unroll
@@ -668,7 +669,7 @@ constexpr int MERGE_SMALL = 512;   // workgroups
 template <int HD, int CH>
 __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     bf16_t* __restrict__ out, const float* __restrict__ part_o, const float* __restrict__ part_ml,
-    const int4* __restrict__ desc, int n_q, int n_kv, int n_tokens) {
+    const int4* __restrict__ desc, int n_split, int n_q, int n_kv, int n_tokens) {
     constexpr int ROWS = 128;
     __shared__ float red_m[MERGE_GROUPS][ROWS];
     __shared__ float red_l[MERGE_GROUPS][ROWS];
@@ -676,20 +677,20 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     const int item = blockIdx.x, kvh = blockIdx.y;
     const int4 it = desc[2 * item];
     const int4 at = desc[2 * item + 1];
-    const int qtile = it.y, G = n_q / n_kv, L = it.z, rs = at.x, used = at.z;         // parts of the item
+    const int qtile = it.y, G = n_q / n_kv, L = it.z, rs = at.x, used = at.y;         // parts of the item
     if (it.x < 0 || rs < 0 || L > n_tokens - rs) return;                              // as in attn_kernel
     const int n_rows = L * G, R0 = qtile * ROWS;
     if (R0 >= n_rows) return;
     if (used == 1) return;   // the attention kernel wrote the final rows itself (uniform over the workgroup)
     const int row = threadIdx.x % ROWS, g = threadIdx.x / ROWS, row_id = R0 + row;
     const bool live = row_id < n_rows;
-    const size_t blk0 = (size_t)at.y * n_kv + kvh;   // part z: z * n_kv further on
+    const size_t blk0 = ((size_t)item * n_kv + kvh) * n_split;
     const float* pm = part_ml + blk0 * (size_t)(2 * ROWS) + row;
     // every load below is independent of the others: unrolled so that many are in flight at once
     float m_g = -INFINITY;
     if (live) {
 #pragma unroll 4
-        for (int z = g; z < used; z += MERGE_GROUPS) m_g = fmaxf(m_g, pm[(size_t)z * n_kv * 2 * ROWS]);
+        for (int z = g; z < used; z += MERGE_GROUPS) m_g = fmaxf(m_g, pm[(size_t)z * 2 * ROWS]);
     }
     red_m[g][row] = m_g;
     __syncthreads();
@@ -705,11 +706,11 @@ __global__ __launch_bounds__(128 * MERGE_GROUPS) void attn_merge_kernel(
     if (live) {
 #pragma unroll 4
         for (int z = g; z < used; z += MERGE_GROUPS) {
-            const float w = __builtin_amdgcn_exp2f(pm[(size_t)z * n_kv * 2 * ROWS] - m_all);
+            const float w = __builtin_amdgcn_exp2f(pm[(size_t)z * 2 * ROWS] - m_all);
             f32x4 v[CH];
 #pragma unroll
-            for (int c = 0; c < CH; ++c) v[c] = po[((size_t)z * n_kv * (HD / 4) + c) * ROWS];
-            l_g = __builtin_fmaf(w, pm[(size_t)z * n_kv * 2 * ROWS + ROWS], l_g);
+            for (int c = 0; c < CH; ++c) v[c] = po[((size_t)z * (HD / 4) + c) * ROWS];
+            l_g = __builtin_fmaf(w, pm[(size_t)z * 2 * ROWS + ROWS], l_g);
 #pragma unroll
             for (int c = 0; c < CH; ++c)
 #pragma unroll
@@ -770,24 +771,24 @@ int launch_attn_persistent(const bf16_t* q, bf16_t* out, float* part, int n_wgs,
 
 template <int HD>
 int launch_attn_split(const bf16_t* q, bf16_t* out, float* part, const bf16_t* k_pool, const bf16_t* v_pool,
-                      const int4* desc, const int4* parts, const int* page_table,
+                      const int4* desc, const int* page_table,
                       int max_pages, const int* tile_start, int n_seq, int max_items, int n_split,
                       int n_q, int n_kv, int n_pool_pages, int n_tokens, hipStream_t s) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
     const size_t blocks = (size_t)max_items * n_kv * n_split;
     float* part_o = part;
     float* part_ml = part + blocks * 128 * HD;
-    hipLaunchKernelGGL((attn_kernel<HD, 4, true, false>), dim3(max_items * n_split, n_kv), dim3(256), 0, s, q, out, part_o, part_ml,
-                       k_pool, v_pool, parts, page_table, max_pages, tile_start, n_seq,
+    hipLaunchKernelGGL((attn_kernel<HD, 4, true, false>), dim3(max_items, n_kv, n_split), dim3(256), 0, s, q, out, part_o, part_ml,
+                       k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq,
                        n_q, n_kv, scale_log2e, n_pool_pages, n_tokens, max_items, nullptr);
     LAPS_LAUNCH_CHECK();
     // slices of head_dim a workgroup merges: one where all of them are on the chip at once, four from there on
     if ((long)max_items * n_kv * (HD / 4) <= MERGE_SMALL) {
         hipLaunchKernelGGL((attn_merge_kernel<HD, 1>), dim3(max_items, n_kv, HD / 4), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
-                       desc, n_q, n_kv, n_tokens);
+                       desc, n_split, n_q, n_kv, n_tokens);
     } else {
         hipLaunchKernelGGL((attn_merge_kernel<HD, 4>), dim3(max_items, n_kv, HD / 16), dim3(128 * MERGE_GROUPS), 0, s, out, part_o, part_ml,
-                       desc, n_q, n_kv, n_tokens);
+                       desc, n_split, n_q, n_kv, n_tokens);
     }
     LAPS_LAUNCH_CHECK();
     return LAPS_OK;
@@ -870,14 +871,13 @@ static size_t item_table_ints(int max_tokens, int max_seqs, int group) {   // it
 }
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group) {
     const size_t n = item_table_ints(max_tokens, max_seqs, group);
-    return 2 * n * sizeof(int) + (LAPS_ATTN_MAX_WGS + 1 + 2 * n + 2 * (kSplitTargetBlocks + kSplitBelowBlocks)) * sizeof(int4);
+    return 2 * n * sizeof(int) + (LAPS_ATTN_MAX_WGS + 1 + 2 * n) * sizeof(int4);
 }
-void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc, int4** blocks) {
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc) {
     const size_t n = item_table_ints(n_tokens, n_seq, group);
     *pre = item_seq + n;
     *bounds = reinterpret_cast<int4*>(item_seq + 2 * n);
     *desc = *bounds + LAPS_ATTN_MAX_WGS + 1;
-    *blocks = *desc + 2 * n;
 }
 
 // The persistent kernel takes un-split launches of 256-row blocks where units differ enough in length for equal shares to
@@ -923,8 +923,8 @@ int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, co
     attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split, &min_tiles);
     const int n_wgs = partial ? laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes) : 0;
     int* pre;
-    int4 *bounds, *desc, *parts;
-    laps_attn_item_tables(const_cast<int*>(item_seq), n_tokens, n_seq, n_q / n_kv, &pre, &bounds, &desc, &parts);
+    int4 *bounds, *desc;
+    laps_attn_item_tables(const_cast<int*>(item_seq), n_tokens, n_seq, n_q / n_kv, &pre, &bounds, &desc);
     if (n_wgs > 0) {
         auto launch = hd == 128 ? launch_attn_persistent<128> : launch_attn_persistent<64>;
         return launch(q, out, partial, n_wgs, bounds, k_pool, v_pool, desc, page_table, max_pages,
@@ -935,8 +935,8 @@ int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, co
             laps_set_error("attention: key-split launch needs the partial-result workspace");
             return LAPS_EINVAL;
         }
-        if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, desc, parts, page_table, max_pages, tile_start, n_seq, max_items, n_split, n_q, n_kv, n_pool_pages, n_tokens, s);
-        if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, desc, parts, page_table, max_pages, tile_start, n_seq, max_items, n_split, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (hd == 128) return launch_attn_split<128>(q, out, partial, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_split, n_q, n_kv, n_pool_pages, n_tokens, s);
+        if (hd == 64) return launch_attn_split<64>(q, out, partial, k_pool, v_pool, desc, page_table, max_pages, tile_start, n_seq, max_items, n_split, n_q, n_kv, n_pool_pages, n_tokens, s);
     }
     // 128-row blocks that would be 256-row ones over more key tiles: summed up as those do, so that the width of the page table
     // does not show in the result (the sums of rounded probabilities are also the ones that match the second product:

@@ -29,7 +29,7 @@ extern "C" const char* laps_version(void) { return "laps-gfx950 0.1"; }
 // of the process.  In host code the array's name is only a handle for hipGetSymbolAddress; the address the
 // kernels are given is the one resolved below, per device, with that device current.
 #define LAPS_STATIC_SCRATCH_BYTES ((size_t)128 << 20)
-// The attention's work-item tables (a few tens of KB) come on top, so that what they take is not missing from the 128 MiB.
+// The attention's work-item tables (a few KB; 40 bytes an item) come on top, so that what they take is not missing from the 128 MiB.
 #define LAPS_STATIC_TABLE_BYTES ((size_t)1 << 20)
 static __device__ __align__(256) unsigned char scratch[LAPS_STATIC_SCRATCH_BYTES + LAPS_STATIC_TABLE_BYTES];
 
@@ -325,7 +325,7 @@ static BeginArgs begin_args(const laps_ctx* c, const BatchDesc& b, unsigned char
     a.tok_slot = reinterpret_cast<int*>(ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(ws + L.item_seq);
-    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc, &a.attn_blocks);
+    laps_attn_item_tables(a.item_seq, b.n_tokens, b.n_seq, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc);
     a.d = cf.hidden;
     a.eps = cf.rms_eps;
     return a;
@@ -770,7 +770,7 @@ static int graph_stage_launch(laps_graph* g, int n_real, const int* seq_len, con
     a.tok_slot = reinterpret_cast<int*>(g->ws + L.tok_slot);
     a.tile_start = reinterpret_cast<int*>(g->ws + L.tile_start);
     a.item_seq = reinterpret_cast<int*>(g->ws + L.item_seq);
-    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc, &a.attn_blocks);
+    laps_attn_item_tables(a.item_seq, M, g->depth, a.group, &a.attn_pre, &a.attn_bounds, &a.attn_desc);
     a.x_in = g->x_in;
     a.ln_w = g->ln1_first;
     a.r0 = g->r0;

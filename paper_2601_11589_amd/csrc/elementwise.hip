@@ -136,10 +136,8 @@ __global__ __launch_bounds__(ROW_THREADS) void begin_kernel(const BeginArgs a) {
         }
         __syncthreads();   // the lengths written above are read below by other threads of this workgroup
         laps_dev_attn_sched(a.new_len, a.n_seq, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, sums);
-        laps_dev_attn_desc(a.new_len, a.prefix_len, a.row_start, a.n_seq, a.max_pages, a.tile_start, a.item_seq, a.max_items, a.attn_desc);
-        if (a.n_split > 1)
-            laps_dev_attn_split(a.new_len, a.prefix_len, a.row_start, a.n_seq, a.group, a.rows_per_wg, a.max_pages, a.tile_start,
-                                a.item_seq, a.max_items, a.n_split, a.min_tiles, a.attn_desc, a.attn_blocks, sums);
+        laps_dev_attn_desc(a.new_len, a.prefix_len, a.row_start, a.n_seq, a.group, a.rows_per_wg, a.max_pages, a.tile_start, a.item_seq,
+                           a.max_items, a.n_split, a.min_tiles, a.attn_desc);
         if (a.attn_wgs > 0)
             laps_dev_attn_bounds(a.new_len, a.prefix_len, a.n_seq, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
                                  a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, sums);
@@ -622,11 +620,8 @@ __global__ __launch_bounds__(ROW_THREADS) void stage_kernel(const StageArgs a) {
         if (t == ROW_THREADS - 1) a.row_start_out[depth] = run;
         __syncthreads();   // the lengths written above are read below by other threads of this workgroup
         laps_dev_attn_sched(a.new_len_out, depth, a.group, a.rows_per_wg, a.tile_start, a.item_seq, a.max_items, sums);
-        laps_dev_attn_desc(a.new_len_out, a.prefix_out, a.row_start_out, depth, a.max_pages, a.tile_start, a.item_seq, a.max_items,
-                           a.attn_desc);
-        if (a.n_split > 1)
-            laps_dev_attn_split(a.new_len_out, a.prefix_out, a.row_start_out, depth, a.group, a.rows_per_wg, a.max_pages,
-                                a.tile_start, a.item_seq, a.max_items, a.n_split, a.min_tiles, a.attn_desc, a.attn_blocks, sums);
+        laps_dev_attn_desc(a.new_len_out, a.prefix_out, a.row_start_out, depth, a.group, a.rows_per_wg, a.max_pages, a.tile_start,
+                           a.item_seq, a.max_items, a.n_split, a.min_tiles, a.attn_desc);
         if (a.attn_wgs > 0)
             laps_dev_attn_bounds(a.new_len_out, a.prefix_out, depth, a.group, a.n_kv, a.max_pages, a.tile_start, a.item_seq,
                                  a.max_items, a.attn_wgs, a.attn_pre, a.attn_bounds, sums);

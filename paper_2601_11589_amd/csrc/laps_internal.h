@@ -91,7 +91,7 @@ struct BeginArgs {
     int group, rows_per_wg, max_items, n_kv, attn_wgs;          // attention blocking; attn_wgs as laps_attn_persistent_wgs
     int n_split, min_tiles;                                     // as laps_attn_plan
     int *new_len, *tok_pos, *tok_slot, *tile_start, *item_seq, *attn_pre;
-    int4 *attn_bounds, *attn_desc, *attn_blocks;
+    int4 *attn_bounds, *attn_desc;
     const float* x;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -130,7 +130,7 @@ struct StageArgs {
     int *seq_len_out, *prefix_out, *row_start_out, *page_table_out;   // the graph's staging block
     int *new_len_out, *tok_pos, *tok_slot, *tile_start, *item_seq;    // the graph's workspace
     int* attn_pre;
-    int4 *attn_bounds, *attn_desc, *attn_blocks;
+    int4 *attn_bounds, *attn_desc;
     float* x_in;
     const bf16_t* ln_w;
     bf16_t* r0;
@@ -190,63 +190,37 @@ static __device__ __forceinline__ int laps_dev_clamp_prefix(int h, int new_len, 
     return h > 0 ? h : 0;
 }
 
+constexpr int LAPS_ATTN_KT = 64;          // keys per tile
+
 // What a workgroup of the attention needs to know of a work item, two int4 an item: (sequence, row block, new tokens, cached
-// tokens) and (first row; with split key ranges also the item's first part, its parts, -); the items past the batch's last one
-// have a sequence of -1.  One scalar load instead of the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a
-// link.  Runs in ONE workgroup of 256 threads after laps_dev_attn_sched.
+// tokens) and (first row, parts of its key range, key tiles of a part, -); the items past the batch's last one have a sequence of
+// -1.  One scalar load instead of the chain item -> sequence -> lengths -> first row, at 0.3 to 0.5 us a link.
+// Key-range splits of a batch whose (item, kv head) blocks leave compute units idle (n_split > 1): an item's key tiles go out in
+// parts of equal length, at least min_tiles each and n_split of them at most.  Where an item is cut follows from its own length and
+// the launch's shape alone, so that the bits of a request do not depend on the lengths it is batched with.  (Parts of equal length
+// over the whole batch would spare the longest item's parts, 32B, turns of 17 to 32 tokens over 512 to 4096 keys, up to 9 tiles
+// where all parts together are 4 tiles for every place on the chip: a layer's graph 252 -> 247 us.  They need a table of the parts:
+// written by the items' threads, 15 parts of one turn took 5 us.)
+// Runs in ONE workgroup of 256 threads after laps_dev_attn_sched.
 static __device__ __forceinline__ void laps_dev_attn_desc(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
-                                                          const int* __restrict__ row_start, int n_seq, int max_pages,
-                                                          const int* tile_start, const int* item_seq, int max_items,
-                                                          int4* __restrict__ desc) {
+                                                          const int* __restrict__ row_start, int n_seq, int group, int rows_per_wg,
+                                                          int max_pages, const int* tile_start, const int* item_seq, int max_items,
+                                                          int n_split, int min_tiles, int4* __restrict__ desc) {
     __syncthreads();   // tile_start and item_seq were written by other threads of this workgroup
     const int total = tile_start[n_seq];
     for (int k = threadIdx.x; k < max_items; k += 256) {
         const bool any = k < total;
-        const int i = any ? item_seq[k] : 0, L = new_len[i];
-        desc[2 * k] = any ? make_int4(i, k - tile_start[i], L, laps_dev_clamp_prefix(prefix_len[i], L, max_pages)) : make_int4(-1, 0, 0, 0);
-        desc[2 * k + 1] = make_int4(row_start[i], 0, 0, 0);
-    }
-}
-
-constexpr int LAPS_ATTN_KT = 64;          // keys per tile
-
-// Key-range splits of a batch whose (item, kv head) blocks leave compute units idle: an item's key tiles go out in parts of
-// equal length, at least min_tiles each and n_split of them at most.  Where an item is cut follows from its own length and the
-// launch's shape alone, so that the bits of a request do not depend on the lengths it is batched with.  (Parts of equal length
-// over the whole batch would spare the longest item's parts, 32B, turns of 17 to 32 tokens over 512 to 4096 keys, up to 9 tiles
-// where all parts together are 4 tiles for every place on the chip: a layer's graph 252 -> 247 us.)
-// blocks: two int4 a part, (sequence, row block, new tokens, cached tokens) and (first row, its number among the item's parts, key
-// tiles of a part, the item's parts); a sequence of -1 past the last one, max_items * n_split in all.
-// Runs in ONE workgroup of 256 threads after laps_dev_attn_sched; max_items < 256.
-static __device__ __forceinline__ void laps_dev_attn_split(const int* __restrict__ new_len, const int* __restrict__ prefix_len,
-                                                           const int* __restrict__ row_start, int n_seq, int group,
-                                                           int rows_per_wg, int max_pages, const int* tile_start, const int* item_seq,
-                                                           int max_items, int n_split, int min_tiles, int4* desc, int4* blocks,
-                                                           int* sums) {
-    __syncthreads();   // desc was written by other threads of this workgroup
-    const int k = threadIdx.x, cap = max_items * n_split;
-    const int n_items = tile_start[n_seq] < max_items ? tile_start[n_seq] : max_items;
-    const bool any = k < n_items;
-    int4 it = make_int4(-1, 0, 0, 0);
-    int each = 0, parts = 0, used;
-    if (any) {
-        const int i = item_seq[k], L = new_len[i], H = laps_dev_clamp_prefix(prefix_len[i], L, max_pages), q = k - tile_start[i];
-        const int last = ((q + 1) * rows_per_wg < L * group ? (q + 1) * rows_per_wg : L * group) - 1;
-        it = make_int4(i, q, L, H);
-        const int nt = (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT, most = nt / min_tiles < n_split ? nt / min_tiles : n_split;
-        each = most > 1 ? (nt + most - 1) / most : nt;
-        parts = (nt + each - 1) / each;   // none of them empty
-    }
-    const int first = laps_dev_scan(parts, sums, &used) - parts;
-    if (any) {
-        const int rs = row_start[it.x];
-        desc[2 * k + 1] = make_int4(rs, first, parts, 0);
-        for (int z = 0; z < parts; ++z) {
-            blocks[2 * (first + z)] = it;
-            blocks[2 * (first + z) + 1] = make_int4(rs, z, each, parts);
+        const int i = any ? item_seq[k] : 0, L = new_len[i], H = laps_dev_clamp_prefix(prefix_len[i], L, max_pages), q = any ? k - tile_start[i] : 0;
+        int parts = 1, each = 0;
+        if (n_split > 1 && any) {
+            const int last = ((q + 1) * rows_per_wg < L * group ? (q + 1) * rows_per_wg : L * group) - 1;
+            const int nt = (H + last / group + LAPS_ATTN_KT) / LAPS_ATTN_KT, most = nt / min_tiles < n_split ? nt / min_tiles : n_split;
+            each = most > 1 ? (nt + most - 1) / most : nt;
+            parts = (nt + each - 1) / each;   // none of them empty
         }
+        desc[2 * k] = any ? make_int4(i, q, L, H) : make_int4(-1, 0, 0, 0);
+        desc[2 * k + 1] = make_int4(row_start[i], parts, each, 0);
     }
-    for (int x = used + k; x < cap; x += 256) blocks[2 * x] = make_int4(-1, 0, 0, 0);
 }
 
 // Equal shares of a batch's attention for `n_wgs` workgroups (the persistent long-prompt kernel).  A unit is one
@@ -338,10 +312,9 @@ static __device__ __forceinline__ void laps_dev_attn_bounds(const int* __restric
 // calls for splitting the key range; it may be NULL only if max_pages * 16 < 512.  partial_bytes must be that of the table's shares.
 // tile_start: n_seq + 1 ints; item_seq: laps_attn_item_table_bytes (sequence of every row-block work item).
 size_t laps_attn_partial_bytes(int hd, int max_pages);   // 0 when page tables this narrow never split
-// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel, the items' descriptions and
-// the parts of split key ranges.
+// Work-item table: item_seq, then the cost prefix sums and the bounds of the persistent kernel and the items' descriptions.
 size_t laps_attn_item_table_bytes(int max_tokens, int max_seqs, int group);
-void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc, int4** blocks);
+void laps_attn_item_tables(int* item_seq, int n_tokens, int n_seq, int group, int** pre, int4** bounds, int4** desc);
 // Workgroups of the persistent long-prompt kernel for a launch shape with partial_bytes of room for the results of cut
 // units (two slots per workgroup); 0: the launch does not use it.
 int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int hd, int max_pages, size_t partial_bytes);

@@ -1,7 +1,7 @@
-// Runs the device code that cuts a batch's attention into parts of its key ranges on the CPU, with the coroutines of the
-// driver next to it.  Reads batches from stdin, one line of numbers each:
+// Runs the device code that describes a batch's attention work items, and cuts their key ranges into parts, on the CPU, with the
+// coroutines of the driver next to it.  Reads batches from stdin, one line of numbers each:
 //   n_split min_tiles group max_pages rows_per_wg max_items n_seq  new_len[n_seq]  prefix_len[n_seq]
-// and prints, a line per batch: eight numbers per item of the table, then eight per part, both with a guard entry behind.
+// and prints, a line per batch, eight numbers per item of the table and a guard entry behind.
 #define main shares_main
 #include "attn_shares_driver.cpp"
 #undef main
@@ -9,19 +9,14 @@
 namespace {
 int n_split, min_tiles;
 std::vector<int> row_start;
-std::vector<int4> desc, parts;
+std::vector<int4> desc;
 
 void split_main() {
     laps_dev_attn_sched(b.new_len.data(), b.n_seq, b.group, b.rows_per_wg, b.tile_start.data(), b.item_seq.data(), b.max_items, sums);
-    laps_dev_attn_desc(b.new_len.data(), b.prefix_len.data(), row_start.data(), b.n_seq, b.max_pages, b.tile_start.data(),
-                       b.item_seq.data(), b.max_items, desc.data());
-    laps_dev_attn_split(b.new_len.data(), b.prefix_len.data(), row_start.data(), b.n_seq, b.group, b.rows_per_wg, b.max_pages,
-                        b.tile_start.data(), b.item_seq.data(), b.max_items, n_split, min_tiles, desc.data(), parts.data(), sums);
+    laps_dev_attn_desc(b.new_len.data(), b.prefix_len.data(), row_start.data(), b.n_seq, b.group, b.rows_per_wg, b.max_pages,
+                       b.tile_start.data(), b.item_seq.data(), b.max_items, n_split, min_tiles, desc.data());
     done[threadIdx.x] = true;
     barrier();
-}
-void print(const std::vector<int4>& table) {
-    for (const int4& v : table) std::printf("%d %d %d %d ", v.x, v.y, v.z, v.w);
 }
 }  // namespace
 
@@ -40,7 +35,6 @@ int main() {
         b.tile_start.assign(b.n_seq + 1, -1);
         b.item_seq.assign(b.max_items, -1);
         desc.assign(2 * (b.max_items + 1), int4{-7, -7, -7, -7});
-        parts.assign(2 * (b.max_items * n_split + 1), int4{-7, -7, -7, -7});
         for (int t = 0; t < kThreads; ++t) {
             done[t] = false;
             getcontext(&fiber[t]);
@@ -56,8 +50,7 @@ int main() {
                 swapcontext(&scheduler, &fiber[t]);
                 left -= done[t];
             }
-        print(desc);
-        print(parts);
+        for (const int4& v : desc) std::printf("%d %d %d %d ", v.x, v.y, v.z, v.w);
         std::printf("\n");
     }
     return 0;
