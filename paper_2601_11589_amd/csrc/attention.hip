@@ -916,9 +916,9 @@ int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int h
 }
 
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,
-                          const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
-                          int max_pages, int n_seq, int n_tokens, const int* tile_start, const int* item_seq,
-                          float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s) {
+                          const int* page_table, int max_pages, int n_seq, int n_tokens, const int* tile_start,
+                          const int* item_seq, float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages,
+                          hipStream_t s) {
     int mt, max_items, n_split, min_tiles;
     attn_blocking(n_seq, n_tokens, n_q / n_kv, n_kv, max_pages, &mt, &max_items, &n_split, &min_tiles);
     const int n_wgs = partial ? laps_attn_persistent_wgs(n_seq, n_tokens, n_q / n_kv, n_kv, hd, max_pages, partial_bytes) : 0;

@@ -343,7 +343,6 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
     const WsLayout L = ws_layout(cf, M, b.n_seq, b.ws_pages);
     int* tok_pos = reinterpret_cast<int*>(ws + L.tok_pos);
     int* tok_slot = reinterpret_cast<int*>(ws + L.tok_slot);
-    int* new_len = reinterpret_cast<int*>(ws + L.new_len);
     int* tile_start = reinterpret_cast<int*>(ws + L.tile_start);
     int* item_seq = reinterpret_cast<int*>(ws + L.item_seq);
     bf16_t* r = reinterpret_cast<bf16_t*>(ws + L.r);
@@ -385,9 +384,8 @@ static int run_layers(laps_ctx* c, const laps_layer_weights* w, int n_layers, co
         }
         {
             ProfScope ps(c, s, LAPS_K_ATTN, capturing);
-            LAPS_TRY(laps_launch_attention(q, attn, kp, vp, b.row_start, new_len, b.prefix_len, b.page_table, b.max_pages,
-                                           b.n_seq, M, tile_start, item_seq, partial, partial_bytes, cf.n_q_heads,
-                                           cf.n_kv_heads, hd, c->pool_pages, s));
+            LAPS_TRY(laps_launch_attention(q, attn, kp, vp, b.page_table, b.max_pages, b.n_seq, M, tile_start, item_seq,
+                                           partial, partial_bytes, cf.n_q_heads, cf.n_kv_heads, hd, c->pool_pages, s));
         }
         // x_mid = resid + attn W_o^T ; r = rmsnorm(x_mid; ln2)
         LAPS_TRY(run_gemm(c, LAPS_K_GEMM_O, capturing, attn, static_cast<const bf16_t*>(lw.w_o), M, d, qd, EPI_RESID,
@@ -666,7 +664,6 @@ extern "C" int laps_attention(laps_ctx* c, int32_t n_seq, int32_t n_tokens, cons
     }
     unsigned char* w8 = static_cast<unsigned char*>(ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int* new_len = reinterpret_cast<int*>(w8 + L.new_len);
     BatchDesc b = {};
     b.n_seq = n_seq;
     b.n_tokens = n_tokens;
@@ -678,10 +675,9 @@ extern "C" int laps_attention(laps_ctx* c, int32_t n_seq, int32_t n_tokens, cons
     LAPS_TRY(laps_launch_begin(begin_args(c, b, w8, L), s));
     const size_t partial_bytes = L.total - L.partial;
     return laps_launch_attention(static_cast<const bf16_t*>(q), static_cast<bf16_t*>(out),
-                                 static_cast<const bf16_t*>(k_pool), static_cast<const bf16_t*>(v_pool), cu, new_len,
-                                 prefix_len, pt, max_pages, n_seq, n_tokens, reinterpret_cast<int*>(w8 + L.tile_start),
-                                 reinterpret_cast<int*>(w8 + L.item_seq), reinterpret_cast<float*>(w8 + L.partial), partial_bytes,
-                                 c->cfg.n_q_heads, c->cfg.n_kv_heads, c->cfg.head_dim, c->pool_pages, s);
+                                 static_cast<const bf16_t*>(k_pool), static_cast<const bf16_t*>(v_pool), pt, max_pages, n_seq, n_tokens,
+                                 reinterpret_cast<int*>(w8 + L.tile_start), reinterpret_cast<int*>(w8 + L.item_seq),
+                                 reinterpret_cast<float*>(w8 + L.partial), partial_bytes, c->cfg.n_q_heads, c->cfg.n_kv_heads, c->cfg.head_dim, c->pool_pages, s);
 }
 
 // ----------------------------------------------------------------------------- launch plans (host only)

@@ -322,7 +322,8 @@ int laps_attn_persistent_wgs(int n_seq, int n_tokens, int group, int n_kv, int h
 // bound on the (sequence, row block) items, key-range splits (1 = none), fewest key tiles a split may get.
 void laps_attn_plan(int n_seq, int n_tokens, int group, int n_kv, int max_pages, int* rows_per_wg, int* max_items,
                     int* n_split, int* min_tiles_per_split);
+// Lengths and row offsets are those that the kernel which began or staged the batch has put into the table.
 int laps_launch_attention(const bf16_t* q, bf16_t* out, const bf16_t* k_pool, const bf16_t* v_pool,
-                          const int* row_start, const int* new_len, const int* prefix_len, const int* page_table,
-                          int max_pages, int n_seq, int n_tokens, const int* tile_start, const int* item_seq,
-                          float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages, hipStream_t s);
+                          const int* page_table, int max_pages, int n_seq, int n_tokens, const int* tile_start,
+                          const int* item_seq, float* partial, size_t partial_bytes, int n_q, int n_kv, int hd, int n_pool_pages,
+                          hipStream_t s);
