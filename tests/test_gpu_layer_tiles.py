@@ -94,7 +94,7 @@ def test_320_row_tile_matches_float64(m, k, split):
         run(Plan(TILE_320, split, per, epi, 1), m, 512, k)
 
 
-# every width with its first tile: 160, 224, 192 and none
+# widths that 256 x 160, 224 and 192 divide and that they do not; which tile runs is test_every_tile_by_live_rows_is_chosen's
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,epi", [(5120, PARTIAL), (5120, RESID), (7168, PARTIAL), (3584, RESID), (4608, PARTIAL), (27648, SWIGLU), (37888, SWIGLU)])
 def test_tile_by_live_rows_matches_float64(n, epi):
@@ -181,7 +181,7 @@ def test_last_column_tile_past_n_matches_float64(cfg, m):
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,epi", [(5120, RESID), (3584, RESID), (4608, PARTIAL), (27648, SWIGLU)])
 def test_tile_by_live_rows_of_large_batches_matches_float64(n, epi):
-    for rows in (1111, 1847, 2776, 3000):      # 256 x 160, 256 x 224, 256 x 192 and others, the last column tile past n or not
+    for rows in (1111, 1847, 2776, 3000):
         run(Plan(2, 1, 1024, epi, 1), 3000, n, 1024, torch.tensor([rows], dtype=torch.int32, device="cuda"), rows)
 
 
@@ -228,3 +228,88 @@ def test_columns_behind_whole_rounds_match_float64(cfg, m, n, rest):
             C.c_bool(False), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
         want = a[:rows].double() @ w.double().T
         assert float((out[:rows].double() - want).norm() / want.norm()) < 2e-6
+
+
+# The tile that gemm_live_kernel gives a number of rows, from the cost table and margins it is compiled with
+_GEMM = open(os.path.join(os.path.dirname(api.__file__), "csrc", "gemm.hip")).read()
+_LIST = lambda name: [int(v) for v in re.search(name + r"\[kLiveTiles\] = \{([^}]*)\}", _GEMM).group(1).split(",")]
+LIVE_ROWS, LIVE_COLS, LIVE_CFG = _LIST("kLiveRows"), _LIST("kLiveCols"), _LIST("cfg")
+COST = [[float(v) for v in t.split(",")] for t in re.findall(r"^    \{(\d+, \d+, \d, [\d.]+, [\d.]+, [\d.]+)\}, +// \d+:", _GEMM, re.M)]
+MARGIN = [float(re.search(name + r" = ([\d.]+)", _GEMM).group(1)) for name in ("kRaggedMargin", "kMore192Margin")]
+
+
+def tile_by_live_rows(m, n, k, epi):
+    """Index among the tiles, and how far the next one is behind."""
+    costs = []
+    for i in range(5 if epi == SWIGLU else 7):
+        _, _, _, fill, slab, part = COST[LIVE_CFG[i]]
+        tiles_m = -(-m // LIVE_ROWS[i])
+        tiles = tiles_m * -(-n // LIVE_COLS[i])
+        us = -(-tiles // 256) * (fill + slab * (k // 64) * (1 - part * max(0, 1 - tiles / 256)))
+        costs.append(us * (MARGIN[0] if n % LIVE_COLS[i] else MARGIN[1] if LIVE_ROWS[i] == 192 and tiles_m != -(-m // 256) else 1))
+    best = sorted(costs)
+    return costs.index(best[0]), best[1] / best[0]
+
+
+# (rows, columns, K): tile, the last column tile past n or not; rows that fill no tile
+LIVE = {(579, 16384, 192): (0, False), (257, 256, 192): (1, False), (257, 18944, 192): (2, True), (775, 8448, 192): (2, False),
+        (257, 37888, 192): (3, False), (257, 27648, 192): (4, False), (390, 27648, 1024): (5, True), (1548, 7168, 192): (5, False),
+        (257, 18944, 1024): (6, True), (3842, 2560, 320): (6, False)}
+LIVE_CASES = [(c, epi) for c in LIVE for epi in (PARTIAL, RESID, SWIGLU) if epi != SWIGLU or LIVE[c][0] < 5]
+
+
+def test_every_tile_by_live_rows_is_chosen():
+    assert len(COST) == 11 and len(LIVE_ROWS) == len(LIVE_COLS) == len(LIVE_CFG) == 7
+    assert all((LIVE_ROWS[i], LIVE_COLS[i]) == tuple(COST[LIVE_CFG[i]][:2]) for i in range(7))
+    for epi in (PARTIAL, RESID, SWIGLU):
+        seen = set()
+        for case, e in LIVE_CASES:
+            if e == epi:
+                tile, lead = tile_by_live_rows(*case, epi)
+                assert (tile, case[1] % LIVE_COLS[tile] != 0) == LIVE[case] and lead > 1.01, (case, epi)
+                assert case[0] % LIVE_ROWS[tile] != 0
+                seen.add(tile)
+        assert seen == set(range(5 if epi == SWIGLU else 7))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case,epi", LIVE_CASES)
+def test_every_tile_by_live_rows_matches_float64(case, epi):
+    rows, n, k = case
+    run(Plan(2, 1, k, epi, 1), rows + 61, n, k, torch.tensor([rows], dtype=torch.int32, device="cuda"), rows)
+
+
+# Padding between the sequences (row_live), as a batch with lengths shorter than its row offsets has it
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,rest,m,n", [(9, None, 300, 320), (3, None, 700, 640), (4, None, 513, 448), (0, None, 300, 192), (7, None, 500, 320),
+                                          (2, 0, 700, 22272), (2, 7, 513, 22016), (10, 8, 961, 16640), (10, 0, 1300, 16640)])
+def test_padding_between_sequences_on_ragged_and_mixed_tiles(cfg, rest, m, n):
+    k = 320
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    live = torch.rand(m, device="cuda", generator=g) < 0.6
+    live[256:640] = False       # whole row tiles of every height
+    live[m - 1] = True
+    a = torch.empty((m, k), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    a[~live] = float("nan")
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=g)
+    flags = torch.where(live, 3, -1).to(torch.int32)
+    resid = torch.empty((m, n), device="cuda").normal_(0, 4, generator=g)
+    want = a[live].double() @ w.double().T
+    p = lambda t: C.c_void_p(t.data_ptr())
+    for epi in (PARTIAL, RESID) + ((SWIGLU,) if cfg not in (3, 4) else ()):
+        plan = Plan(cfg, 1, k, epi, 1) if rest is None else mixed(cfg, rest, k, epi)
+        out = torch.full((m + 7, n), 7.0, device="cuda")
+        act = torch.full((m + 7, n // 2), 7.0, dtype=torch.bfloat16, device="cuda")
+        assert api.lib()._Z16laps_gemm_launchRK8GemmPlanPKtS3_iiiPfPKfPtPKiS9_bP12ihipStream_t(
+            C.byref(plan), p(a), p(w), C.c_int(m), C.c_int(n), C.c_int(k), p(out), p(resid), p(act), p(flags), None, C.c_bool(False),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0, api.lib().laps_last_error()
+        torch.cuda.synchronize()
+        assert bool((out[m:] == 7).all()) and bool((act[m:] == 7).all())
+        if epi == SWIGLU:      # bounds as in run()
+            gate, up = want.view(-1, n // 64, 2, 32).unbind(2)
+            ref = (torch.nn.functional.silu(gate) * up).reshape(-1, n // 2)
+            slack = (6 * 2.0 ** -24 * 0.02 * k / 4 * (1.1 * up.abs() + gate.abs())).reshape(-1, n // 2) + 1e-6
+            assert bool(((act[:m][live].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all())
+        else:
+            ref = want if epi == PARTIAL else want + resid[live].double()
+            assert float((out[:m][live].double() - ref).norm() / ref.norm()) < 2e-6
