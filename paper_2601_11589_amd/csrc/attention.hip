@@ -28,8 +28,8 @@
 // where few workgroups make it pay); every part writes its un-normalised accumulator with its running maximum
 // and row sum, and a second kernel merges the parts of a block in key order, so the result depends neither on
 // scheduling nor on the lengths of other sequences.  The number of workgroups is a function of launch shapes only
-// (row blocks, kv heads, page-table width), which keeps captured graphs replayable; which part a workgroup
-// takes, if any, is worked out on the device from the batch's lengths.
+// (row blocks, kv heads, page-table width), which keeps captured graphs replayable; how many of the parts a
+// block really has is worked out on the device from its length.
 //
 // Many query rows over page tables that allow long prefixes (chunks of long prompts, mixed batches, groups of turns) make
 // blocks of very different lengths.  Such launches run the 8-wave loop in a fixed number of workgroups, each of which walks
